@@ -215,19 +215,32 @@ int pick_variant_padded(int G, int64_t M_pad_cap, int N, int K) {
   return pick_variant(G, rows, N, K);
 }
 
-// Grid of the row kernels (a workgroup takes rows in pairs).  With K-block-major scales and at least 8 workgroups the
-// pairs are dealt out by XCD (see pair_of in quant_kernel.h), which needs a grid that is a multiple of 8.
-int64_t row_kernel_grid(int64_t M_total, bool kmajor, int* by_xcd) {
-  int64_t grid = (int64_t)device_cus() * 8;
-  const int64_t npairs = (M_total + 1) / 2;
-  if (grid > npairs) grid = npairs;
-  *by_xcd = 0;
-  if (kmajor && grid >= kXcds) {
-    grid -= grid % kXcds;
-    *by_xcd = 1;
-  }
-  return grid < 1 ? 1 : grid;
+// Work split of the row kernels: `slots` blocks per workgroup (one pass), KB blocks per row; see RowWork.
+gg::RowWork row_work(int64_t M_total, int KB, bool kmajor, int slots, unsigned* grid) {
+  gg::RowWork w;
+  w.pieces = (KB + slots - 1) / slots;
+  w.blocks = (KB + w.pieces - 1) / w.pieces;
+  w.rows = w.pieces == 1 ? slots / w.blocks : 1;
+  // few rows: fewer per workgroup, so that they spread over the chip
+  const int64_t spread = 2 * (int64_t)device_cus();
+  if (w.rows > 1 && M_total < w.rows * spread) w.rows = (int)((M_total + spread - 1) / spread);
+  w.magic = (unsigned)((65536 + w.blocks - 1) / w.blocks);
+  int64_t groups = (M_total + w.rows - 1) / w.rows;
+  w.sector = !kmajor ? 0 : groups >= 2048 ? 32 : 8;
+  if (w.sector) groups = (groups + 8 * w.sector - 1) / (8 * w.sector) * (8 * w.sector);
+  groups *= w.pieces;
+  w.groups = (unsigned)groups;
+  *grid = (unsigned)(groups < (1 << 23) ? groups : (1 << 23));     // threads of a launch stay below 2^32
+  return w;
 }
+
+// Cache policy of the row kernels (template arguments LNT, SNT).  A row that is read once is read with the streaming
+// policy (31.0 against 35.8 us on 8192 x 7168; rows that a gather reads again stay cacheable: 55 against 60 us on 16384
+// rows out of 8192).  The activation kernel's input comes straight from a GEMM: up to 192 MB it may still be in the
+// last-level cache and is read through it (16.9 against 17.4 us on 8192 x 4096).  The bytes are written with it when they are more than the last-level cache would hold for the
+// GEMM that reads them next (118 against 133 us on 32768 x 7168), and left cacheable below that (a whole MLP forward
+// pass on 8192 x 7168, 58.7 MB of bytes: 414 against 418 us).
+bool row_bytes_stream(int64_t bytes) { return bytes > ((int64_t)96 << 20); }
 
 // Device scratch a GEMM call with this variant uses: the split-K variants keep the fp32 partial sums of the two
 // halves of the K loop, [2][M_total][N]; the others nothing.
@@ -639,13 +652,15 @@ int gg_fp8_quantize_rows_ex(const void* X, const int32_t* row_src, void* A, floa
   if (K % 128 != 0) return GG_ERR_UNSUPPORTED;
   if (M_total == 0) return GG_OK;
   if (!A || !SA || (!X && T > 0)) return GG_ERR_NULL;
-  int by_xcd = 0;
-  const int64_t grid = row_kernel_grid(M_total, (flags & GG_SA_KMAJOR) != 0, &by_xcd);
-  hipLaunchKernelGGL(gg::gg_quantize_rows_kernel, dim3((unsigned)grid), dim3(gg::Q_THREADS), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(X), row_src,
-                     static_cast<uint8_t*>(A), SA, T, (int)M_total, K, K / 128,
-                     (flags & GG_SA_KMAJOR) ? (int64_t)1 : (int64_t)(K / 128), (flags & GG_SA_KMAJOR) ? M_total : (int64_t)1,
-                     by_xcd);
+  const bool km = (flags & GG_SA_KMAJOR) != 0;
+  unsigned grid;
+  const gg::RowWork rw = row_work(M_total, K / 128, km, 64, &grid);
+  const bool snt = row_bytes_stream(M_total * K);
+  const auto kernel = M_total > T ? (snt ? &gg::gg_quantize_rows_kernel<false, true> : &gg::gg_quantize_rows_kernel<false, false>)
+                                  : (snt ? &gg::gg_quantize_rows_kernel<true, true> : &gg::gg_quantize_rows_kernel<true, false>);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(gg::Q_THREADS), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(X),
+                     row_src, static_cast<uint8_t*>(A), SA, T, (int)M_total, K, K / 128, km ? (int64_t)1 : (int64_t)(K / 128),
+                     km ? M_total : (int64_t)1, rw);
   return hipGetLastError() == hipSuccess ? GG_OK : GG_ERR_HIP;
 }
 
@@ -662,13 +677,14 @@ int gg_fp8_swiglu_quantize_rows_ex(const void* H, void* A, float* SA, void* act_
   if (I % 128 != 0) return GG_ERR_UNSUPPORTED;
   if (M_total == 0) return GG_OK;
   if (!H || !A || !SA) return GG_ERR_NULL;
-  int by_xcd = 0;
-  const int64_t grid = row_kernel_grid(M_total, (flags & GG_SA_KMAJOR) != 0, &by_xcd);
-  hipLaunchKernelGGL(gg::gg_swiglu_quantize_rows_kernel, dim3((unsigned)grid), dim3(gg::Q_THREADS), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(H), static_cast<uint8_t*>(A), SA,
-                     static_cast<uint16_t*>(act_out), (int)M_total, I, I / 128,
-                     (flags & GG_SA_KMAJOR) ? (int64_t)1 : (int64_t)(I / 128), (flags & GG_SA_KMAJOR) ? M_total : (int64_t)1,
-                     by_xcd);
+  const bool km = (flags & GG_SA_KMAJOR) != 0;
+  unsigned grid;
+  const gg::RowWork rw = row_work(M_total, I / 128, km, 32, &grid);
+  const auto kernel = row_bytes_stream(M_total * I) ? &gg::gg_swiglu_quantize_rows_kernel<true, true>
+                      : 4 * M_total * I > ((int64_t)192 << 20) ? &gg::gg_swiglu_quantize_rows_kernel<true, false> : &gg::gg_swiglu_quantize_rows_kernel<false, false>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(gg::Q_THREADS), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(H),
+                     static_cast<uint8_t*>(A), SA, static_cast<uint16_t*>(act_out), (int)M_total, I, I / 128,
+                     km ? (int64_t)1 : (int64_t)(I / 128), km ? M_total : (int64_t)1, rw);
   return hipGetLastError() == hipSuccess ? GG_OK : GG_ERR_HIP;
 }
 

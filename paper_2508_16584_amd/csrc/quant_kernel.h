@@ -9,10 +9,13 @@
 // The two divisions per block, the product and the conversion are the hardware's correctly rounded ones, so the
 // bytes and scales are reproducible bit for bit on the host.
 //
-// Mapping: 16 lanes (one DPP row) own one block: a lane loads 8 bf16 (16 B), the row reduces amax with four
-// row rotations, a lane stores 8 bytes.  A workgroup of 256 threads takes 32 blocks of one row per pass, both
-// loads of a lane issued before any arithmetic; rows are strided over the grid.  HBM-bound: 2K bytes in,
-// K + K/32 out per row.
+// Mapping: 8 lanes own one block.  A lane loads 16 bytes of either half of it (a half is one 128-byte line for the
+// eight lanes), reduces amax over its 16 values and the eight lanes, and after an exchange of 8 bytes with its
+// neighbour stores 16 bytes.  A workgroup of 256 threads takes up to 64 blocks in one pass, all its loads issued before
+// any arithmetic: a piece of one row, or several short rows.  One pass per workgroup: the grid covers the tensor.
+// HBM-bound: 2K bytes in, K + K/32 out per row.  8192 x 7168 gathered: 33.5 us (5.3 TB/s), 16384 x 7168 out of 8192 rows
+// 57 (6.3), 32768 x 7168 118 (6.0); with 16 lanes and 8-byte stores per block, row pairs strided over 8 workgroups per
+// compute unit and no streaming policy they took 40, 72 and 146 us.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -24,143 +27,167 @@ constexpr int Q_THREADS = 256;
 typedef int q_v4i __attribute__((ext_vector_type(4)));
 typedef int q_v2i __attribute__((ext_vector_type(2)));
 
-// max over the 16 lanes of a DPP row, result in every lane
-__device__ __forceinline__ unsigned row16_max(unsigned v) {
-#define GG_ROR(x, n) ((unsigned)__builtin_amdgcn_update_dpp(0, (int)(x), 0x120 + (n), 0xF, 0xF, false))
+// max over the 8 lanes of half a DPP row, result in every lane
+__device__ __forceinline__ unsigned max8(unsigned v) {
   unsigned t;
-  t = GG_ROR(v, 8); v = v > t ? v : t;
-  t = GG_ROR(v, 4); v = v > t ? v : t;
-  t = GG_ROR(v, 2); v = v > t ? v : t;
-  t = GG_ROR(v, 1); v = v > t ? v : t;
-#undef GG_ROR
-  return v;
+  t = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);       // quad_perm [1, 0, 3, 2]
+  v = v > t ? v : t;
+  t = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);       // quad_perm [2, 3, 0, 1]
+  v = v > t ? v : t;
+  t = (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false);      // row_half_mirror: the other quad of the eight
+  return v > t ? v : t;
 }
 
-__device__ __forceinline__ void quantize_block(const q_v4i raw, uint8_t* dst, float* dst_scale, int sub) {
-  float v[8];
-  unsigned u[8];
+// The block quantiser's arithmetic for callers that hold a block's values spread over lanes in a way of their own:
+// amax_bits_of() of every value, reduced by the caller with an integer max, then block_amax() and e4m3x4_of().
+__device__ __forceinline__ unsigned amax_bits_of(float v) {
+  const unsigned u = __builtin_bit_cast(unsigned, v) & 0x7FFFFFFFu;
+  return u > 0x7F800000u ? 0u : u;                             // a NaN (quiet or signalling) counts as zero
+}
+__device__ __forceinline__ float block_amax(unsigned top) {
+  top = top > 0x0D800000u ? top : 0x0D800000u;                 // floor 2^-100: 448 / amax stays finite
+  return __builtin_bit_cast(float, top);
+}
+// four values -> four e4m3 bytes in a dword (value 0 in the low byte); SPECIAL: NaNs and infinities may be among them
+template <bool SPECIAL = true>
+__device__ __forceinline__ int e4m3x4_of(const float* v, float inv) {
+  float y[4];
+  unsigned nan = 0;                                            // 0x7F in the byte of every NaN, whatever its sign or payload
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    v[2 * i] = __builtin_bit_cast(float, raw[i] << 16);
-    v[2 * i + 1] = __builtin_bit_cast(float, raw[i] & (int)0xFFFF0000);
+    const float t = v[i] * inv;
+    if constexpr (SPECIAL) {
+      const bool is_nan = t != t;
+      y[i] = is_nan ? 0.f : __builtin_fminf(__builtin_fmaxf(t, -448.0f), 448.0f);
+      nan |= is_nan ? (0x7Fu << (8 * i)) : 0u;
+    } else {
+      y[i] = __builtin_amdgcn_fmed3f(t, -448.0f, 448.0f);
+    }
   }
-  // |x| of non-NaN floats orders like its bit pattern
+  int w = 0;
+  w = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], w, false);
+  w = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], w, true);
+  return w | (int)nan;
+}
+
+// One block: lane `sub` of its eight holds bf16 columns 8 sub .. + 7 in lo and 64 + 8 sub .. + 7 in hi.
+template <bool SNT>
+__device__ __forceinline__ void quantize_block(const q_v4i lo, const q_v4i hi, uint8_t* dst, float* dst_scale, int sub) {
+  float v[16];
   unsigned top = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    u[i] = __builtin_bit_cast(unsigned, v[i]) & 0x7FFFFFFFu;
-    top = top > u[i] ? top : u[i];
+    const unsigned two = (unsigned)(i < 4 ? lo[i & 3] : hi[i & 3]);
+    v[2 * i] = __builtin_bit_cast(float, two << 16);
+    v[2 * i + 1] = __builtin_bit_cast(float, two & 0xFFFF0000u);
+    const unsigned a0 = (two << 16) & 0x7FFFFFFFu, a1 = two & 0x7FFF0000u;      // |x| of non-NaN values orders like its bit pattern
+    top = top > a0 ? top : a0;
+    top = top > a1 ? top : a1;
   }
   // NaNs and infinities are rare: one wave-uniform branch keeps their handling out of the common path
   const bool special = __builtin_amdgcn_ballot_w64(top >= 0x7F800000u) != 0;
   if (special) {
     top = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const unsigned t = u[i] > 0x7F800000u ? 0u : u[i];     // a NaN (quiet or signalling) counts as zero
+    for (int i = 0; i < 16; ++i) {
+      const unsigned t = amax_bits_of(v[i]);
       top = top > t ? top : t;
     }
   }
-  top = row16_max(top);
-  top = top > 0x0D800000u ? top : 0x0D800000u;               // floor 2^-100: 448 / amax stays finite
-  const float amax = __builtin_bit_cast(float, top);
+  const float amax = block_amax(max8(top));
   const float scale = amax / 448.0f;
   const float inv = 448.0f / amax;
-  int lo = 0, hi = 0;
-  if (!special) {
-    float y[8];
+  int w[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) y[i] = __builtin_amdgcn_fmed3f(v[i] * inv, -448.0f, 448.0f);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
-  } else {
-    float y[8];
-    unsigned nan_lo = 0, nan_hi = 0;                         // 0x7F in the byte of every NaN, whatever its sign or payload
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float t = v[i] * inv;
-      const bool is_nan = t != t;
-      y[i] = is_nan ? 0.f : __builtin_fminf(__builtin_fmaxf(t, -448.0f), 448.0f);
-      if (i < 4) nan_lo |= is_nan ? (0x7Fu << (8 * i)) : 0u;
-      else nan_hi |= is_nan ? (0x7Fu << (8 * (i - 4))) : 0u;
-    }
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], lo, false);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], lo, true);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[4], y[5], hi, false);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(y[6], y[7], hi, true);
-    lo |= (int)nan_lo;
-    hi |= (int)nan_hi;
-  }
-  *(q_v2i*)dst = (q_v2i){lo, hi};
+  for (int d = 0; d < 4; ++d) w[d] = special ? e4m3x4_of(v + 4 * d, inv) : e4m3x4_of<false>(v + 4 * d, inv);
+  // w[0], w[1] are bytes 8 sub .. + 7 of the block and w[2], w[3] bytes 64 + 8 sub .. + 7: an even lane gives the latter
+  // away for its neighbour's former, so that every lane has 16 consecutive bytes
+  const bool odd = sub & 1;
+  const int r0 = __builtin_amdgcn_update_dpp(0, odd ? w[0] : w[2], 0xB1, 0xF, 0xF, false);
+  const int r1 = __builtin_amdgcn_update_dpp(0, odd ? w[1] : w[3], 0xB1, 0xF, 0xF, false);
+  const q_v4i out = odd ? (q_v4i){r0, r1, w[2], w[3]} : (q_v4i){w[0], w[1], r0, r1};
+  q_v4i* const p = (q_v4i*)(dst + (odd ? 64 + 8 * (sub - 1) : 8 * sub));
+  if constexpr (SNT) __builtin_nontemporal_store(out, p);
+  else *p = out;
   if (sub == 0) *dst_scale = scale;
 }
 
-// A workgroup works on two adjacent rows at a time.  Pair t of workgroup b (t = 0, 1, ...):
-//   by_xcd = 0: pair number b + t * grid (pairs dealt out round-robin);
-//   by_xcd = 1 (grid a multiple of 8): the eight rows of a "sector" (8 adjacent rows: with K-block-major scales their
-//     eight 4-byte scale stores of one K block make up one 32-byte piece of memory) go to four workgroups in
-//     neighbouring slots of ONE XCD (workgroup b runs on XCD b % 8), which run at the same time, so the pieces leave
-//     that XCD's L2 as whole writes.  Dealt out round-robin they come from four XCDs, and each L2 writes a masked
-//     32-byte piece for its 8 bytes.
-// pair_of() returns the pair number, -1 when the workgroup is done, -2 for a pair to skip.  The 2 * KB blocks of a
-// pair are numbered through and
-// taken 32 per pass, so that short rows (KB <= 16) still fill both load slots of every lane.
-__device__ __forceinline__ int64_t pair_of(int64_t t, int64_t npairs, int by_xcd) {
-  const int64_t b = blockIdx.x, grid = gridDim.x;
-  if (!by_xcd) {
-    const int64_t p = b + t * grid;
-    return p < npairs ? p : -1;
-  }
-  const int64_t u = b / 8 + t * (grid / 8);          // position in this XCD's list of pairs: 4 per sector
-  const int64_t sector = (u / 4) * 8 + b % 8;
-  const int64_t p = sector * 4 + u % 4;
-  if (sector * 4 >= npairs) return -1;               // sectors only grow with t
-  return p < npairs ? p : -2;                        // a pair past the end inside the last sector
-}
+// Work of a workgroup: up to 64 blocks, `rows` adjacent rows of `blocks` blocks (rows > 1 only where a row has few).
+// Which rows depends on the storage order of the scales:
+//   sector == 0: workgroup b takes piece b of the row-major list of pieces;
+//   sector == 8 or 32: with K-block-major scales the 4-byte scale stores of 8 adjacent rows make up a 32-byte piece of
+//     memory (of 32 rows a line).  Runs of `sector` adjacent row groups go to ONE XCD (workgroup b runs on XCD b % 8) in
+//     neighbouring slots, which run at about the same time, so that they leave that XCD's L2 together; dealt out one by
+//     one, every XCD's L2 would write a masked piece of its own.
+struct RowWork {
+  int rows;          // rows of one workgroup
+  int blocks;        // blocks of a row it takes
+  int pieces;        // pieces of a row: ceil(KB / blocks)
+  unsigned magic;    // ceil(2^16 / blocks): v / blocks = v * magic >> 16 for v < 64
+  int sector;
+  unsigned groups;   // workgroups' worth of work: groups of rows x pieces, rounded up to whole runs of sectors
+};
 
-struct RowPairSlot {
-  bool valid;     // this 16-lane group has a block in this pass
+struct RowSlot {
+  bool valid;
   int row, blk;
 };
-__device__ __forceinline__ RowPairSlot row_pair_slot(int v, int KB, int r, int r2, int M_total) {
-  const bool second = v >= KB;
-  RowPairSlot s;
-  s.row = second ? r2 : r;
-  s.blk = v - (second ? KB : 0);
-  s.valid = v < 2 * KB && s.row < M_total;
+// slot v (of rows * blocks) of work item `id`
+__device__ __forceinline__ RowSlot row_slot(const RowWork& rw, unsigned id, int v, int KB, int M_total) {
+  unsigned g = id, piece = 0;
+  if (rw.pieces > 1) {
+    g = id / (unsigned)rw.pieces;
+    piece = id - g * (unsigned)rw.pieces;
+  }
+  if (rw.sector) {
+    const unsigned x = g & 7, i = g >> 3, n = (unsigned)rw.sector;
+    g = (i / n) * (8 * n) + x * n + i % n;
+  }
+  const int rr = (int)((unsigned)v * rw.magic >> 16);
+  const int64_t row = (int64_t)g * rw.rows + rr;
+  RowSlot s;
+  s.blk = (int)piece * rw.blocks + (v - rr * rw.blocks);
+  s.valid = v < rw.rows * rw.blocks && row < M_total && s.blk < KB;
+  s.row = (int)row;
   return s;
 }
 
+template <bool NT>
+__device__ __forceinline__ q_v4i load_16(const uint16_t* p) {
+  if constexpr (NT) return __builtin_nontemporal_load((const q_v4i*)p);
+  return *(const q_v4i*)p;
+}
+
+// LNT, SNT: the rows are read, the bytes written, with the streaming policy (see row_bytes_stream() in gg_fp8.hip)
+template <bool LNT, bool SNT>
 __global__ void __launch_bounds__(Q_THREADS) gg_quantize_rows_kernel(const uint16_t* __restrict__ X,
                                                                      const int32_t* __restrict__ row_src,
                                                                      uint8_t* __restrict__ A, float* __restrict__ SA,
                                                                      int64_t T, int M_total, int K, int KB,
                                                                      int64_t sa_rs, int64_t sa_ks,     // SA[row * sa_rs + blk * sa_ks]
-                                                                     int by_xcd) {
-  const int grp = threadIdx.x >> 4, sub = threadIdx.x & 15;
-  const int64_t npairs = ((int64_t)M_total + 1) / 2;
-  for (int64_t t = 0;; ++t) {
-    const int64_t pr = pair_of(t, npairs, by_xcd);
-    if (pr == -1) break;
-    if (pr < 0) continue;
-    const int64_t r64 = 2 * pr;
-    const int r = (int)r64;
-    const int r2 = r64 + 1 < M_total ? (int)(r64 + 1) : M_total;     // M_total = no second row
-    const int64_t s1 = row_src ? (int64_t)row_src[r] : (int64_t)r;
-    const int64_t s2 = r2 < M_total ? (row_src ? (int64_t)row_src[r2] : (int64_t)r2) : -1;
-    for (int v0 = 0; v0 < 2 * KB; v0 += 32) {
-      const RowPairSlot a = row_pair_slot(v0 + grp, KB, r, r2, M_total);            // uniform over the 16 lanes of a row
-      const RowPairSlot b = row_pair_slot(v0 + 16 + grp, KB, r, r2, M_total);
-      const int64_t sa = a.row == r ? s1 : s2, sb = b.row == r ? s1 : s2;
-      // a source outside [0, T) stands for a row of zeros
-      q_v4i rawA = {0, 0, 0, 0}, rawB = {0, 0, 0, 0};
-      if (a.valid && sa >= 0 && sa < T) rawA = *(const q_v4i*)(X + sa * K + a.blk * 128 + sub * 8);
-      if (b.valid && sb >= 0 && sb < T) rawB = *(const q_v4i*)(X + sb * K + b.blk * 128 + sub * 8);
-      if (a.valid) quantize_block(rawA, A + (int64_t)a.row * K + a.blk * 128 + sub * 8, SA + a.row * sa_rs + a.blk * sa_ks, sub);
-      if (b.valid) quantize_block(rawB, A + (int64_t)b.row * K + b.blk * 128 + sub * 8, SA + b.row * sa_rs + b.blk * sa_ks, sub);
+                                                                     RowWork rw) {
+  const int grp = threadIdx.x >> 3, sub = threadIdx.x & 7;
+  for (unsigned id = blockIdx.x; id < rw.groups; id += gridDim.x) {
+    RowSlot s[2];
+    int64_t src[2];
+    q_v4i lo[2], hi[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      s[u] = row_slot(rw, id, u * 32 + grp, KB, M_total);                  // uniform over the 8 lanes of a block
+      src[u] = !s[u].valid ? -1 : row_src ? (int64_t)row_src[s[u].row] : (int64_t)s[u].row;
     }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      lo[u] = hi[u] = (q_v4i){0, 0, 0, 0};
+      if (src[u] >= 0 && src[u] < T) {                                     // a source outside [0, T) stands for a row of zeros
+        const uint16_t* p = X + src[u] * K + s[u].blk * 128 + sub * 8;
+        lo[u] = load_16<LNT>(p);
+        hi[u] = load_16<LNT>(p + 64);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (s[u].valid) quantize_block<SNT>(lo[u], hi[u], A + (int64_t)s[u].row * K + s[u].blk * 128, SA + s[u].row * sa_rs + s[u].blk * sa_ks, sub);
   }
 }
 
@@ -168,7 +195,7 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_rows_kernel(const uint1
 // (columns [0, I): gate projection, [I, 2I): up projection) ->
 //     act = bf16_rne( silu(gate) * up ),  silu(g) = g / (1 + exp(-g))   in fp32
 // and then exactly quantize_block on the bf16 bits of act.  act is also written out when act_out is not null.
-// Same mapping: 16 lanes own one block of 128 activation columns, a lane loads 8 gate and 8 up values.
+// Same mapping: 8 lanes own one block of 128 activation columns, a lane loads 16 gate and 16 up values.
 // two (gate, up) pairs, each a dword of two bf16 -> one dword of two bf16 activations
 __device__ __forceinline__ int swiglu2(const int g_raw, const int u_raw) {
   float g[2] = {__builtin_bit_cast(float, g_raw << 16), __builtin_bit_cast(float, g_raw & (int)0xFFFF0000)};
@@ -195,35 +222,6 @@ __device__ __forceinline__ q_v4i swiglu8(const q_v4i g_raw, const q_v4i u_raw) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) out[i] = swiglu2(g_raw[i], u_raw[i]);
   return out;
-}
-
-// The block quantiser's arithmetic for callers that hold a block's values spread over lanes in another way than
-// quantize_block's 16 x 8: amax_bits_of() of every value, reduced by the caller with an integer max, then
-// block_scale() and e4m3_of().  Same results as quantize_block, bit for bit (its fast path and its NaN/inf path
-// agree on ordinary values; this is the general path throughout).
-__device__ __forceinline__ unsigned amax_bits_of(float v) {
-  const unsigned u = __builtin_bit_cast(unsigned, v) & 0x7FFFFFFFu;
-  return u > 0x7F800000u ? 0u : u;                             // a NaN counts as zero
-}
-__device__ __forceinline__ float block_amax(unsigned top) {
-  top = top > 0x0D800000u ? top : 0x0D800000u;                 // floor 2^-100
-  return __builtin_bit_cast(float, top);
-}
-// four values -> four e4m3 bytes in a dword (value 0 in the low byte)
-__device__ __forceinline__ int e4m3x4_of(const float* v, float inv) {
-  float y[4];
-  unsigned nan = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float t = v[i] * inv;
-    const bool is_nan = t != t;
-    y[i] = is_nan ? 0.f : __builtin_fminf(__builtin_fmaxf(t, -448.0f), 448.0f);
-    nan |= is_nan ? (0x7Fu << (8 * i)) : 0u;
-  }
-  int w = 0;
-  w = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], w, false);
-  w = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], w, true);
-  return w | (int)nan;
 }
 
 // The producer of the weight-gradient GEMM's operands: the same block quantiser ALONG THE TOKENS, with the transpose
@@ -297,29 +295,12 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
           m = m > a ? m : a;
         }
       }
-      unsigned o;
-      o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xF, 0xF, false);       // quad_perm [1, 0, 3, 2]
-      m = m > o ? m : o;
-      o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xF, 0xF, false);       // quad_perm [2, 3, 0, 1]
-      m = m > o ? m : o;
-      o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x141, 0xF, 0xF, false);      // row_half_mirror: the other quad of the eight
-      m = m > o ? m : o;
-      const float amax = block_amax(m << 16);
+      const float amax = block_amax(max8(m) << 16);
       scale[f] = amax / 448.0f;
       const float inv = 448.0f / amax;
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        if (!special) {
-          float y[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = __builtin_amdgcn_fmed3f(v[f][4 * d + e] * inv, -448.0f, 448.0f);
-          int wd = 0;
-          wd = __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], wd, false);
-          wd = __builtin_amdgcn_cvt_pk_fp8_f32(y[2], y[3], wd, true);
-          out[f][d] = wd;
-        } else {
-          out[f][d] = e4m3x4_of(v[f] + 4 * d, inv);
-        }
+        out[f][d] = special ? e4m3x4_of(v[f] + 4 * d, inv) : e4m3x4_of<false>(v[f] + 4 * d, inv);
       }
     }
     // M_total is a multiple of 16: a 16-byte piece of a row of XT exists whole or not at all
@@ -334,48 +315,26 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
   }
 }
 
+template <bool LNT, bool SNT>
 __global__ void __launch_bounds__(Q_THREADS) gg_swiglu_quantize_rows_kernel(const uint16_t* __restrict__ H,
                                                                             uint8_t* __restrict__ A, float* __restrict__ SA,
                                                                             uint16_t* __restrict__ act_out,
                                                                             int M_total, int I, int IB,
                                                                             int64_t sa_rs, int64_t sa_ks,     // SA[row * sa_rs + blk * sa_ks]
-                                                                            int by_xcd) {
-  const int grp = threadIdx.x >> 4, sub = threadIdx.x & 15;
-  const int64_t npairs = ((int64_t)M_total + 1) / 2;
-  for (int64_t t = 0;; ++t) {
-    const int64_t pr = pair_of(t, npairs, by_xcd);
-    if (pr == -1) break;
-    if (pr < 0) continue;
-    const int64_t r64 = 2 * pr;
-    const int r = (int)r64;
-    const int r2 = r64 + 1 < M_total ? (int)(r64 + 1) : M_total;
-    for (int v0 = 0; v0 < 2 * IB; v0 += 32) {
-      const RowPairSlot a = row_pair_slot(v0 + grp, IB, r, r2, M_total);
-      const RowPairSlot b = row_pair_slot(v0 + 16 + grp, IB, r, r2, M_total);
-      q_v4i gA = {0, 0, 0, 0}, uA = {0, 0, 0, 0}, gB = {0, 0, 0, 0}, uB = {0, 0, 0, 0};
-      if (a.valid) {
-        const uint16_t* src = H + (int64_t)a.row * 2 * I + a.blk * 128 + sub * 8;
-        gA = *(const q_v4i*)src;
-        uA = *(const q_v4i*)(src + I);
-      }
-      if (b.valid) {
-        const uint16_t* src = H + (int64_t)b.row * 2 * I + b.blk * 128 + sub * 8;
-        gB = *(const q_v4i*)src;
-        uB = *(const q_v4i*)(src + I);
-      }
-      if (a.valid) {
-        const q_v4i act = swiglu8(gA, uA);
-        const int64_t o = (int64_t)a.row * I + a.blk * 128 + sub * 8;
-        if (act_out) *(q_v4i*)(act_out + o) = act;
-        quantize_block(act, A + o, SA + a.row * sa_rs + a.blk * sa_ks, sub);
-      }
-      if (b.valid) {
-        const q_v4i act = swiglu8(gB, uB);
-        const int64_t o = (int64_t)b.row * I + b.blk * 128 + sub * 8;
-        if (act_out) *(q_v4i*)(act_out + o) = act;
-        quantize_block(act, A + o, SA + b.row * sa_rs + b.blk * sa_ks, sub);
-      }
+                                                                            RowWork rw) {
+  const int grp = threadIdx.x >> 3, sub = threadIdx.x & 7;
+  for (unsigned id = blockIdx.x; id < rw.groups; id += gridDim.x) {
+    const RowSlot s = row_slot(rw, id, grp, IB, M_total);
+    if (!s.valid) continue;
+    const uint16_t* p = H + (int64_t)s.row * 2 * I + s.blk * 128 + sub * 8;
+    const q_v4i g0 = load_16<LNT>(p), g1 = load_16<LNT>(p + 64), u0 = load_16<LNT>(p + I), u1 = load_16<LNT>(p + I + 64);
+    const q_v4i lo = swiglu8(g0, u0), hi = swiglu8(g1, u1);
+    const int64_t o = (int64_t)s.row * I + s.blk * 128;
+    if (act_out) {
+      __builtin_nontemporal_store(lo, (q_v4i*)(act_out + o + sub * 8));
+      __builtin_nontemporal_store(hi, (q_v4i*)(act_out + o + 64 + sub * 8));
     }
+    quantize_block<SNT>(lo, hi, A + o, SA + s.row * sa_rs + s.blk * sa_ks, sub);
   }
 }
 
