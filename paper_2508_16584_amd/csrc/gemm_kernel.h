@@ -120,13 +120,21 @@ struct GemmCfg {
   static constexpr int B_BYTES = BN * 128;
   static constexpr int SA_WAVES = (BM + 63) / 64;   // one 64-lane dword DMA fetches the scales of 64 rows
   static constexpr int SA_ROWS = SA_WAVES * 64;
-  static constexpr int SA_BYTES = SA_ROWS * 4;
   static constexpr int SB_BYTES = 256;         // BN/128 scales of B per K block, replicated over one wave-wide DMA
-  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES + SA_BYTES + SB_BYTES;
+  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES + SB_BYTES;
+  // LDS for the scales of A (see "activation scales" in the kernel): chunks of four K blocks, of which STAGES consecutive
+  // K blocks take at most SA_BUFS (the last chunk of a tile may hold a single block); where those do not fit beside the
+  // ring (160 x 256), one slot of one K block per ring buffer.
+  static constexpr int SA_SLOT = SA_ROWS * 4, SA_CHUNK = SA_ROWS * 16;
+  static constexpr int SA_BUFS = STAGES_ <= 2 ? 2 : STAGES_ <= 6 ? 3 : 4;
+  static constexpr bool WIDE = !XPF_ && STAGES_ * STAGE_BYTES + SA_BUFS * SA_CHUNK + 256 <= 160 * 1024;
+  static constexpr int SA_BASE = STAGES_ * STAGE_BYTES;
+  static constexpr int DUMP_BASE = SA_BASE + (WIDE ? SA_BUFS * SA_CHUNK : STAGES_ * SA_SLOT);      // 256 bytes nobody reads (empty fetches)
+  static_assert(STAGES_ <= 8, "four chunks");
   static constexpr int SB_WAVE = NW - 1;      // the wave that fetches them
   static constexpr int MFMAS = (BM / WM / 16) * (BN / WN / 16);   // MFMAs per wave per K block
   static constexpr int PIPE = MFMAS < PIPE_ ? MFMAS : PIPE_;               // MFMAs in flight before their FMAs are issued
-  static constexpr int LDS_BYTES = STAGES * STAGE_BYTES;
+  static constexpr int LDS_BYTES = DUMP_BASE + (WIDE ? 256 : 0);
   // cross-block operand prefetch with a mid-stream barrier (see the kernel): needs a ring of 3 and an even TM
   static constexpr bool XPF = XPF_;
   static_assert(!XPF_ || (STAGES_ >= 3 && (BM_ / WM_ / 16) % 2 == 0), "XPF needs a ring of 3 buffers and an even TM");
@@ -238,6 +246,14 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   // byte k_rem of the block belong to the next row; those lanes fetch from an out-of-range offset, i.e. zeros
   const bool a_tail = RAGGED && ((pch ^ keyA_ld) << 4) >= a.k_rem;
   const bool b_tail = RAGGED && ((pch ^ keyB_ld) << 4) >= a.k_rem;
+  // Activation scales.  Row-major, the scales of a K block lie one row pitch apart, a cache line each: fetched 4 bytes
+  // per row and K block they are as many requests as the A tile itself, for 1/32 of the bytes.  They are fetched 16
+  // bytes (four K blocks) per row every fourth K block instead ("wide"; a DMA takes any 4-byte aligned source, and what a
+  // piece at the end of a row takes from the next row is not used): a weight stream with 128 rows of A beside it
+  // reaches 5.6 TB/s like that, 5.1 with 4-byte fetches and 5.7 without any scales (128 x 256 tile on 52 groups of 128
+  // rows, N = 4096, K = 7168: 332 -> 306 us, 301 K-block-major; 64 groups of 32 rows on average: 315 -> 296 us).
+  // K-block-major, the scales of a K block are a few lines and fetched per K block ("narrow").
+  const bool wide = Cfg::WIDE && !a.sa_kmajor;
   const int vSA = (w * 64 + l) * a.sa_row_stride;
   const int vSB = (l < BN / 128 ? l : BN / 128 - 1) * KB * 4;        // lane -> which 128-wide N block of the tile
 
@@ -254,8 +270,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   const int aRd1 = (wm * WTM + r) * 128 + (((2 * q + 1) ^ keyA_rd) << 4);
   const int bRd0 = Cfg::A_BYTES + (wn * WTN + rowB_rd) * 128 + (((2 * q) ^ keyB_rd) << 4);
   const int bRd1 = Cfg::A_BYTES + (wn * WTN + rowB_rd) * 128 + (((2 * q + 1) ^ keyB_rd) << 4);
-  const int saRd = Cfg::A_BYTES + Cfg::B_BYTES + (wm * WTM + r) * 4;
-  const int sbRd = Cfg::A_BYTES + Cfg::B_BYTES + Cfg::SA_BYTES + ((wn * WTN) >> 7) * 4;
+  const int saRd = Cfg::SA_BASE + (wm * WTM + r) * (wide ? 16 : 4);      // + the K block's place (sa_place) + mt * sa_mt
+  const int sa_mt = wide ? 256 : 64;
+  const int sbRd = Cfg::A_BYTES + Cfg::B_BYTES + ((wn * WTN) >> 7) * 4;
 
   // ---- persistent walk over the tile list ---------------------------------------------------------
   // A workgroup knows its next tile while it works on the current one: in the ring-of-buffers path without the
@@ -342,6 +359,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   int rot = k_start(cur);
   bool primed = false;      // the first STAGES-1 K blocks of `cur` were already fetched by the previous tile
   int stage = 0;            // LDS buffer of the current K block; runs on across tiles
+  constexpr int SA_TOTAL = Cfg::SA_BUFS * Cfg::SA_CHUNK;
+  int ch_fetch = SA_TOTAL - Cfg::SA_CHUNK, ch_read = ch_fetch;     // wide: chunk of the newest fetch, of the current K block; both run on
+  auto next_chunk = [&](int c) __attribute__((always_inline)) -> int { return c + Cfg::SA_CHUNK == SA_TOTAL ? 0 : c + Cfg::SA_CHUNK; };
   for (int it = 0;; ++it) {
     const int n0 = cur.n0, rows_valid = cur.rows_valid;
     const int n_rem = N - n0;
@@ -375,14 +395,21 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
           __builtin_amdgcn_raw_ptr_buffer_load_lds(dB, GG_LDS_PTR(st + Cfg::A_BYTES + (w + i * NW) * 1024), 16, vB, i * (NW * 8) * K + kb * 128, 0, kBAux);
       }
     };
-    auto dma_head = [&](int kb_l, int stg) {   // everything that is not issued inside the stream
+    // everything that is not issued inside the stream; on: the K block will be read (see `prefetch`)
+    auto dma_head = [&](int kb_l, int stg, bool on) {
       const int kb = k_wrapped(kb_l + rot, KB);
       const bool last = kb == KB - 1;
       uint8_t* st = lds + stg * Cfg::STAGE_BYTES;
-      if (w < Cfg::SA_WAVES)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(st + Cfg::A_BYTES + Cfg::B_BYTES + w * 256), 4, vSA, kb * a.sa_kb_stride, 0, 0);
+      const bool chunk_start = wide && on && (kb_l & 3) == 0;
+      if (chunk_start) ch_fetch = next_chunk(ch_fetch);
+      if (w < Cfg::SA_WAVES) {       // one fetch per K block either way (the waits count them)
+        if (chunk_start)
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + Cfg::SA_BASE + ch_fetch + w * 1024), 16, vSA, kb * 4, 0, 0);
+        else
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + (wide ? Cfg::DUMP_BASE : Cfg::SA_BASE + stg * Cfg::SA_SLOT + w * 256)), 4, wide ? GG_OOB_OFFSET : vSA, kb * a.sa_kb_stride, 0, 0);
+      }
       if (w == Cfg::SB_WAVE)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(dSB, GG_LDS_PTR(st + Cfg::A_BYTES + Cfg::B_BYTES + Cfg::SA_BYTES), 4, vSB, kb * 4, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(dSB, GG_LDS_PTR(st + Cfg::A_BYTES + Cfg::B_BYTES), 4, vSB, kb * 4, 0, 0);
       if constexpr (Cfg::A_SLABS % NW != 0) {
         if (w < Cfg::A_SLABS % NW)
           __builtin_amdgcn_raw_ptr_buffer_load_lds(dA, GG_LDS_PTR(st + (w + A_FULL * NW) * 1024), 16, (RAGGED && last && a_tail) ? GG_OOB_OFFSET : vA + A_FULL * (NW * 8) * K, kb * 128, 0, 0);
@@ -395,7 +422,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
       }
     };
     auto dma_all = [&](int kb, int stg) {
-      dma_head(kb, stg);
+      dma_head(kb, stg, true);
       static_for<0, NDMA_ALL>([&](auto ic) { dma_tile(ic, kb, stg); });
     };
 
@@ -445,7 +472,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) bfr[j] = read_b(j, st);
         afr[0] = read_a(0, st);
-        sa_c = *(const float*)(st + saRd);
+        sa_c = *(const float*)(lds + saRd);
         sb_c = *(const float*)(st + sbRd);
       }
 
@@ -467,11 +494,11 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
             constexpr int mt = t / TN, j = t % TN;
             if constexpr (j == 0 && mt + 1 < TM) {
               afr[(mt + 1) & 1] = read_a(mt + 1, st);
-              s[mt + 1] = *(const float*)(st + saRd + (mt + 1) * 64) * sb_c;
+              s[mt + 1] = *(const float*)(lds + saRd + stage * Cfg::SA_SLOT + (mt + 1) * 64) * sb_c;
             }
             if constexpr (j == 0 && mt + 1 == TM && !LAST) {
               afr[0] = read_a(0, st1);                      // TM is even: slot 0 is free during the last block
-              sa_n = *(const float*)(st1 + saRd);
+              sa_n = *(const float*)(lds + saRd + stage1 * Cfg::SA_SLOT);
               sb_n = *(const float*)(st1 + sbRd);
             }
             p[t] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(bfr[j], afr[mt & 1], (v4f){0.f, 0.f, 0.f, 0.f}, 0, 0, 0, 0, 0, 0);
@@ -511,7 +538,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         if constexpr (ISSUE) {
-          dma_head(kb + STAGES - 1, stageN);
+          dma_head(kb + STAGES - 1, stageN, true);
           static_for<NDMA_X, NDMA_ALL>([&](auto ic) { dma_tile(ic, kb + STAGES - 1, stageN); });
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -584,13 +611,15 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
         afr[0] = read_a(0, st);
         const float sb = *(const float*)(st + sbRd);
         float sa[TM];
-        sa[0] = *(const float*)(st + saRd);
+        if (wide && (kb & 3) == 0) ch_read = next_chunk(ch_read);
+        const uint8_t* const sa_place = lds + saRd + (wide ? ch_read + (kb & 3) * 4 : stage * Cfg::SA_SLOT);
+        sa[0] = *(const float*)sa_place;
 #pragma unroll
         for (int j = 1; j < TN; ++j) bfr[j] = read_b(j, st);
 #pragma unroll
-        for (int mt = 1; mt < TM; ++mt) sa[mt] = *(const float*)(st + saRd + mt * 64);
+        for (int mt = 1; mt < TM; ++mt) sa[mt] = *(const float*)(sa_place + mt * sa_mt);
         if constexpr (ISSUE) {
-          dma_head(kb_new, nstage);
+          dma_head(kb_new, nstage, MODE == 1 || prefetch);
           static_for<NDMA_STREAM, NDMA_ALL>([&](auto ic) { dma_tile(ic, kb_new, nstage); });
         }
         __builtin_amdgcn_sched_barrier(0);   // the reads above keep their order; the stream below is ordered by hand

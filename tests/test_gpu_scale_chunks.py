@@ -1,0 +1,52 @@
+"""Row-major activation scales are fetched four K blocks at a time: numbers of K blocks around the multiples of four
+(a last chunk of one, two, three blocks; fewer blocks than the ring has buffers), several tiles per workgroup so that
+chunks run on from tile to tile.  The K-block-major order is fetched per K block and must give the same bits; one shape
+is checked against the oracle as well."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2508_16584_amd as gg
+from oracle import gg_oracle as orc
+from gg_testlib import assert_parity, bits_of
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def problem(sizes, N, K, seed):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    M, G, KB, NB = int(sum(sizes)), len(sizes), -(-K // 128), -(-N // 128)
+    A = torch.randint(0, 256, (M, K), generator=gen, device=DEV, dtype=torch.uint8) & 0xBF       # no NaN codes
+    B = torch.randint(0, 256, (G, N, K), generator=gen, device=DEV, dtype=torch.uint8) & 0xBF
+    SA = torch.rand((M, KB), generator=gen, device=DEV) + 0.5
+    SB = torch.rand((G, NB, KB), generator=gen, device=DEV) + 0.5
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)).to(DEV)
+    return A, SA, B, SB, off
+
+
+@pytest.mark.parametrize("K", [128, 256, 384, 512, 640, 1152, 1280, 1408, 1424])
+def test_row_major_equals_kmajor_bitwise(K):
+    sizes, N = [170, 0, 330, 40], 16384
+    A, SA, B, SB, off = problem(sizes, N, K, K)
+    SAk = SA.t().contiguous()
+    want = None
+    for v in [-1] + list(range(gg.num_variants())):
+        name = gg.variant_name(v) if v >= 0 else "auto"
+        try:
+            row = gg.grouped_gemm(A, SA, B, SB, off, variant=v)
+            km = gg.grouped_gemm(A, SAk, B, SB, off, variant=v, sa_kmajor=True)
+        except gg.GGError:
+            continue                                    # a variant that does not take this K
+        assert torch.equal(row.view(torch.int16), km.view(torch.int16)), name
+        if "-rbk" not in name and "-k2" not in name:    # those add in an order of their own
+            want = row if want is None else want
+            assert torch.equal(row.view(torch.int16), want.view(torch.int16)), name
+
+
+def test_row_major_against_the_oracle():
+    sizes, N, K = [20, 3, 70], 512, 640
+    dev = problem(sizes, N, K, 9)
+    ref = orc.grouped_gemm(*(t.cpu().numpy() for t in dev), with_abs_sum=True)
+    assert_parity(bits_of(gg.grouped_gemm(*dev)), ref, empirical=False, what="five K blocks")
