@@ -24,7 +24,7 @@
 // pipeline and end with an idle one).  A wave holds the 4 + 4 operand fragments and the scales of the block it
 // multiplies in registers and refills them from the next block's buffer while it multiplies, and 64 x 64 fp32
 // accumulators; one v_mfma_f32_16x16x128_f8f6f4 from zero per scale block (dY^T fragment first, and the features
-// permuted on their way into LDS: an output row's 16 lanes then hold 32 consecutive features, two each), then
+// permuted on their way into LDS: an output row's 16 lanes then hold 64 consecutive features, four each), then
 // acc += p * (sdy * sx) with sdy one of the lane's four dY^T rows and sx the lane's feature: 8 vector instructions
 // per matrix instruction (the factor differs per output element, not per lane as in the forward pass).
 #pragma once
@@ -138,9 +138,9 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   const int slab_row = w * 8 + lrow;                               // + 64 i
   const int vRow = slab_row * M + ((pch ^ swz_key_a(slab_row)) << 4);   // key(row + 64 i) == key(row)
   // Features change places on the way into LDS: slot 16 f + r of a wave's 64 features (fragment f, row r) holds
-  // feature 32 (f / 2) + 2 r + f % 2, so that the lane of row r has two neighbouring features in the accumulators of
-  // a fragment pair and the 16 lanes of an output row write 128 consecutive bytes.
-  auto feature_of_slot = [](int s) { return 32 * (s >> 5) + 2 * (s & 15) + ((s >> 4) & 1); };
+  // feature 4 r + f, so that the lane of row r has four neighbouring features in the accumulators of the four
+  // fragments and the 16 lanes of an output row write its 64 features with one store of 16 (bfloat16: 8) bytes each.
+  auto feature_of_slot = [](int s) { return 64 * (s >> 6) + 4 * (s & 15) + ((s >> 4) & 3); };
   const int vRowX = feature_of_slot(slab_row) * M + ((pch ^ swz_key_a(slab_row)) << 4);
   // scale fetch, one per wave: waves 0..3 the scales of 64 features each, waves 4, 5 those of 64 dY^T rows each,
   // waves 6, 7 an out-of-range offset into a dump area (every wave issues the same number of fetches)
@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   // One token block out of the registers, while they are refilled from `nx` (the LDS buffer of the following block).
   // Where the block holds tokens before the group's first or from the group's end on (it is the group's first or
   // last block), their bytes are cleared in both operands first.
-  auto block = [&](int first, int lo, int hi, const uint8_t* nx, uint8_t* fst, v2f (&acc)[2][4][4]) __attribute__((always_inline)) {   // first: the block's first token; fst: the buffer the prepared fetches go to
+  auto block = [&](int first, int lo, int hi, const uint8_t* nx, uint8_t* fst, v4f (&acc)[4][4]) __attribute__((always_inline)) {   // first: the block's first token; fst: the buffer the prepared fetches go to
     const bool cut_lo = !(TIMING & kWgNoMask) && lo > first, cut_hi = !(TIMING & kWgNoMask) && hi < first + 128;
     if (cut_lo || cut_hi) {
       const int lo4 = 4 * (lo - first - 32 * q), hi4 = 4 * (hi - first - 32 * q);    // valid tokens of the block: [lo - first, hi - first)
@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
       if constexpr (t >= 2) {
         constexpr int u = t - 2, nf = u / 4, kf = u % 4;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[kf >> 1][nf][i][kf & 1] += p[u][i] * (sy[nf][i] * sx[kf]);
+        for (int i = 0; i < 4; ++i) acc[nf][i][kf] += p[u][i] * (sy[nf][i] * sx[kf]);
       }
       if constexpr (!(TIMING & kWgNoFetch) && t % 2 == 1 && t / 2 < Cfg::NDMA) fetch_piece(std::integral_constant<int, t / 2>{}, fst);
       if constexpr (!(TIMING & kWgNoLdsReads)) {
@@ -281,11 +281,9 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
     __builtin_amdgcn_sched_barrier(0);
     // the accumulators are "used" here, so that every update above lands in the accumulator's own register
 #pragma unroll
-    for (int pr = 0; pr < 2; ++pr)
+    for (int nf = 0; nf < 4; ++nf)
 #pragma unroll
-      for (int nf = 0; nf < 4; ++nf)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(acc[pr][nf][i]));
+      for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(acc[nf][i]));
   };
 
   // ---- ring of 3 LDS buffers + the registers: while block b is multiplied out of the registers, block b + 1 has
@@ -304,19 +302,18 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
     sy[f] = *(const v4f*)(lds + syRd + f * 64);
   }
   int stage = 0;            // the buffer the block in the registers came from
-  int st_prev = 0, st_prev2 = 0;   // batches of 32 stores issued since the last top of a step / between the two before
+  int st_prev = 0, st_prev2 = 0;   // batches of 16 stores issued since the last top of a step / between the two before
   // The top of a step.  This wave has read all of the block it multiplies next, and its part of the following block
   // has landed: those fetches were issued two steps ago; newer are the fetches of the last step and the stores of
   // the tiles finished since, which may all stay in flight (vector memory operations of a wave complete in the order
   // they were issued; the counter holds 63 and never gets there: no batch of stores begins with more than 31
-  // outstanding and no step's fetches with more than 56, and with two batches and a fetch behind it the awaited fetch
-  // cannot be among 56 outstanding operations).
+  // outstanding, and with three batches behind it the awaited fetch cannot be among them).
   auto top = [&]() __attribute__((always_inline)) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const int batches = st_prev + st_prev2;
     if (batches == 0) wait_vmcnt<Cfg::NDMA>();
-    else if (batches == 1) wait_vmcnt<Cfg::NDMA + 32>();
-    else wait_vmcnt<63 - Cfg::NDMA>();          // room for this step's fetches
+    else if (batches == 1) wait_vmcnt<Cfg::NDMA + 16>();
+    else wait_vmcnt<Cfg::NDMA + 32>();
     st_prev2 = st_prev;
     st_prev = 0;
     if constexpr (!(TIMING & kWgNoBarrier)) __builtin_amdgcn_s_barrier();       // ... and everybody's; nobody reads the buffer of the coming block any more
@@ -326,41 +323,41 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   for (int it = 0;; ++it) {
     const Tile cur = tile_at(it);
     if (!cur.valid) break;
-    v2f acc[2][4][4];             // [pair of feature fragments][dY^T fragment][row 4 q + i]: two neighbouring features
+    v4f acc[4][4];                // [dY^T fragment][row 4 q + i]: four neighbouring features
 #pragma unroll
-    for (int pr = 0; pr < 2; ++pr)
+    for (int nf = 0; nf < 4; ++nf)
 #pragma unroll
-      for (int nf = 0; nf < 4; ++nf)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[pr][nf][i] = (v2f){0.f, 0.f};
+      for (int i = 0; i < 4; ++i) acc[nf][i] = (v4f){0.f, 0.f, 0.f, 0.f};
     for (int s = 0; s < cur.steps; ++s) {
       top();
       const int next_stage = stage == 2 ? 0 : stage + 1;
       block((cur.j0 + s) * 128, cur.lo, cur.hi, lds + next_stage * Cfg::STAGE_BYTES, lds + stage * Cfg::STAGE_BYTES, acc);
       stage = next_stage;
     }
-    // ---- epilogue: fp32 through a view of the tile, 8 bytes per lane: the 16 lanes of a dY^T row write 128
-    // consecutive bytes (with the features in a lane's registers and 16 bytes per lane, neighbouring lanes would write
-    // to different rows and every lane's piece would be a request of its own: a quarter of the store rate).  Written
-    // once and never read here, so the stores carry the streaming cache policy (sc0 sc1 nt): the gradients do not
-    // push the operand tiles out of the L2 and the fetches beside them keep their latency.
+    // ---- epilogue: fp32 through a view of the tile, 16 bytes per lane: the 16 lanes of a dY^T row write 256
+    // consecutive bytes (with the features in a lane's registers, neighbouring lanes would write to different rows and
+    // every lane's piece would be a request of its own: a quarter of the store rate).  Written once and never read
+    // here, so the stores carry the streaming cache policy (sc0 sc1 nt): the gradients do not push the operand tiles
+    // out of the L2 and the fetches beside them keep their latency.
+    // 64 groups of 32 tokens on average, 4096 x 7168, bfloat16: 740 us (5.1 TB/s; a fill of the same size reaches
+    // 5.3 - 5.7), 816 with two neighbouring features per lane and stores of 8 bytes (bfloat16: 4) per lane; 32 groups of
+    // 512 tokens, 7168 x 2048, fp32: 573, 582 us.
     constexpr int ES = OUT16 ? 2 : 4;      // bytes per element of dW
     const __amdgpu_buffer_rsrc_t dOut = __builtin_amdgcn_make_buffer_rsrc((void*)((uint8_t*)a.dW + (((int64_t)cur.g * a.N + cur.n0) * a.K + cur.k0) * ES), 0, ((Cfg::TN - 1) * a.K + Cfg::TK) * ES, GG_RSRC_FLAGS);
-    const int vOut = (4 * q * a.K + 2 * r) * ES;
+    const int vOut = (4 * q * a.K + 4 * r) * ES;
     wait_vmcnt<31>();
 #pragma unroll
     for (int nf = 0; nf < 4; ++nf)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int pr = 0; pr < 2; ++pr) {
-          const v2f v = acc[pr][nf][i];
-          if constexpr (TIMING & kWgNoStore) asm volatile("" : : "v"(v));
-          else if constexpr (OUT16)      // the lane's two neighbouring features in one dword: a row's 16 lanes write 64 bytes
-            __builtin_amdgcn_raw_buffer_store_b32(pack2_rne(v.x, v.y, false), dOut, vOut + 64 * pr, ((wn * 64 + 16 * nf + i) * a.K + wk * 64) * 2, kStoreStreaming);
-          else
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, v), dOut, vOut + 128 * pr, ((wn * 64 + 16 * nf + i) * a.K + wk * 64) * 4, kStoreStreaming);
-        }
+      for (int i = 0; i < 4; ++i) {
+        const v4f v = acc[nf][i];
+        const int row = ((wn * 64 + 16 * nf + i) * a.K + wk * 64) * ES;
+        if constexpr (TIMING & kWgNoStore) asm volatile("" : : "v"(v));
+        else if constexpr (OUT16)
+          __builtin_amdgcn_raw_buffer_store_b64((v2i){pack2_rne(v[0], v[1], false), pack2_rne(v[2], v[3], false)}, dOut, vOut, row, kStoreStreaming);
+        else
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), dOut, vOut, row, kStoreStreaming);
+      }
     ++st_prev;
   }
   wait_vmcnt<0>();     // the fetches past the last block still write zeros into this workgroup's LDS: let them land
