@@ -62,10 +62,17 @@ namespace gg {
 // memory; the operands in LDS stay what the prologue fetched).
 enum : int { kTimingNoFetch = 1, kTimingFetchNowhere = 2, kTimingNoBarrier = 4, kTimingNoLdsReads = 8, kTimingNoFetchWaits = 16,
              kTimingFetchToRegs = 64 };
-template <int BM_, int AFR_ = 4, bool KP_ = false, bool FUSE_ = false, bool SKIP_ = false, bool RAGGED_ = false, bool ODDK_ = RAGGED_, int TIMING_ = 0>
+// WIDE (row-major activation scales): the scales of a K block lie one row pitch apart, so a fetch of 4 bytes per row and
+// K block is as many requests as two thirds of the A tile for 1/32 of its bytes.  16-byte pieces (four K blocks of a row)
+// are fetched every fourth K block of a tile instead, as in the first kernel, the weight scales likewise, into two
+// buffers in turn: a tile has an even number of K blocks, so a buffer's last K block is done with before the fetches
+// of the next but one begin.
+template <int BM_, int AFR_ = 4, bool KP_ = false, bool FUSE_ = false, bool SKIP_ = false, bool RAGGED_ = false, bool ODDK_ = RAGGED_, int TIMING_ = 0, bool WIDE_ = false>
 struct RbCfg {
   static constexpr bool KP = KP_, FUSE = FUSE_, SKIP = SKIP_, RAGGED = RAGGED_, ODDK = ODDK_;
   static constexpr int TIMING = TIMING_;
+  static constexpr bool WIDE = WIDE_;
+  static_assert(!(WIDE_ && (FUSE_ || SKIP_ || KP_ || TIMING_)), "four K blocks of scales per fetch: the plain tile only");
   static_assert(TIMING_ == 0 || !(FUSE_ || SKIP_ || RAGGED_ || ODDK_), "measurement builds exist for the plain tile only");
   static_assert(!(FUSE_ && SKIP_), "the activation epilogue runs full K steps only");
   static_assert(!(FUSE_ && RAGGED_), "the activation epilogue takes whole blocks only");
@@ -82,14 +89,17 @@ struct RbCfg {
   // end where the register's previous band has had its last use by then, else right after that use).
   static constexpr int NBAND = SA_WAVES;
   static constexpr int R_NEXT = BM / 16 - 3 > 4 * NBAND - 5 ? BM / 16 - 3 : 4 * NBAND - 5;
-  static constexpr int SA_BYTES = SA_WAVES * 256;
-  static constexpr int SB_BYTES = 256;
-  static constexpr int DUMP_BYTES = 256;           // target of the scale DMA of waves that have no scales to fetch
+  static constexpr int SA_BYTES = WIDE ? 0 : SA_WAVES * 256;
+  static constexpr int SB_BYTES = WIDE ? 0 : 256;
+  static constexpr int DUMP_BYTES = WIDE ? 0 : 256;           // target of the scale DMA of waves that have no scales to fetch
   static constexpr int STAGE_BYTES = A_BYTES + SA_BYTES + SB_BYTES + DUMP_BYTES;
   static constexpr int B_SLOTS = 3, B_SLOT_BYTES = 2048;        // per wave: fragments of 16 rows x 128 B
   static constexpr int B_BASE = S * STAGE_BYTES;
   static constexpr int RED_BASE = B_BASE + NW * B_SLOTS * B_SLOT_BYTES;   // FUSE: per row, the 8 waves' partial maxima
-  static constexpr int LDS_BYTES = RED_BASE + (FUSE ? BM * NW * 4 : 0);
+  // WIDE: two buffers of four K blocks of scales, 16 bytes per row (64 rows per fetching wave) and weight scale block,
+  // and 1 KB nobody reads for the fetches that fetch nothing
+  static constexpr int W_BASE = RED_BASE, W_CHUNK = (SA_WAVES + 1) * 1024, W_DUMP = W_BASE + 2 * W_CHUNK;
+  static constexpr int LDS_BYTES = WIDE ? W_DUMP + 1024 : RED_BASE + (FUSE ? BM * NW * 4 : 0);
   static constexpr int SB_WAVE = NW - 1;
   static constexpr int MFMAS = TM * TN;
   // MFMAs in flight before their FMAs are issued: the two of one activation block (at 256 rows 1 % faster than 3,
@@ -98,7 +108,7 @@ struct RbCfg {
   static constexpr int PIPE = 2;
   static constexpr int AFR = AFR_;                 // ring of activation fragments (prefetch distance AFR-1 blocks)
   // fetches per wave per K block, in issue order: 1 scale DMA, A_ITERS A slabs, 2 + 2 weight-slot refills
-  static constexpr int N_A = 1 + A_ITERS;
+  static constexpr int N_A = 1 + A_ITERS;          // WIDE: no scale DMA in the odd K blocks
   // SPREAD: the fetches of a K step are dealt out over its matrix instructions one at a time (an A slab after every
   // third, the two halves of a refill two apart) instead of in groups of three and two: the eight waves of a
   // workgroup run in step, so a group in the source is a burst of 16 to 24 KB-sized requests at the fetch path.
@@ -114,7 +124,7 @@ struct RbCfg {
   static constexpr int W_TOP = 4;
   // in flight across the mid-block wait: the later refill of the previous block (2), this block's scale and A
   // DMAs (N_A) and its first refill (2)
-  static constexpr int W_MID = 2 + N_A + 2;
+  static constexpr int W_MID = 2 + N_A + 2;        // WIDE, odd K block: one less
   static_assert(BM % 16 == 0 && BM <= 256 && AFR_ >= 2 && TM % AFR_ == 0, "BM a multiple of 16, fragment ring a divisor of BM/16");
   static_assert(PIPE == TN, "the FMAs of an activation block are issued with the MFMAs of the next one");
   static_assert(SA_WAVES <= SB_WAVE, "scale fetchers must be distinct waves");
@@ -192,7 +202,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
   // activation scales: lane l fetches the scale of row 64w + 16*(l%4) + l/4 of the tile, so that LDS word 4r + i of
   // the wave's 256 bytes holds row 16i + r and a lane reads the scales of its row r in four consecutive activation
   // blocks with ONE 16-byte read (a 4-byte read per block costs the LDS pipe as much as a quarter of the operand reads)
-  const int vS = sa_wave ? (w * 64 + 16 * (l & 3) + (l >> 2)) * a.sa_row_stride : sb_wave ? (l < BN / 128 ? l : BN / 128 - 1) * (Cfg::FUSE ? inter >> 7 : 1) * KB * 4 : GG_OOB_OFFSET;
+  // (WIDE: lane l the 16-byte piece of row 64w + l; the scale of a row and K block is then a 4-byte read)
+  const int vS = sa_wave ? (w * 64 + (Cfg::WIDE ? l : 16 * (l & 3) + (l >> 2))) * a.sa_row_stride : sb_wave ? (l < BN / 128 ? l : BN / 128 - 1) * (Cfg::FUSE ? inter >> 7 : 1) * KB * 4 : GG_OOB_OFFSET;
+  const int ldsW = Cfg::W_BASE + (sa_wave ? w : Cfg::SA_WAVES) * 1024;     // WIDE: + the buffer
   const int ldsS = Cfg::A_BYTES + (sa_wave ? w * 256 : sb_wave ? Cfg::SA_BYTES : Cfg::SA_BYTES + Cfg::SB_BYTES);
   // operand reads: row r, chunks (2q, 2q+1), or (q, 4+q) with KP
   const int keyR = Cfg::KP ? swz_key_a1(r) : swz_key_a(r);
@@ -288,6 +300,8 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
   float sb_next = 0.f, sb_next_up = 0.f;     // FUSE: the weight scales of the gate block and of the up block
   int stage = 0;                  // LDS buffer of block kb
   int bslot = 2;                  // slot of fragment 2*kb + 2
+  int ch_fetch = Cfg::W_CHUNK, ch_read = Cfg::W_CHUNK;   // WIDE: buffer of the newest scale fetch, of K block kb + 1; both run on across tiles
+  int sc_cur = 0, sc_next = 0;    // WIDE: LDS offset of the scales of K block kb, kb + 1
   for (int it = 0;; ++it) {
     const int n0 = cur.n0, rows_valid = cur.rows_valid;
     const int64_t grow = cur.grow;
@@ -314,6 +328,14 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
     };
     auto dma_scales = [&](int kb_t, int stage) __attribute__((always_inline)) {     // exactly one DMA in every wave
       const int kb = kb_t - kbase;
+      if constexpr (Cfg::WIDE) {       // called for even kb only
+        const bool start = (kb & 3) == 0;
+        ch_fetch = start ? Cfg::W_CHUNK - ch_fetch : ch_fetch;
+        const int dst = start ? (sa_wave || sb_wave ? ldsW + ch_fetch : Cfg::W_DUMP) : Cfg::W_DUMP;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(dS, GG_LDS_PTR(lds + dst), 16, start ? vS : GG_OOB_OFFSET,
+                                                 __builtin_amdgcn_readfirstlane(k_wrapped(kb + rot, KB) * 4), 0, 0);
+        return;
+      }
       const int vo = (Cfg::TIMING & kTimingFetchNowhere) ? GG_OOB_OFFSET : !Cfg::ODDK || kb < KB ? vS : GG_OOB_OFFSET;
       if constexpr (Cfg::TIMING & kTimingFetchToRegs)
         timing_fetch4(sink, vo, dS, __builtin_amdgcn_readfirstlane(k_wrapped(kb + rot, KB) * s_kb_stride));
@@ -347,6 +369,12 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
       return (v8i){lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
     };
 
+    // WIDE: the scales of row r in four consecutive activation blocks, LDS offset sc
+    auto wide_band = [&](int sc) __attribute__((always_inline)) -> v4f {
+      const float* p = (const float*)(lds + sc + r * 16);
+      return (v4f){p[0], p[64], p[128], p[192]};
+    };
+    const int sbRdW = Cfg::SA_WAVES * 1024 + ((w * 32) >> 7) * 16;
     // The next tile is looked up here, not where it is first needed: the four K steps at the end of the tile stay
     // one basic block.
     const Tile nxt = find_tile(it + 1);
@@ -371,9 +399,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
       dma_b(0, J0, 0);
       dma_b(0, J1, 1);
       dma_b(1, J0, 2);
-      dma_scales(1, 1);
+      if constexpr (!Cfg::WIDE) dma_scales(1, 1);
       static_for<0, Cfg::A_ITERS>([&](auto ic) __attribute__((always_inline)) { dma_a(ic, 1, 1); });
-      wait_vmcnt<2 + Cfg::N_A>();
+      wait_vmcnt<2 + Cfg::N_A - (Cfg::WIDE ? 1 : 0)>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
 
@@ -381,13 +409,19 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
       bfr[0][1] = read_frag(bslots + Cfg::B_SLOT_BYTES);
 #pragma unroll
       for (int i = 0; i < AFR - 1; ++i) afr[i] = read_frag(lds + i * 2048);
-      sa4[0] = *(const v4f*)(lds + saRd);
+      if constexpr (Cfg::WIDE) {
+        ch_read = Cfg::W_CHUNK - ch_read;
+        sc_next = Cfg::W_BASE + ch_read;
+        sa4[0] = wide_band(sc_next);
+      } else {
+        sa4[0] = *(const v4f*)(lds + saRd);
+      }
       // the slot reads must be done before their slots are refilled
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       dma_b(1, J1, 0);
       dma_b(2, J0, 1);
 
-      sb_next = *(const float*)(lds + sbRd);                   // weight scale of block 0
+      sb_next = *(const float*)(lds + (Cfg::WIDE ? sc_next + sbRdW : sbRd));                   // weight scale of block 0
       if constexpr (Cfg::FUSE) sb_next_up = *(const float*)(lds + sbRd + 4);
       stage = 0;
       bslot = 2;
@@ -395,8 +429,11 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
     // One K block; BS = kb % 2 is the register set that holds its weights.  PRED: the step of a partly filled tile,
     // which runs the activation blocks [0, tm_act) only; the fetches, the copies of the weight fragments and the
     // reads of the next K block's first activation fragments are those of a full step.
-    auto kstep = [&](int kb, auto bs_c, auto pred_c) __attribute__((always_inline)) {
+    auto kstep = [&](int kb, auto bs_c, auto pred_c, auto last_c) __attribute__((always_inline)) {
       constexpr int BS = decltype(bs_c)::value;
+      constexpr bool LAST = decltype(last_c)::value;           // the tile's last step
+      // WIDE: what an odd number of K blocks leaves in the place of the empty step's scales is the next row's
+      const bool no_scales = Cfg::WIDE && Cfg::ODDK && LAST && KBe != KB;
       constexpr bool PRED = decltype(pred_c)::value;
       static_assert(!(PRED && Cfg::FUSE), "the activation epilogue runs full steps only");
       // opaque to the compiler, which otherwise hoists the tests on it out of the K loop and keeps one copy of the
@@ -414,9 +451,19 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
       // every wave has its part of block kb+1 in LDS and is done reading block kb-1
       if constexpr (!(Cfg::TIMING & kTimingNoBarrier)) __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
+      if constexpr (Cfg::WIDE) {
+        sc_cur = sc_next;
+        sc_next += 4;
+        if constexpr (BS == 1) {
+          if (LAST || ((kb + 1) & 3) == 0) {
+            ch_read = Cfg::W_CHUNK - ch_read;
+            sc_next = Cfg::W_BASE + ch_read;
+          }
+        }
+      }
       const float sb = sb_next, sb_up = sb_next_up;            // read a block ago: no LDS wait ahead of the first MFMA
       bfr[BS ^ 1][0] = read_frag(bslots + bslot * Cfg::B_SLOT_BYTES);
-      if constexpr (!(Cfg::TIMING & kTimingNoFetch)) dma_scales(kb + 2, stageN);
+      if constexpr (!(Cfg::TIMING & kTimingNoFetch) && !(Cfg::WIDE && BS == 1)) dma_scales(kb + 2, stageN);
       __builtin_amdgcn_sched_barrier(0);
 
       v4f p[MF];
@@ -432,6 +479,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
           // the empty asm makes the register's old contents a new value for the compiler, as a read would
           if constexpr (mt % 4 == 1 && mt / 4 + 1 < Cfg::NBAND) asm volatile("" : "+v"(sa4[band_reg(mt / 4 + 1)]));
           if constexpr (mt == Cfg::R_NEXT) asm volatile("" : "+v"(sa4[band_reg(Cfg::NBAND)]));
+        } else if constexpr (Cfg::WIDE) {
+          if constexpr (mt % 4 == 1 && mt / 4 + 1 < Cfg::NBAND) sa4[band_reg(mt / 4 + 1)] = wide_band(sc_cur + (mt / 4 + 1) * 1024);
+          if constexpr (mt == Cfg::R_NEXT) sa4[band_reg(Cfg::NBAND)] = wide_band(sc_next);
         } else {
           if constexpr (mt % 4 == 1 && mt / 4 + 1 < Cfg::NBAND) sa4[band_reg(mt / 4 + 1)] = *(const v4f*)(st + saRd + (mt / 4 + 1) * 256);
           if constexpr (mt == Cfg::R_NEXT) sa4[band_reg(Cfg::NBAND)] = *(const v4f*)(st1 + saRd);
@@ -443,6 +493,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
           constexpr int mt = t / TN, j = t % TN;
           if constexpr (j == 0) {
             s[mt] = sa4[band_reg(mt / 4)][mt % 4] * sb;
+            if constexpr (Cfg::WIDE && Cfg::ODDK && LAST) s[mt] = no_scales ? 0.f : s[mt];
             if constexpr (Cfg::FUSE) s_up[mt] = sa4[band_reg(mt / 4)][mt % 4] * sb_up;
             // fragment of activation block mt + AFR - 1 into the slot block mt - 1 has left; past the end of
             // this K block that is the next K block's, published by the barrier above
@@ -454,7 +505,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
             } else {
               afr[nb % AFR] = read_frag(st1 + (nb - TM) * 2048);
               if constexpr (nb == TM) {                                         // next block's weight scale(s)
-                sb_next = *(const float*)(st1 + sbRd);
+                sb_next = *(const float*)(Cfg::WIDE ? lds + sc_next + sbRdW : st1 + sbRd);
                 if constexpr (Cfg::FUSE) sb_next_up = *(const float*)(st1 + sbRd + 4);
               }
             }
@@ -488,11 +539,11 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
         if constexpr (t < MF) {
           constexpr int j = t % TN;
           if constexpr (j == 0) {
-            __builtin_amdgcn_sched_group_barrier(0x002, Cfg::FUSE ? 2 : 1, 0);                   // scale product(s)
+            __builtin_amdgcn_sched_group_barrier(0x002, Cfg::FUSE || (Cfg::WIDE && Cfg::ODDK && LAST) ? 2 : 1, 0);                   // scale product(s)
             constexpr int mt = t / TN;                                                           // DS reads: 2 of a fragment,
             if constexpr (!(Cfg::TIMING & kTimingNoLdsReads))
               __builtin_amdgcn_sched_group_barrier(0x100, 2 + (mt + AFR - 1 == TM ? (Cfg::FUSE ? 2 : 1) : 0)   // weight scale(s),
-                                                              + (mt % 4 == 1 && mt / 4 + 1 < Cfg::NBAND ? 1 : 0) + (mt == Cfg::R_NEXT ? 1 : 0), 0);   // a band of scales
+                                                              + (Cfg::WIDE ? 2 : 1) * ((mt % 4 == 1 && mt / 4 + 1 < Cfg::NBAND ? 1 : 0) + (mt == Cfg::R_NEXT ? 1 : 0)), 0);   // a band of scales
           }
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                     // 1 MFMA
           if constexpr (t >= Cfg::T_A0 && t < Cfg::T_A0 + Cfg::A_STEP * Cfg::A_ITERS && (t - Cfg::T_A0) % Cfg::A_STEP == 0) {
@@ -518,7 +569,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
         constexpr int mt = decltype(mc)::value;
         if constexpr (mt * TN == Cfg::T_MID) {
           // weight fragment 2kb+3, fetched a K block ago, is older than the W_MID newest fetches
-          if constexpr (!(Cfg::TIMING & kTimingNoFetchWaits)) wait_vmcnt<Cfg::W_MID>();
+          if constexpr (!(Cfg::TIMING & kTimingNoFetchWaits)) wait_vmcnt<Cfg::W_MID - (Cfg::WIDE && BS == 1 ? 1 : 0)>();
           bfr[BS ^ 1][1] = read_frag(bslots + bslot1 * Cfg::B_SLOT_BYTES);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -583,26 +634,27 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
     // block would be live at once).
     constexpr std::integral_constant<int, 0> SET0{};
     constexpr std::integral_constant<int, 1> SET1{};
+    constexpr std::false_type no{};
     {
       for (int kb = 0; kb < KBe - 4; kb += 2) {
-        kstep(kb, SET0, pred_c);
-        kstep(kb + 1, SET1, pred_c);
+        kstep(kb, SET0, pred_c, no);
+        kstep(kb + 1, SET1, pred_c, no);
       }
       // step KB-4 issues the last fetch of this tile's j = 0 fragments (block KB-1); step KB-3 the last fetches of
       // its activations, scales and j = 1 fragments.  After each, that stream moves on to the next tile.
-      kstep(KBe - 4, SET0, pred_c);
+      kstep(KBe - 4, SET0, pred_c, no);
       dB0 = desc_b(nxt, has_next);
       rot0 = k_rotation(a, nxt.n0);
       kbase0 = KBe;
-      kstep(KBe - 3, SET1, pred_c);
+      kstep(KBe - 3, SET1, pred_c, no);
       dA0 = band(nxt, 0, has_next); dA1 = band(nxt, 1 % Cfg::A_ITERS, has_next);
       dA2 = band(nxt, 2 % Cfg::A_ITERS, has_next); dA3 = band(nxt, 3 % Cfg::A_ITERS, has_next);
       dB = dB0;
       dS = desc_s(nxt, has_next);
       rot = rot0;
       kbase = KBe;
-      kstep(KBe - 2, SET0, pred_c);
-      kstep(KBe - 1, SET1, pred_c);
+      kstep(KBe - 2, SET0, pred_c, no);
+      kstep(KBe - 1, SET1, pred_c, std::true_type{});
       kbase = kbase0 = 0;
     }
 

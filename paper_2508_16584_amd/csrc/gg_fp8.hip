@@ -52,6 +52,9 @@ struct Variant {
   bool splitk = false;         // two work units per tile (halves of the K loop) and a combine pass; needs a workspace
   // the same tile with the streaming cache policy on the weight fetches, for groups of at most one row tile; null: none
   hipError_t (*launch_bstream)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
+  // the second kernel on row-major activation scales: four K blocks of them per fetch (launch, launch_ragged); null: none
+  hipError_t (*launch_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
+  hipError_t (*launch_ragged_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
 };
 
 template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false>
@@ -115,11 +118,14 @@ const Variant kVariants[] = {
     GG_VARIANT(128, 128, 2, 4, 4, true, 0, 1),    // 9
     GG_VARIANT(32, 256, 1, 8, 4, true, 0, 1),     // 10
     GG_VARIANT(128, 128, 2, 4, 2, false, 0, 2),   // 11
-    {"256x256/1x8w/3s-rb", 256, 256, gg::RbCfg<256, 2, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<256, 2, false>>, &launch_gemm_rb<gg::RbCfg<256, 2, false, false, false, true>>, true},   // 12
+    {"256x256/1x8w/3s-rb", 256, 256, gg::RbCfg<256, 2, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<256, 2, false>>, &launch_gemm_rb<gg::RbCfg<256, 2, false, false, false, true>>, true, false, nullptr,
+     &launch_gemm_rb<gg::RbCfg<256, 2, false, false, false, false, false, 0, true>>, &launch_gemm_rb<gg::RbCfg<256, 2, false, false, false, true, true, 0, true>>},   // 12
     {"256x256/1x8w/3s-rbk", 256, 256, gg::RbCfg<256, 2, true>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<256, 2, true>>, nullptr, true},    // 13
     // ring of 4 activation fragments at 192 rows: 1 % faster than 2 there, no gain (and 249 VGPRs) at 256 rows
-    {"192x256/1x8w/3s-rb", 192, 256, gg::RbCfg<192, 4, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<192, 4, false>>, &launch_gemm_rb<gg::RbCfg<192, 4, false, false, false, true>>, true},   // 14
-    {"224x256/1x8w/3s-rb", 224, 256, gg::RbCfg<224, 2, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<224, 2, false>>, &launch_gemm_rb<gg::RbCfg<224, 2, false, false, false, true>>, true},   // 15
+    {"192x256/1x8w/3s-rb", 192, 256, gg::RbCfg<192, 4, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<192, 4, false>>, &launch_gemm_rb<gg::RbCfg<192, 4, false, false, false, true>>, true, false, nullptr,
+     &launch_gemm_rb<gg::RbCfg<192, 4, false, false, false, false, false, 0, true>>, &launch_gemm_rb<gg::RbCfg<192, 4, false, false, false, true, true, 0, true>>},   // 14
+    {"224x256/1x8w/3s-rb", 224, 256, gg::RbCfg<224, 2, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<224, 2, false>>, &launch_gemm_rb<gg::RbCfg<224, 2, false, false, false, true>>, true, false, nullptr,
+     &launch_gemm_rb<gg::RbCfg<224, 2, false, false, false, false, false, 0, true>>, &launch_gemm_rb<gg::RbCfg<224, 2, false, false, false, true, true, 0, true>>},   // 15
     {"128x256/1x8w/3s-rb", 128, 256, gg::RbCfg<128, 4, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<128, 4, false>>, &launch_gemm_rb<gg::RbCfg<128, 4, false, false, false, true>>, true},   // 16
     {"160x256/1x8w/3s-rb", 160, 256, gg::RbCfg<160, 2, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<160, 2, false>>, nullptr, true},   // 17
     {"96x256/1x8w/3s-rb", 96, 256, gg::RbCfg<96, 2, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<96, 2, false>>, nullptr, true},   // 18
@@ -345,7 +351,11 @@ int run_gemm(const void* A, const float* SA, const void* B, const float* SB, con
   }
   // groups of at most one row tile on average: every weight byte is fetched once, and streamed past the L2
   const bool bstream = !ragged && v.launch_bstream && M_total <= (int64_t)G * v.BM;
-  hipError_t e = (ragged ? v.launch_ragged : bstream ? v.launch_bstream : v.launch)(args, (int)grid, static_cast<hipStream_t>(stream));
+  // row-major scales, four K blocks of them per fetch: from K = 4096 on (8 groups of 1024 rows, N = 4096: K = 7168
+  // 247.3 -> 240.8 us, 7040 246.9 -> 240.5, 4096 147.2 -> 146.5; 32 groups of 512 rows, N = 7168, K = 2048: 285.5 -> 287.3)
+  const bool wide = v.launch_wide && !args.sa_kmajor && K >= 4096;
+  hipError_t e = (ragged ? (wide ? v.launch_ragged_wide : v.launch_ragged) : wide ? v.launch_wide : bstream ? v.launch_bstream : v.launch)(
+      args, (int)grid, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return GG_ERR_HIP;
   if (v.splitk) {
     const int64_t groups8 = M_total * (int64_t)(N / 8);
