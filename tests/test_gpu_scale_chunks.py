@@ -50,3 +50,25 @@ def test_row_major_against_the_oracle():
     dev = problem(sizes, N, K, 9)
     ref = orc.grouped_gemm(*(t.cpu().numpy() for t in dev), with_abs_sum=True)
     assert_parity(bits_of(gg.grouped_gemm(*dev)), ref, empirical=False, what="five K blocks")
+
+
+@pytest.mark.parametrize("K", [4096, 4224, 4352, 4480, 4400])
+def test_second_kernel_row_major_equals_kmajor_bitwise(K):
+    """From K = 4096 on the second kernel fetches four K blocks of scales at a time too: last chunks of one to four
+    blocks, even, odd and ragged numbers of K blocks, several tiles per workgroup.  A row's scales that are NaN stay in
+    that row (what a chunk at the end of a row takes from the next one is not used, whatever it is)."""
+    sizes, N = [700, 0, 300, 41], 8192
+    A, SA, B, SB, off = problem(sizes, N, K, K)
+    bad = [5, 17, 256, 700, 1040]
+    SA[bad] = float("nan")
+    SAk = SA.t().contiguous()
+    want = gg.grouped_gemm(A, SAk, B, SB, off, variant=3, sa_kmajor=True)         # the first kernel, per K block
+    for v in [-1] + [u for u in range(gg.num_variants()) if gg.variant_name(u).endswith("-rb")]:
+        try:
+            row = gg.grouped_gemm(A, SA, B, SB, off, variant=v)
+        except gg.GGError:
+            continue                                    # a variant that does not take this K
+        assert torch.equal(row.view(torch.int16), want.view(torch.int16)) or \
+            (torch.equal(row.isnan(), want.isnan()) and torch.equal(row.nan_to_num().view(torch.int16), want.nan_to_num().view(torch.int16))), v
+        nan_rows = row.isnan().any(dim=1).nonzero().flatten().tolist()
+        assert nan_rows == bad, v
