@@ -97,6 +97,15 @@ struct GemmArgs {
   float* P;
 };
 
+// Buffer descriptor from wave-uniform values.  readfirstlane states the uniformity for the compiler, which
+// otherwise may keep a descriptor in vector registers and loop over its values at every use.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* ptr, int bytes) {
+  const uint64_t p = (uint64_t)ptr;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, __builtin_amdgcn_readfirstlane(bytes), GG_RSRC_FLAGS);
+}
+
 // Length in bytes of the view of SA that starts at the scale of (first row of a tile, K block 0).  The K-block part
 // of a scale's address travels in the scalar offset of the fetch, which the range check adds to the lane offset
 // before it compares with the length.  Row-major: rows_valid scale rows, so rows past the group's end read as
@@ -131,6 +140,10 @@ struct GemmCfg {
   static constexpr int SA_BASE = STAGES_ * STAGE_BYTES;
   static constexpr int DUMP_BASE = SA_BASE + (WIDE ? SA_BUFS * SA_CHUNK : STAGES_ * SA_SLOT);      // 256 bytes nobody reads (empty fetches)
   static_assert(STAGES_ <= 8, "four chunks");
+  // ONE_CHUNK (160 x 256): one chunk buffer in the place of the slots, whose scales a wave takes into registers at once
+  // (see the kernel)
+  static constexpr bool ONE_CHUNK = !XPF_ && !WIDE && STAGES_ == 3;
+  static constexpr int ONE_DUMP = SA_BASE + SA_CHUNK, ONE_LDS_BYTES = ONE_DUMP + 256;
   static constexpr int SB_WAVE = NW - 1;      // the wave that fetches them
   static constexpr int MFMAS = (BM / WM / 16) * (BN / WN / 16);   // MFMAs per wave per K block
   static constexpr int PIPE = MFMAS < PIPE_ ? MFMAS : PIPE_;               // MFMAs in flight before their FMAs are issued
@@ -206,6 +219,107 @@ __device__ __forceinline__ int swz_key_b(int row) {   // rows read: base + 8*(r/
   return b1 | (b4 << 1) | (b4 << 2);
 }
 
+// Tile counts of the groups, summed up over the groups: lane l holds, for groups l, 64 + l, 128 + l and 192 + l, the tiles of
+// all groups up to and including that one, so that the group of a tile is found by a ballot.  Walking the offsets with
+// scalar loads instead costs 0.12 us per group (a chain of loads), for every workgroup and for every group, those without
+// rows too: 128 groups of 2 rows, N = K = 2048, 84.8 -> 73.5 us per launch, 64 groups of 64 rows, N = 1024, K = 2048, 53.2 -> 47.9.
+// Groups past the first 256 are walked.  The sums saturate: offsets that are not sorted may add up to anything, and the
+// tile found must be one of its group's in any case.
+//
+// It also deals the tiles out.  Workgroup b runs on XCD b % 8, and every XCD takes a run of `slots` neighbouring tiles
+// (they share operand panels in its L2) in every full round over the workgroups.  The tiles of the last, partly filled
+// round are split evenly over the XCDs where memory bounds the launch or it is the only round: dealt out in whole runs, half a
+// round is four XCDs with all their compute units busy and four idle (52 groups of 39 rows on average, N = 4096, K = 7168, 3.5
+// rounds: 290 -> 286 us; 32 x 64 tiles, 768 workgroups, 256 to 512 tiles: 1.2 times).  Larger compute-bound launches keep whole
+// runs, which share more (8 groups of 375 rows, N = 4104, K = 7232, 1.5 rounds: 159.5 against 162).
+struct GroupIndex {
+  static constexpr int NONE = 0x7FFFFFFF;      // a work unit that does not exist
+  unsigned pre[4];
+  int g, base;          // the walk behind the first 256 groups: groups before g hold `base` tiles
+  int full, rem_run;    // full rounds over the workgroups; tiles per XCD of the last one
+
+  __device__ __forceinline__ static unsigned add_sat(unsigned x, unsigned y) { return __builtin_elementwise_add_sat(x, y); }
+
+  // tiles of the groups up to group0 + l, from group0 on
+  __device__ __forceinline__ static unsigned scan64(const GemmArgs& a, int BM, int group0, int l) {
+    const int g0 = group0 + l < a.G ? group0 + l : a.G, g1 = g0 + 1 < a.G ? g0 + 1 : a.G;
+    const int row0 = clampi(a.off[g0], 0, a.M_total);
+    const int rows = clampi(a.off[g1], row0, a.M_total) - row0;
+    unsigned x = (unsigned)((rows + BM - 1) / BM) * (unsigned)a.n_tiles;
+    x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false));      // inclusive scan: row_shr 1, 2, 4, 8 ...
+    x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false));
+    x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false));
+    x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false));
+    x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));      // ... lane 15 to the next row of 16,
+    return add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));   // lane 31 to the upper half
+  }
+
+  // split: see above; units: work units per tile (split-K: 2)
+  __device__ __forceinline__ void init(const GemmArgs& a, int BM, int l, bool split, int units = 1) {
+    unsigned before = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      pre[c] = before;
+      if (64 * c < a.G) {
+        pre[c] = add_sat(scan64(a, BM, 64 * c, l), before);
+        before = (unsigned)__builtin_amdgcn_readlane((int)pre[c], 63);
+      }
+    }
+    g = 256;
+    base = (int)(before < 0x7FFFFFFFu ? before : 0x7FFFFFFFu);
+    for (int c = 256; c < a.G; c += 64) before = add_sat(before, (unsigned)__builtin_amdgcn_readlane((int)scan64(a, BM, c, l), 63));
+    before = before < 0x7FFFFFFFu / (unsigned)units ? before * (unsigned)units : 0x7FFFFFFFu;
+    const unsigned grid = gridDim.x;
+    full = __builtin_amdgcn_readfirstlane((int)(before / grid));
+    rem_run = full == 0 || split ? __builtin_amdgcn_readfirstlane((int)((before - (unsigned)full * grid + 7) >> 3)) : a.slots;
+  }
+
+  // work unit `it` of this workgroup, NONE past the last one
+  __device__ __forceinline__ int unit(const GemmArgs& a, int it) const {
+    if (a.slots <= 0) return it * (int)gridDim.x + (int)blockIdx.x;
+    const int xcd = (int)(blockIdx.x & 7), i = (int)(blockIdx.x >> 3);
+    if (it < full) return (it * 8 + xcd) * a.slots + i;
+    return it == full && i < rem_run ? full * (int)gridDim.x + xcd * rem_run + i : NONE;
+  }
+
+  // The group of tile T and the tiles before that group, false when there is no such tile.  T never decreases.
+  // (readfirstlane states the uniformity for the compiler, which otherwise loops over descriptors at every fetch.)
+  __device__ __forceinline__ bool find(const GemmArgs& a, int BM, int T, int& group, int& tiles_before) {
+    int gr = -1, tb = 0;
+    locate(a, BM, T, gr, tb);
+    group = __builtin_amdgcn_readfirstlane(gr);
+    tiles_before = __builtin_amdgcn_readfirstlane(tb);
+    return group >= 0;
+  }
+
+  __device__ __forceinline__ void locate(const GemmArgs& a, int BM, int T, int& group, int& tiles_before) {
+    int before = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (64 * c >= a.G) return;
+      const uint64_t past = __builtin_amdgcn_ballot_w64(pre[c] > (unsigned)T);
+      if (past) {
+        const int lane = __builtin_ctzll(past);
+        group = 64 * c + lane;
+        tiles_before = lane ? __builtin_amdgcn_readlane((int)pre[c], lane - 1) : before;
+        return;
+      }
+      before = __builtin_amdgcn_readlane((int)pre[c], 63);
+    }
+    const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
+    for (; g < a.G; ++g) {
+      const int row0 = clampi(offc[g], 0, a.M_total);
+      const int cnt = (clampi(offc[g + 1], row0, a.M_total) - row0 + BM - 1) / BM * a.n_tiles;
+      if (T < base + cnt) {
+        group = g;
+        tiles_before = base;
+        return;
+      }
+      base += cnt;
+    }
+  }
+};
+
 // RAGGED: N need not be a multiple of the tile width nor K of 128 (the ceilings in Table 1 of the paper); costs a
 // few lane selects per fetch, so shapes made of whole blocks use the instantiation without it.
 // SPLITK: the work list holds two units per tile, one per half of the K loop (K blocks [0, KB/2) and [KB/2, KB)),
@@ -216,7 +330,11 @@ __device__ __forceinline__ int swz_key_b(int row) {   // rows read: base + 8*(r/
 // weight byte is fetched once; left to the default policy the 7.5 GB of a 256-expert layer push the activation tiles
 // (which the 16 column tiles of a group share) out of the L2.  Where several row tiles share a group's weights the
 // policy costs 17 - 35 %, so the host asks for it only when M_total <= G * BM.
-template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false>
+// ONE: row-major scales four K blocks at a time on a tile that has room for one chunk of them only.  A chunk's scales go
+// into registers in its first K step, and the fetch of the next one, two steps before that is needed, finds the buffer
+// free: a tile's last chunk must have begun two steps before its end, so the number of K blocks is 0 or 3 modulo 4.
+// 256 groups of 128 rows, N = 4096, K = 7168: 1432 us, 1533 with 4-byte fetches per K block.
+template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false, bool ONE = false>
 __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   constexpr int kBAux = BSTREAM ? (2 | 16) : 0;
   static_assert(!(SPLITK && (RAGGED || Cfg::XPF)), "split-K: whole tiles, the ring-of-buffers path");
@@ -253,7 +371,8 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   // reaches 5.6 TB/s like that, 5.1 with 4-byte fetches and 5.7 without any scales (128 x 256 tile on 52 groups of 128
   // rows, N = 4096, K = 7168: 332 -> 306 us, 301 K-block-major; 64 groups of 32 rows on average: 315 -> 296 us).
   // K-block-major, the scales of a K block are a few lines and fetched per K block ("narrow").
-  const bool wide = Cfg::WIDE && !a.sa_kmajor;
+  const bool wide = ONE || (Cfg::WIDE && !a.sa_kmajor);
+  static_assert(!ONE || (Cfg::ONE_CHUNK && !SPLITK), "one chunk buffer: the tiles that have no room for more");
   const int vSA = (w * 64 + l) * a.sa_row_stride;
   const int vSB = (l < BN / 128 ? l : BN / 128 - 1) * KB * 4;        // lane -> which 128-wide N block of the tile
 
@@ -284,31 +403,23 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
     int64_t grow;
     int ks;          // SPLITK: which half of the K loop
   };
-  int g = 0, base = 0;
-  const int nwg = gridDim.x;
+  GroupIndex groups;
+  groups.init(a, BM, l, BSTREAM, SPLITK ? 2 : 1);
   const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
   auto find_tile = [&](int it) __attribute__((always_inline)) -> Tile {
     Tile t = {false, 0, 0, 0, 0, 0};
-    int T;
-    if (a.slots > 0) T = (it * 8 + (int)(blockIdx.x & 7)) * a.slots + (int)(blockIdx.x >> 3);
-    else T = it * nwg + blockIdx.x;
+    int T = groups.unit(a, it);
+    if (T == GroupIndex::NONE) return t;
     if constexpr (SPLITK) {          // the two halves of a tile are neighbours in the list
       t.ks = T & 1;
       T >>= 1;
     }
 
-    int row0 = 0, Mg = 0, mtiles = 0;
-    for (;;) {
-      if (g >= a.G) return t;
-      row0 = clampi(offc[g], 0, a.M_total);
-      const int row1 = clampi(offc[g + 1], row0, a.M_total);
-      Mg = row1 - row0;
-      mtiles = (Mg + BM - 1) / BM;
-      const int cnt = mtiles * a.n_tiles;
-      if (T < base + cnt) break;
-      base += cnt;
-      ++g;
-    }
+    int g = 0, base = 0;
+    if (!groups.find(a, BM, T, g, base)) return t;
+    const int row0 = clampi(offc[g], 0, a.M_total);
+    const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
+    const int mtiles = (Mg + BM - 1) / BM;
     // order inside a group: chunks of n_chunk n-tiles; inside a chunk m-tile major, n-tile minor
     const int local = T - base;
     const int per_chunk = mtiles * a.n_chunk;
@@ -359,7 +470,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   int rot = k_start(cur);
   bool primed = false;      // the first STAGES-1 K blocks of `cur` were already fetched by the previous tile
   int stage = 0;            // LDS buffer of the current K block; runs on across tiles
-  constexpr int SA_TOTAL = Cfg::SA_BUFS * Cfg::SA_CHUNK;
+  constexpr int SA_TOTAL = ONE ? Cfg::SA_CHUNK : Cfg::SA_BUFS * Cfg::SA_CHUNK;
+  constexpr int SA_DUMP = ONE ? Cfg::ONE_DUMP : Cfg::DUMP_BASE;
+  v4f sa4[TM];          // ONE: the scales of the chunk's K blocks that are still to come
   int ch_fetch = SA_TOTAL - Cfg::SA_CHUNK, ch_read = ch_fetch;     // wide: chunk of the newest fetch, of the current K block; both run on
   auto next_chunk = [&](int c) __attribute__((always_inline)) -> int { return c + Cfg::SA_CHUNK == SA_TOTAL ? 0 : c + Cfg::SA_CHUNK; };
   for (int it = 0;; ++it) {
@@ -406,7 +519,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
         if (chunk_start)
           __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + Cfg::SA_BASE + ch_fetch + w * 1024), 16, vSA, kb * 4, 0, 0);
         else
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + (wide ? Cfg::DUMP_BASE : Cfg::SA_BASE + stg * Cfg::SA_SLOT + w * 256)), 4, wide ? GG_OOB_OFFSET : vSA, kb * a.sa_kb_stride, 0, 0);
+          __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + (wide ? SA_DUMP : Cfg::SA_BASE + stg * Cfg::SA_SLOT + w * 256)), 4, wide ? GG_OOB_OFFSET : vSA, kb * a.sa_kb_stride, 0, 0);
       }
       if (w == Cfg::SB_WAVE)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(dSB, GG_LDS_PTR(st + Cfg::A_BYTES + Cfg::B_BYTES), 4, vSB, kb * 4, 0, 0);
@@ -612,12 +725,21 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
         const float sb = *(const float*)(st + sbRd);
         float sa[TM];
         if (wide && (kb & 3) == 0) ch_read = next_chunk(ch_read);
+        if constexpr (ONE) {
+          if ((kb & 3) == 0) {
+#pragma unroll
+            for (int mt = 0; mt < TM; ++mt) sa4[mt] = *(const v4f*)(lds + saRd + mt * 256);
+          } else {
+#pragma unroll
+            for (int mt = 0; mt < TM; ++mt) sa4[mt] = (v4f){sa4[mt][1], sa4[mt][2], sa4[mt][3], sa4[mt][3]};
+          }
+        }
         const uint8_t* const sa_place = lds + saRd + (wide ? ch_read + (kb & 3) * 4 : stage * Cfg::SA_SLOT);
-        sa[0] = *(const float*)sa_place;
+        sa[0] = ONE ? sa4[0][0] : *(const float*)sa_place;
 #pragma unroll
         for (int j = 1; j < TN; ++j) bfr[j] = read_b(j, st);
 #pragma unroll
-        for (int mt = 1; mt < TM; ++mt) sa[mt] = *(const float*)(sa_place + mt * sa_mt);
+        for (int mt = 1; mt < TM; ++mt) sa[mt] = ONE ? sa4[mt][0] : *(const float*)(sa_place + mt * sa_mt);
         if constexpr (ISSUE) {
           dma_head(kb_new, nstage, MODE == 1 || prefetch);
           static_for<NDMA_STREAM, NDMA_ALL>([&](auto ic) { dma_tile(ic, kb_new, nstage); });

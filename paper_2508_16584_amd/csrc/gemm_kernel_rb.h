@@ -139,15 +139,6 @@ __device__ __forceinline__ int swz_key_a1(int row) {
   return u ^ (((u >> 1) ^ (u >> 2)) & 1);
 }
 
-// Buffer descriptor from wave-uniform values.  readfirstlane states the uniformity for the compiler, which
-// otherwise may keep a descriptor in vector registers and loop over its values at every use.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t uniform_rsrc(const void* ptr, int bytes) {
-  const uint64_t p = (uint64_t)ptr;
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc((void*)(((uint64_t)hi << 32) | lo), 0, __builtin_amdgcn_readfirstlane(bytes), GG_RSRC_FLAGS);
-}
-
 // kTimingFetchToRegs: the fetch as an ordinary load into registers that stay allocated to the end of the kernel
 // (the compiler does not know that the asm is a load; "+v" keeps it from giving the registers to anything else)
 __device__ __forceinline__ void timing_fetch16(v4i& sink, int voffset, __amdgpu_buffer_rsrc_t rsrc, int soffset) {
@@ -220,26 +211,18 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_rb_kernel(const GemmArgs a) {
     int g, n0, rows_valid;
     int64_t grow;
   };
-  int g = 0, base = 0;
-  const int nwg = gridDim.x;
+  GroupIndex groups;
+  groups.init(a, BM, l, false);
   const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
   auto find_tile = [&](int it) __attribute__((always_inline)) -> Tile {
     Tile t = {false, 0, 0, 0, 0};
-    int T;
-    if (a.slots > 0) T = (it * 8 + (int)(blockIdx.x & 7)) * a.slots + (int)(blockIdx.x >> 3);
-    else T = it * nwg + blockIdx.x;
-    int row0 = 0, Mg = 0, mtiles = 0;
-    for (;;) {
-      if (g >= a.G) return t;
-      row0 = clampi(offc[g], 0, a.M_total);
-      const int row1 = clampi(offc[g + 1], row0, a.M_total);
-      Mg = row1 - row0;
-      mtiles = (Mg + BM - 1) / BM;
-      const int cnt = mtiles * a.n_tiles;
-      if (T < base + cnt) break;
-      base += cnt;
-      ++g;
-    }
+    const int T = groups.unit(a, it);
+    if (T == GroupIndex::NONE) return t;
+    int g = 0, base = 0;
+    if (!groups.find(a, BM, T, g, base)) return t;
+    const int row0 = clampi(offc[g], 0, a.M_total);
+    const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
+    const int mtiles = (Mg + BM - 1) / BM;
     const int local = T - base;
     const int per_chunk = mtiles * a.n_chunk;
     const int nc = local / per_chunk;
