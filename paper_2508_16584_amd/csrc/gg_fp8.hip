@@ -52,25 +52,28 @@ struct Variant {
   bool splitk = false;         // two work units per tile (halves of the K loop) and a combine pass; needs a workspace
   // the same tile with the streaming cache policy on the weight fetches, for groups of at most one row tile; null: none
   hipError_t (*launch_bstream)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
-  // the second kernel on row-major activation scales: four K blocks of them per fetch (launch, launch_ragged); null: none
+  // row-major activation scales, four K blocks of them per fetch, where that is an instantiation of its own (the second
+  // kernel; the first one's tile with one chunk buffer): launch, launch_ragged, launch_bstream; null: none
   hipError_t (*launch_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
   hipError_t (*launch_ragged_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
+  hipError_t (*launch_bstream_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
 };
 
-template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false>
+template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false, bool ONE = false>
 hipError_t launch_gemm(const gg::GemmArgs& args, int grid, hipStream_t stream) {
+  constexpr int lds = ONE ? Cfg::ONE_LDS_BYTES : Cfg::LDS_BYTES;
   static std::atomic<int> prepared[64];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < 64 && !prepared[dev].load(std::memory_order_acquire)) {
     // more than 64 KB of LDS per workgroup has to be requested explicitly
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM, ONE>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     prepared[dev].store(1, std::memory_order_release);
   }
-  hipLaunchKernelGGL((gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, stream, args);
+  hipLaunchKernelGGL((gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM, ONE>), dim3(grid), dim3(Cfg::NT), lds, stream, args);
   return hipGetLastError();
 }
 
@@ -105,8 +108,12 @@ hipError_t launch_gemm_rb(const gg::GemmArgs& args, int grid, hipStream_t stream
 #define XPF_SUFFIX_false ""
 #define XPF_SUFFIX_true "x"
 
+using Cfg160 = gg::GemmCfg<160, 256, 2, 4, 3, false, 2>;
+
 const Variant kVariants[] = {
-    GG_VARIANT_RS(160, 256, 2, 4, 3, false, 2, 1),   // 0: the largest tile that leaves room for a ring of 3 in 160 KB of LDS
+    {"160x256/2x4w/3s", 160, 256, Cfg160::ONE_LDS_BYTES, 1, &launch_gemm<Cfg160>, &launch_gemm<Cfg160, true>, false, false,
+     &launch_gemm<Cfg160, false, false, true>, &launch_gemm<Cfg160, false, false, false, true>, &launch_gemm<Cfg160, true, false, false, true>,
+     &launch_gemm<Cfg160, false, false, true, true>},   // 0: the largest tile that leaves room for a ring of 3 in 160 KB of LDS
     GG_VARIANT(256, 256, 2, 4, 2, false, 2, 1),   // 1: the largest tile the accumulators allow; ring of 2 only
     GG_VARIANT_R(128, 128, 2, 4, 4, false, 0, 1),   // 2: for N % 256 != 0
     GG_VARIANT_RS(128, 256, 2, 4, 3, false, 0, 1),   // 3
@@ -351,11 +358,13 @@ int run_gemm(const void* A, const float* SA, const void* B, const float* SB, con
   }
   // groups of at most one row tile on average: every weight byte is fetched once, and streamed past the L2
   const bool bstream = !ragged && v.launch_bstream && M_total <= (int64_t)G * v.BM;
-  // row-major scales, four K blocks of them per fetch: from K = 4096 on (8 groups of 1024 rows, N = 4096: K = 7168
-  // 247.3 -> 240.8 us, 7040 246.9 -> 240.5, 4096 147.2 -> 146.5; 32 groups of 512 rows, N = 7168, K = 2048: 285.5 -> 287.3)
-  const bool wide = v.launch_wide && !args.sa_kmajor && K >= 4096;
-  hipError_t e = (ragged ? (wide ? v.launch_ragged_wide : v.launch_ragged) : wide ? v.launch_wide : bstream ? v.launch_bstream : v.launch)(
-      args, (int)grid, static_cast<hipStream_t>(stream));
+  // row-major scales, four K blocks of them per fetch; second kernel: from K = 4096 on (8 groups of 1024 rows, N = 4096:
+  // K = 7168 247.3 -> 240.8 us, 7040 246.9 -> 240.5, 4096 147.2 -> 146.5; 32 groups of 512 rows, N = 7168, K = 2048: 285.5 ->
+  // 287.3); first kernel: where the number of K blocks allows one chunk buffer
+  const bool wide = v.launch_wide && !args.sa_kmajor && (v.min_kb3 ? K >= 4096 : args.KB % 4 == 0 || args.KB % 4 == 3);
+  const auto launch = ragged ? (wide ? v.launch_ragged_wide : v.launch_ragged)
+                      : bstream ? (wide ? v.launch_bstream_wide : v.launch_bstream) : (wide ? v.launch_wide : v.launch);
+  hipError_t e = launch(args, (int)grid, static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return GG_ERR_HIP;
   if (v.splitk) {
     const int64_t groups8 = M_total * (int64_t)(N / 8);
