@@ -255,6 +255,16 @@ gg::RowWork row_work(int64_t M_total, int KB, bool kmajor, int slots, unsigned* 
 // pass on 8192 x 7168, 58.7 MB of bytes: 414 against 418 us).
 bool row_bytes_stream(int64_t bytes) { return bytes > ((int64_t)96 << 20); }
 
+// Cache policy of the column quantiser's bytes.  Streamed, its own time falls (16384 tokens out of 8192, 7168 features:
+// 63.3 against 78.8 us; 8192 x 7168 30.6 against 37.7), but the weight-gradient GEMM that reads the bytes next loses more
+// than that while they would have stayed in the last-level cache (quantisers and GEMM together, 8192 x 7168 and 8192 x
+// 4096: 485 against 542 us).  So only bytes that are too many for it, beside input rows that are read again (together
+// 278.1 against 278.9 us at 16384 out of 8192 x 7168; 16384 x 8192 with every row read once: 223.5 against 218.2), and
+// only in whole 128-byte lines (16368 tokens, 4096 features: 46.3 against 34.8).
+bool cols_bytes_stream(const void* XT, int64_t T, int64_t M_total, int K) {
+  return M_total > T && M_total % 128 == 0 && ((uintptr_t)XT & 127) == 0 && M_total * K > ((int64_t)96 << 20);
+}
+
 // Device scratch a GEMM call with this variant uses: the split-K variants keep the fp32 partial sums of the two
 // halves of the K loop, [2][M_total][N]; the others nothing.
 size_t workspace_need(int variant, int64_t M_total, int N) {
@@ -723,7 +733,8 @@ int gg_fp8_quantize_cols(const void* X, const int32_t* row_src, void* XT, float*
   const int64_t tiles = mb * (K / gg::QC_FEATS);
   int64_t grid = (int64_t)device_cus() * 5;      // five workgroups fit a compute unit (registers); each walks its tiles with the next one's rows in flight
   if (grid > tiles) grid = tiles;
-  hipLaunchKernelGGL(gg::gg_quantize_cols_kernel, dim3((unsigned)grid), dim3(gg::Q_THREADS), 0,
+  const auto kernel = cols_bytes_stream(XT, T, M_total, K) ? &gg::gg_quantize_cols_kernel<true> : &gg::gg_quantize_cols_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(gg::Q_THREADS), 0,
                      static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(X), row_src,
                      static_cast<uint8_t*>(XT), SX, T, (int)M_total, K, (int)mb);
   return hipGetLastError() == hipSuccess ? GG_OK : GG_ERR_HIP;

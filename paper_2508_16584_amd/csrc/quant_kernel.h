@@ -236,6 +236,8 @@ __device__ __forceinline__ q_v4i swiglu8(const q_v4i g_raw, const q_v4i u_raw) {
 constexpr int QC_FEATS = 64;
 constexpr int QC_LDS_BYTES = 128 * 128 + 7 * 32;
 
+// SNT: the bytes are written with the streaming policy (see cols_bytes_stream() in gg_fp8.hip).
+template <bool SNT>
 __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint16_t* __restrict__ X,
                                                                      const int32_t* __restrict__ row_src,
                                                                      uint8_t* __restrict__ XT, float* __restrict__ SX,
@@ -307,8 +309,13 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
     const int tok0 = 128 * j + 16 * part;
     if (tok0 < M_total) {
       uint8_t* dst = XT + (int64_t)(k0 + 2 * fp) * M_total + tok0;
-      *(q_v4i*)dst = out[0];
-      *(q_v4i*)(dst + M_total) = out[1];
+      if constexpr (SNT) {
+        __builtin_nontemporal_store(out[0], (q_v4i*)dst);
+        __builtin_nontemporal_store(out[1], (q_v4i*)(dst + M_total));
+      } else {
+        *(q_v4i*)dst = out[0];
+        *(q_v4i*)(dst + M_total) = out[1];
+      }
     }
     if (part == 0) *(q_v2i*)(SX + (int64_t)j * K + k0 + 2 * fp) = (q_v2i){__builtin_bit_cast(int, scale[0]), __builtin_bit_cast(int, scale[1])};
     __syncthreads();                                        // before the next tile's rows overwrite these

@@ -115,3 +115,18 @@ def test_quantised_operands_feed_the_weight_gradient_gemm():
     err = np.abs(got.astype(np.float64) - ref["D"])
     bound = np.spacing(np.abs(ref["D"]).astype(np.float32)).astype(np.float64) + 2.0 ** -13 * ref["S"]
     assert np.all(err <= bound) and np.all(got[1] == 0)
+
+
+def test_streamed_bytes_equal_the_others():
+    """Large outputs of a repeated gather are written past the caches when their lines are whole (a 128-byte aligned
+    tensor); 16 bytes further on the same call takes the ordinary stores."""
+    T, M, K = 2048, 16384, 6208
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    X = torch.randn((T, K), generator=gen, device=DEV).to(torch.bfloat16)
+    src = torch.randint(-3, T + 3, (M,), generator=gen, device=DEV, dtype=torch.int32)
+    buf = torch.zeros(K * M + 128, dtype=torch.uint8, device=DEV)
+    want, s_want = gg.quantize_cols(X, src, XT=buf[16:16 + K * M].view(K, M))
+    got, s_got = gg.quantize_cols(X, src)
+    assert got.data_ptr() % 128 == 0 and want.data_ptr() % 128 == 16
+    assert torch.equal(got, want) and torch.equal(s_got.view(torch.int32), s_want.view(torch.int32))
