@@ -153,7 +153,7 @@ size_t gg_fp8_noalloc_max_elements(void);
  * every kernel here; this is the "neighbouring kernel" of Sec. 4 moved into the GEMM.  Bit-identical to the
  * two-call sequence unless K % 8192 == 4096 (there the plain GEMM adds the K blocks in a rotated order).
  * flags: GG_SA_KMAJOR (applies to SA and to SA2) or 0.  variant: -1, or one of the second kernel's "-rb" variants
- * with 192, 224 or 256 rows.  I a multiple of 128, K a multiple of 256 and >= 512 (GG_ERR_UNSUPPORTED otherwise:
+ * with 192, 224 or 256 rows, or the third kernel's "32x128" or "64x128" (32 or 64 rows).  I a multiple of 128, K a multiple of 256 and >= 512 (GG_ERR_UNSUPPORTED otherwise:
  * use the two calls); 2*I*K below 2^31.  A2, act_out 16-byte aligned.  Asynchronous on `stream`. */
 int gg_fp8_grouped_gemm_swiglu(const void* A, const float* SA, const void* B, const float* SB,
                                const int32_t* group_offsets, void* A2, float* SA2, void* act_out,

@@ -11,6 +11,7 @@
 
 #include "gemm_kernel.h"
 #include "gemm_kernel_rb.h"
+#include "gemm_kernel_sm.h"
 #include "pad_kernels.h"
 #include "quant_kernel.h"
 #include "wgrad_kernel.h"
@@ -95,6 +96,26 @@ hipError_t launch_gemm_rb(const gg::GemmArgs& args, int grid, hipStream_t stream
   return hipGetLastError();
 }
 
+template <class Cfg, bool RAGGED = false, bool BSTREAM = false>
+hipError_t launch_gemm_sm(const gg::GemmArgs& args, int grid, hipStream_t stream) {
+  static std::atomic<int> prepared[64];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev >= 0 && dev < 64 && !prepared[dev].load(std::memory_order_acquire)) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gg::gg_gemm_sm_kernel<Cfg, RAGGED, BSTREAM>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, Cfg::LDS_BYTES);
+    if (e != hipSuccess) return e;
+    prepared[dev].store(1, std::memory_order_release);
+  }
+  hipLaunchKernelGGL((gg::gg_gemm_sm_kernel<Cfg, RAGGED, BSTREAM>), dim3(grid), dim3(Cfg::NT), Cfg::LDS_BYTES, stream, args);
+  return hipGetLastError();
+}
+
+#define GG_VARIANT_SM(BM, BN, WM, WN, ST)   /* the third kernel: ragged shapes and streamed weights included */         \
+  {#BM "x" #BN "/" #WM "x" #WN "w/" #ST "s", BM, BN, gg::SmCfg<BM, BN, WM, WN, ST>::LDS_BYTES, gg::SmCfg<BM, BN, WM, WN, ST>::WG_PER_CU, \
+   &launch_gemm_sm<gg::SmCfg<BM, BN, WM, WN, ST>>, &launch_gemm_sm<gg::SmCfg<BM, BN, WM, WN, ST>, true>, false, false,  \
+   &launch_gemm_sm<gg::SmCfg<BM, BN, WM, WN, ST>, false, true>}
 #define GG_VARIANT(BM, BN, WM, WN, ST, XPF, GAP, WGPC)                                                        \
   {#BM "x" #BN "/" #WM "x" #WN "w/" #ST "s" XPF_SUFFIX_##XPF, BM, BN, gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>::LDS_BYTES, \
    WGPC, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>, nullptr}
@@ -144,26 +165,33 @@ const Variant kVariants[] = {
      &launch_gemm<gg::GemmCfg<128, 256, 2, 4, 3, false, 0>, false, true>, nullptr, false, true},
     {"64x256/1x8w/3s-k2", 64, 256, gg::GemmCfg<64, 256, 1, 8, 3, false, 0>::LDS_BYTES, 1,
      &launch_gemm<gg::GemmCfg<64, 256, 1, 8, 3, false, 0>, false, true>, nullptr, false, true},
+    // the third kernel: small tiles, several workgroups per compute unit (see pick_variant)
+    GG_VARIANT_SM(32, 64, 2, 2, 4),     // 23
+    GG_VARIANT_SM(32, 128, 1, 4, 3),    // 24
+    GG_VARIANT_SM(64, 128, 2, 2, 3),    // 25
 };
 constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
-constexpr int kDefaultSplitK = kNumVariants - 2;   // 128 x 256 tile
+constexpr int kDefaultSplitK = 21;   // the 128 x 256 tile of "-k2"
 
-// The second kernel with the activation epilogue (gg_fp8_grouped_gemm_swiglu): same tiles as variants 14, 15, 12.
+// The second and the third kernel with the activation epilogue (gg_fp8_grouped_gemm_swiglu): rows per tile as in
+// variants 14, 15, 12, 24, 25.
 struct FusedVariant {
   int variant;   // the plain variant it is the twin of
   int BM;
   hipError_t (*launch)(const gg::GemmArgs&, int, hipStream_t);
   // the instantiation for an odd number of K blocks (one more value in a scalar register: only the 192-row tile
-  // has room for it); null: even numbers only
+  // has room for it; the third kernel takes any number); null: even numbers only
   hipError_t (*launch_odd)(const gg::GemmArgs&, int, hipStream_t);
 };
 const FusedVariant kFused[] = {
     {14, 192, &launch_gemm_rb<gg::RbCfg<192, 2, false, true>>, &launch_gemm_rb<gg::RbCfg<192, 2, false, true, false, false, true>>},
     {15, 224, &launch_gemm_rb<gg::RbCfg<224, 2, false, true>>, nullptr},
     {12, 256, &launch_gemm_rb<gg::RbCfg<256, 2, false, true>>, nullptr},
+    {24, 32, &launch_gemm_sm<gg::SmCfg<32, 256, 1, 4, 4, true>>, &launch_gemm_sm<gg::SmCfg<32, 256, 1, 4, 4, true>>},
+    {25, 64, &launch_gemm_sm<gg::SmCfg<64, 256, 1, 4, 3, true>>, &launch_gemm_sm<gg::SmCfg<64, 256, 1, 4, 3, true>>},
 };
 
-// Automatic choice.  The host sees only sizes (the offsets stay on the device), so the choice works with the
+// Automatic choice, first among the tiles of the two larger kernels.  The host sees only sizes (the offsets stay on the device), so the choice works with the
 // expected tile count: a group ends in a partial tile half of the time on average, which adds G/2 tiles per
 // column of tiles.  Candidates and their measured character on MI355X:
 //   160x256, ring 3 (variant 0): the safe default; best when groups are short;
@@ -186,7 +214,7 @@ const FusedVariant kFused[] = {
 // before every launch: mean loss against the per-point best of the five 0.8 % (224 rows at 1.08 fitted the grid
 // equally well; 1.07 also takes the 192-row tile on the strongly skewed sizes of the down workload, where it is 0 - 4 %
 // the faster of the two).
-int pick_variant(int G, int64_t M_total, int N, int K) {
+int pick_large(int G, int64_t M_total, int N, int K) {
   const double avg = G > 0 ? (double)M_total / G : 0.0;
   const int n_tiles = (N + 255) / 256;
   const bool ragged = N % 256 != 0 || K % 128 != 0;
@@ -212,6 +240,66 @@ int pick_variant(int G, int64_t M_total, int N, int K) {
   if (second_kernel) consider(12, cost(256, 1.10));
   if (!ragged) consider(1, cost(256, K >= 4096 ? 1.02 : 0.94));   // the 256 x 256 ring-2 tile takes whole blocks only
   return best;
+}
+
+// ... then against the small tiles of the third kernel.  Estimated time of a launch, in us:
+//     4.2 + (a^4 + b^4 + c^4 + d^4)^(1/4),   a = rounds over the workgroups, at least one, x K steps x latency of a step
+//                                            b = tiles x K steps x work of a step on one compute unit / compute units
+//                                            c = bytes at 6.8 TB/s
+//                                            d = weight bytes / bytes of them in flight x the time a fetch takes
+// with K steps = K blocks + what a tile's start and end cost, and the expected number of row tiles (groups with rows, one
+// partial tile in two); a fetch takes 1.6 us from memory, 0.7 where the weights are few enough for the last-level cache.
+// Latency, work and extra steps per tile shape are a fit to 450 random problems (G 1 ... 256, M 1 ... 32768, N and K 256
+// ... 8192, sizes from even to strongly skewed), mean error 11 to 15 % per shape, most of which is the group sizes that the
+// host does not see.  On those the choice is 1.05 of the best of 25 tiles, 1.64 without the small tiles: 8 groups of 8
+// rows, N = 4096, K = 7168 40 against 65 us (128 x 256), one row, N = K = 4096 12 against 32, 5 groups of 250 rows, N = 768,
+// K = 1280 9.1 against 16.6.  The small tile has to win by a tenth: on the problems of more than 60 us that loses least.
+struct TileTime {
+  int variant;
+  double latency, work, extra;
+  int in_flight;         // bytes of weights that a workgroup has on their way
+};
+const TileTime kTileTimes[] = {
+    {0, 1.03, 1.14, 2.91, 64 << 10},  {1, 1.29, 1.28, 4.35, 32 << 10},  {2, 0.572, 0.575, 3.64, 48 << 10}, {3, 0.906, 0.985, 3.20, 64 << 10},
+    {12, 1.29, 1.28, 4.35, 72 << 10}, {14, 1.05, 1.13, 4.16, 72 << 10}, {15, 1.17, 1.22, 4.38, 72 << 10},
+    {23, 0.244, 0.214, 4.05, 24 << 10}, {24, 0.391, 0.291, 2.29, 32 << 10}, {25, 0.473, 0.386, 3.08, 32 << 10},
+};
+constexpr int kFirstSmall = 23;
+
+double estimate_us(const TileTime& t, int BM, int n_tiles, int wg_per_cu, int G, int64_t M_total, double weight_bytes, double row_bytes, int K) {
+  const double cus = (double)device_cus();
+  const double filled = G * (1.0 - std::exp(-(double)M_total / G));            // groups with rows, if they were dealt out evenly
+  const double m_tiles = std::fmax(filled, (double)M_total / BM + 0.5 * filled);
+  const double tiles = m_tiles * n_tiles, steps = (K + 127) / 128 + t.extra;
+  const double a = std::fmax(tiles / (cus * wg_per_cu), 1.0) * steps * t.latency;
+  const double b = tiles * steps * t.work / cus;
+  const double weights = filled * weight_bytes;
+  const double c = (weights + (double)M_total * row_bytes) / 6.8e6;
+  const double d = weights / (std::fmin(tiles, cus * wg_per_cu) * t.in_flight) * (weights > 64e6 ? 1.6 : 0.7);
+  return 4.2 + std::sqrt(std::sqrt(a * a * a * a + b * b * b * b + c * c * c * c + d * d * d * d));
+}
+
+// The same constants of the tiles with the activation epilogue (by the number of their plain twin).
+const TileTime kFusedTimes[] = {
+    {14, 1.11, 1.20, 9.08, 72 << 10}, {15, 1.33, 1.41, 7.83, 72 << 10}, {12, 1.44, 1.66, 9.18, 72 << 10},
+    {24, 0.681, 0.589, 5.25, 96 << 10}, {25, 0.935, 0.817, 5.65, 64 << 10},
+};
+
+int pick_variant(int G, int64_t M_total, int N, int K) {
+  const int large = pick_large(G, M_total, N, K);
+  if (G <= 0 || M_total <= 0) return large;
+  double t_large = 0, t_small = 0;
+  int small = -1;
+  for (const TileTime& t : kTileTimes) {
+    const Variant& v = kVariants[t.variant];
+    const bool is_small = t.variant >= kFirstSmall;
+    if (!is_small && t.variant != large) continue;
+    if (is_small && (double)(M_total / v.BM + G) * ((N + v.BN - 1) / v.BN) > 2147483647.0) continue;     // tiles are counted in 32 bits
+    const double us = estimate_us(t, v.BM, (N + v.BN - 1) / v.BN, v.wg_per_cu, G, M_total, (double)N * K, K + 2.0 * N, K);
+    if (!is_small) t_large = us;
+    else if (small < 0 || us < t_small) { t_small = us; small = t.variant; }
+  }
+  return t_small < 0.9 * t_large ? small : large;
 }
 
 // The padded problem (Sec. 3: every group a multiple of 128 rows; M_pad_cap = 128 * (ceil(M_total / 128) + G) is a
@@ -558,7 +646,7 @@ int gg_fp8_grouped_gemm_swiglu(const void* A, const float* SA, const void* B, co
   const FusedVariant* fv = nullptr;
   const bool odd_kb = ((K / 128) & 1) != 0;
   if (variant < 0 && odd_kb) {
-    fv = &kFused[0];
+    fv = &kFused[0];     // the only larger tile that takes an odd number
   } else if (variant < 0) {
     // the cheapest of the three tile heights under the cost model of the automatic choice
     double c_best = 0;
@@ -569,6 +657,18 @@ int gg_fp8_grouped_gemm_swiglu(const void* A, const float* SA, const void* B, co
       const double c = (whole + (frac > 1e-9 ? 0.3 + 0.7 * frac : 0.0)) * kFused[i].BM / eff[i];
       if (!fv || c < c_best) { c_best = c; fv = &kFused[i]; }
     }
+  }
+  if (variant < 0) {
+    // ... and, if it wins by a tenth, the better of the small tiles, by the estimate of the plain GEMM's choice with
+    // constants of their own (a fit to 200 random problems; the choice is 1.02 of the best of the five tiles, 1.45 without
+    // the small ones: 8 groups of 8 rows, I = 2048, K = 7168 56 against 81 us, 8 groups of 64 rows 67 against 82)
+    auto us = [&](const FusedVariant& f) {
+      for (const TileTime& t : kFusedTimes)
+        if (t.variant == f.variant) return estimate_us(t, f.BM, I / 128, 1, G, M_total, (double)N * K, (double)K + I, K);
+      return 1e30;
+    };
+    const FusedVariant* const small = us(kFused[3]) < us(kFused[4]) ? &kFused[3] : &kFused[4];
+    if (us(*small) < 0.9 * us(*fv)) fv = small;
   } else {
     for (const FusedVariant& f : kFused)
       if (f.variant == variant) fv = &f;

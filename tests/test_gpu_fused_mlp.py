@@ -176,3 +176,21 @@ def test_fused_at_the_largest_weight_offsets():
     blk = cols[::128] // 128                                           # the 128-column blocks these columns come from
     ref = orc.grouped_gemm(A, SA, Bs, np.ascontiguousarray(SB[:, blk]), off, with_abs_sum=True)
     assert_parity(u16(H[:, torch.from_numpy(cols).to(DEV)]), ref, empirical=False, what="H at the ends of gate and up")
+
+
+@pytest.mark.parametrize("sizes,inter,K", [
+    ([1], 128, 384),                                # one row, three K blocks
+    ([0, 31, 32, 33, 1], 256, 640),                 # around a tile of 32 rows; an odd number of K blocks
+    ([63, 64, 65, 0, 129], 384, 512),               # around a tile of 64 rows
+    # more groups than a wave has lanes, one tile each.  (Not K = 4096, an odd multiple of 4096: there the plain GEMM adds a
+    # column block's K blocks in a rotated order and the fused one does not, so their activations differ by an ulp of the
+    # plain GEMM's bfloat16 projections, which is not what this test compares.)
+    ([7] * 70, 256, 3968),
+    ([500, 0, 700, 3], 2048, 1152),                 # several tiles per workgroup, nine K blocks
+])
+def test_fused_small_tiles(sizes, inter, K):
+    cfg = WorkloadConfig("fuseds", 5200 + inter + K, len(sizes), K, 2 * inter, 0, "custom", "latency")
+    p = make_problem(cfg, sizes=np.array(sizes))
+    small = [v for v in range(gg.num_variants()) if gg.variant_name(v) in ("32x128/1x4w/3s", "64x128/2x2w/3s")]
+    assert len(small) == 2
+    check_against_two_calls_and_oracle(p, variants=[-1] + small)
