@@ -299,7 +299,7 @@ int pick_variant(int G, int64_t M_total, int N, int K) {
     if (!is_small) t_large = us;
     else if (small < 0 || us < t_small) { t_small = us; small = t.variant; }
   }
-  return t_small < 0.9 * t_large ? small : large;
+  return small >= 0 && t_small < 0.9 * t_large ? small : large;
 }
 
 // The padded problem (Sec. 3: every group a multiple of 128 rows; M_pad_cap = 128 * (ceil(M_total / 128) + G) is a
