@@ -220,17 +220,22 @@ def _check(status: int):
         raise GGError(status, status_str(status))
 
 
+# A small call is bound by what happens here: the helpers below run several times per call, so they make no object
+# that the call does not need (grouped_gemm of a small problem takes 8.8 us of host time, 4.1 of them in the library; 13.0
+# with a Stream and c_void_p objects, a second look at fresh outputs and one test at a time).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _want(t, name, dtype, ndim):
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.dim() == ndim and t.is_cuda and t.is_contiguous():
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch tensor")
     if t.dtype != dtype:
@@ -241,6 +246,14 @@ def _want(t, name, dtype, ndim):
         raise ValueError(f"{name} must be contiguous")
     if not t.is_cuda:
         raise ValueError(f"{name} must live on the GPU")
+
+
+def _output(t, name, dtype, shape, like):
+    """A fresh tensor of this shape on the device of `like`, or the caller's (whose shape the caller of this compares)."""
+    if t is None:
+        return torch.empty(shape, dtype=dtype, device=like.device)
+    _want(t, name, dtype, len(shape))
+    return t
 
 
 GG_OUT_F16, GG_SA_KMAJOR, GG_PADDED_GROUPS, GG_OUT_BF16 = 1, 2, 4, 8        # flags of the _ex entry points
@@ -260,9 +273,9 @@ def _gemm_shapes(A, SA, B, SB, group_offsets, sa_kmajor=False):
         raise ValueError(f"group_offsets must have G+1={G + 1} entries")
     KB, NB = -(-K // 128), -(-N // 128)          # ceilings (Table 1 of the paper)
     sa_shape = (KB, M_total) if sa_kmajor else (M_total, KB)
-    if tuple(SA.shape) != sa_shape:
+    if SA.shape != sa_shape:
         raise ValueError(f"SA must be {list(sa_shape)}")
-    if tuple(SB.shape) != (G, NB, KB):
+    if SB.shape != (G, NB, KB):
         raise ValueError(f"SB must be [{G}, {NB}, {KB}]")
     return G, M_total, N, K
 
@@ -312,6 +325,8 @@ _ws_cache = {}
 def _workspace(G, M_total, N, K, device, workspace=None, stream=None, variant=-1):
     """The scratch buffer of a GEMM call: the caller's, or one per (device, stream) kept by this binding (calls on one
     stream run in order, so they may share it; the library clears what it uses at the start of every call)."""
+    if workspace is None and variant < 0:
+        return None, 0                           # the variants that the library picks by itself need none
     n = workspace_bytes(G, M_total, N, K, variant)
     if workspace is not None:
         _want(workspace, "workspace", torch.uint8, 1)
@@ -346,12 +361,13 @@ def grouped_gemm(A, SA, B, SB, group_offsets, C=None, variant: int = -1, stream=
         raise TypeError("C must be bfloat16 or float16")
     if C is None:
         C = torch.empty((M_total, N), dtype=out_dtype, device=A.device)
-    _want(C, "C", out_dtype, 2)
-    if tuple(C.shape) != (M_total, N):
-        raise ValueError(f"C must be [{M_total}, {N}]")
+    else:
+        _want(C, "C", out_dtype, 2)
+        if C.shape != (M_total, N):
+            raise ValueError(f"C must be [{M_total}, {N}]")
     ws, n = _workspace(G, M_total, N, K, A.device, workspace, stream, variant)
-    args = (_ptr(A), _ptr(SA), _ptr(B), _ptr(SB), _ptr(group_offsets), _ptr(C), G, M_total, N, K, _ptr(ws), n,
-            _stream(stream), int(variant))
+    args = (A.data_ptr(), SA.data_ptr(), B.data_ptr(), SB.data_ptr(), group_offsets.data_ptr(), C.data_ptr(), G, M_total, N, K,
+            _ptr(ws), n, _stream(stream), int(variant))
     if variant == -1 and not sa_kmajor and out_dtype == torch.bfloat16:
         _check(lib.gg_fp8_grouped_gemm(*args[:-1]))
     elif sa_kmajor:
@@ -391,19 +407,14 @@ def grouped_gemm_swiglu(A, SA, B, SB, group_offsets, A2=None, SA2=None, act_out=
     if N % 2:
         raise ValueError("B must hold an even number of rows per group (gate | up)")
     inter = N // 2
-    if A2 is None:
-        A2 = torch.empty((M_total, inter), dtype=torch.uint8, device=A.device)
-    if SA2 is None:
-        SA2 = torch.empty((inter // 128, M_total) if sa_kmajor else (M_total, inter // 128), dtype=torch.float32, device=A.device)
-    if act_out is None and want_act:
-        act_out = torch.empty((M_total, inter), dtype=torch.bfloat16, device=A.device)
-    _want(A2, "A2", torch.uint8, 2)
-    _want(SA2, "SA2", torch.float32, 2)
-    if act_out is not None:
-        _want(act_out, "act_out", torch.bfloat16, 2)
-        if tuple(act_out.shape) != (M_total, inter):
+    a_shape, sa_shape = (M_total, inter), (inter // 128, M_total) if sa_kmajor else (M_total, inter // 128)
+    A2 = _output(A2, "A2", torch.uint8, a_shape, A)
+    SA2 = _output(SA2, "SA2", torch.float32, sa_shape, A)
+    if act_out is not None or want_act:
+        act_out = _output(act_out, "act_out", torch.bfloat16, a_shape, A)
+        if act_out.shape != a_shape:
             raise ValueError(f"act_out must be [{M_total}, {inter}]")
-    if tuple(A2.shape) != (M_total, inter) or tuple(SA2.shape) != ((inter // 128, M_total) if sa_kmajor else (M_total, inter // 128)):
+    if A2.shape != a_shape or SA2.shape != sa_shape:
         raise ValueError("A2 or SA2 does not have the shape of the output")
     _check(lib.gg_fp8_grouped_gemm_swiglu(_ptr(A), _ptr(SA), _ptr(B), _ptr(SB), _ptr(group_offsets), _ptr(A2), _ptr(SA2),
                                           _ptr(act_out), G, M_total, inter, K, _stream(stream), int(variant),
@@ -425,16 +436,11 @@ def grouped_gemm_wgrad(XT, SX, DYT, SDY, group_offsets, dW=None, stream=None, ou
     N = DYT.shape[0]
     MB = (M_total + 127) // 128
     G = group_offsets.shape[0] - 1
-    if DYT.shape[1] != M_total or tuple(SX.shape) != (MB, K) or tuple(SDY.shape) != (MB, N):
+    if DYT.shape[1] != M_total or SX.shape != (MB, K) or SDY.shape != (MB, N):
         raise ValueError("XT [K, M_total], DYT [N, M_total], SX [ceil(M_total/128), K], SDY [ceil(M_total/128), N] expected")
-    for t, name in ((XT, "XT"), (SX, "SX"), (DYT, "DYT"), (SDY, "SDY"), (group_offsets, "group_offsets")):
-        if not t.is_cuda or not t.is_contiguous():
-            raise ValueError(f"{name} must be a contiguous device tensor")
     out_dtype = torch.bfloat16 if out_bf16 else torch.float32
-    if dW is None:
-        dW = torch.empty((G, N, K), dtype=out_dtype, device=XT.device)
-    _want(dW, "dW", out_dtype, 3)
-    if tuple(dW.shape) != (G, N, K) or not dW.is_cuda or not dW.is_contiguous():
+    dW = _output(dW, "dW", out_dtype, (G, N, K), XT)
+    if dW.shape != (G, N, K):
         raise ValueError(f"dW must be a contiguous device tensor [{G}, {N}, {K}]")
     args = (_ptr(XT), _ptr(SX), _ptr(DYT), _ptr(SDY), _ptr(group_offsets), _ptr(dW), G, M_total, N, K, _stream(stream))
     _check(lib.gg_fp8_grouped_gemm_wgrad_ex(*args, GG_OUT_BF16) if out_bf16 else lib.gg_fp8_grouped_gemm_wgrad(*args))
@@ -454,13 +460,9 @@ def quantize_cols(X, row_src=None, M_total=None, XT=None, SX=None, stream=None):
     elif M_total is None:
         M_total = T
     MB = (M_total + 127) // 128
-    if XT is None:
-        XT = torch.empty((K, M_total), dtype=torch.uint8, device=X.device)
-    if SX is None:
-        SX = torch.empty((MB, K), dtype=torch.float32, device=X.device)
-    _want(XT, "XT", torch.uint8, 2)
-    _want(SX, "SX", torch.float32, 2)
-    if tuple(XT.shape) != (K, M_total) or tuple(SX.shape) != (MB, K):
+    XT = _output(XT, "XT", torch.uint8, (K, M_total), X)
+    SX = _output(SX, "SX", torch.float32, (MB, K), X)
+    if XT.shape != (K, M_total) or SX.shape != (MB, K):
         raise ValueError("XT or SX does not have the shape of the output")
     _check(lib.gg_fp8_quantize_cols(_ptr(X), _ptr(row_src), _ptr(XT), _ptr(SX), T, M_total, K, _stream(stream)))
     return XT, SX
@@ -550,13 +552,10 @@ def quantize_rows(X, row_src=None, M_total=None, A=None, SA=None, stream=None, s
         M_total = row_src.shape[0]
     elif M_total is None:
         M_total = T
-    if A is None:
-        A = torch.empty((M_total, K), dtype=torch.uint8, device=X.device)
-    if SA is None:
-        SA = torch.empty((K // 128, M_total) if sa_kmajor else (M_total, K // 128), dtype=torch.float32, device=X.device)
-    _want(A, "A", torch.uint8, 2)
-    _want(SA, "SA", torch.float32, 2)
-    if tuple(SA.shape) != ((K // 128, M_total) if sa_kmajor else (M_total, K // 128)) or tuple(A.shape) != (M_total, K):
+    a_shape, sa_shape = (M_total, K), (K // 128, M_total) if sa_kmajor else (M_total, K // 128)
+    A = _output(A, "A", torch.uint8, a_shape, X)
+    SA = _output(SA, "SA", torch.float32, sa_shape, X)
+    if SA.shape != sa_shape or A.shape != a_shape:
         raise ValueError("A or SA does not have the shape of the output")
     args = (_ptr(X), _ptr(row_src), _ptr(A), _ptr(SA), T, M_total, K, _stream(stream))
     _check(lib.gg_fp8_quantize_rows_ex(*args, GG_SA_KMAJOR) if sa_kmajor else lib.gg_fp8_quantize_rows(*args))
@@ -572,17 +571,12 @@ def swiglu_quantize_rows(H, A=None, SA=None, act_out=None, want_act=False, strea
     if two_i % 2:
         raise ValueError("H must have an even number of columns")
     inter = two_i // 2
-    if A is None:
-        A = torch.empty((M, inter), dtype=torch.uint8, device=H.device)
-    if SA is None:
-        SA = torch.empty((inter // 128, M) if sa_kmajor else (M, inter // 128), dtype=torch.float32, device=H.device)
-    if act_out is None and want_act:
-        act_out = torch.empty((M, inter), dtype=torch.bfloat16, device=H.device)
-    _want(A, "A", torch.uint8, 2)
-    _want(SA, "SA", torch.float32, 2)
-    if act_out is not None:
-        _want(act_out, "act_out", torch.bfloat16, 2)
-    if tuple(SA.shape) != ((inter // 128, M) if sa_kmajor else (M, inter // 128)) or tuple(A.shape) != (M, inter):
+    a_shape, sa_shape = (M, inter), (inter // 128, M) if sa_kmajor else (M, inter // 128)
+    A = _output(A, "A", torch.uint8, a_shape, H)
+    SA = _output(SA, "SA", torch.float32, sa_shape, H)
+    if act_out is not None or want_act:
+        act_out = _output(act_out, "act_out", torch.bfloat16, a_shape, H)
+    if SA.shape != sa_shape or A.shape != a_shape:
         raise ValueError("A or SA does not have the shape of the output")
     args = (_ptr(H), _ptr(A), _ptr(SA), _ptr(act_out), M, inter, _stream(stream))
     _check(lib.gg_fp8_swiglu_quantize_rows_ex(*args, GG_SA_KMAJOR) if sa_kmajor else lib.gg_fp8_swiglu_quantize_rows(*args))
