@@ -249,10 +249,13 @@ def _want(t, name, dtype, ndim):
 
 
 def _output(t, name, dtype, shape, like):
-    """A fresh tensor of this shape on the device of `like`, or the caller's (whose shape the caller of this compares)."""
+    """A fresh tensor of this shape on the device of `like`, or the caller's, which has to have it: the kernels write all of
+    it and see no more than its address."""
     if t is None:
         return torch.empty(shape, dtype=dtype, device=like.device)
     _want(t, name, dtype, len(shape))
+    if t.shape != shape:
+        raise ValueError(f"{name} must be {list(shape)}")
     return t
 
 
@@ -412,10 +415,6 @@ def grouped_gemm_swiglu(A, SA, B, SB, group_offsets, A2=None, SA2=None, act_out=
     SA2 = _output(SA2, "SA2", torch.float32, sa_shape, A)
     if act_out is not None or want_act:
         act_out = _output(act_out, "act_out", torch.bfloat16, a_shape, A)
-        if act_out.shape != a_shape:
-            raise ValueError(f"act_out must be [{M_total}, {inter}]")
-    if A2.shape != a_shape or SA2.shape != sa_shape:
-        raise ValueError("A2 or SA2 does not have the shape of the output")
     _check(lib.gg_fp8_grouped_gemm_swiglu(_ptr(A), _ptr(SA), _ptr(B), _ptr(SB), _ptr(group_offsets), _ptr(A2), _ptr(SA2),
                                           _ptr(act_out), G, M_total, inter, K, _stream(stream), int(variant),
                                           GG_SA_KMAJOR if sa_kmajor else 0))
@@ -440,8 +439,6 @@ def grouped_gemm_wgrad(XT, SX, DYT, SDY, group_offsets, dW=None, stream=None, ou
         raise ValueError("XT [K, M_total], DYT [N, M_total], SX [ceil(M_total/128), K], SDY [ceil(M_total/128), N] expected")
     out_dtype = torch.bfloat16 if out_bf16 else torch.float32
     dW = _output(dW, "dW", out_dtype, (G, N, K), XT)
-    if dW.shape != (G, N, K):
-        raise ValueError(f"dW must be a contiguous device tensor [{G}, {N}, {K}]")
     args = (_ptr(XT), _ptr(SX), _ptr(DYT), _ptr(SDY), _ptr(group_offsets), _ptr(dW), G, M_total, N, K, _stream(stream))
     _check(lib.gg_fp8_grouped_gemm_wgrad_ex(*args, GG_OUT_BF16) if out_bf16 else lib.gg_fp8_grouped_gemm_wgrad(*args))
     return dW
@@ -462,8 +459,6 @@ def quantize_cols(X, row_src=None, M_total=None, XT=None, SX=None, stream=None):
     MB = (M_total + 127) // 128
     XT = _output(XT, "XT", torch.uint8, (K, M_total), X)
     SX = _output(SX, "SX", torch.float32, (MB, K), X)
-    if XT.shape != (K, M_total) or SX.shape != (MB, K):
-        raise ValueError("XT or SX does not have the shape of the output")
     _check(lib.gg_fp8_quantize_cols(_ptr(X), _ptr(row_src), _ptr(XT), _ptr(SX), T, M_total, K, _stream(stream)))
     return XT, SX
 
@@ -555,8 +550,6 @@ def quantize_rows(X, row_src=None, M_total=None, A=None, SA=None, stream=None, s
     a_shape, sa_shape = (M_total, K), (K // 128, M_total) if sa_kmajor else (M_total, K // 128)
     A = _output(A, "A", torch.uint8, a_shape, X)
     SA = _output(SA, "SA", torch.float32, sa_shape, X)
-    if SA.shape != sa_shape or A.shape != a_shape:
-        raise ValueError("A or SA does not have the shape of the output")
     args = (_ptr(X), _ptr(row_src), _ptr(A), _ptr(SA), T, M_total, K, _stream(stream))
     _check(lib.gg_fp8_quantize_rows_ex(*args, GG_SA_KMAJOR) if sa_kmajor else lib.gg_fp8_quantize_rows(*args))
     return A, SA
@@ -576,8 +569,6 @@ def swiglu_quantize_rows(H, A=None, SA=None, act_out=None, want_act=False, strea
     SA = _output(SA, "SA", torch.float32, sa_shape, H)
     if act_out is not None or want_act:
         act_out = _output(act_out, "act_out", torch.bfloat16, a_shape, H)
-    if SA.shape != sa_shape or A.shape != a_shape:
-        raise ValueError("A or SA does not have the shape of the output")
     args = (_ptr(H), _ptr(A), _ptr(SA), _ptr(act_out), M, inter, _stream(stream))
     _check(lib.gg_fp8_swiglu_quantize_rows_ex(*args, GG_SA_KMAJOR) if sa_kmajor else lib.gg_fp8_swiglu_quantize_rows(*args))
     return A, SA, act_out
