@@ -259,6 +259,16 @@ def _output(t, name, dtype, shape, like):
     return t
 
 
+def _rows_of_output(t, name, rows, cols, like):
+    """The same for the bfloat16 rows of the padded path, of which a caller's tensor may have more."""
+    if t is None:
+        return torch.empty((rows, cols), dtype=torch.bfloat16, device=like.device)
+    _want(t, name, torch.bfloat16, 2)
+    if t.shape[0] < rows or t.shape[1] != cols:
+        raise ValueError(f"{name} must have at least {rows} rows of {cols}")
+    return t
+
+
 GG_OUT_F16, GG_SA_KMAJOR, GG_PADDED_GROUPS, GG_OUT_BF16 = 1, 2, 4, 8        # flags of the _ex entry points
 
 
@@ -504,18 +514,14 @@ def grouped_gemm_padded(A_pad, SA_pad, B, SB, padded_offsets, C_pad=None, stream
     lib = load_library()
     if sa_kmajor:
         G, M_pad_cap, N, K = _gemm_shapes(A_pad, SA_pad, B, SB, padded_offsets, True)
-        if C_pad is None:
-            C_pad = torch.empty((M_pad_cap, N), dtype=torch.bfloat16, device=A_pad.device)
-        _want(C_pad, "C_pad", torch.bfloat16, 2)
+        C_pad = _rows_of_output(C_pad, "C_pad", M_pad_cap, N, A_pad)
         ws, n = _workspace(G, M_pad_cap, N, K, A_pad.device, None, stream)
         _check(lib.gg_fp8_grouped_gemm_ex(_ptr(A_pad), _ptr(SA_pad), _ptr(B), _ptr(SB), _ptr(padded_offsets), _ptr(C_pad),
                                           G, M_pad_cap, N, K, _ptr(ws), n, _stream(stream), -1,
                                           GG_SA_KMAJOR | GG_PADDED_GROUPS))
         return C_pad
     G, M_pad_cap, N, K = _gemm_shapes(A_pad, SA_pad, B, SB, padded_offsets)
-    if C_pad is None:
-        C_pad = torch.empty((M_pad_cap, N), dtype=torch.bfloat16, device=A_pad.device)
-    _want(C_pad, "C_pad", torch.bfloat16, 2)
+    C_pad = _rows_of_output(C_pad, "C_pad", M_pad_cap, N, A_pad)
     ws, n = _workspace(G, M_pad_cap, N, K, A_pad.device, None, stream)
     _check(lib.gg_fp8_grouped_gemm_padded(_ptr(A_pad), _ptr(SA_pad), _ptr(B), _ptr(SB), _ptr(padded_offsets),
                                           _ptr(C_pad), G, M_pad_cap, N, K, _ptr(ws), n, _stream(stream)))
@@ -526,10 +532,13 @@ def unpad(C_pad, group_offsets, padded_offsets, M_total: int, C=None, stream=Non
     """gg_fp8_unpad: gathers the valid rows of C_pad into C [M_total, N]."""
     lib = load_library()
     _want(C_pad, "C_pad", torch.bfloat16, 2)
+    _want(group_offsets, "group_offsets", torch.int32, 1)
+    _want(padded_offsets, "padded_offsets", torch.int32, 1)
     N = C_pad.shape[1]
     G = group_offsets.shape[0] - 1
-    if C is None:
-        C = torch.empty((M_total, N), dtype=torch.bfloat16, device=C_pad.device)
+    if padded_offsets.shape[0] != G + 1:
+        raise ValueError(f"padded_offsets must have G+1={G + 1} entries")
+    C = _rows_of_output(C, "C", M_total, N, C_pad)
     _check(lib.gg_fp8_unpad(_ptr(C_pad), _ptr(group_offsets), _ptr(padded_offsets), _ptr(C), G, M_total, N,
                             _stream(stream)))
     return C

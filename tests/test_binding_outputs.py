@@ -85,3 +85,25 @@ def test_an_output_of_another_shape_is_refused(library, case):
                 with pytest.raises(ValueError):
                     call(**{name: dev(*shape, dtype=fits.dtype)})
                 assert not library.calls, f"{name} {shape}"
+
+
+# The padded path: rows past the problem's are left alone, so there may be more of them, but not fewer, and no other width.
+PADDED = {
+    "grouped_gemm_padded": lambda rows, cols, km=False: gg.grouped_gemm_padded(
+        dev(M, K), f32(3, M) if km else f32(M, 3), dev(G, I, K), f32(G, 2, 3), i32(G + 1), C_pad=bf16(rows, cols), stream=STREAM, sa_kmajor=km),
+    "grouped_gemm_padded K-block-major": lambda rows, cols: PADDED["grouped_gemm_padded"](rows, cols, True),
+    "unpad": lambda rows, cols: gg.unpad(bf16(2 * M, I), i32(G + 1), i32(G + 1), M, C=bf16(rows, cols), stream=STREAM),
+}
+
+
+@pytest.mark.parametrize("case", PADDED)
+def test_the_padded_path_refuses_an_output_that_is_too_small(library, case):
+    for rows in (M, M + 1, 3 * M):
+        PADDED[case](rows, I)
+    done = len(library.calls)
+    for rows, cols in ((M - 1, I), (0, I), (M, I - 8), (M, I + 8), (M, 0)):
+        with pytest.raises(ValueError):
+            PADDED[case](rows, cols)
+    with pytest.raises(ValueError):
+        gg.unpad(bf16(2 * M, I), i32(G + 1), i32(G), M, stream=STREAM)        # offsets of another number of groups
+    assert len(library.calls) == done
