@@ -115,6 +115,10 @@ __device__ __forceinline__ int sa_view_bytes(const GemmArgs& a, int64_t grow, in
   return a.sa_kmajor ? (int)(((int64_t)a.KB * a.M_total - grow) * 4) : rows_valid * a.sa_row_stride;
 }
 
+// How the scales of A reach LDS (see "activation scales" in the first kernel): per K block, in chunks of four K blocks through
+// a ring of chunk buffers, the same through one buffer and registers.
+enum : int { kScalesPerBlock = 0, kScalesChunks = 1, kScalesOneChunk = 2 };
+
 template <int BM_, int BN_, int WM_, int WN_, int STAGES_, bool XPF_ = false, int GAP_ = 0, int PIPE_ = 3>
 struct GemmCfg {
   static constexpr int GAP = GAP_;            // MFMAs between two in-stream DMAs (0 = spread over the whole stream)
@@ -131,23 +135,22 @@ struct GemmCfg {
   static constexpr int SA_ROWS = SA_WAVES * 64;
   static constexpr int SB_BYTES = 256;         // BN/128 scales of B per K block, replicated over one wave-wide DMA
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES + SB_BYTES;
-  // LDS for the scales of A (see "activation scales" in the kernel): chunks of four K blocks, of which STAGES consecutive
-  // K blocks take at most SA_BUFS (the last chunk of a tile may hold a single block); where those do not fit beside the
-  // ring (160 x 256), one slot of one K block per ring buffer.
+  // LDS behind the ring, for the scales of A.  Per block: a slot per ring buffer.  In chunks: of four K blocks, of which
+  // STAGES consecutive K blocks take at most SA_BUFS (the last chunk of a tile may hold a single block), and 256 bytes
+  // nobody reads (empty fetches).  Where those do not fit beside the ring (160 x 256): one chunk, whose scales a wave
+  // takes into registers at once.
   static constexpr int SA_SLOT = SA_ROWS * 4, SA_CHUNK = SA_ROWS * 16;
   static constexpr int SA_BUFS = STAGES_ <= 2 ? 2 : STAGES_ <= 6 ? 3 : 4;
-  static constexpr bool WIDE = !XPF_ && STAGES_ * STAGE_BYTES + SA_BUFS * SA_CHUNK + 256 <= 160 * 1024;
   static constexpr int SA_BASE = STAGES_ * STAGE_BYTES;
-  static constexpr int DUMP_BASE = SA_BASE + (WIDE ? SA_BUFS * SA_CHUNK : STAGES_ * SA_SLOT);      // 256 bytes nobody reads (empty fetches)
   static_assert(STAGES_ <= 8, "four chunks");
-  // ONE_CHUNK (160 x 256): one chunk buffer in the place of the slots, whose scales a wave takes into registers at once
-  // (see the kernel)
-  static constexpr bool ONE_CHUNK = !XPF_ && !WIDE && STAGES_ == 3;
-  static constexpr int ONE_DUMP = SA_BASE + SA_CHUNK, ONE_LDS_BYTES = ONE_DUMP + 256;
+  static constexpr int SA_BYTES[3] = {STAGES_ * SA_SLOT, SA_BUFS * SA_CHUNK + 256, SA_CHUNK + 256};
+  static constexpr int lds_bytes(int scales) { return SA_BASE + SA_BYTES[scales]; }
+  static constexpr bool chunks_fit = !XPF_ && SA_BASE + SA_BYTES[kScalesChunks] <= 160 * 1024;
+  static constexpr bool one_chunk_fits = !XPF_ && STAGES_ == 3 && SA_BASE + SA_BYTES[kScalesOneChunk] <= 160 * 1024;
   static constexpr int SB_WAVE = NW - 1;      // the wave that fetches them
   static constexpr int MFMAS = (BM / WM / 16) * (BN / WN / 16);   // MFMAs per wave per K block
   static constexpr int PIPE = MFMAS < PIPE_ ? MFMAS : PIPE_;               // MFMAs in flight before their FMAs are issued
-  static constexpr int LDS_BYTES = DUMP_BASE + (WIDE ? 256 : 0);
+  static constexpr int LDS_BYTES = SA_BASE + SA_BYTES[kScalesPerBlock];
   // cross-block operand prefetch with a mid-stream barrier (see the kernel): needs a ring of 3 and an even TM
   static constexpr bool XPF = XPF_;
   static_assert(!XPF_ || (STAGES_ >= 3 && (BM_ / WM_ / 16) % 2 == 0), "XPF needs a ring of 3 buffers and an even TM");
@@ -330,11 +333,11 @@ struct GroupIndex {
 // weight byte is fetched once; left to the default policy the 7.5 GB of a 256-expert layer push the activation tiles
 // (which the 16 column tiles of a group share) out of the L2.  Where several row tiles share a group's weights the
 // policy costs 17 - 35 %, so the host asks for it only when M_total <= G * BM.
-// ONE: row-major scales four K blocks at a time on a tile that has room for one chunk of them only.  A chunk's scales go
+// SCALES: how the scales of A are fetched.  kScalesOneChunk is for a tile that has room for one chunk only.  A chunk's scales go
 // into registers in its first K step, and the fetch of the next one, two steps before that is needed, finds the buffer
 // free: a tile's last chunk must have begun two steps before its end, so the number of K blocks is 0 or 3 modulo 4.
 // 256 groups of 128 rows, N = 4096, K = 7168: 1432 us, 1533 with 4-byte fetches per K block.
-template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false, bool ONE = false>
+template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false, int SCALES = kScalesPerBlock>
 __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   constexpr int kBAux = BSTREAM ? (2 | 16) : 0;
   static_assert(!(SPLITK && (RAGGED || Cfg::XPF)), "split-K: whole tiles, the ring-of-buffers path");
@@ -365,14 +368,18 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   const bool a_tail = RAGGED && ((pch ^ keyA_ld) << 4) >= a.k_rem;
   const bool b_tail = RAGGED && ((pch ^ keyB_ld) << 4) >= a.k_rem;
   // Activation scales.  Row-major, the scales of a K block lie one row pitch apart, a cache line each: fetched 4 bytes
-  // per row and K block they are as many requests as the A tile itself, for 1/32 of the bytes.  They are fetched 16
-  // bytes (four K blocks) per row every fourth K block instead ("wide"; a DMA takes any 4-byte aligned source, and what a
-  // piece at the end of a row takes from the next row is not used): a weight stream with 128 rows of A beside it
+  // per row and K block they are as many requests as the A tile itself, for 1/32 of the bytes.  Where it pays (chunks_pay
+  // in gg_fp8.hip) they are fetched 16 bytes (four K blocks) per row every fourth K block instead ("wide"): a DMA takes any
+  // 4-byte aligned source, what a piece at the end of a row takes from the next row is not used, and past the end of SA
+  // nothing is read (the range check acts on each dword of a piece).  A weight stream with 128 rows of A beside it
   // reaches 5.6 TB/s like that, 5.1 with 4-byte fetches and 5.7 without any scales (128 x 256 tile on 52 groups of 128
-  // rows, N = 4096, K = 7168: 332 -> 306 us, 301 K-block-major; 64 groups of 32 rows on average: 315 -> 296 us).
+  // rows, N = 4096, K = 7168: 332 -> 306 us, 301 K-block-major; 64 groups of 32 rows on average: 322 -> 294 us).
   // K-block-major, the scales of a K block are a few lines and fetched per K block ("narrow").
-  const bool wide = ONE || (Cfg::WIDE && !a.sa_kmajor);
-  static_assert(!ONE || (Cfg::ONE_CHUNK && !SPLITK), "one chunk buffer: the tiles that have no room for more");
+  // The forms are instantiations of their own: looked up at run time, the branches in a K step cost launches that matrix
+  // instructions bound 2 to 17 % in either order (4096 rows, N = K = 4096, 32 x 256 tile: 127 -> 149 us).
+  constexpr bool ONE = SCALES == kScalesOneChunk, wide = SCALES != kScalesPerBlock;
+  static_assert(SCALES != kScalesChunks || Cfg::chunks_fit, "a ring of chunk buffers");
+  static_assert(!ONE || (Cfg::one_chunk_fits && !SPLITK), "one chunk buffer: a ring of three");
   const int vSA = (w * 64 + l) * a.sa_row_stride;
   const int vSB = (l < BN / 128 ? l : BN / 128 - 1) * KB * 4;        // lane -> which 128-wide N block of the tile
 
@@ -390,7 +397,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   const int bRd0 = Cfg::A_BYTES + (wn * WTN + rowB_rd) * 128 + (((2 * q) ^ keyB_rd) << 4);
   const int bRd1 = Cfg::A_BYTES + (wn * WTN + rowB_rd) * 128 + (((2 * q + 1) ^ keyB_rd) << 4);
   const int saRd = Cfg::SA_BASE + (wm * WTM + r) * (wide ? 16 : 4);      // + the K block's place (sa_place) + mt * sa_mt
-  const int sa_mt = wide ? 256 : 64;
+  constexpr int sa_mt = wide ? 256 : 64;
   const int sbRd = Cfg::A_BYTES + Cfg::B_BYTES + ((wn * WTN) >> 7) * 4;
 
   // ---- persistent walk over the tile list ---------------------------------------------------------
@@ -471,7 +478,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   bool primed = false;      // the first STAGES-1 K blocks of `cur` were already fetched by the previous tile
   int stage = 0;            // LDS buffer of the current K block; runs on across tiles
   constexpr int SA_TOTAL = ONE ? Cfg::SA_CHUNK : Cfg::SA_BUFS * Cfg::SA_CHUNK;
-  constexpr int SA_DUMP = ONE ? Cfg::ONE_DUMP : Cfg::DUMP_BASE;
+  constexpr int SA_DUMP = Cfg::SA_BASE + SA_TOTAL;
   v4f sa4[TM];          // ONE: the scales of the chunk's K blocks that are still to come
   int ch_fetch = SA_TOTAL - Cfg::SA_CHUNK, ch_read = ch_fetch;     // wide: chunk of the newest fetch, of the current K block; both run on
   auto next_chunk = [&](int c) __attribute__((always_inline)) -> int { return c + Cfg::SA_CHUNK == SA_TOTAL ? 0 : c + Cfg::SA_CHUNK; };
@@ -513,13 +520,17 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
       const int kb = k_wrapped(kb_l + rot, KB);
       const bool last = kb == KB - 1;
       uint8_t* st = lds + stg * Cfg::STAGE_BYTES;
-      const bool chunk_start = wide && on && (kb_l & 3) == 0;
-      if (chunk_start) ch_fetch = next_chunk(ch_fetch);
-      if (w < Cfg::SA_WAVES) {       // one fetch per K block either way (the waits count them)
-        if (chunk_start)
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + Cfg::SA_BASE + ch_fetch + w * 1024), 16, vSA, kb * 4, 0, 0);
-        else
-          __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + (wide ? SA_DUMP : Cfg::SA_BASE + stg * Cfg::SA_SLOT + w * 256)), 4, wide ? GG_OOB_OFFSET : vSA, kb * a.sa_kb_stride, 0, 0);
+      if constexpr (wide) {
+        const bool chunk_start = on && (kb_l & 3) == 0;
+        if (chunk_start) ch_fetch = next_chunk(ch_fetch);
+        if (w < Cfg::SA_WAVES) {       // one fetch per K block either way (the waits count them)
+          if (chunk_start)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + Cfg::SA_BASE + ch_fetch + w * 1024), 16, vSA, kb * 4, 0, 0);
+          else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + SA_DUMP), 4, GG_OOB_OFFSET, 0, 0, 0);
+        }
+      } else if (w < Cfg::SA_WAVES) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(dSA, GG_LDS_PTR(lds + Cfg::SA_BASE + stg * Cfg::SA_SLOT + w * 256), 4, vSA, kb * a.sa_kb_stride, 0, 0);
       }
       if (w == Cfg::SB_WAVE)
         __builtin_amdgcn_raw_ptr_buffer_load_lds(dSB, GG_LDS_PTR(st + Cfg::A_BYTES + Cfg::B_BYTES), 4, vSB, kb * 4, 0, 0);

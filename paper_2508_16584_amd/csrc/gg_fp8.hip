@@ -53,28 +53,27 @@ struct Variant {
   bool splitk = false;         // two work units per tile (halves of the K loop) and a combine pass; needs a workspace
   // the same tile with the streaming cache policy on the weight fetches, for groups of at most one row tile; null: none
   hipError_t (*launch_bstream)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
-  // row-major activation scales, four K blocks of them per fetch, where that is an instantiation of its own (the second
-  // kernel; the first one's tile with one chunk buffer): launch, launch_ragged, launch_bstream; null: none
+  // launch, launch_ragged, launch_bstream for row-major activation scales, four K blocks of them per fetch; null: none
   hipError_t (*launch_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
   hipError_t (*launch_ragged_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
   hipError_t (*launch_bstream_wide)(const gg::GemmArgs&, int grid, hipStream_t) = nullptr;
 };
 
-template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false, bool ONE = false>
+template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false, int SCALES = gg::kScalesPerBlock>
 hipError_t launch_gemm(const gg::GemmArgs& args, int grid, hipStream_t stream) {
-  constexpr int lds = ONE ? Cfg::ONE_LDS_BYTES : Cfg::LDS_BYTES;
+  constexpr int lds = Cfg::lds_bytes(SCALES);
   static std::atomic<int> prepared[64];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev >= 0 && dev < 64 && !prepared[dev].load(std::memory_order_acquire)) {
     // more than 64 KB of LDS per workgroup has to be requested explicitly
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM, ONE>),
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM, SCALES>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     prepared[dev].store(1, std::memory_order_release);
   }
-  hipLaunchKernelGGL((gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM, ONE>), dim3(grid), dim3(Cfg::NT), lds, stream, args);
+  hipLaunchKernelGGL((gg::gg_gemm_kernel<Cfg, RAGGED, SPLITK, BSTREAM, SCALES>), dim3(grid), dim3(Cfg::NT), lds, stream, args);
   return hipGetLastError();
 }
 
@@ -116,35 +115,40 @@ hipError_t launch_gemm_sm(const gg::GemmArgs& args, int grid, hipStream_t stream
   {#BM "x" #BN "/" #WM "x" #WN "w/" #ST "s", BM, BN, gg::SmCfg<BM, BN, WM, WN, ST>::LDS_BYTES, gg::SmCfg<BM, BN, WM, WN, ST>::WG_PER_CU, \
    &launch_gemm_sm<gg::SmCfg<BM, BN, WM, WN, ST>>, &launch_gemm_sm<gg::SmCfg<BM, BN, WM, WN, ST>, true>, false, false,  \
    &launch_gemm_sm<gg::SmCfg<BM, BN, WM, WN, ST>, false, true>}
-#define GG_VARIANT(BM, BN, WM, WN, ST, XPF, GAP, WGPC)                                                        \
-  {#BM "x" #BN "/" #WM "x" #WN "w/" #ST "s" XPF_SUFFIX_##XPF, BM, BN, gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>::LDS_BYTES, \
-   WGPC, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>, nullptr}
-#define GG_VARIANT_R(BM, BN, WM, WN, ST, XPF, GAP, WGPC)   /* with the instantiation for ragged N and K */         \
-  {#BM "x" #BN "/" #WM "x" #WN "w/" #ST "s" XPF_SUFFIX_##XPF, BM, BN, gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>::LDS_BYTES, \
-   WGPC, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, true>}
-#define GG_VARIANT_RS(BM, BN, WM, WN, ST, XPF, GAP, WGPC)   /* ... and the one with streamed weight fetches */     \
-  {#BM "x" #BN "/" #WM "x" #WN "w/" #ST "s" XPF_SUFFIX_##XPF, BM, BN, gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>::LDS_BYTES, \
-   WGPC, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, true>, \
-   false, false, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, false, false, true>}
+#define GG_FIRST_TILE(BM, BN, WM, WN, ST, XPF, GAP, WGPC)                                                                     \
+  #BM "x" #BN "/" #WM "x" #WN "w/" #ST "s" XPF_SUFFIX_##XPF, BM, BN, gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>::LDS_BYTES, WGPC
+#define GG_VARIANT_B(BM, BN, WM, WN, ST, XPF, GAP, WGPC)   /* one instantiation: scales per K block in either order */         \
+  {GG_FIRST_TILE(BM, BN, WM, WN, ST, XPF, GAP, WGPC), &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>}
+#define GG_VARIANT(BM, BN, WM, WN, ST, XPF, GAP, WGPC)     /* per K block, and in chunks */                                    \
+  {GG_FIRST_TILE(BM, BN, WM, WN, ST, XPF, GAP, WGPC), &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>, nullptr, false, \
+   false, nullptr, &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, false, false, false, gg::kScalesChunks>}
+#define GG_VARIANT_R(BM, BN, WM, WN, ST, XPF, GAP, WGPC)   /* ... each for ragged N and K too */                                \
+  {GG_FIRST_TILE(BM, BN, WM, WN, ST, XPF, GAP, WGPC), &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>,                 \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, true>, false, false, nullptr,                                       \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, false, false, false, gg::kScalesChunks>,                            \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, true, false, false, gg::kScalesChunks>}
+#define GG_VARIANT_RS(BM, BN, WM, WN, ST, XPF, GAP, WGPC, SCALES)   /* ... and with streamed weight fetches */                 \
+  {GG_FIRST_TILE(BM, BN, WM, WN, ST, XPF, GAP, WGPC), &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>>,                 \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, true>, false, false,                                                \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, false, false, true>,                                                \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, false, false, false, SCALES>,                                       \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, true, false, false, SCALES>,                                        \
+   &launch_gemm<gg::GemmCfg<BM, BN, WM, WN, ST, XPF, GAP>, false, false, true, SCALES>}
 #define XPF_SUFFIX_false ""
 #define XPF_SUFFIX_true "x"
 
-using Cfg160 = gg::GemmCfg<160, 256, 2, 4, 3, false, 2>;
-
 const Variant kVariants[] = {
-    {"160x256/2x4w/3s", 160, 256, Cfg160::ONE_LDS_BYTES, 1, &launch_gemm<Cfg160>, &launch_gemm<Cfg160, true>, false, false,
-     &launch_gemm<Cfg160, false, false, true>, &launch_gemm<Cfg160, false, false, false, true>, &launch_gemm<Cfg160, true, false, false, true>,
-     &launch_gemm<Cfg160, false, false, true, true>},   // 0: the largest tile that leaves room for a ring of 3 in 160 KB of LDS
-    GG_VARIANT(256, 256, 2, 4, 2, false, 2, 1),   // 1: the largest tile the accumulators allow; ring of 2 only
+    GG_VARIANT_RS(160, 256, 2, 4, 3, false, 2, 1, gg::kScalesOneChunk),   // 0: the largest tile that leaves room for a ring of 3 in 160 KB of LDS
+    GG_VARIANT_B(256, 256, 2, 4, 2, false, 2, 1),   // 1: the largest tile the accumulators allow; ring of 2 only
     GG_VARIANT_R(128, 128, 2, 4, 4, false, 0, 1),   // 2: for N % 256 != 0
-    GG_VARIANT_RS(128, 256, 2, 4, 3, false, 0, 1),   // 3
+    GG_VARIANT_RS(128, 256, 2, 4, 3, false, 0, 1, gg::kScalesChunks),   // 3
     GG_VARIANT(64, 256, 1, 8, 3, false, 0, 1),    // 4
     GG_VARIANT_R(32, 256, 1, 8, 4, false, 0, 1),    // 5
-    GG_VARIANT(16, 256, 1, 8, 2, false, 0, 2),    // 6
+    GG_VARIANT_B(16, 256, 1, 8, 2, false, 0, 2),    // 6
     GG_VARIANT(256, 128, 4, 2, 3, false, 0, 1),   // 7
-    GG_VARIANT(128, 256, 2, 4, 3, true, 0, 1),    // 8
-    GG_VARIANT(128, 128, 2, 4, 4, true, 0, 1),    // 9
-    GG_VARIANT(32, 256, 1, 8, 4, true, 0, 1),     // 10
+    GG_VARIANT_B(128, 256, 2, 4, 3, true, 0, 1),    // 8
+    GG_VARIANT_B(128, 128, 2, 4, 4, true, 0, 1),    // 9
+    GG_VARIANT_B(32, 256, 1, 8, 4, true, 0, 1),     // 10
     GG_VARIANT(128, 128, 2, 4, 2, false, 0, 2),   // 11
     {"256x256/1x8w/3s-rb", 256, 256, gg::RbCfg<256, 2, false>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<256, 2, false>>, &launch_gemm_rb<gg::RbCfg<256, 2, false, false, false, true>>, true, false, nullptr,
      &launch_gemm_rb<gg::RbCfg<256, 2, false, false, false, false, false, 0, true>>, &launch_gemm_rb<gg::RbCfg<256, 2, false, false, false, true, true, 0, true>>},   // 12
@@ -162,9 +166,11 @@ const Variant kVariants[] = {
     {"192x256/1x8w/3s-rbs", 192, 256, gg::RbCfg<192, 4, false, false, true>::LDS_BYTES, 1, &launch_gemm_rb<gg::RbCfg<192, 4, false, false, true>>, nullptr, true},   // 20
     // "-k2": split-K, two halves of the K loop per tile and a combine pass (needs K % 256 == 0 and a workspace)
     {"128x256/2x4w/3s-k2", 128, 256, gg::GemmCfg<128, 256, 2, 4, 3, false, 0>::LDS_BYTES, 1,
-     &launch_gemm<gg::GemmCfg<128, 256, 2, 4, 3, false, 0>, false, true>, nullptr, false, true},
+     &launch_gemm<gg::GemmCfg<128, 256, 2, 4, 3, false, 0>, false, true>, nullptr, false, true, nullptr,
+     &launch_gemm<gg::GemmCfg<128, 256, 2, 4, 3, false, 0>, false, true, false, gg::kScalesChunks>},
     {"64x256/1x8w/3s-k2", 64, 256, gg::GemmCfg<64, 256, 1, 8, 3, false, 0>::LDS_BYTES, 1,
-     &launch_gemm<gg::GemmCfg<64, 256, 1, 8, 3, false, 0>, false, true>, nullptr, false, true},
+     &launch_gemm<gg::GemmCfg<64, 256, 1, 8, 3, false, 0>, false, true>, nullptr, false, true, nullptr,
+     &launch_gemm<gg::GemmCfg<64, 256, 1, 8, 3, false, 0>, false, true, false, gg::kScalesChunks>},
     // the third kernel: small tiles, several workgroups per compute unit (see pick_variant)
     GG_VARIANT_SM(32, 64, 2, 2, 4),     // 23
     GG_VARIANT_SM(32, 128, 1, 4, 3),    // 24
@@ -266,14 +272,19 @@ const TileTime kTileTimes[] = {
 };
 constexpr int kFirstSmall = 23;
 
+// groups with rows, if they were dealt out evenly; row tiles, if a group ends in a partial one half of the time
+double expected_groups(int G, int64_t M_total) { return G * (1.0 - std::exp(-(double)M_total / G)); }
+double expected_row_tiles(int G, int64_t M_total, int BM) {
+  const double filled = expected_groups(G, M_total);
+  return std::fmax(filled, (double)M_total / BM + 0.5 * filled);
+}
+
 double estimate_us(const TileTime& t, int BM, int n_tiles, int wg_per_cu, int G, int64_t M_total, double weight_bytes, double row_bytes, int K) {
   const double cus = (double)device_cus();
-  const double filled = G * (1.0 - std::exp(-(double)M_total / G));            // groups with rows, if they were dealt out evenly
-  const double m_tiles = std::fmax(filled, (double)M_total / BM + 0.5 * filled);
-  const double tiles = m_tiles * n_tiles, steps = (K + 127) / 128 + t.extra;
+  const double tiles = expected_row_tiles(G, M_total, BM) * n_tiles, steps = (K + 127) / 128 + t.extra;
   const double a = std::fmax(tiles / (cus * wg_per_cu), 1.0) * steps * t.latency;
   const double b = tiles * steps * t.work / cus;
-  const double weights = filled * weight_bytes;
+  const double weights = expected_groups(G, M_total) * weight_bytes;
   const double c = (weights + (double)M_total * row_bytes) / 6.8e6;
   const double d = weights / (std::fmin(tiles, cus * wg_per_cu) * t.in_flight) * (weights > 64e6 ? 1.6 : 0.7);
   return 4.2 + std::sqrt(std::sqrt(a * a * a * a + b * b * b * b + c * c * c * c + d * d * d * d));
@@ -388,6 +399,28 @@ int validate_gemm(const void* A, const float* SA, const void* B, const float* SB
   return GG_OK;
 }
 
+// First kernel, row-major activation scales: four K blocks of them per fetch, or one.  Chunks save requests (128 x 128 tile,
+// 8 groups of 1024 rows, N = 4096, K = 7168 345 -> 319 us; 128 x 256, 64 groups of 32 rows 322 -> 294) and cost branches in
+// the K step.  Both forms on 1860 random problems, by K, rows per group and rounds over the workgroups:
+//  * rings of three and four buffers, from K = 2048 on with 4 rows per group: 2 to 16 % faster on half of the problems and
+//    at most 3 % slower on the others, which the host cannot tell apart (few tiles, even or skewed group sizes); below, from
+//    K = 1280 on, up to 6 % faster on half a round or more of groups of less than 400 rows, up to 1.5 % slower elsewhere;
+//    with fewer rows, 1 to 2.5 % slower at any K (few requests either way, and a K step is a chain of latencies);
+//  * 32 x 256, which multiplies least per K block: 1 to 4 % faster from K = 2048 on with half a round or more of groups of 4
+//    to 400 rows, else up to 9 % slower (4096 rows, N = K = 4096: 128 -> 137 us);
+//  * 128 x 128 with two buffers and two workgroups per compute unit: 2 to 9 % faster from K = 1280 on, else slower;
+//  * the other rings of two are slower with them (256 x 256, 4096 rows, N = K = 4096 63.0 -> 64.6 us; 16 x 256 204 -> 213)
+//    and have no such form.
+// The 160 x 256 tile has one chunk buffer, which takes numbers of K blocks that are 0 or 3 modulo 4 (see the kernel).
+bool chunks_pay(const Variant& v, int G, int64_t M_total, int K, int n_tiles) {
+  if (v.BM == 160) return (K + 127) / 128 % 4 == 0 || (K + 127) / 128 % 4 == 3;
+  if (v.wg_per_cu == 2) return K >= 1280;
+  const double avg = (double)M_total / G, rounds = expected_row_tiles(G, M_total, v.BM) * n_tiles / device_cus();
+  if (K < 1280 || avg < 4) return false;
+  const bool filled = rounds >= 0.5 && avg < 400;
+  return v.BM == 32 ? K >= 2048 && filled : K >= 2048 || filled;
+}
+
 int run_gemm(const void* A, const float* SA, const void* B, const float* SB, const int32_t* off, void* C,
              int G, int64_t M_total, int N, int K, void* workspace, size_t workspace_bytes, void* stream, int variant,
              unsigned flags = 0) {
@@ -458,8 +491,8 @@ int run_gemm(const void* A, const float* SA, const void* B, const float* SB, con
   const bool bstream = !ragged && v.launch_bstream && M_total <= (int64_t)G * v.BM;
   // row-major scales, four K blocks of them per fetch; second kernel: from K = 4096 on (8 groups of 1024 rows, N = 4096:
   // K = 7168 247.3 -> 240.8 us, 7040 246.9 -> 240.5, 4096 147.2 -> 146.5; 32 groups of 512 rows, N = 7168, K = 2048: 285.5 ->
-  // 287.3); first kernel: where the number of K blocks allows one chunk buffer
-  const bool wide = v.launch_wide && !args.sa_kmajor && (v.min_kb3 ? K >= 4096 : args.KB % 4 == 0 || args.KB % 4 == 3);
+  // 287.3); first kernel: see chunks_pay
+  const bool wide = v.launch_wide && !args.sa_kmajor && (v.min_kb3 ? K >= 4096 : chunks_pay(v, G, M_total, K, args.n_tiles));
   const auto launch = ragged ? (wide ? v.launch_ragged_wide : v.launch_ragged)
                       : bstream ? (wide ? v.launch_bstream_wide : v.launch_bstream) : (wide ? v.launch_wide : v.launch);
   hipError_t e = launch(args, (int)grid, static_cast<hipStream_t>(stream));

@@ -72,3 +72,28 @@ def test_second_kernel_row_major_equals_kmajor_bitwise(K):
             (torch.equal(row.isnan(), want.isnan()) and torch.equal(row.nan_to_num().view(torch.int16), want.nan_to_num().view(torch.int16))), v
         nan_rows = row.isnan().any(dim=1).nonzero().flatten().tolist()
         assert nan_rows == bad, v
+
+
+@pytest.mark.parametrize("K", [2032, 2048, 2064, 2176, 2304, 2432])
+def test_first_kernel_row_major_equals_kmajor_bitwise(K):
+    """On such a problem all tiles of the first kernel that can fetch four K blocks of scales at a time do so from K = 2048 on: last chunks of one to four blocks, a ragged K, several tiles per workgroup; and NaN scales stay in their rows."""
+    sizes, N = [170, 0, 330, 40], 16384
+    A, SA, B, SB, off = problem(sizes, N, K, K)
+    bad = [0, 169, 170, 333, 539]
+    SA[bad] = float("nan")
+    SAk = SA.t().contiguous()
+    ran = []
+    for v in range(gg.num_variants()):
+        if "-rb" in gg.variant_name(v):
+            continue
+        try:
+            row = gg.grouped_gemm(A, SA, B, SB, off, variant=v)
+        except gg.GGError as e:
+            assert e.status == 3                        # whole K blocks (an even number of them: split-K) only
+            continue
+        ran.append(v)
+        km = gg.grouped_gemm(A, SAk, B, SB, off, variant=v, sa_kmajor=True)
+        assert torch.equal(row.isnan(), km.isnan()) and torch.equal(row.nan_to_num().view(torch.int16), km.nan_to_num().view(torch.int16)), v
+        assert row.isnan().any(dim=1).nonzero().flatten().tolist() == bad, v
+    assert ran == [v for v in range(gg.num_variants()) if "-rb" not in gg.variant_name(v)
+                   and (K % 128 == 0 or v in (0, 2, 3, 5, 23, 24, 25)) and (K % 256 == 0 or "-k2" not in gg.variant_name(v))]
