@@ -327,14 +327,22 @@ int pick_variant_padded(int G, int64_t M_pad_cap, int N, int K) {
   return pick_variant(G, rows, N, K);
 }
 
-// Work split of the row kernels: `slots` blocks per workgroup (one pass), KB blocks per row; see RowWork.
-gg::RowWork row_work(int64_t M_total, int KB, bool kmajor, int slots, unsigned* grid) {
+// Sixteen lanes per block instead of eight in the row kernels: for up to 32 blocks per compute unit (two workgroups of
+// sixteen lanes).  A launch of that size is one chain of latencies, in which a lane's arithmetic counts: 64 rows of 7168
+// 3.2 us, 3.9 with eight lanes; 640 rows of 640 activations 3.45, 3.9.  Above that the wider stores win (512 rows of 4096: 4.0 us,
+// 4.5 with sixteen lanes; 8192 rows of 1280 9.2, 12.0).
+bool few_blocks(int64_t blocks) { return blocks <= 32 * (int64_t)device_cus(); }
+
+// Work split of the row kernels: KB blocks per row; `lanes` per block and `slots` blocks per workgroup (one pass); see
+// RowWork.
+gg::RowWork row_work(int64_t M_total, int KB, bool kmajor, int lanes, int slots, unsigned* grid) {
   gg::RowWork w;
   w.pieces = (KB + slots - 1) / slots;
   w.blocks = (KB + w.pieces - 1) / w.pieces;
   w.rows = w.pieces == 1 ? slots / w.blocks : 1;
-  // few rows: fewer per workgroup, so that they spread over the chip
-  const int64_t spread = 2 * (int64_t)device_cus();
+  // few rows: fewer per workgroup, so that they spread over the chip (sixteen lanes: one workgroup per compute unit, the
+  // second would wait for its launch: 512 rows of 256 activations 3.2 us, 3.3 with two)
+  const int64_t spread = (lanes == 16 ? 1 : 2) * (int64_t)device_cus();
   if (w.rows > 1 && M_total < w.rows * spread) w.rows = (int)((M_total + spread - 1) / spread);
   w.magic = (unsigned)((65536 + w.blocks - 1) / w.blocks);
   int64_t groups = (M_total + w.rows - 1) / w.rows;
@@ -816,9 +824,11 @@ int gg_fp8_quantize_rows_ex(const void* X, const int32_t* row_src, void* A, floa
   if (!A || !SA || (!X && T > 0)) return GG_ERR_NULL;
   const bool km = (flags & GG_SA_KMAJOR) != 0;
   unsigned grid;
-  const gg::RowWork rw = row_work(M_total, K / 128, km, 64, &grid);
+  const bool few = few_blocks(M_total * (K / 128));
+  const gg::RowWork rw = few ? row_work(M_total, K / 128, km, 16, 16, &grid) : row_work(M_total, K / 128, km, 8, 64, &grid);
   const bool snt = row_bytes_stream(M_total * K);
-  const auto kernel = M_total > T ? (snt ? &gg::gg_quantize_rows_kernel<false, true> : &gg::gg_quantize_rows_kernel<false, false>)
+  const auto kernel = few ? &gg::gg_quantize_rows_kernel<false, false, 16>
+                      : M_total > T ? (snt ? &gg::gg_quantize_rows_kernel<false, true> : &gg::gg_quantize_rows_kernel<false, false>)
                                   : (snt ? &gg::gg_quantize_rows_kernel<true, true> : &gg::gg_quantize_rows_kernel<true, false>);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(gg::Q_THREADS), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(X),
                      row_src, static_cast<uint8_t*>(A), SA, T, (int)M_total, K, K / 128, km ? (int64_t)1 : (int64_t)(K / 128),
@@ -841,8 +851,10 @@ int gg_fp8_swiglu_quantize_rows_ex(const void* H, void* A, float* SA, void* act_
   if (!H || !A || !SA) return GG_ERR_NULL;
   const bool km = (flags & GG_SA_KMAJOR) != 0;
   unsigned grid;
-  const gg::RowWork rw = row_work(M_total, I / 128, km, 32, &grid);
-  const auto kernel = row_bytes_stream(M_total * I) ? &gg::gg_swiglu_quantize_rows_kernel<true, true>
+  const bool few = few_blocks(M_total * (I / 128));
+  const gg::RowWork rw = few ? row_work(M_total, I / 128, km, 16, 16, &grid) : row_work(M_total, I / 128, km, 8, 32, &grid);
+  const auto kernel = few ? &gg::gg_swiglu_quantize_rows_kernel<false, false, 16>
+                      : row_bytes_stream(M_total * I) ? &gg::gg_swiglu_quantize_rows_kernel<true, true>
                       : 4 * M_total * I > ((int64_t)192 << 20) ? &gg::gg_swiglu_quantize_rows_kernel<true, false> : &gg::gg_swiglu_quantize_rows_kernel<false, false>;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(gg::Q_THREADS), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(H),
                      static_cast<uint8_t*>(A), SA, static_cast<uint16_t*>(act_out), (int)M_total, I, I / 128,

@@ -13,6 +13,9 @@
 // eight lanes), reduces amax over its 16 values and the eight lanes, and after an exchange of 8 bytes with its
 // neighbour stores 16 bytes.  A workgroup of 256 threads takes up to 64 blocks in one pass, all its loads issued before
 // any arithmetic: a piece of one row, or several short rows.  One pass per workgroup: the grid covers the tensor.
+// Few blocks are a chain of latencies (load, reduce, divide, convert, store), in which 16 values per lane cost more than the
+// second store request: there 16 lanes own one block, 16 bytes in and 8 bytes out each, and a workgroup takes up to 16
+// blocks (few_blocks in gg_fp8.hip; one row of 512: 2.75 us, 2.95 with eight lanes, 64 rows of 7168 3.2, 3.9).
 // HBM-bound: 2K bytes in, K + K/32 out per row.  8192 x 7168 gathered: 33.5 us (5.3 TB/s), 16384 x 7168 out of 8192 rows
 // 57 (6.3), 32768 x 7168 118 (6.0); with 16 lanes and 8-byte stores per block, row pairs strided over 8 workgroups per
 // compute unit and no streaming policy they took 40, 72 and 146 us.
@@ -70,13 +73,15 @@ __device__ __forceinline__ int e4m3x4_of(const float* v, float inv) {
   return w | (int)nan;
 }
 
-// One block: lane `sub` of its eight holds bf16 columns 8 sub .. + 7 in lo and 64 + 8 sub .. + 7 in hi.
-template <bool SNT>
+// One block.  LANES 8: lane `sub` of its eight holds bf16 columns 8 sub .. + 7 in lo and 64 + 8 sub .. + 7 in hi.  LANES 16:
+// lane `sub` of its sixteen holds columns 8 sub .. + 7 in lo.
+template <bool SNT, int LANES>
 __device__ __forceinline__ void quantize_block(const q_v4i lo, const q_v4i hi, uint8_t* dst, float* dst_scale, int sub) {
-  float v[16];
+  constexpr int NV = 128 / LANES;
+  float v[NV];
   unsigned top = 0;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < NV / 2; ++i) {
     const unsigned two = (unsigned)(i < 4 ? lo[i & 3] : hi[i & 3]);
     v[2 * i] = __builtin_bit_cast(float, two << 16);
     v[2 * i + 1] = __builtin_bit_cast(float, two & 0xFFFF0000u);
@@ -89,30 +94,38 @@ __device__ __forceinline__ void quantize_block(const q_v4i lo, const q_v4i hi, u
   if (special) {
     top = 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < NV; ++i) {
       const unsigned t = amax_bits_of(v[i]);
       top = top > t ? top : t;
     }
   }
-  const float amax = block_amax(max8(top));
+  top = max8(top);
+  if constexpr (LANES == 16) {
+    const unsigned t = (unsigned)__builtin_amdgcn_update_dpp(0, (int)top, 0x128, 0xF, 0xF, false);      // row_ror 8: the other eight
+    top = top > t ? top : t;
+  }
+  const float amax = block_amax(top);
   const float scale = amax / 448.0f;
   const float inv = 448.0f / amax;
-  int w[4];
+  int w[NV / 4];
 #pragma unroll
-  for (int d = 0; d < 4; ++d) w[d] = special ? e4m3x4_of(v + 4 * d, inv) : e4m3x4_of<false>(v + 4 * d, inv);
+  for (int d = 0; d < NV / 4; ++d) w[d] = special ? e4m3x4_of(v + 4 * d, inv) : e4m3x4_of<false>(v + 4 * d, inv);
+  if (sub == 0) *dst_scale = scale;
+  if constexpr (LANES == 16) *(q_v2i*)(dst + 8 * sub) = (q_v2i){w[0], w[1]};
   // w[0], w[1] are bytes 8 sub .. + 7 of the block and w[2], w[3] bytes 64 + 8 sub .. + 7: an even lane gives the latter
   // away for its neighbour's former, so that every lane has 16 consecutive bytes
-  const bool odd = sub & 1;
-  const int r0 = __builtin_amdgcn_update_dpp(0, odd ? w[0] : w[2], 0xB1, 0xF, 0xF, false);
-  const int r1 = __builtin_amdgcn_update_dpp(0, odd ? w[1] : w[3], 0xB1, 0xF, 0xF, false);
-  const q_v4i out = odd ? (q_v4i){r0, r1, w[2], w[3]} : (q_v4i){w[0], w[1], r0, r1};
-  q_v4i* const p = (q_v4i*)(dst + (odd ? 64 + 8 * (sub - 1) : 8 * sub));
-  if constexpr (SNT) __builtin_nontemporal_store(out, p);
-  else *p = out;
-  if (sub == 0) *dst_scale = scale;
+  if constexpr (LANES == 8) {
+    const bool odd = sub & 1;
+    const int r0 = __builtin_amdgcn_update_dpp(0, odd ? w[0] : w[2], 0xB1, 0xF, 0xF, false);
+    const int r1 = __builtin_amdgcn_update_dpp(0, odd ? w[1] : w[3], 0xB1, 0xF, 0xF, false);
+    const q_v4i out = odd ? (q_v4i){r0, r1, w[2], w[3]} : (q_v4i){w[0], w[1], r0, r1};
+    q_v4i* const p = (q_v4i*)(dst + (odd ? 64 + 8 * (sub - 1) : 8 * sub));
+    if constexpr (SNT) __builtin_nontemporal_store(out, p);
+    else *p = out;
+  }
 }
 
-// Work of a workgroup: up to 64 blocks, `rows` adjacent rows of `blocks` blocks (rows > 1 only where a row has few).
+// Work of a workgroup: up to 64 blocks (16 with sixteen lanes each), `rows` adjacent rows of `blocks` blocks (rows > 1 only where a row has few).
 // Which rows depends on the storage order of the scales:
 //   sector == 0: workgroup b takes piece b of the row-major list of pieces;
 //   sector == 8 or 32: with K-block-major scales the 4-byte scale stores of 8 adjacent rows make up a 32-byte piece of
@@ -159,35 +172,36 @@ __device__ __forceinline__ q_v4i load_16(const uint16_t* p) {
 }
 
 // LNT, SNT: the rows are read, the bytes written, with the streaming policy (see row_bytes_stream() in gg_fp8.hip)
-template <bool LNT, bool SNT>
+template <bool LNT, bool SNT, int LANES = 8>
 __global__ void __launch_bounds__(Q_THREADS) gg_quantize_rows_kernel(const uint16_t* __restrict__ X,
                                                                      const int32_t* __restrict__ row_src,
                                                                      uint8_t* __restrict__ A, float* __restrict__ SA,
                                                                      int64_t T, int M_total, int K, int KB,
                                                                      int64_t sa_rs, int64_t sa_ks,     // SA[row * sa_rs + blk * sa_ks]
                                                                      RowWork rw) {
-  const int grp = threadIdx.x >> 3, sub = threadIdx.x & 7;
+  constexpr int U = LANES == 8 ? 2 : 1, GROUPS = Q_THREADS / LANES;      // blocks per lane, blocks per workgroup / U
+  const int grp = threadIdx.x / LANES, sub = threadIdx.x % LANES;
   for (unsigned id = blockIdx.x; id < rw.groups; id += gridDim.x) {
-    RowSlot s[2];
-    int64_t src[2];
-    q_v4i lo[2], hi[2];
+    RowSlot s[U];
+    int64_t src[U];
+    q_v4i lo[U], hi[U];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      s[u] = row_slot(rw, id, u * 32 + grp, KB, M_total);                  // uniform over the 8 lanes of a block
+    for (int u = 0; u < U; ++u) {
+      s[u] = row_slot(rw, id, u * GROUPS + grp, KB, M_total);              // uniform over the lanes of a block
       src[u] = !s[u].valid ? -1 : row_src ? (int64_t)row_src[s[u].row] : (int64_t)s[u].row;
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
       lo[u] = hi[u] = (q_v4i){0, 0, 0, 0};
       if (src[u] >= 0 && src[u] < T) {                                     // a source outside [0, T) stands for a row of zeros
         const uint16_t* p = X + src[u] * K + s[u].blk * 128 + sub * 8;
         lo[u] = load_16<LNT>(p);
-        hi[u] = load_16<LNT>(p + 64);
+        if constexpr (LANES == 8) hi[u] = load_16<LNT>(p + 64);
       }
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
-      if (s[u].valid) quantize_block<SNT>(lo[u], hi[u], A + (int64_t)s[u].row * K + s[u].blk * 128, SA + s[u].row * sa_rs + s[u].blk * sa_ks, sub);
+    for (int u = 0; u < U; ++u)
+      if (s[u].valid) quantize_block<SNT, LANES>(lo[u], hi[u], A + (int64_t)s[u].row * K + s[u].blk * 128, SA + s[u].row * sa_rs + s[u].blk * sa_ks, sub);
   }
 }
 
@@ -195,7 +209,8 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_rows_kernel(const uint1
 // (columns [0, I): gate projection, [I, 2I): up projection) ->
 //     act = bf16_rne( silu(gate) * up ),  silu(g) = g / (1 + exp(-g))   in fp32
 // and then exactly quantize_block on the bf16 bits of act.  act is also written out when act_out is not null.
-// Same mapping: 8 lanes own one block of 128 activation columns, a lane loads 16 gate and 16 up values.
+// Same mapping: 8 lanes own one block of 128 activation columns, a lane loads 16 gate and 16 up values (of few blocks: 16
+// lanes, 8 and 8).
 // two (gate, up) pairs, each a dword of two bf16 -> one dword of two bf16 activations
 __device__ __forceinline__ int swiglu2(const int g_raw, const int u_raw) {
   float g[2] = {__builtin_bit_cast(float, g_raw << 16), __builtin_bit_cast(float, g_raw & (int)0xFFFF0000)};
@@ -322,26 +337,33 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
   }
 }
 
-template <bool LNT, bool SNT>
+template <bool LNT, bool SNT, int LANES = 8>
 __global__ void __launch_bounds__(Q_THREADS) gg_swiglu_quantize_rows_kernel(const uint16_t* __restrict__ H,
                                                                             uint8_t* __restrict__ A, float* __restrict__ SA,
                                                                             uint16_t* __restrict__ act_out,
                                                                             int M_total, int I, int IB,
                                                                             int64_t sa_rs, int64_t sa_ks,     // SA[row * sa_rs + blk * sa_ks]
                                                                             RowWork rw) {
-  const int grp = threadIdx.x >> 3, sub = threadIdx.x & 7;
+  const int grp = threadIdx.x / LANES, sub = threadIdx.x % LANES;
   for (unsigned id = blockIdx.x; id < rw.groups; id += gridDim.x) {
     const RowSlot s = row_slot(rw, id, grp, IB, M_total);
     if (!s.valid) continue;
     const uint16_t* p = H + (int64_t)s.row * 2 * I + s.blk * 128 + sub * 8;
-    const q_v4i g0 = load_16<LNT>(p), g1 = load_16<LNT>(p + 64), u0 = load_16<LNT>(p + I), u1 = load_16<LNT>(p + I + 64);
-    const q_v4i lo = swiglu8(g0, u0), hi = swiglu8(g1, u1);
     const int64_t o = (int64_t)s.row * I + s.blk * 128;
+    q_v4i lo, hi = {0, 0, 0, 0};
+    if constexpr (LANES == 8) {
+      const q_v4i g0 = load_16<LNT>(p), g1 = load_16<LNT>(p + 64), u0 = load_16<LNT>(p + I), u1 = load_16<LNT>(p + I + 64);
+      lo = swiglu8(g0, u0);
+      hi = swiglu8(g1, u1);
+    } else {
+      const q_v4i g0 = load_16<LNT>(p), u0 = load_16<LNT>(p + I);
+      lo = swiglu8(g0, u0);
+    }
     if (act_out) {
       __builtin_nontemporal_store(lo, (q_v4i*)(act_out + o + sub * 8));
-      __builtin_nontemporal_store(hi, (q_v4i*)(act_out + o + 64 + sub * 8));
+      if constexpr (LANES == 8) __builtin_nontemporal_store(hi, (q_v4i*)(act_out + o + 64 + sub * 8));
     }
-    quantize_block<SNT>(lo, hi, A + o, SA + s.row * sa_rs + s.blk * sa_ks, sub);
+    quantize_block<SNT, LANES>(lo, hi, A + o, SA + s.row * sa_rs + s.blk * sa_ks, sub);
   }
 }
 

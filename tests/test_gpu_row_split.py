@@ -54,6 +54,38 @@ def test_activation_split(M, inter, km):
     assert bool(((act.double() - ref).abs() <= ref.abs() * 2.0 ** -8 + 1e-30).all())
 
 
+# The tests above have up to 32 blocks per compute unit but for three of them: sixteen lanes per block.  The same splits with
+# eight lanes, just above 8192 blocks, and both sides of the line.
+@pytest.mark.parametrize("M,K", [(8192, 128), (8193, 128), (2731, 384), (249, 4224), (131, 8064), (127, 8320), (65, 16512)])
+@pytest.mark.parametrize("km", [False, True])
+def test_quantiser_split_above_the_line(M, K, km):
+    test_quantiser_split(M, K, km)
+
+
+@pytest.mark.parametrize("M,inter", [(8192, 128), (8193, 128), (745, 1408), (265, 3968), (249, 4224)])
+@pytest.mark.parametrize("km", [False, True])
+def test_activation_split_above_the_line(M, inter, km):
+    test_activation_split(M, inter, km)
+
+
+@pytest.mark.parametrize("K", [256, 16640])                       # 2 and 130 blocks per row
+def test_both_lane_counts_agree(K):
+    """Infinities, NaNs, zeros, denormals and the largest values: the same rows in a call of few blocks and in one of many."""
+    rows = 8192 // (K // 128) + 1
+    special = torch.tensor([0x0000, 0x8000, 0x0001, 0x8001, 0x7F7F, 0xFF7F, 0x7F80, 0xFF80, 0x7FC0, 0xFFC1, 0x7F81, 0x0080], device=DEV).to(torch.int32)
+    X = rows_of(rows, K, K).view(torch.int16)
+    mask = torch.rand(X.shape, device=DEV) < 0.01
+    X = torch.where(mask, special[torch.randint(0, 12, X.shape, device=DEV)].to(torch.int16), X).view(torch.bfloat16)
+    A, SA = gg.quantize_rows(X)
+    B, SB = gg.quantize_rows(X[-37:].contiguous())
+    assert torch.equal(A[-37:], B) and torch.equal(SA[-37:].view(torch.int32), SB.view(torch.int32))
+    H = X.view(-1, K)
+    A, SA, act = gg.swiglu_quantize_rows(torch.cat([H, H]), want_act=True)
+    B, SB, act_b = gg.swiglu_quantize_rows(H[-37:].contiguous(), want_act=True)
+    assert torch.equal(A[-37:], B) and torch.equal(SA[-37:].view(torch.int32), SB.view(torch.int32))
+    assert torch.equal(act[-37:].view(torch.int16), act_b.view(torch.int16))
+
+
 def test_streaming_stores_equal_the_others():
     """More than 96 MB of bytes: the instantiations with streaming stores, against the others on some of the same rows."""
     X = rows_of(14400, 7168, 5)
