@@ -354,22 +354,25 @@ gg::RowWork row_work(int64_t M_total, int KB, bool kmajor, int lanes, int slots,
   return w;
 }
 
-// Cache policy of the row kernels (template arguments LNT, SNT).  A row that is read once is read with the streaming
-// policy (31.0 against 35.8 us on 8192 x 7168; rows that a gather reads again stay cacheable: 55 against 60 us on 16384
-// rows out of 8192).  The activation kernel's input comes straight from a GEMM: up to 192 MB it may still be in the
-// last-level cache and is read through it (16.9 against 17.4 us on 8192 x 4096).  The bytes are written with it when they are more than the last-level cache would hold for the
-// GEMM that reads them next (118 against 133 us on 32768 x 7168), and left cacheable below that (a whole MLP forward
-// pass on 8192 x 7168, 58.7 MB of bytes: 414 against 418 us).
-bool row_bytes_stream(int64_t bytes) { return bytes > ((int64_t)96 << 20); }
+// Cache policies of the quantisers (template arguments LNT, SNT: loads, stores past the caches), each for the time of the
+// call and of the GEMM that reads its bytes together.
+//  * A row that is read once is read past the caches: 2 to 3 % of quantiser and GEMM on 60 to 240 MB of bytes, whether the
+//    rows come from memory or from a kernel just before (the quantiser alone: 8 to 15 %), nothing below; rows that a gather
+//    reads again stay cacheable.  The activation kernel's input comes straight from a GEMM: the same above 192 MB of it.
+//  * Bytes are written past the caches from 128 MB on, by the activation kernel and where a gather reads rows again.  Before
+//    that the GEMM loses what the quantiser gains (gathered rows, 1500 problems: quantiser alone 0.98 of the time from 64 MB
+//    on; with its GEMM 1.003 to 1.004 at 64 MB, 1.000 to 1.002 at 112, 0.998 to 0.999 at 128, 0.992 to 0.995 at 176, 0.985 to
+//    0.992 at 208; activations 1.005 at 96, 0.998 at 128, 0.995 at 192).  Rows read once: never (with the loads above, 1.01 of
+//    the time with the GEMM at every size).
+bool bytes_stream(int64_t bytes) { return bytes >= ((int64_t)128 << 20); }
 
-// Cache policy of the column quantiser's bytes.  Streamed, its own time falls (16384 tokens out of 8192, 7168 features:
-// 63.3 against 78.8 us; 8192 x 7168 30.6 against 37.7), but the weight-gradient GEMM that reads the bytes next loses more
-// than that while they would have stayed in the last-level cache (quantisers and GEMM together, 8192 x 7168 and 8192 x
-// 4096: 485 against 542 us).  So only bytes that are too many for it, beside input rows that are read again (together
-// 278.1 against 278.9 us at 16384 out of 8192 x 7168; 16384 x 8192 with every row read once: 223.5 against 218.2), and
-// only in whole 128-byte lines (16368 tokens, 4096 features: 46.3 against 34.8).
+// The same for the column quantiser, in whole 128-byte lines only (16368 tokens, 4096 features: 46.3 against 34.8 us) and
+// where a gather reads tokens again (read once: slower alone, and at most equal with the GEMM).  The line is where the two
+// places a program has for the call balance, in a layer's quantisers, forward GEMM and weight gradient (400 problems):
+// beside the row quantiser, where streaming leaves the rows in the cache, 0.994 of the time at 64 MB of bytes, 0.996 at 104,
+// 0.997 at 120; just in front of the weight gradient, which reads the bytes, 1.039, 1.009, 0.998 (0.992 at 150).
 bool cols_bytes_stream(const void* XT, int64_t T, int64_t M_total, int K) {
-  return M_total > T && M_total % 128 == 0 && ((uintptr_t)XT & 127) == 0 && M_total * K > ((int64_t)96 << 20);
+  return M_total > T && M_total % 128 == 0 && ((uintptr_t)XT & 127) == 0 && M_total * K >= ((int64_t)112 << 20);
 }
 
 // Device scratch a GEMM call with this variant uses: the split-K variants keep the fp32 partial sums of the two
@@ -826,10 +829,9 @@ int gg_fp8_quantize_rows_ex(const void* X, const int32_t* row_src, void* A, floa
   unsigned grid;
   const bool few = few_blocks(M_total * (K / 128));
   const gg::RowWork rw = few ? row_work(M_total, K / 128, km, 16, 16, &grid) : row_work(M_total, K / 128, km, 8, 64, &grid);
-  const bool snt = row_bytes_stream(M_total * K);
   const auto kernel = few ? &gg::gg_quantize_rows_kernel<false, false, 16>
-                      : M_total > T ? (snt ? &gg::gg_quantize_rows_kernel<false, true> : &gg::gg_quantize_rows_kernel<false, false>)
-                                  : (snt ? &gg::gg_quantize_rows_kernel<true, true> : &gg::gg_quantize_rows_kernel<true, false>);
+                      : M_total <= T ? &gg::gg_quantize_rows_kernel<true, false>
+                      : bytes_stream(M_total * K) ? &gg::gg_quantize_rows_kernel<false, true> : &gg::gg_quantize_rows_kernel<false, false>;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(gg::Q_THREADS), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(X),
                      row_src, static_cast<uint8_t*>(A), SA, T, (int)M_total, K, K / 128, km ? (int64_t)1 : (int64_t)(K / 128),
                      km ? M_total : (int64_t)1, rw);
@@ -854,7 +856,7 @@ int gg_fp8_swiglu_quantize_rows_ex(const void* H, void* A, float* SA, void* act_
   const bool few = few_blocks(M_total * (I / 128));
   const gg::RowWork rw = few ? row_work(M_total, I / 128, km, 16, 16, &grid) : row_work(M_total, I / 128, km, 8, 32, &grid);
   const auto kernel = few ? &gg::gg_swiglu_quantize_rows_kernel<false, false, 16>
-                      : row_bytes_stream(M_total * I) ? &gg::gg_swiglu_quantize_rows_kernel<true, true>
+                      : bytes_stream(M_total * I) ? &gg::gg_swiglu_quantize_rows_kernel<true, true>
                       : 4 * M_total * I > ((int64_t)192 << 20) ? &gg::gg_swiglu_quantize_rows_kernel<true, false> : &gg::gg_swiglu_quantize_rows_kernel<false, false>;
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(gg::Q_THREADS), 0, static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(H),
                      static_cast<uint8_t*>(A), SA, static_cast<uint16_t*>(act_out), (int)M_total, I, I / 128,

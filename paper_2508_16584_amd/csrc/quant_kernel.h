@@ -171,7 +171,7 @@ __device__ __forceinline__ q_v4i load_16(const uint16_t* p) {
   return *(const q_v4i*)p;
 }
 
-// LNT, SNT: the rows are read, the bytes written, with the streaming policy (see row_bytes_stream() in gg_fp8.hip)
+// LNT, SNT: the rows are read, the bytes written, with the streaming policy (see bytes_stream() in gg_fp8.hip)
 template <bool LNT, bool SNT, int LANES = 8>
 __global__ void __launch_bounds__(Q_THREADS) gg_quantize_rows_kernel(const uint16_t* __restrict__ X,
                                                                      const int32_t* __restrict__ row_src,
@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(Q_THREADS) gg_swiglu_quantize_rows_kernel(cons
       const q_v4i g0 = load_16<LNT>(p), u0 = load_16<LNT>(p + I);
       lo = swiglu8(g0, u0);
     }
-    if (act_out) {
+    if (act_out) {       // for the backward pass: past the caches (with the GEMM behind this kernel 0.6 to 2 % faster than through them)
       __builtin_nontemporal_store(lo, (q_v4i*)(act_out + o + sub * 8));
       if constexpr (LANES == 8) __builtin_nontemporal_store(hi, (q_v4i*)(act_out + o + 64 + sub * 8));
     }

@@ -120,7 +120,7 @@ def test_quantised_operands_feed_the_weight_gradient_gemm():
 def test_streamed_bytes_equal_the_others():
     """Large outputs of a repeated gather are written past the caches when their lines are whole (a 128-byte aligned
     tensor); 16 bytes further on the same call takes the ordinary stores."""
-    T, M, K = 2048, 16384, 6208
+    T, M, K = 2048, 16384, 8256                    # 129 MB
     gen = torch.Generator(device=DEV)
     gen.manual_seed(3)
     X = torch.randn((T, K), generator=gen, device=DEV).to(torch.bfloat16)

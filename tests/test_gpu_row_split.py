@@ -87,16 +87,17 @@ def test_both_lane_counts_agree(K):
 
 
 def test_streaming_stores_equal_the_others():
-    """More than 96 MB of bytes: the instantiations with streaming stores, against the others on some of the same rows."""
+    """128 MB of bytes and more: the instantiations with streaming stores (rows read again, activations) and loads, against the
+    others on some of the same rows."""
     X = rows_of(14400, 7168, 5)
     A, SA = gg.quantize_rows(X)
     B, SB = gg.quantize_rows(X[7000:7500])
     assert torch.equal(A[7000:7500], B) and torch.equal(SA[7000:7500], SB)
-    src = torch.randint(0, 500, (15000,), device=DEV, dtype=torch.int32)        # rows read again
+    src = torch.randint(0, 500, (18800,), device=DEV, dtype=torch.int32)        # rows read again
     A, SA = gg.quantize_rows(X[7000:7500], src)
     assert torch.equal(A, B[src.long()]) and torch.equal(SA, SB[src.long()])
     H = X.view(-1, 256)
-    H = torch.cat([H, H])
+    H = torch.cat([H, H, H])
     A2, SA2, _ = gg.swiglu_quantize_rows(H)
     B2, SB2, _ = gg.swiglu_quantize_rows(H[-700:])
     assert torch.equal(A2[-700:], B2) and torch.equal(SA2[-700:], SB2)
