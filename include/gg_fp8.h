@@ -98,8 +98,8 @@ const char* gg_fp8_variant_name(int variant);
  * sizes only, never at device memory); a negative gg_status value if the sizes
  * are not supported. */
 int gg_fp8_auto_variant(int G, int64_t M_total, int N, int K);
-/* The same for gg_fp8_grouped_gemm_padded (and for the _ex call with GG_PADDED_GROUPS): the choice among the tile
- * heights that divide groups of 128-row blocks (the padded problem of Sec. 3). */
+/* The same for gg_fp8_grouped_gemm_padded (and for the _ex call with GG_PADDED_GROUPS), on a capacity of rows (the padded
+ * problem of Sec. 3). */
 int gg_fp8_auto_variant_padded(int G, int64_t M_pad_cap, int N, int K);
 
 /* gg_fp8_grouped_gemm_variant with C [M_total, N] written as IEEE binary16 instead of bfloat16: the paper says
@@ -118,9 +118,8 @@ int gg_fp8_grouped_gemm_f16(const void* A, const float* SA, const void* B, const
  *                contiguous, a few cache lines instead of one per row.  M_total * ceil(K/128) must stay below 2^29
  *                (GG_ERR_SHAPE otherwise).  Same arithmetic, bit-identical results.
  *  GG_PADDED_GROUPS  a promise that every group holds a multiple of 128 rows (the pad path of Sec. 3, what
- *                gg_fp8_grouped_gemm_padded passes): the automatic choice (variant = -1) then only considers tile
- *                heights that divide such groups, and reads M_total as a capacity (M_pad_cap).  Results do not
- *                depend on it.
+ *                gg_fp8_grouped_gemm_padded passes): the automatic choice (variant = -1) then reads M_total as a
+ *                capacity (M_pad_cap) and takes the 128-row tile for short groups.  Results do not depend on it.
  *  GG_OUT_BF16   gg_fp8_grouped_gemm_wgrad_ex only: its output is bfloat16 instead of fp32. */
 enum { GG_OUT_F16 = 1, GG_SA_KMAJOR = 2, GG_PADDED_GROUPS = 4, GG_OUT_BF16 = 8 };
 
@@ -153,7 +152,8 @@ size_t gg_fp8_noalloc_max_elements(void);
  * every kernel here; this is the "neighbouring kernel" of Sec. 4 moved into the GEMM.  Bit-identical to the
  * two-call sequence unless K % 8192 == 4096 (there the plain GEMM adds the K blocks in a rotated order).
  * flags: GG_SA_KMAJOR (applies to SA and to SA2) or 0.  variant: -1, or one of the second kernel's "-rb" variants
- * with 192, 224 or 256 rows, or the third kernel's "32x128" or "64x128" (32 or 64 rows).  I a multiple of 128, K a multiple of 256 and >= 512 (GG_ERR_UNSUPPORTED otherwise:
+ * with 192, 224 or 256 rows, or the third kernel's "32x128" or "64x128" (32 or 64 rows).  I a multiple of 128, K a
+ * multiple of 128 and >= 384, a multiple of 256 for the variants with 224 and 256 rows (GG_ERR_UNSUPPORTED otherwise:
  * use the two calls); 2*I*K below 2^31.  A2, act_out 16-byte aligned.  Asynchronous on `stream`. */
 int gg_fp8_grouped_gemm_swiglu(const void* A, const float* SA, const void* B, const float* SB,
                                const int32_t* group_offsets, void* A2, float* SA2, void* act_out,

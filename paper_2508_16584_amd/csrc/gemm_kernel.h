@@ -166,7 +166,10 @@ struct GemmCfg {
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
-// s_waitcnt vmcnt(N): at most N of this wave's vector-memory operations may still be in flight
+// s_waitcnt vmcnt(N): at most N of this wave's vector-memory operations may still be in flight.  They complete in the order
+// they were issued, loads, fetches into LDS and stores alike (LLVM's AMDGPU user guide, memory models of the gfx9 family:
+// completion of vector memory operations is reported to a wavefront in execution order; flat accesses are the exception,
+// and there are none here.  hipcc builds on it: for gfx950 it waits with vmcnt(3) for a load with three stores behind it).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -447,7 +450,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   };
   // bounded views: nothing past the last valid row of a tile is loaded or stored.
   // N not a multiple of the tile width: the weight rows, scale blocks and output columns past N do not exist
-  // (the range check compares lane offset + scalar offset + access size with the view's length, so a view that
+  // (the range check compares lane offset + scalar offset with the view's length, for each dword of a fetch, so a view that
   // ends after the last existing row refuses exactly the fetches past it)
   const int nb_all = RAGGED ? (N + 127) >> 7 : N >> 7;
   // on = false: a view of length zero, through which every fetch is dropped (same instruction count, no traffic)
@@ -711,8 +714,8 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
         if (MODE == 2 && kb_new >= KBu) kb_new = KBu - 1;      // fewer K blocks than ring buffers: dropped anyway
         const int nstage = stage == 0 ? STAGES - 1 : stage - 1;
         // The DMA of this K block (issued STAGES-1 blocks ago by every wave) must have landed; the newer
-        // blocks (of this tile, then of the next) may stay in flight.  Loads complete in order, but stores do not
-        // order with loads, so the first block of a tile drains everything (the previous tile's epilogue stores too).
+        // blocks (of this tile, then of the next) may stay in flight.  The first block of a tile drains
+        // everything: the stores of the previous tile's epilogue are counted too (see wait_vmcnt), and their number is not.
         {
           // every K block issues one group of fetches, so STAGES-2 groups are younger than block kb (KB-1 if the
           // tile has fewer K blocks than the ring has buffers)

@@ -6,7 +6,8 @@
 // 128 tiles on 256 compute units), and one of its K steps takes 0.4 us however little there is to multiply: wait for
 // the fetches, barrier, LDS reads, matrix instructions, FMAs follow one another, and waves find their fetches in
 // branches.  Here
-//  * a workgroup has 4 waves and a tile of 16 x 128 to 64 x 64; several workgroups share a compute unit;
+//  * a workgroup has 4 waves and a tile of 32 x 64, 32 x 128 or 64 x 128 (with the activation epilogue 32 or 64 rows of 256
+//    weight rows); several workgroups share a compute unit;
 //  * a wave multiplies K block kb out of registers, into which the block was read during the step before; the barrier at
 //    the top of the step publishes block kb + 1, whose fragments refill the registers right behind the matrix
 //    instructions that used them, so no LDS latency stands between the barrier and the first matrix instruction;

@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   const int rd0 = r * 128 + (((2 * q) ^ keyR) << 4), rd1 = r * 128 + (((2 * q + 1) ^ keyR) << 4);
   const int xBase = (wk * 64) * 128, yBase = Cfg::X_BYTES + (wn * 64) * 128;
   // a matrix instruction's output has dY^T rows 4 q .. 4 q + 3 of its fragment in the lane's four registers and
-  // feature r of its fragment in the lane, so that the 16 lanes of a row hold 64 consecutive bytes of dW
+  // feature 4 r + f (slot r of fragment f) in the lane: the lane's four fragments hold four neighbouring features of a row
   const int sxRd = Cfg::X_BYTES + Cfg::Y_BYTES + (wk * 64 + r) * 4;                     // + 64 kf
   const int syRd = Cfg::X_BYTES + Cfg::Y_BYTES + Cfg::SX_BYTES + (wn * 64 + 4 * q) * 4;     // + 64 nf: four consecutive rows
   auto read_frag = [&](const uint8_t* p) __attribute__((always_inline)) -> v8i {
@@ -305,8 +305,8 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   int st_prev = 0, st_prev2 = 0;   // batches of 16 stores issued since the last top of a step / between the two before
   // The top of a step.  This wave has read all of the block it multiplies next, and its part of the following block
   // has landed: those fetches were issued two steps ago; newer are the fetches of the last step and the stores of
-  // the tiles finished since, which may all stay in flight (vector memory operations of a wave complete in the order
-  // they were issued; the counter holds 63 and never gets there: no batch of stores begins with more than 31
+  // the tiles finished since, which may all stay in flight (a wave's loads and stores complete in the order they were
+  // issued, see wait_vmcnt; the counter holds 63 and never gets there: no batch of stores begins with more than 31
   // outstanding, and with three batches behind it the awaited fetch cannot be among them).
   auto top = [&]() __attribute__((always_inline)) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
