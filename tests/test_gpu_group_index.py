@@ -27,13 +27,18 @@ def test_every_variant_finds_every_group(G):
     SB = rng.uniform(0.5, 2.0, (G, N // 128, K // 128)).astype(np.float32)
     ref = orc.grouped_gemm(A, SA, B, SB, off, with_abs_sum=True)
     dev = tuple(torch.from_numpy(x).to(DEV) for x in (A, SA, B, SB, off))
-    want = None
+    want, ran = None, []
     for v in [-1] + list(range(gg.num_variants())):
         try:
             got = bits_of(gg.grouped_gemm(*dev, variant=v))
-        except gg.GGError:
-            continue                                    # a variant that does not take this K
+        except gg.GGError as e:
+            assert e.status == 3 and v >= 0             # a variant that does not take this K: three K blocks
+            continue
+        ran.append(v)
         assert_parity(got, ref, empirical=False, what=f"G={G} variant {v}")
         if v < 0 or not gg.variant_name(v).endswith("-rbk"):      # (adds in an order of its own)
             want = got if want is None else want
             assert np.array_equal(got, want), f"variant {v} differs"
+    # all but split-K (an even number of K blocks) and those of the second kernel that have no instantiation for an odd one
+    assert ran == [-1] + [v for v in range(gg.num_variants()) if "-k2" not in gg.variant_name(v)
+                          and ("-rb" not in gg.variant_name(v) or gg.variant_name(v)[:3] in ("256", "224", "192", "128") and gg.variant_name(v).endswith("-rb"))]

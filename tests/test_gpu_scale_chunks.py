@@ -31,18 +31,22 @@ def test_row_major_equals_kmajor_bitwise(K):
     sizes, N = [170, 0, 330, 40], 16384
     A, SA, B, SB, off = problem(sizes, N, K, K)
     SAk = SA.t().contiguous()
-    want = None
+    want, ran = None, []
     for v in [-1] + list(range(gg.num_variants())):
         name = gg.variant_name(v) if v >= 0 else "auto"
         try:
             row = gg.grouped_gemm(A, SA, B, SB, off, variant=v)
             km = gg.grouped_gemm(A, SAk, B, SB, off, variant=v, sa_kmajor=True)
-        except gg.GGError:
-            continue                                    # a variant that does not take this K
+        except gg.GGError as e:
+            assert e.status == 3 and v >= 0             # a variant that does not take this K
+            continue
+        ran.append(v)
         assert torch.equal(row.view(torch.int16), km.view(torch.int16)), name
         if "-rbk" not in name and "-k2" not in name:    # those add in an order of their own
             want = row if want is None else want
             assert torch.equal(row.view(torch.int16), want.view(torch.int16)), name
+    # the tiles that take any K, the second kernel's from three K blocks on
+    assert set(ran) >= {-1, 0, 2, 3, 5, 23, 24, 25} | ({12, 14, 15, 16} if K > 256 else set()) and (K % 256 or len(ran) == 1 + gg.num_variants() or K <= 256)
 
 
 def test_row_major_against_the_oracle():
@@ -63,11 +67,13 @@ def test_second_kernel_row_major_equals_kmajor_bitwise(K):
     SA[bad] = float("nan")
     SAk = SA.t().contiguous()
     want = gg.grouped_gemm(A, SAk, B, SB, off, variant=3, sa_kmajor=True)         # the first kernel, per K block
+    any_k = [-1, 12, 14, 15, 16]                        # must run: the tiles with an instantiation for every K
     for v in [-1] + [u for u in range(gg.num_variants()) if gg.variant_name(u).endswith("-rb")]:
         try:
             row = gg.grouped_gemm(A, SA, B, SB, off, variant=v)
-        except gg.GGError:
-            continue                                    # a variant that does not take this K
+        except gg.GGError as e:
+            assert e.status == 3 and v not in any_k     # whole K blocks, an even number of them, only
+            continue
         assert torch.equal(row.view(torch.int16), want.view(torch.int16)) or \
             (torch.equal(row.isnan(), want.isnan()) and torch.equal(row.nan_to_num().view(torch.int16), want.nan_to_num().view(torch.int16))), v
         nan_rows = row.isnan().any(dim=1).nonzero().flatten().tolist()
@@ -76,7 +82,8 @@ def test_second_kernel_row_major_equals_kmajor_bitwise(K):
 
 @pytest.mark.parametrize("K", [2032, 2048, 2064, 2176, 2304, 2432])
 def test_first_kernel_row_major_equals_kmajor_bitwise(K):
-    """On such a problem all tiles of the first kernel that can fetch four K blocks of scales at a time do so from K = 2048 on: last chunks of one to four blocks, a ragged K, several tiles per workgroup; and NaN scales stay in their rows."""
+    """On such a problem every tile of the first kernel that can fetch four K blocks of scales at a time does so from K = 2048
+    on: last chunks of one to four blocks, a ragged K, several tiles per workgroup; and NaN scales stay in their rows."""
     sizes, N = [170, 0, 330, 40], 16384
     A, SA, B, SB, off = problem(sizes, N, K, K)
     bad = [0, 169, 170, 333, 539]
