@@ -257,7 +257,8 @@ int pick_large(int G, int64_t M_total, int N, int K) {
 // partial tile in two); a fetch takes 1.6 us from memory, 0.7 where the weights are few enough for the last-level cache.
 // Latency, work and extra steps per tile shape are a fit to 450 random problems (G 1 ... 256, M 1 ... 32768, N and K 256
 // ... 8192, sizes from even to strongly skewed), mean error 11 to 15 % per shape, most of which is the group sizes that the
-// host does not see.  On those the choice is 1.05 of the best of 25 tiles, 1.64 without the small tiles: 8 groups of 8
+// host does not see.  `sweep.py --tiles` draws and times such problems and `--fit` makes the fit: on 600 others of them the
+// choice is 1.050 of the best of ten tiles, median 1.013.  Without the small tiles it was 1.64: 8 groups of 8
 // rows, N = 4096, K = 7168 40 against 65 us (128 x 256), one row, N = K = 4096 12 against 32, 5 groups of 250 rows, N = 768,
 // K = 1280 9.1 against 16.6.  The small tile has to win by a tenth: on the problems of more than 60 us that loses least.
 struct TileTime {
@@ -704,8 +705,8 @@ int gg_fp8_grouped_gemm_swiglu(const void* A, const float* SA, const void* B, co
   }
   if (variant < 0) {
     // ... and, if it wins by a tenth, the better of the small tiles, by the estimate of the plain GEMM's choice with
-    // constants of their own (a fit to 200 random problems; the choice is 1.02 of the best of the five tiles, 1.45 without
-    // the small ones: 8 groups of 8 rows, I = 2048, K = 7168 56 against 81 us, 8 groups of 64 rows 67 against 82)
+    // constants of their own (a fit to 200 random problems; on 300 others the choice is 1.027 of the best of the five tiles,
+    // median 1.003; without the small ones it was 1.45: 8 groups of 8 rows, I = 2048, K = 7168 56 against 81 us, 8 groups of 64 rows 67 against 82)
     auto us = [&](const FusedVariant& f) {
       for (const TileTime& t : kFusedTimes)
         if (t.variant == f.variant) return estimate_us(t, f.BM, I / 128, 1, G, M_total, (double)N * K, (double)K + I, K);

@@ -7,6 +7,8 @@ pad kernels + the same GEMM on 128-aligned offsets + optional unpad), so the com
     python sweep.py                      # full grid (576 points), JSON lines to stdout, summary to stderr
     python sweep.py --grid quick         # the 16 corner points
     python sweep.py --out sweep.jsonl --summary sweep.md
+    python sweep.py --tiles 400 --out tiles.jsonl    # another experiment: the automatic tile choice on random problems
+    python sweep.py --fit tiles.jsonl                # ... its estimate's constants from such a file (no GPU, needs scipy)
 
 Per point: time per launch of the three paths (HIP events on the launch stream; same buffers every launch, so small
 problems are served by the Infinity Cache in all three paths alike, unless --cold flushes the caches before every
@@ -18,10 +20,138 @@ G, M/G; memory saving against M/G).
 import argparse
 import ctypes
 import json
+import math
 import sys
 import time
 
 import numpy as np
+
+# ---- the automatic choice between the tiles: random problems, every tile's time, the estimate's constants -------------------
+# bytes of weights that a workgroup of each tile has on their way, and workgroups per compute unit, as in csrc/gg_fp8.hip
+PLAIN_TILES = {0: (64, 1), 1: (32, 1), 2: (48, 1), 3: (64, 1), 12: (72, 1), 14: (72, 1), 15: (72, 1), 23: (24, 4), 24: (32, 3), 25: (32, 2)}
+FUSED_TILES = {14: (72, 1), 15: (72, 1), 12: (72, 1), 24: (96, 1), 25: (64, 1)}
+FUSED_ROWS = {14: 192, 15: 224, 12: 256, 24: 32, 25: 64}
+
+
+def random_problem(rng, fused):
+    """G 1 ... 256, M 1 ... 32768, N and K 256 ... 8192 (fused: I to 4096), spread over the logarithm, group sizes from even to
+    strongly skewed."""
+    from workloads.configs import WorkloadConfig, group_sizes
+    spread = lambda lo, hi, step=1: min(hi, max(lo, int(round(lo * (hi / lo) ** rng.random() / step)) * step))
+    while True:
+        G, M, K = spread(1, 256), spread(1, 32768), spread(512 if fused else 256, 8192, 128)
+        N = 2 * spread(256, 4096, 128) if fused else spread(256, 8192, 8 if rng.random() < 0.25 else 128)
+        if G * N * K > 2e9 or 2.0 * M * N * K > 4e11:
+            continue
+        law = str(rng.choice(["dirichlet100", "dirichlet1", "dirichlet0.3", "poisson128"]))
+        return G, M, N, K, law, group_sizes(WorkloadConfig("random", 0, G, K, N, M, law, "mfma"), int(rng.integers(1 << 30)))
+
+
+def time_tiles(args):
+    import torch
+    import paper_2508_16584_amd as gg
+    dev, rng = torch.device("cuda:0"), np.random.default_rng(args.seed)
+    sink = open(args.out, "w") if args.out else sys.stdout
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(args.seed)
+    tiles = FUSED_TILES if args.fused else PLAIN_TILES
+
+    def graph_us(launch, n):
+        launch(0)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for i in range(n):
+                launch(i)
+        e0, e1, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e30
+        for _ in range(4):
+            e0.record()
+            graph.replay()
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1) / n * 1e3)
+        return best
+
+    for point in range(args.tiles):
+        G, M, N, K, law, sizes = random_problem(rng, args.fused)
+        km, KB, NB = bool(rng.random() < 0.5), -(-K // 128), -(-N // 128)
+        off = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)).to(dev)
+        copies = max(1, min(6, int(5e8 / (G * N * K)) + 1))             # weights of several layers in turn, as a model has them
+        data = []
+        for _ in range(copies):
+            A = torch.randint(0, 256, (M, K), generator=gen, device=dev, dtype=torch.uint8) & 0xBF
+            B = torch.randint(0, 256, (G, N, K), generator=gen, device=dev, dtype=torch.uint8) & 0xBF
+            data.append((A, torch.rand((KB, M) if km else (M, KB), generator=gen, device=dev) + 0.5, B, torch.rand((G, NB, KB), generator=gen, device=dev) + 0.5, off))
+        if args.fused:
+            A2 = torch.empty((M, N // 2), dtype=torch.uint8, device=dev)
+            SA2 = torch.empty((N // 256, M) if km else (M, N // 256), device=dev)
+            call = lambda i, v: gg.grouped_gemm_swiglu(*data[i % copies], A2=A2, SA2=SA2, sa_kmajor=km, variant=v)
+        else:
+            C = torch.empty((M, N), dtype=torch.bfloat16, device=dev)
+            call = lambda i, v: gg.grouped_gemm(*data[i % copies], C=C, sa_kmajor=km, variant=v)
+        times = {}
+        for v in [-1] + list(tiles):
+            try:
+                times[v] = round(graph_us(lambda i: call(i, v), 2 * copies), 2)
+            except gg.GGError as e:
+                assert e.status == 3 and v >= 0                         # the tile does not take this N or K
+        sink.write(json.dumps(dict(G=G, M=M, N=N, K=K, law=law, km=km, fused=args.fused, us=times)) + "\n")
+        sink.flush()
+        if point % 50 == 49:
+            print(f"[tiles] {point + 1} problems", file=sys.stderr, flush=True)
+        del data
+    if args.out:
+        sink.close()
+        choice_summary(args.out)
+
+
+def read_tiles(path):
+    rows = [json.loads(line) for line in open(path)]
+    for r in rows:
+        r["us"] = {int(v): t for v, t in r["us"].items()}
+    return rows
+
+
+def choice_summary(path):
+    loss = sorted(r["us"][-1] / min(r["us"].values()) for r in read_tiles(path))
+    mean = math.exp(sum(map(math.log, loss)) / len(loss))
+    print(f"{len(loss)} problems: the automatic choice takes {mean:.3f} of the best tile's time (geometric mean), "
+          f"median {loss[len(loss) // 2]:.3f}, 9 of 10 within {loss[9 * len(loss) // 10]:.3f}, worst {loss[-1]:.2f}", file=sys.stderr)
+
+
+def fit_tiles(path):
+    """latency, work and extra K steps of every tile: the estimate of csrc/gg_fp8.hip fitted to the measured times."""
+    import paper_2508_16584_amd as gg
+    from scipy.optimize import minimize
+    rows = read_tiles(path)
+    fused = rows[0]["fused"]
+    choice_summary(path)
+    for v, (kb_in_flight, per_cu) in (FUSED_TILES if fused else PLAIN_TILES).items():
+        BM, BN = (FUSED_ROWS[v], 256) if fused else (int(x) for x in gg.variant_name(v).split("/")[0].split("x"))
+        f, t = [], []
+        for r in rows:
+            if v not in r["us"]:
+                continue
+            G, M, N, K = r["G"], r["M"], r["N"], r["K"]
+            groups = G * (1 - math.exp(-M / G))
+            tiles = max(groups, M / BM + 0.5 * groups) * -(-N // BN)
+            weights = groups * N * K
+            d = weights / (min(tiles, 256 * per_cu) * kb_in_flight * 1024) * (1.6 if weights > 64e6 else 0.7)
+            f.append((tiles, -(-K // 128), (weights + M * (K + (0.5 if fused else 2) * N)) / 6.8e6, d))
+            t.append(r["us"][v])
+        tiles, kb, c, d = np.array(f).T
+        t = np.array(t)
+
+        def estimate(p):
+            latency, work, extra = np.exp(p)
+            a, b = np.maximum(tiles / (256 * per_cu), 1) * (kb + extra) * latency, tiles * (kb + extra) * work / 256
+            return 4.2 + (a ** 4 + b ** 4 + c ** 4 + d ** 4) ** 0.25
+
+        fits = [minimize(lambda p: np.mean(np.abs(np.log(estimate(p) / t)) ** 1.5), np.log([s, s, 4]), method="Nelder-Mead",
+                         options=dict(maxiter=6000, maxfev=6000)) for s in (0.3, 1.2)]
+        best = min(fits, key=lambda x: x.fun).x
+        print(f"{v:3d} {gg.variant_name(v):22s} latency {math.exp(best[0]):.3f} work {math.exp(best[1]):.3f} extra {math.exp(best[2]):.2f}  "
+              f"mean error {np.mean(np.abs(np.log(estimate(best) / t))):.3f} on {len(t)} problems")
 
 
 def main():
@@ -44,7 +174,12 @@ def main():
     ap.add_argument("--seed", type=int, default=20250816)
     ap.add_argument("--out", type=str, default=None, help="write the JSON lines here instead of stdout")
     ap.add_argument("--summary", type=str, default=None, help="write the summary (markdown) here as well as to stderr")
+    ap.add_argument("--tiles", type=int, default=0, help="time every tile on this many random problems instead of the grid")
+    ap.add_argument("--fused", action="store_true", help="with --tiles: the GEMM with the activation epilogue")
+    ap.add_argument("--fit", type=str, default=None, help="fit the constants of the tile choice to a file that --tiles wrote")
     args = ap.parse_args()
+    if args.tiles or args.fit:
+        return fit_tiles(args.fit) if args.fit else time_tiles(args)
 
     import torch
     import paper_2508_16584_amd as gg
