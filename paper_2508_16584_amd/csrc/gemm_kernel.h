@@ -339,7 +339,7 @@ struct GroupIndex {
 // SCALES: how the scales of A are fetched.  kScalesOneChunk is for a tile that has room for one chunk only.  A chunk's scales go
 // into registers in its first K step, and the fetch of the next one, two steps before that is needed, finds the buffer
 // free: a tile's last chunk must have begun two steps before its end, so the number of K blocks is 0 or 3 modulo 4.
-// 256 groups of 128 rows, N = 4096, K = 7168: 1432 us, 1533 with 4-byte fetches per K block.
+// 256 groups of 128 rows on average, N = 4096, K = 7168: 1465 us, 1568 with 4-byte fetches per K block.
 template <class Cfg, bool RAGGED = false, bool SPLITK = false, bool BSTREAM = false, int SCALES = kScalesPerBlock>
 __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
   constexpr int kBAux = BSTREAM ? (2 | 16) : 0;

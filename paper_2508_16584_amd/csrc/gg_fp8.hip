@@ -415,7 +415,7 @@ int validate_gemm(const void* A, const float* SA, const void* B, const float* SB
 // 8 groups of 1024 rows, N = 4096, K = 7168 345 -> 319 us; 128 x 256, 64 groups of 32 rows 322 -> 294) and cost branches in
 // the K step.  Both forms on 1860 random problems, by K, rows per group and rounds over the workgroups:
 //  * rings of three and four buffers, from K = 2048 on with 4 rows per group: 2 to 16 % faster on half of the problems and
-//    at most 3 % slower on the others, which the host cannot tell apart (few tiles, even or skewed group sizes); below, from
+//    up to 5 % slower on a few of the others, which the host cannot tell apart (few tiles, even or skewed group sizes); below, from
 //    K = 1280 on, up to 6 % faster on half a round or more of groups of less than 400 rows, up to 1.5 % slower elsewhere;
 //    with fewer rows, 1 to 2.5 % slower at any K (few requests either way, and a K step is a chain of latencies);
 //  * 32 x 256, which multiplies least per K block: 1 to 4 % faster from K = 2048 on with half a round or more of groups of 4
@@ -501,9 +501,10 @@ int run_gemm(const void* A, const float* SA, const void* B, const float* SB, con
   }
   // groups of at most one row tile on average: every weight byte is fetched once, and streamed past the L2
   const bool bstream = !ragged && v.launch_bstream && M_total <= (int64_t)G * v.BM;
-  // row-major scales, four K blocks of them per fetch; second kernel: from K = 4096 on (8 groups of 1024 rows, N = 4096:
-  // K = 7168 247.3 -> 240.8 us, 7040 246.9 -> 240.5, 4096 147.2 -> 146.5; 32 groups of 512 rows, N = 7168, K = 2048: 285.5 ->
-  // 287.3); first kernel: see chunks_pay
+  // row-major scales, four K blocks of them per fetch; second kernel: from K = 4096 on.  Time against the fetch per K block,
+  // 192-, 224- and 256-row tiles on 2828 random problems: geometric mean 0.98 (0.99 at K = 4096 and 7168, 0.975 from 8320 on),
+  // 0.92 to 1.02 for nine in ten; 8 groups, 8192 rows, N = 4096, K = 7168: 0.98 to 1.02 over routings and tiles.  32 groups of
+  // 512 rows, N = 7168, K = 2048: 285.5 -> 287.3 us.  First kernel: see chunks_pay
   const bool wide = v.launch_wide && !args.sa_kmajor && (v.min_kb3 ? K >= 4096 : chunks_pay(v, G, M_total, K, args.n_tiles));
   const auto launch = ragged ? (wide ? v.launch_ragged_wide : v.launch_ragged)
                       : bstream ? (wide ? v.launch_bstream_wide : v.launch_bstream) : (wide ? v.launch_wide : v.launch);
