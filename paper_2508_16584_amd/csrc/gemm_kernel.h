@@ -167,6 +167,11 @@ struct GemmCfg {
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : (v > hi ? hi : v); }
 
+// Tiles of BM rows that `rows` rows make.  A group may hold up to 2^31 - 1 rows: the sum is formed unsigned.
+__host__ __device__ constexpr int row_tiles(int rows, int BM) { return (int)(((unsigned)rows + (unsigned)(BM - 1)) / (unsigned)BM); }
+// Height, a multiple of 32, of the tiles where `tiles` tiles of about the same height hold `rows` >= 1 rows.
+__host__ __device__ constexpr int even_height(int rows, int tiles) { return ((rows - 1) / tiles + 32) & ~31; }
+
 // s_waitcnt vmcnt(N): at most N of this wave's vector-memory operations may still be in flight.  They complete in the order
 // they were issued, loads, fetches into LDS and stores alike (LLVM's AMDGPU user guide, memory models of the gfx9 family:
 // completion of vector memory operations is reported to a wavefront in execution order; flat accesses are the exception,
@@ -264,7 +269,7 @@ struct GroupIndex {
 
   // tiles of the groups up to group0 + l, from group0 on; rows: those of group group0 + l
   __device__ __forceinline__ static unsigned scan64(const GemmArgs& a, int BM, int rows) {
-    unsigned x = (unsigned)((rows + BM - 1) / BM) * (unsigned)a.n_tiles;
+    unsigned x = (unsigned)row_tiles(rows, BM) * (unsigned)a.n_tiles;
     x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false));      // inclusive scan: row_shr 1, 2, 4, 8 ...
     x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false));
     x = add_sat(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false));
@@ -333,7 +338,7 @@ struct GroupIndex {
     const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
     for (; g < a.G; ++g) {
       const int row0 = clampi(offc[g], 0, a.M_total);
-      const int cnt = (clampi(offc[g + 1], row0, a.M_total) - row0 + BM - 1) / BM * a.n_tiles;
+      const int cnt = row_tiles(clampi(offc[g + 1], row0, a.M_total) - row0, BM) * a.n_tiles;
       if (T < base + cnt) {
         group = g;
         tiles_before = base;
@@ -353,7 +358,7 @@ __device__ __forceinline__ void count_row_tiles(const GemmArgs& a, const GroupIn
   for (int i = 0; i < NB; ++i) tiles[i] = 0;
   auto add = [&](int rows) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < NB; ++i) tiles[i] += (int)(((unsigned)rows + (unsigned)(bm[i] - 1)) / (unsigned)bm[i]);
+    for (int i = 0; i < NB; ++i) tiles[i] += row_tiles(rows, bm[i]);
   };
 #pragma unroll
   for (int c = 0; c < 4; ++c)
@@ -471,7 +476,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
     if (!groups.find(a, BM, T, g, base)) return t;
     const int row0 = clampi(offc[g], 0, a.M_total);
     const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
-    const int mtiles = (Mg + BM - 1) / BM;
+    const int mtiles = row_tiles(Mg, BM);
     // order inside a group: chunks of n_chunk n-tiles; inside a chunk m-tile major, n-tile minor
     const int local = T - base;
     const int per_chunk = mtiles * a.n_chunk;

@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(PcCfg::NT) gg_gemm_pc_kernel(const GemmArgs a)
       if (!groups.find(a, bm, T, g, base)) return t;
       const int row0 = clampi(offc[g], 0, a.M_total);
       const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
-      const int mtiles = (Mg + bm - 1) / bm;
+      const int mtiles = row_tiles(Mg, bm);
       const int local = T - base;
       const int per_chunk = mtiles * a.n_chunk;
       const int nc = local / per_chunk;
@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(PcCfg::NT) gg_gemm_pc_kernel(const GemmArgs a)
       int csz = a.n_tiles - nc * a.n_chunk;
       csz = csz < a.n_chunk ? csz : a.n_chunk;
       const int mtile = rem / csz;
-      const int h = ((Mg + mtiles - 1) / mtiles + 31) & ~31;           // height of the group's tiles: h * mtiles >= Mg, h <= bm
+      const int h = even_height(Mg, mtiles);                             // height of the group's tiles: h * mtiles >= Mg, h <= bm
       t.g = g;
       t.n0 = (nc * a.n_chunk + (rem - mtile * csz)) * BN;
       t.rows = Mg - mtile * h < h ? Mg - mtile * h : h;

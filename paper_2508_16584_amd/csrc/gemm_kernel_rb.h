@@ -227,7 +227,7 @@ __device__ __forceinline__ void rb_run(const GemmArgs& a, const GroupIndex::Rows
     if (!groups.find(a, BM, T, g, base)) return t;
     const int row0 = clampi(offc[g], 0, a.M_total);
     const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
-    const int mtiles = (Mg + BM - 1) / BM;
+    const int mtiles = row_tiles(Mg, BM);
     const int local = T - base;
     const int per_chunk = mtiles * a.n_chunk;
     const int nc = local / per_chunk;
