@@ -13,6 +13,7 @@ import os
 import subprocess
 import sys
 import sysconfig
+import warnings
 
 import torch
 
@@ -63,19 +64,24 @@ def calls_path() -> str:
 
 
 def _build_calls(verbose: bool) -> None:
-    """csrc/gg_calls.cpp, host code only.  Left out where Python's headers are not installed."""
+    """csrc/gg_calls.cpp, host code only.  Where it cannot be built (no g++, no headers of Python's, torch's or HIP's) there is a
+    warning, no file, and every call takes this module's own code."""
+    out = calls_path()
     python_include = sysconfig.get_paths()["include"]
-    if not os.path.exists(os.path.join(python_include, "Python.h")):
-        return
     torch_dir = os.path.dirname(os.path.abspath(torch.__file__))
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
-    out = calls_path()
     cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(_ROOT, "include"),
            "-I", os.path.join(torch_dir, "include"), "-I", os.path.join(rocm, "include"), "-I", python_include,
            "-o", out + ".tmp", os.path.join(_PKG_DIR, "csrc", "gg_calls.cpp"), "-L", os.path.join(torch_dir, "lib"),
            "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-lc10_hip"]
-    _run(cmd, verbose)
+    try:
+        _run(cmd, verbose)
+    except (OSError, RuntimeError) as e:
+        if os.path.exists(out):
+            os.remove(out)                       # what an earlier source or compiler left
+        warnings.warn(f"the binding's native calls are not built: {e}")
+        return
     os.replace(out + ".tmp", out)
 
 
@@ -247,15 +253,20 @@ _calls = None
 
 def _load_calls(lib) -> None:
     global _calls
+    _calls = None
     path = calls_path()
     if not os.path.exists(path):
         return
-    loader = importlib.machinery.ExtensionFileLoader("_gg_calls", path)
-    calls = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_gg_calls", path, loader=loader))
-    loader.exec_module(calls)
-    calls.bind(*(ctypes.cast(fn, ctypes.c_void_p).value for fn in (
-        lib.gg_fp8_grouped_gemm_ex, lib.gg_fp8_grouped_gemm_swiglu, lib.gg_fp8_grouped_gemm_wgrad_ex,
-        lib.gg_fp8_quantize_rows_ex, lib.gg_fp8_quantize_cols, lib.gg_fp8_swiglu_quantize_rows_ex)))
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("_gg_calls", path)
+        calls = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_gg_calls", path, loader=loader))
+        loader.exec_module(calls)
+        calls.bind(*(ctypes.cast(fn, ctypes.c_void_p).value for fn in (
+            lib.gg_fp8_grouped_gemm_ex, lib.gg_fp8_grouped_gemm_swiglu, lib.gg_fp8_grouped_gemm_wgrad_ex,
+            lib.gg_fp8_quantize_rows_ex, lib.gg_fp8_quantize_cols, lib.gg_fp8_swiglu_quantize_rows_ex)))
+    except (ImportError, AttributeError, TypeError) as e:         # built for another torch of this version, or from another source
+        warnings.warn(f"the binding's native calls are not used: {e}")
+        return
     _calls = calls
 
 

@@ -46,6 +46,31 @@ def test_not_on_the_gpu_is_left_alone():
         gg.quantize_cols(X)
 
 
+@pytest.mark.parametrize("failure", [FileNotFoundError("g++"), RuntimeError("g++ failed")])
+def test_a_build_that_fails_leaves_the_python_code(monkeypatch, tmp_path, failure):
+    def run(cmd, verbose):
+        raise failure
+
+    old = tmp_path / "calls.so"
+    old.write_bytes(b"of another source")
+    monkeypatch.setattr(binding, "calls_path", lambda: str(old))
+    monkeypatch.setattr(binding, "_run", run)
+    with pytest.warns(UserWarning, match="not built"):
+        binding._build_calls(False)
+    assert not old.exists()
+
+
+def test_a_file_that_does_not_load_leaves_the_python_code(monkeypatch, tmp_path):
+    bad = tmp_path / "calls.so"
+    bad.write_bytes(b"no library")
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    monkeypatch.setattr(binding, "calls_path", lambda: str(bad))
+    with pytest.warns(UserWarning, match="not used"):
+        binding.load_library()
+    assert binding._calls is None and gg.num_variants() > 0
+
+
 @pytest.mark.gpu
 def test_left_to_the_python_code():
     c, (A, SA, B, SB, off) = calls(), operands("cuda")
