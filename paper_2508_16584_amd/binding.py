@@ -263,7 +263,7 @@ def _load_calls(lib) -> None:
         loader.exec_module(calls)
         calls.bind(*(ctypes.cast(fn, ctypes.c_void_p).value for fn in (
             lib.gg_fp8_grouped_gemm_ex, lib.gg_fp8_grouped_gemm_swiglu, lib.gg_fp8_grouped_gemm_wgrad_ex,
-            lib.gg_fp8_quantize_rows_ex, lib.gg_fp8_quantize_cols, lib.gg_fp8_swiglu_quantize_rows_ex)))
+            lib.gg_fp8_quantize_rows_ex, lib.gg_fp8_quantize_cols, lib.gg_fp8_swiglu_quantize_rows_ex)), _check)
     except (ImportError, AttributeError, TypeError) as e:         # built for another torch of this version, or from another source
         warnings.warn(f"the binding's native calls are not used: {e}")
         return

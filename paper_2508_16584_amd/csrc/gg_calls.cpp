@@ -5,7 +5,8 @@
 // of a small layer's forward and backward pass (64 tokens): 65.8 -> 48.4 us, of which the GPU now works nearly all.
 // A function takes only what is plainly right - tensors of exactly torch's type, shapes, types and devices as the library
 // wants them, no mode or transform at work - and returns None otherwise, without having launched anything: the binding's
-// own code then takes the call, or says what is wrong with it.  The same when the library refuses the call.
+// own code then takes the call, or says what is wrong with it.  The same when the library refuses the arguments.  An error of the
+// HIP runtime, after which a launch may or may not be queued, is raised at once: the call is never made twice.
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/ATen.h>
@@ -29,6 +30,7 @@ struct Library {
   decltype(&gg_fp8_quantize_cols) quantize_cols;
   decltype(&gg_fp8_swiglu_quantize_rows_ex) swiglu_quantize_rows;
 } lib;
+PyObject* check;      // the binding's function that raises the exception of a status
 
 // a contiguous tensor of this type in device memory, and nothing that stands for one
 const at::Tensor* plain(PyObject* o, at::ScalarType type, int64_t dim) {
@@ -93,12 +95,14 @@ struct Gemm {
 };
 
 // The library's call without the interpreter's lock, as ctypes makes it: a launch can wait for room in the stream's queue.
+// False with an exception set: an error of the HIP runtime; without: the library refused the arguments.
 template <class F, class... Args>
 bool call(F* f, Args... args) {
   int status;
   Py_BEGIN_ALLOW_THREADS;
   status = f(args...);
   Py_END_ALLOW_THREADS;
+  if (status == GG_ERR_HIP) Py_XDECREF(PyObject_CallFunction(check, "i", status));
   return status == GG_OK;
 }
 
@@ -249,11 +253,11 @@ PyObject* swiglu_quantize_rows(PyObject*, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
-// (addresses of the six functions, in the order of Library)
+// (addresses of the six functions, in the order of Library; the function for `check`)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
   void* p[6];
-  if (n != 6) {
-    PyErr_SetString(PyExc_TypeError, "six addresses");
+  if (n != 7 || !PyCallable_Check(args[6])) {
+    PyErr_SetString(PyExc_TypeError, "six addresses and a function");
     return nullptr;
   }
   for (int i = 0; i < 6; ++i) {
@@ -263,6 +267,8 @@ PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
   // A forked child may not use the GPU that its parent has used: torch says so, in the binding's own code.
   static const int forked = pthread_atfork(nullptr, nullptr, [] { lib = {}; });
   if (forked) Py_RETURN_NONE;
+  Py_INCREF(args[6]);
+  Py_XSETREF(check, args[6]);
   lib.gemm = reinterpret_cast<decltype(lib.gemm)>(p[0]);
   lib.gemm_swiglu = reinterpret_cast<decltype(lib.gemm_swiglu)>(p[1]);
   lib.wgrad = reinterpret_cast<decltype(lib.wgrad)>(p[2]);

@@ -1,4 +1,6 @@
 """The binding's native calls (csrc/gg_calls.cpp): what they leave to the Python code, and that both give the same."""
+import ctypes
+
 import pytest
 import torch
 from torch.utils._python_dispatch import TorchDispatchMode
@@ -135,3 +137,32 @@ def test_both_routes_give_the_same(km, monkeypatch):
         assert len(fast) == len(slow) and fast[0].dtype == torch.bfloat16 and fast[1].dtype == torch.float16
         for a, b in zip(fast, slow):
             assert a.dtype == b.dtype and a.shape == b.shape and a.device == b.device and torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.gpu
+def test_an_error_of_the_runtime_is_raised_and_the_call_made_once():
+    """A library whose functions report an error of the HIP runtime (nothing is launched): the status reaches the caller, and the
+    Python code, which has the real library, does not make the call again."""
+    c, ops = calls(), operands("cuda")
+    made = []
+
+    def fake(*types):
+        return ctypes.CFUNCTYPE(ctypes.c_int, *types)(lambda *args: made.append(len(args)) or 5)
+
+    vp, i32, i64, u32 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_uint
+    fakes = [fake(*[vp] * 6, i32, i64, i32, i32, vp, ctypes.c_size_t, vp, i32, u32), fake(*[vp] * 8, i32, i64, i32, i32, vp, i32, u32),
+             fake(*[vp] * 6, i32, i64, i32, i32, vp, u32), fake(*[vp] * 4, i64, i64, i32, vp, u32), fake(*[vp] * 4, i64, i64, i32, vp),
+             fake(*[vp] * 4, i64, i32, vp, u32)]
+    A, SA, B, SB, off = ops
+    X = torch.zeros(32, 256, dtype=torch.bfloat16, device="cuda")
+    XT, SX = gg.quantize_cols(X)
+    runs = [lambda: gg.grouped_gemm(*ops), lambda: gg.grouped_gemm_swiglu(*ops), lambda: gg.grouped_gemm_wgrad(XT, SX, XT, SX, off),
+            lambda: gg.quantize_rows(X), lambda: gg.quantize_cols(X), lambda: gg.swiglu_quantize_rows(X)]
+    try:
+        c.bind(*(ctypes.cast(f, vp).value for f in fakes), binding._check)
+        for i, run in enumerate(runs):
+            with pytest.raises(gg.GGError) as e:
+                run()
+            assert e.value.status == 5 and len(made) == i + 1
+    finally:
+        binding._load_calls(binding.load_library())
