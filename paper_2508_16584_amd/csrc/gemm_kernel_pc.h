@@ -45,8 +45,9 @@ struct PcCfg {
 };
 
 // Height of the tallest tile: the one whose tiles fill the rounds over the workgroups best.  A tile's K step costs 4.24 and one
-// for each 32 rows (fitted: 0.56 + 0.13 us per 32 rows), a partly filled round nearly a full one.  On 1500 random problems the
-// time is 1.013 of the best of the five heights; with 160 rows throughout it is 1.076, with 128 1.097, with 96 1.153.
+// for each 32 rows (0.56 + 0.13 us per 32 rows), a partly filled round nearly a full one.  On 2500 random problems of 60 GFLOP and
+// more (`sweep.py --tiles 2500 --min-gflop 60 --seed 303`) the time is 1.008 of the best of the five heights; with 160 rows
+// throughout it is 1.022, with 128 1.087, with 96 1.200.  (Smaller ones of 15 us and more: 1.025, 1.052, 1.066, 1.092.)
 __device__ __forceinline__ int pc_height(const GemmArgs& a, const GroupIndex::Rows& rows, int l) {
   int t[5];
   count_row_tiles<32, 64, 96, 128, 160>(a, rows, l, t);

@@ -7,8 +7,10 @@ pad kernels + the same GEMM on 128-aligned offsets + optional unpad), so the com
     python sweep.py                      # full grid (576 points), JSON lines to stdout, summary to stderr
     python sweep.py --grid quick         # the 16 corner points
     python sweep.py --out sweep.jsonl --summary sweep.md
-    python sweep.py --tiles 400 --out tiles.jsonl    # another experiment: the automatic tile choice on random problems
-    python sweep.py --fit tiles.jsonl                # ... its estimate's constants from such a file (no GPU, needs scipy)
+    python sweep.py --build-fit                      # another experiment: the automatic choice on random problems.  A library that
+                                                     # takes the kernels it chooses between by number (no GPU, needs hipcc) ...
+    python sweep.py --tiles 400 --out tiles.jsonl    # ... every kernel's time ...
+    python sweep.py --fit tiles.jsonl                # ... the estimates' constants from such files (no GPU, needs scipy)
 
 Per point: time per launch of the three paths (HIP events on the launch stream; same buffers every launch, so small
 problems are served by the Infinity Cache in all three paths alike, unless --cold flushes the caches before every
@@ -26,62 +28,102 @@ import time
 
 import numpy as np
 
-# ---- the automatic choice between the tiles: random problems, every tile's time, the estimate's constants -------------------
-# bytes of weights that a workgroup of each tile has on their way, and workgroups per compute unit, as in csrc/gg_fp8.hip
-PLAIN_TILES = {0: (64, 1), 1: (32, 1), 2: (48, 1), 3: (64, 1), 12: (72, 1), 14: (72, 1), 15: (72, 1), 23: (24, 4), 24: (32, 3), 25: (32, 2)}
-FUSED_TILES = {14: (72, 1), 15: (72, 1), 12: (72, 1), 24: (96, 1), 25: (64, 1)}
-FUSED_ROWS = {14: 192, 15: 224, 12: 256, 24: 32, 25: 64}
+# ---- the automatic choice between the kernels: random problems, every kernel's time, the estimates' constants ----------------
+# What the choice is made between: the second and the fourth kernel with the height they choose themselves (numbers that only the
+# library built by --build-fit takes), 128 x 128, the small tiles.  Beside them, the heights that those two choose between.
+RB, PC = 26, 27
+CHOICES = {RB: "second kernel", PC: "fourth kernel", 2: "128x128", 23: "32x64", 24: "32x128", 25: "64x128"}
+HEIGHTS = {RB: {12: 256, 15: 224, 14: 192, 16: 128}, PC: {28: 32, 29: 64, 30: 96, 31: 128, 32: 160}}
+# rows and columns of a tile, KB of weights that a workgroup has on their way, workgroups per compute unit, as in csrc/gg_fp8.hip
+SMALL_TILES = {23: (32, 64, 24, 4), 24: (32, 128, 32, 3), 25: (64, 128, 32, 2)}
+FUSED_TILES = {14: (192, 256, 72, 1), 15: (224, 256, 72, 1), 12: (256, 256, 72, 1), 24: (32, 256, 96, 1), 25: (64, 256, 64, 1)}
 
 
-def random_problem(rng, fused):
-    """G 1 ... 256, M 1 ... 32768, N and K 256 ... 8192 (fused: I to 4096), spread over the logarithm, group sizes from even to
-    strongly skewed."""
+def fit_library():
+    import paper_2508_16584_amd as gg
+    return gg.library_path().replace("libgg_fp8.so", "libgg_fp8_fit.so")
+
+
+def build_fit_library():
+    from paper_2508_16584_amd import binding
+    flags, binding.HIPCC_FLAGS = binding.HIPCC_FLAGS, binding.HIPCC_FLAGS + ["-DGG_FIT_BUILD"]
+    binding._hipcc(binding.library_path().replace("libgg_fp8.so", "csrc/gg_fp8.hip"), fit_library(), False)
+    binding.HIPCC_FLAGS = flags
+
+
+def random_problem(rng, fused, min_flop=0.0):
+    """G 1 ... 256, M 1 ... 32768, N and K 256 ... 8192 (fused: I to 4096), spread over the logarithm, a quarter with an N and an
+    eighth with a K that are no multiples of 128; group sizes from even to strongly skewed."""
     from workloads.configs import WorkloadConfig, group_sizes
     spread = lambda lo, hi, step=1: min(hi, max(lo, int(round(lo * (hi / lo) ** rng.random() / step)) * step))
     while True:
         G, M, K = spread(1, 256), spread(1, 32768), spread(512 if fused else 256, 8192, 128)
         N = 2 * spread(256, 4096, 128) if fused else spread(256, 8192, 8 if rng.random() < 0.25 else 128)
-        if G * N * K > 2e9 or 2.0 * M * N * K > 4e11:
+        if not fused and rng.random() < 0.125:
+            K = spread(256, 8192, 16)
+        if G * N * K > 2e9 or not min_flop <= 2.0 * M * N * K <= 4e11:
             continue
         law = str(rng.choice(["dirichlet100", "dirichlet1", "dirichlet0.3", "poisson128"]))
         return G, M, N, K, law, group_sizes(WorkloadConfig("random", 0, G, K, N, M, law, "mfma"), int(rng.integers(1 << 30)))
 
 
 def time_tiles(args):
+    import os
+
     import torch
     import paper_2508_16584_amd as gg
+    from paper_2508_16584_amd import binding
+    if not args.fused:
+        if not os.path.exists(fit_library()):
+            sys.exit(f"{fit_library()} is missing: build it with `python sweep.py --build-fit`")
+        binding._LIB_NAME = os.path.basename(fit_library())
+        assert gg.num_variants() == RB
     dev, rng = torch.device("cuda:0"), np.random.default_rng(args.seed)
     sink = open(args.out, "w") if args.out else sys.stdout
     gen = torch.Generator(device=dev)
     gen.manual_seed(args.seed)
-    tiles = FUSED_TILES if args.fused else PLAIN_TILES
+    tiles = list(FUSED_TILES) if args.fused else list(CHOICES) + [v for h in HEIGHTS.values() for v in h]
+    # operand bytes: normal samples in units of a quarter of e4m3's range, as a block quantiser leaves them
+    pool = torch.cat([(torch.randn(1 << 24, generator=gen, device=dev) * 112).clamp(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8) for _ in range(8)])
 
-    def graph_us(launch, n):
+    def operand(*shape):
+        t = torch.empty(shape, dtype=torch.uint8, device=dev)
+        flat, at = t.view(-1), 0
+        while at < flat.numel():
+            start = int(rng.integers(1 << 20)) * 16
+            n = min(flat.numel() - at, pool.numel() - start)
+            flat[at:at + n] = pool[start:start + n]
+            at += n
+        return t
+
+    def captured(launch, n):
         launch(0)
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
             for i in range(n):
                 launch(i)
-        e0, e1, best = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True), 1e30
-        for _ in range(4):
-            e0.record()
-            graph.replay()
-            e1.record()
-            torch.cuda.synchronize()
-            best = min(best, e0.elapsed_time(e1) / n * 1e3)
-        return best
+        return graph
+
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+
+    def replay_us(graph, n):
+        e0.record()
+        graph.replay()
+        e1.record()
+        torch.cuda.synchronize()
+        return e0.elapsed_time(e1) / n * 1e3
 
     for point in range(args.tiles):
-        G, M, N, K, law, sizes = random_problem(rng, args.fused)
+        G, M, N, K, law, sizes = random_problem(rng, args.fused, 1e9 * args.min_gflop)
         km, KB, NB = bool(rng.random() < 0.5), -(-K // 128), -(-N // 128)
         off = torch.from_numpy(np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)).to(dev)
         copies = max(1, min(6, int(5e8 / (G * N * K)) + 1))             # weights of several layers in turn, as a model has them
+        launches = copies * max(2, min(8, int(40 / (copies * (5 + 2.0 * M * N * K / 2e9)))))
         data = []
         for _ in range(copies):
-            A = torch.randint(0, 256, (M, K), generator=gen, device=dev, dtype=torch.uint8) & 0xBF
-            B = torch.randint(0, 256, (G, N, K), generator=gen, device=dev, dtype=torch.uint8) & 0xBF
-            data.append((A, torch.rand((KB, M) if km else (M, KB), generator=gen, device=dev) + 0.5, B, torch.rand((G, NB, KB), generator=gen, device=dev) + 0.5, off))
+            data.append((operand(M, K), torch.rand((KB, M) if km else (M, KB), generator=gen, device=dev) + 0.5, operand(G, N, K),
+                         torch.rand((G, NB, KB), generator=gen, device=dev) + 0.5, off))
         if args.fused:
             A2 = torch.empty((M, N // 2), dtype=torch.uint8, device=dev)
             SA2 = torch.empty((N // 256, M) if km else (M, N // 256), device=dev)
@@ -89,45 +131,127 @@ def time_tiles(args):
         else:
             C = torch.empty((M, N), dtype=torch.bfloat16, device=dev)
             call = lambda i, v: gg.grouped_gemm(*data[i % copies], C=C, sa_kmajor=km, variant=v)
-        times = {}
-        for v in [-1] + list(tiles):
+        graphs, times = {}, {}
+        for v in [-1] + tiles:
             try:
-                times[v] = round(graph_us(lambda i: call(i, v), 2 * copies), 2)
+                graphs[v] = captured(lambda i: call(i, v), launches)
             except gg.GGError as e:
                 assert e.status == 3 and v >= 0                         # the tile does not take this N or K
-        sink.write(json.dumps(dict(G=G, M=M, N=N, K=K, law=law, km=km, fused=args.fused, us=times)) + "\n")
+        # the kernels in turn, in another order every time: what ran before moves the clock by several per cent
+        for _ in range(6):
+            for v in rng.permutation(list(graphs)).tolist():
+                times.setdefault(v, []).append(replay_us(graphs[v], launches))
+        times = {v: round(float(np.median(t[1:])), 2) for v, t in times.items()}
+        del graphs
+        sink.write(json.dumps(dict(G=G, M=M, N=N, K=K, law=law, km=km, fused=args.fused, sizes=sizes.tolist(), us=times)) + "\n")
         sink.flush()
         if point % 50 == 49:
             print(f"[tiles] {point + 1} problems", file=sys.stderr, flush=True)
         del data
     if args.out:
         sink.close()
-        choice_summary(args.out)
+        choice_summary([args.out])
 
 
-def read_tiles(path):
-    rows = [json.loads(line) for line in open(path)]
+def read_tiles(paths):
+    rows = [json.loads(line) for path in paths for line in open(path)]
     for r in rows:
         r["us"] = {int(v): t for v, t in r["us"].items()}
     return rows
 
 
-def choice_summary(path):
-    loss = sorted(r["us"][-1] / min(r["us"].values()) for r in read_tiles(path))
+def choice_summary(paths):
+    loss = sorted(r["us"][-1] / min(r["us"][v] for v in r["us"] if v >= 0 and (r["fused"] or v in CHOICES)) for r in read_tiles(paths))
     mean = math.exp(sum(map(math.log, loss)) / len(loss))
     print(f"{len(loss)} problems: the automatic choice takes {mean:.3f} of the best tile's time (geometric mean), "
           f"median {loss[len(loss) // 2]:.3f}, 9 of 10 within {loss[9 * len(loss) // 10]:.3f}, worst {loss[-1]:.2f}", file=sys.stderr)
 
 
-def fit_tiles(path):
-    """latency, work and extra K steps of every tile: the estimate of csrc/gg_fp8.hip fitted to the measured times."""
-    import paper_2508_16584_amd as gg
+def fit_large(rows):
+    """The estimates of the second kernel, the fourth one and the 128 x 128 tile (kRbTime, kPcTime, kNarrowTime and the steps beside
+    them in csrc/gg_fp8.hip), fitted to every other problem and tried on the rest.  The first two are fitted together: besides
+    their errors, what the problems of 25 us and more lose where the smaller estimate is the wrong one counts."""
     from scipy.optimize import minimize
-    rows = read_tiles(path)
+    G, M, N, K = (np.array([r[x] for r in rows], float) for x in "GMNK")
+    T = {v: np.array([r["us"].get(v, np.inf) for r in rows]) for v in CHOICES}
+    best = np.min(list(T.values()), axis=0)
+    half = np.arange(len(rows)) % 2 == 0
+    groups, blocks = G * (1 - np.exp(-M / G)), np.ceil(K / 128)
+    row_tiles = {bm: np.maximum(groups, M / bm + 0.5 * groups) for bm in (32, 64, 96, 128, 160, 192, 224, 256)}
+    step_cost = {128: 1.036, 192: 1.332, 224: 1.5, 256: 1.647}           # rb_step_cost
+
+    def rounds(bm, columns, first):
+        f = row_tiles[bm] * np.ceil(N / columns) / 256 * np.array([[0.96], [0.98], [1], [1.02], [1.04]])
+        part = f - np.floor(f)
+        return np.mean(np.floor(f) + np.where(part > 0, first + (1 - first) * part, 0), axis=0)
+
+    def launch(steps, tbs, start, ragged, store):
+        steps, data = np.where(K % 128 > 0, ragged, 1) * steps, (groups * N * K + M * (K + 2 * N)) / (tbs * 1e6)
+        return start + (steps ** 4 + data ** 4) ** 0.25 + store * 2e-6 * M * N
+
+    def pc(x):
+        extra, step, step32, first, *rest = x
+        return launch(np.min([(blocks + extra) * (step + step32 * row_tiles[32] / row_tiles[bm]) * rounds(bm, 256, first)
+                              for bm in (32, 64, 96, 128, 160)], axis=0), *rest)
+
+    def rb(x):
+        extra, step, odd, first, *rest = x
+        steps = np.min([(blocks + extra) * step * step_cost[bm] * rounds(bm, 256, first) for bm in step_cost], axis=0)
+        return launch(np.where(blocks % 2 > 0, odd, 1) * steps, *rest)
+
+    def narrow(x):
+        extra, step, first, *rest = x
+        return launch((blocks + extra) * step * rounds(128, 128, first), *rest)
+
+    def bounded(x, first):                                              # a partly filled round costs a full one at most
+        x = np.abs(x)
+        x[first] = min(x[first], 1.0)
+        return x
+
+    def smallest(f, x):
+        for _ in range(8):
+            x = minimize(f, x, method="Nelder-Mead", options=dict(maxiter=4000, maxfev=4000, adaptive=True)).x
+        return x
+
+    both, large = np.isfinite(T[RB]), np.isfinite(T[RB]) & (np.minimum(T[RB], T[PC]) > 25)
+    near = {v: T[v] < 1.5 * best for v in (RB, PC)}
+
+    def losses(x):
+        p, b = np.log(pc(bounded(x[:8], 3))), np.log(rb(bounded(x[8:], 3)))
+        lp, lb = np.log(T[PC]), np.log(np.where(both, T[RB], 1))
+        share = 1 / (1 + np.exp(np.clip((b - p) / 0.03, -50, 50)))       # of the second kernel, a step that has been rounded off
+        return p - lp, b - lb, share * lb + (1 - share) * lp - np.minimum(lb, lp)
+
+    def loss(x):
+        ep, eb, lost = losses(x)
+        return np.mean(lost[half & large]) + 0.1 * (np.mean(np.abs(ep[half & near[PC]]) ** 1.5) + np.mean(np.abs(eb[half & near[RB]]) ** 1.5))
+
+    x = smallest(loss, np.array([2.0, 0.6, 0.1, 0.9, 6.0, 5.5, 1.1, 0.02, 3.0, 0.9, 1.05, 0.9, 6.0, 5.5, 1.1, 0.02]))
+    ep, eb, _ = losses(x)
+    wrong = np.where((rb(bounded(x[8:], 3)) <= pc(bounded(x[:8], 3)))[~half & large], T[RB][~half & large], T[PC][~half & large])
+    names = "first tbs start ragged store".split()
+    print("fourth kernel  ", *(f"{n} {v:.3f}" for n, v in zip(["extra", "step", "per 32 rows"] + names, bounded(x[:8], 3))),
+          f"mean error {np.mean(np.abs(ep[~half & near[PC]])):.3f}")
+    print("second kernel  ", *(f"{n} {v:.3f}" for n, v in zip(["extra", "step", "odd"] + names, bounded(x[8:], 3))),
+          f"mean error {np.mean(np.abs(eb[~half & near[RB]])):.3f}")
+    print(f"the one with the smaller estimate / the better one: {np.exp(np.mean(np.log(wrong / np.minimum(T[RB], T[PC])[~half & large]))):.4f} "
+          f"on {len(wrong)} problems of 25 us and more that played no part")
+    some = half & np.isfinite(T[2]) & (T[2] > 12)
+    x = bounded(smallest(lambda x: np.mean(np.abs(np.log(narrow(bounded(x, 2)) / T[2])[some]) ** 1.5), np.array([3.0, 0.6, 0.8, 6.0, 4.5, 1.1, 0.05])), 2)
+    other = ~half & np.isfinite(T[2]) & (T[2] > 12)
+    print("128 x 128      ", *(f"{n} {v:.3f}" for n, v in zip(["extra", "step"] + names, x)),
+          f"mean error {np.mean(np.abs(np.log(narrow(x) / T[2])[other])):.3f}")
+
+
+def fit_tiles(paths):
+    """latency, work and extra K steps of the small tiles and of the tiles of the fused kernel (kTileTimes, kFusedTimes)."""
+    from scipy.optimize import minimize
+    rows = read_tiles(paths)
     fused = rows[0]["fused"]
-    choice_summary(path)
-    for v, (kb_in_flight, per_cu) in (FUSED_TILES if fused else PLAIN_TILES).items():
-        BM, BN = (FUSED_ROWS[v], 256) if fused else (int(x) for x in gg.variant_name(v).split("/")[0].split("x"))
+    choice_summary(paths)
+    if not fused:
+        fit_large(rows)
+    for v, (BM, BN, kb_in_flight, per_cu) in (FUSED_TILES if fused else SMALL_TILES).items():
         f, t = [], []
         for r in rows:
             if v not in r["us"]:
@@ -150,7 +274,7 @@ def fit_tiles(path):
         fits = [minimize(lambda p: np.mean(np.abs(np.log(estimate(p) / t)) ** 1.5), np.log([s, s, 4]), method="Nelder-Mead",
                          options=dict(maxiter=6000, maxfev=6000)) for s in (0.3, 1.2)]
         best = min(fits, key=lambda x: x.fun).x
-        print(f"{v:3d} {gg.variant_name(v):22s} latency {math.exp(best[0]):.3f} work {math.exp(best[1]):.3f} extra {math.exp(best[2]):.2f}  "
+        print(f"{v:3d} {BM}x{BN}{' fused' if fused else ''} latency {math.exp(best[0]):.3f} work {math.exp(best[1]):.3f} extra {math.exp(best[2]):.2f}  "
               f"mean error {np.mean(np.abs(np.log(estimate(best) / t))):.3f} on {len(t)} problems")
 
 
@@ -175,9 +299,13 @@ def main():
     ap.add_argument("--out", type=str, default=None, help="write the JSON lines here instead of stdout")
     ap.add_argument("--summary", type=str, default=None, help="write the summary (markdown) here as well as to stderr")
     ap.add_argument("--tiles", type=int, default=0, help="time every tile on this many random problems instead of the grid")
+    ap.add_argument("--min-gflop", type=float, default=0.0, help="with --tiles: larger problems only")
     ap.add_argument("--fused", action="store_true", help="with --tiles: the GEMM with the activation epilogue")
-    ap.add_argument("--fit", type=str, default=None, help="fit the constants of the tile choice to a file that --tiles wrote")
+    ap.add_argument("--build-fit", action="store_true", help="compile the library that --tiles times (no GPU)")
+    ap.add_argument("--fit", type=str, nargs="+", help="fit the constants of the choice to files that --tiles wrote")
     args = ap.parse_args()
+    if args.build_fit:
+        return build_fit_library()
     if args.tiles or args.fit:
         return fit_tiles(args.fit) if args.fit else time_tiles(args)
 

@@ -1,0 +1,29 @@
+"""The automatic choice between the kernels, where measured times say clearly which one it should be: random problems of sweep.py
+--tiles, each with the times (us) of the second kernel (tiles "-rb") and of the fourth (160x256/2x4w/3s, 128x256/2x4w/3s)."""
+import pytest
+
+import paper_2508_16584_amd as gg
+
+FOURTH = ("160x256/2x4w/3s", "128x256/2x4w/3s")
+
+
+@pytest.mark.parametrize("G,M,N,K,second,fourth", [
+    (2, 28849, 5248, 640, 148.7, 116.6), (3, 30129, 5504, 640, 157.9, 127.7), (3, 25644, 5888, 640, 145.5, 121.6),       # 5 K blocks
+    (11, 2715, 7424, 6784, 234.6, 189.2), (34, 21212, 4224, 2176, 249.1, 217.7), (1, 13083, 1536, 6016, 135.0, 116.6),   # 53, 17, 47
+    (7, 3123, 5760, 640, 27.3, 20.6), (1, 1289, 4480, 5504, 55.4, 44.2)])
+def test_an_odd_number_of_k_blocks_costs_the_second_kernel(G, M, N, K, second, fourth):
+    assert K // 128 % 2 == 1 and fourth < 0.9 * second
+    assert gg.variant_name(gg.auto_variant(G, M, N, K)) in FOURTH
+
+
+def test_the_odd_number_is_the_only_step_along_k():
+    """The odd number's cost is the only step in K: where the second kernel is chosen with an odd number of K blocks, it is with
+    both even neighbours."""
+    second = lambda G, M, N, kb: gg.variant_name(gg.auto_variant(G, M, N, 128 * kb)).endswith("-rb")
+    seen = 0
+    for G, M, N in [(8, 3001, 4096), (8, 8192, 4096), (4, 12000, 2048), (16, 16384, 7168), (32, 16384, 7168), (2, 6000, 8192)]:
+        for kb in range(5, 64, 2):
+            if second(G, M, N, kb):
+                seen += 1
+                assert second(G, M, N, kb - 1) and second(G, M, N, kb + 1), (G, M, N, kb)
+    assert seen > 20
