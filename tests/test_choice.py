@@ -27,3 +27,10 @@ def test_the_odd_number_is_the_only_step_along_k():
                 seen += 1
                 assert second(G, M, N, kb - 1) and second(G, M, N, kb + 1), (G, M, N, kb)
     assert seen > 20
+
+
+@pytest.mark.parametrize("G,M,N,K,small,narrow", [(4, 8090, 336, 7168, 71.5, 43.9), (5, 12196, 184, 5888, 57.9, 35.3), (2, 8029, 336, 3072, 31.4, 22.7),
+                                                  (22, 6786, 320, 5632, 44.2, 34.8), (18, 1952, 1120, 7808, 60.9, 48.8)])
+def test_ragged_n_that_a_256_wide_tile_would_mostly_waste(G, M, N, K, small, narrow):
+    """... and here those of the 64 x 128 and the 128 x 128 tile."""
+    assert narrow < 0.9 * small and gg.variant_name(gg.auto_variant(G, M, N, K)) == "128x128/2x4w/4s"
