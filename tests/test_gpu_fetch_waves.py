@@ -1,5 +1,7 @@
 """The kernel whose waves either fetch or multiply (tiles 160x256 and 128x256): the same bits as the first kernel's 128x128
-tile, which takes every shape, where its tiles, its K loop and its chunks of scales end."""
+tile, which takes every shape, where its tiles, its K loop and its chunks of scales end, and at every height it chooses."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -46,11 +48,42 @@ def test_tile_heights_and_k_blocks(N, K):
 
 
 @pytest.mark.parametrize("sizes", [[128] * 40, [97, 30, 200] * 60, [3] * 300 + [170], [0] * 70 + [90] + [0] * 250 + [150]])
-def test_chosen_height_and_many_groups(sizes):
-    """Launches of several rounds, whose tile height the kernel chooses; more groups than one index holds."""
+def test_many_tiles_and_many_groups(sizes):
+    """Launches of several rounds; more groups than one index holds."""
     N, K = 2048, 640
-    assert gg.auto_variant(len(sizes), sum(sizes), N, K) >= 0
     check(problem(sizes, N, K, len(sizes)), K, f"{len(sizes)} groups")
+
+
+def chosen_height(sizes, N):
+    """The rule of the kernel (pc_height), written out again: another height gives the same bits, so this only says which heights
+    the cases below are meant to reach."""
+    columns = -(-N // 256)
+    grid = min(256, (sum(sizes) // 32 + len(sizes)) * columns)
+    grid -= grid % 8 if grid >= 8 else 0
+    tiles = {bm: sum(-(-s // bm) for s in sizes) for bm in (160, 128, 96, 64, 32)}
+
+    def cost(bm):
+        rounds = tiles[bm] * columns / grid
+        part = rounds - math.floor(rounds)
+        return (math.floor(rounds) + (0.91 + 0.09 * part if part else 0)) * (4.24 + tiles[32] / tiles[bm])
+    return min(tiles, key=cost)
+
+
+MANY = np.random.default_rng(31).integers(0, 83, 300).tolist()
+
+
+# N, and N - 8, whose last tile is cut; five K blocks, eleven with a short last one, seventeen
+@pytest.mark.parametrize("sizes,N,Ks,want", [([17, 34, 17, 8] * 10, 1024, [2048, 2176], 32), ([350, 175] * 14, 1024, [640, 1296], 64),
+                                             ([500, 1000, 1000], 2048, [640, 1296, 2176], 96), ([1158, 1158, 579], 2048, [640, 1296, 2176], 128),
+                                             ([258, 517, 1034], 4096, [640, 1296, 2176], 160), (MANY, 512, [640, 2176], 64), ([150] * 280, 512, [640, 1296], 160)])
+def test_every_height_that_the_kernel_chooses(sizes, N, Ks, want):
+    """The automatic choice sends these to the fourth kernel, which chooses each of its five heights, and two of them over more
+    groups than one index holds."""
+    for n in (N, N - 8):
+        assert torch.cuda.get_device_properties(0).multi_processor_count != 256 or chosen_height(sizes, n) == want
+        for K in Ks:
+            assert gg.auto_variant(len(sizes), sum(sizes), n, K) in (0, 3)
+            check(problem(sizes, n, K, n + K), K, f"{len(sizes)} groups, N={n} K={K}")
 
 
 def test_scales_that_are_nan_stay_in_their_rows():
