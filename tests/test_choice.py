@@ -34,3 +34,9 @@ def test_the_odd_number_is_the_only_step_along_k():
 def test_ragged_n_that_a_256_wide_tile_would_mostly_waste(G, M, N, K, small, narrow):
     """... and here those of the 64 x 128 and the 128 x 128 tile."""
     assert narrow < 0.9 * small and gg.variant_name(gg.auto_variant(G, M, N, K)) == "128x128/2x4w/4s"
+
+
+@pytest.mark.parametrize("G,M,N,K", [(64, 2048, 4096, 7168), (256, 32768, 4096, 7168), (8, 8192, 4096, 7168), (40, 300, 1024, 2048), (12, 900, 768, 640), (3, 5, 512, 512)])
+def test_padded_problems_go_by_the_rows_that_their_groups_are_expected_to_hold(G, M, N, K):
+    cap = gg.padded_rows_cap(G, M)
+    assert gg.auto_variant_padded(G, cap, N, K) == gg.auto_variant(G, cap - 64 * G, N, K)
