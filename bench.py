@@ -742,11 +742,11 @@ def main():
     vname = gg.variant_name(used)
     roof["traffic"] = profiled_traffic("grouped_gemm", args.workload, args.sa_layout, vname)
     roof["traffic_source"] = TRAFFIC_SOURCE if roof["traffic"] is not None else None
-    # the variant the library reports for these sizes (gg_fp8_auto_variant; the second and the fourth kernel settle the tile
-    # height on the device), or the one asked for
+    # the kernel of the variant that the library expects for these sizes (gg_fp8_auto_variant), or of the one asked for
     name = {0: "gg_gemm_pc_kernel", 3: "gg_gemm_pc_kernel", 23: "gg_gemm_sm_kernel", 24: "gg_gemm_sm_kernel", 25: "gg_gemm_sm_kernel"}.get(
         used, "gg_gemm_rb_kernel" if "-rb" in vname and args.variant >= 0 else "gg_gemm_rb_any_kernel" if "-rb" in vname else "gg_gemm_kernel")
-    roof["kernel"] = f"{name}<{vname}>"
+    on_device = args.variant < 0 and (used in (0, 3) or "-rb" in vname)       # these kernels settle the tile height themselves
+    roof["kernel"] = f"{name} (height chosen on the device, expected: {vname})" if on_device else f"{name}<{vname}>"
     roof["kernel_avg_ms"] = round(kern_avg_ms, 4)
     roof["kernel_median_ms"] = round(float(np.median(kern_ms)), 4)
     roof["kernel_min_ms"] = round(float(kern_ms.min()), 4)

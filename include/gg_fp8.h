@@ -35,7 +35,7 @@
  *    0 <= off[0] and off[G] <= M_total.  If it is not, rows may be skipped or
  *    computed with the wrong group, but nothing outside C[0:M_total] is written.
  *    Rows of C outside [off[0], off[G]) are never written.
- *  - Return value: a gg_status.  On any error nothing has been enqueued.
+ *  - Return value: a gg_status.  On any error but GG_ERR_HIP nothing has been enqueued.
  *    G == 0 or M_total == 0 returns GG_OK without a launch.
  */
 #ifndef GG_FP8_H
@@ -84,7 +84,7 @@ int gg_fp8_grouped_gemm(const void* A, const float* SA, const void* B, const flo
                         int G, int64_t M_total, int N, int K,
                         void* workspace, size_t workspace_bytes, void* stream);
 
-/* Same operation with an explicit tile variant (for benchmarking and tests).
+/* Same operation with an explicit tile variant (for benchmarking and tests), at the tile height of its name.
  * variant < 0 selects automatically, exactly like gg_fp8_grouped_gemm.
  * gg_fp8_num_variants() variants exist; gg_fp8_variant_name(v) describes one
  * ("BMxBN/waves/stages"), NULL if v is out of range. */
@@ -94,9 +94,11 @@ int gg_fp8_grouped_gemm_variant(const void* A, const float* SA, const void* B, c
                                 void* workspace, size_t workspace_bytes, void* stream, int variant);
 int gg_fp8_num_variants(void);
 const char* gg_fp8_variant_name(int variant);
-/* The variant gg_fp8_grouped_gemm would use for these sizes (the choice looks at
- * sizes only, never at device memory); a negative gg_status value if the sizes
- * are not supported. */
+/* The variant whose tile gg_fp8_grouped_gemm is expected to use for these sizes; a negative gg_status value if
+ * the sizes are not supported.  The host looks at sizes only and chooses a kernel; the kernels of variants 0 and 3
+ * and of 12, 14, 15 and 16 ("-rb"), where they are not asked for by name, then take the tile height that suits the
+ * groups, whose sizes they find in group_offsets.  The index passed as `variant` therefore launches the same kernel at
+ * the named height: the same results, not always the same time. */
 int gg_fp8_auto_variant(int G, int64_t M_total, int N, int K);
 /* The same for gg_fp8_grouped_gemm_padded (and for the _ex call with GG_PADDED_GROUPS), on a capacity of rows (the padded
  * problem of Sec. 3). */

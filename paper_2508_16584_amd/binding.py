@@ -377,7 +377,7 @@ def num_variants() -> int:
 
 
 def auto_variant_padded(G: int, M_pad_cap: int, N: int, K: int) -> int:
-    """Index of the variant gg_fp8_grouped_gemm_padded (or GG_PADDED_GROUPS with variant = -1) uses."""
+    """auto_variant for gg_fp8_grouped_gemm_padded (or GG_PADDED_GROUPS with variant = -1)."""
     v = load_library().gg_fp8_auto_variant_padded(G, M_pad_cap, N, K)
     if v < 0:
         raise ValueError(f"gg_fp8_auto_variant_padded: {status_str(-v)}")
@@ -385,7 +385,9 @@ def auto_variant_padded(G: int, M_pad_cap: int, N: int, K: int) -> int:
 
 
 def auto_variant(G: int, M_total: int, N: int, K: int) -> int:
-    """Index of the variant grouped_gemm(variant=-1) uses for these sizes."""
+    """Index of the variant whose tile grouped_gemm(variant=-1) is expected to use for these sizes.  The kernels of the variants
+    0, 3, 12, 14, 15 and 16 settle the tile height on the device, from the group sizes; passed as variant, the index runs
+    the named height."""
     v = load_library().gg_fp8_auto_variant(G, M_total, N, K)
     if v < 0:
         raise ValueError(f"gg_fp8_auto_variant: {status_str(-v)}")
