@@ -243,7 +243,8 @@ __device__ __forceinline__ int swz_key_b(int row) {   // rows read: base + 8*(r/
 // round are split evenly over the XCDs where memory bounds the launch or it is the only round: dealt out in whole runs, half a
 // round is four XCDs with all their compute units busy and four idle (52 groups of 39 rows on average, N = 4096, K = 7168, 3.5
 // rounds: 290 -> 286 us; 32 x 64 tiles, 768 workgroups, 256 to 512 tiles: 1.2 times).  Larger compute-bound launches keep whole
-// runs, which share more (8 groups of 375 rows, N = 4104, K = 7232, 1.5 rounds: 159.5 against 162).
+// runs, which share more; in the fourth kernel's 160-row tiles it makes 1 % either way (8 groups of 375 rows, N = 4104, K = 7232 153.4
+// us, split 152.7; of 640, N = 4096, K = 7168 152.2 and 150.3; of 1120 269.8 and 271.0).
 struct GroupIndex {
   static constexpr int NONE = 0x7FFFFFFF;      // a work unit that does not exist
   unsigned pre[4];

@@ -2,10 +2,9 @@
 // per element as gemm_kernel.h, so the same bits): small tiles, for problems whose tiles of the other two kernels would
 // leave most of the chip idle, or whose K loop would be a chain of latencies.
 //
-// With few rows per group the 160 x 256 and 128 x 256 tiles of the first kernel are few (8 groups of 8 rows, N = 4096:
-// 128 tiles on 256 compute units), and one of its K steps takes 0.4 us however little there is to multiply: wait for
-// the fetches, barrier, LDS reads, matrix instructions, FMAs follow one another, and waves find their fetches in
-// branches.  Here
+// With few rows per group 256-wide tiles are few (8 groups of 8 rows, N = 4096: 128 tiles on 256 compute units), and a
+// K step of the other kernels takes 0.4 (first) to 0.8 us (fourth) however little there is to multiply: wait for the fetches,
+// barrier, LDS reads, matrix instructions and FMAs follow one another.  Here
 //  * a workgroup has 4 waves and a tile of 32 x 64, 32 x 128 or 64 x 128 (with the activation epilogue 32 or 64 rows of 256
 //    weight rows); several workgroups share a compute unit;
 //  * a wave multiplies K block kb out of registers, into which the block was read during the step before; the barrier at
