@@ -121,7 +121,7 @@ int gg_fp8_grouped_gemm_f16(const void* A, const float* SA, const void* B, const
  *                (GG_ERR_SHAPE otherwise).  Same arithmetic, bit-identical results.
  *  GG_PADDED_GROUPS  a promise that every group holds a multiple of 128 rows (the pad path of Sec. 3, what
  *                gg_fp8_grouped_gemm_padded passes): the automatic choice (variant = -1) then reads M_total as a
- *                capacity (M_pad_cap), of which the groups hold about 64 rows each less.  Results do not depend on it.
+ *                capacity (M_pad_cap) of which about 64 rows per group stay empty.  Results do not depend on it.
  *  GG_OUT_BF16   gg_fp8_grouped_gemm_wgrad_ex only: its output is bfloat16 instead of fp32. */
 enum { GG_OUT_F16 = 1, GG_SA_KMAJOR = 2, GG_PADDED_GROUPS = 4, GG_OUT_BF16 = 8 };
 
