@@ -105,3 +105,12 @@ def test_against_the_oracle():
     ref = orc.grouped_gemm(*(t.cpu().numpy() for t in dev), with_abs_sum=True)
     for v in (0, 3):
         assert_parity(bits_of(gg.grouped_gemm(*dev, variant=v)), ref, empirical=False, what=f"variant {v}")
+
+
+def test_every_negative_variant_is_the_automatic_choice():
+    sizes, N, K = [500, 1000, 1000], 2048, 640
+    assert gg.auto_variant(len(sizes), sum(sizes), N, K) in (0, 3)
+    dev = problem(sizes, N, K, 5)
+    want = gg.grouped_gemm(*dev).view(torch.int16)
+    for v in (-2, -27, -2 ** 31, -2 ** 31 + 25):
+        assert torch.equal(gg.grouped_gemm(*dev, variant=v).view(torch.int16), want), v
