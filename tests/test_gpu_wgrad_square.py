@@ -1,0 +1,50 @@
+"""gg_fp8_grouped_gemm_wgrad on launches large enough for its tiles of 256 x 256.
+
+Every intermediate is exact (integers up to 4, scales 1/2, 1 and 2, at most 2100 tokens per group: sums below 2^24 in units of
+1/4), so the fp32 result must equal the product in float64, and the bfloat16 one its rounding.  One group's tokens are NaN in
+both operands: its neighbours fetch some of them in their first and last 16 tokens and must not show them.
+"""
+import pytest
+import torch
+
+import paper_2508_16584_amd as gg
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+LENGTHS = [1, 0, 16, 15, 127, 128, 129, 400, 512, 513, 0, 900, 3]
+
+
+# runs of tiles dealt by cost: whole ones, a partial one per group; listed in order: more than 64 groups, few token blocks per group
+@pytest.mark.parametrize("N,K,G", [(5120, 4096, 8), (4608, 4352, 9), (1280, 2304, 70), (2048, 2048, 41)])
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_exact_over_lengths(N, K, G, out_bf16):
+    gen = torch.Generator().manual_seed(N + G)
+    sizes = [LENGTHS[i] for i in torch.randint(0, len(LENGTHS), (G,), generator=gen).tolist()]
+    nan, i = G // 2, 0
+    sizes[nan] = 35
+    while sum(sizes) < 220 * G:                  # groups of many blocks, until the launch is one for these tiles
+        sizes[i] = 2100 - i
+        i += 1
+    off = torch.tensor([0] + sizes).cumsum(0) + 5
+    M = -(-int(off[-1]) // 16) * 16
+    MB = -(-M // 128)
+    gen = torch.Generator(device=DEV).manual_seed(G)
+
+    def operand(rows):
+        v = torch.randint(-4, 5, (rows, M), generator=gen, device=DEV).float()
+        s = 2.0 ** torch.randint(-1, 2, (MB, rows), generator=gen, device=DEV).float()
+        exact = v * s.t().repeat_interleave(128, dim=1)[:, :M]
+        q = v.to(torch.float8_e4m3fn).view(torch.uint8)
+        q[:, off[nan]:off[nan + 1]] = 0x7F
+        q[:, :5] = 0xFF                          # nobody's tokens
+        return q, s, exact
+
+    XT, SX, X = operand(K)
+    DYT, SDY, DY = operand(N)
+    got = gg.grouped_gemm_wgrad(XT, SX, DYT, SDY, off.int().to(DEV), out_bf16=out_bf16)
+    for g in range(G):
+        if g == nan:
+            assert torch.isnan(got[g]).all()
+            continue
+        want = (DY[:, off[g]:off[g + 1]].double() @ X[:, off[g]:off[g + 1]].double().t().contiguous()).float()
+        assert torch.equal(got[g], want.bfloat16() if out_bf16 else want), (g, sizes[g])
