@@ -43,6 +43,7 @@ struct WgradArgs {
   int n_tiles, k_tiles;   // N / 128, K / 256
   int tiles;              // G * n_tiles * k_tiles
   int slots;              // workgroups per XCD when the grid is a multiple of 8, else 0 (plain round-robin)
+  int touch;              // 256 x 256 tiles: the operands are brought into the last-level cache first
   int balanced;           // 256 x 256 tiles: runs of `slots` tiles are dealt to the XCDs by the groups' cost
   int blocked;            // 1: a group's tiles are listed in blocks of 4 k tiles x 8 n tiles (k_tiles % 4 == 0, n_tiles % 8 == 0)
 };

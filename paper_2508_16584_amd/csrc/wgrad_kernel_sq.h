@@ -27,6 +27,35 @@
 
 namespace gg {
 
+// Brings the operands into the last-level cache ahead of their fetches.  Those take 128 bytes of each of 500 rows per token block,
+// a row pitch apart, in the order in which the tiles come up and beside the stores of the gradients: from memory they cost far
+// more than their bytes (8 groups, 8000 tokens, 4096 x 7168, fp32: 360 us with the operands in the cache, 433 without).  Here
+// every wave of the launch fetches 1 KB pieces of single rows (1024 tokens), in the order of the tokens, into 1 KB of LDS that
+// nobody reads: a dozen ahead of its first tile, eight ahead of each tile until all are there.  433 -> 381 us; where the
+// operands are in the cache already, 359 -> 361.
+struct OperandTouch {
+  static constexpr int FIRST = 12, TILE = 8;
+  int row, tok, step, first;
+  __device__ __forceinline__ void init(const WgradArgs& a, int w) {
+    step = 8 * (int)gridDim.x;
+    row = first = 8 * (int)blockIdx.x + w;
+    tok = a.touch ? 0 : a.M_total;
+  }
+  __device__ __forceinline__ bool left(const WgradArgs& a) const { return tok < a.M_total; }
+  // one piece, or none past the last one: the same number of fetches either way
+  __device__ __forceinline__ void piece(const WgradArgs& a, __amdgpu_buffer_rsrc_t dX, __amdgpu_buffer_rsrc_t dY, int l, uint8_t* dump) {
+    const bool y = row >= a.K, in = row < a.K + a.N && left(a);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(y ? dY : dX, GG_LDS_PTR(dump), 16, in && tok + 16 * l < a.M_total ? 16 * l : GG_OOB_OFFSET,
+                                             __builtin_amdgcn_readfirstlane(in ? (row - (y ? a.K : 0)) * a.M_total + tok : 0), 0, 0);
+    if (!left(a)) return;
+    row += step;
+    if (row >= a.K + a.N) {
+      row = first;
+      tok = tok > a.M_total - 1024 ? a.M_total : tok + 1024;
+    }
+  }
+};
+
 struct WgradSqCfg {
   static constexpr int TK = 256, TN = 256, NW = 8, NT = 512;
   // X: two buffers of a token block (the registers are the third); dY^T: a ring of five halves of a block; scales of three blocks
@@ -205,7 +234,8 @@ __global__ void __launch_bounds__(WgradSqCfg::NT) gg_wgrad_sq_kernel(const Wgrad
   constexpr int kNewer = 2 + Cfg::ND1 + Cfg::ND2;
   auto wait_fetched = [&](int stores) __attribute__((always_inline)) {
     if (__builtin_expect(stores < 8, 1)) wait_vmcnt<kNewer>();
-    else if (stores < 32) wait_vmcnt<kNewer + 8>();
+    else if (stores < 16) wait_vmcnt<kNewer + 8>();
+    else if (stores < 32) wait_vmcnt<kNewer + 16>();
     else wait_vmcnt<kNewer + 32>();
   };
 
@@ -231,6 +261,9 @@ __global__ void __launch_bounds__(WgradSqCfg::NT) gg_wgrad_sq_kernel(const Wgrad
     sy[nf & 1] = *(const v4f*)(lds + syRd + ss * Cfg::S_BYTES + nf * 64);
   };
 
+  OperandTouch touch;
+  touch.init(a, w);
+  for (int i = 0; i < OperandTouch::FIRST && touch.left(a); ++i) touch.piece(a, dX, dY, l, lds + Cfg::DUMP_BASE);
   // ---- prologue: blocks 0 and 1
   int cut0 = 0, cut1 = 0;               // of the block that is multiplied and of the next one
   for (int b = 0; b < 2; ++b) {
@@ -261,6 +294,11 @@ __global__ void __launch_bounds__(WgradSqCfg::NT) gg_wgrad_sq_kernel(const Wgrad
   for (int it = 0;; ++it) {
     const Tile cur = tile_at(it);
     if (!cur.valid) break;
+    if (touch.left(a)) {
+#pragma unroll
+      for (int i = 0; i < OperandTouch::TILE; ++i) touch.piece(a, dX, dY, l, lds + Cfg::DUMP_BASE);
+      st_cur += OperandTouch::TILE;       // they count like stores
+    }
     v4f acc[8][4];
 #pragma unroll
     for (int nf = 0; nf < 8; ++nf)

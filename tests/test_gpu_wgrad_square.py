@@ -48,3 +48,20 @@ def test_exact_over_lengths(N, K, G, out_bf16):
             continue
         want = (DY[:, off[g]:off[g + 1]].double() @ X[:, off[g]:off[g + 1]].double().t().contiguous()).float()
         assert torch.equal(got[g], want.bfloat16() if out_bf16 else want), (g, sizes[g])
+
+
+# Operands of 80 MB and more are brought into the last-level cache first: token counts that are and are not whole pieces of
+# 1024, rows that do and do not divide over the waves
+@pytest.mark.parametrize("M,N,K,G", [(8192, 4096, 7168, 8), (9008, 6144, 3328, 10), (15376, 1280, 5120, 28)])
+def test_large_operands(M, N, K, G):
+    assert (N + K) * M >= 80 << 20
+    gen = torch.Generator(device=DEV).manual_seed(M)
+    XT = torch.randint(0, 2, (K, M), generator=gen, device=DEV, dtype=torch.uint8) * 0x38          # 0 and 1
+    DYT = torch.randint(0, 2, (N, M), generator=gen, device=DEV, dtype=torch.uint8) * 0x40         # 0 and 2
+    one = lambda rows: torch.ones((-(-M // 128), rows), device=DEV)
+    off = torch.linspace(0, M, G + 1).int()
+    off[1] -= 77
+    got = gg.grouped_gemm_wgrad(XT, one(K), DYT, one(N), off.to(DEV))
+    X, DY = (XT != 0).float(), (DYT != 0).float() * 2          # products of small integers: exact in float32
+    for g in range(G):
+        assert torch.equal(got[g], DY[:, off[g]:off[g + 1]] @ X[:, off[g]:off[g + 1]].t().contiguous()), g
