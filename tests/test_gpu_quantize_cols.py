@@ -130,3 +130,11 @@ def test_streamed_bytes_equal_the_others():
     got, s_got = gg.quantize_cols(X, src)
     assert got.data_ptr() % 128 == 0 and want.data_ptr() % 128 == 16
     assert torch.equal(got, want) and torch.equal(s_got.view(torch.int32), s_want.view(torch.int32))
+
+
+@pytest.mark.parametrize("tiles", [1, 3, 4, 5, 8, 11])
+@pytest.mark.parametrize("tokens", [16, 128, 400, 2064])
+def test_strips_of_feature_tiles(tiles, tokens):
+    """The tile list runs in strips of four feature tiles: fewer, whole strips, a narrower last one; one token block to seventeen."""
+    rng = np.random.default_rng(100 * tiles + tokens)
+    check(bf16_bits(rng.normal(0, 1, (tokens, 64 * tiles)).astype(np.float32)))
