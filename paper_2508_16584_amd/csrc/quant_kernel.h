@@ -248,11 +248,9 @@ __device__ __forceinline__ q_v4i swiglu8(const q_v4i g_raw, const q_v4i u_raw) {
 // owns tokens 16 p .. 16 p + 15 of features 2 f and 2 f + 1 (one 4-byte LDS read per token): amax over its 16 values
 // per feature and over the eight lanes, 16 bytes out per feature - the eight lanes of a feature write one 128-byte
 // line of XT.
-// Tiles are listed in strips of QC_STRIP feature tiles, a strip's token blocks one after the other: the workgroups at work at one time
-// write neighbouring lines of a few rows of XT (listed by token blocks, lines of all rows, a row pitch apart) and read 512
-// bytes of a token.  16384 tokens out of 8192, 7168 features 73 -> 64 us (3.7 TB/s), with the row quantiser in front of it
-// 128 -> 116; 16384 read once 86 -> 71; 8192 39 -> 37.  Single tiles instead of four 71 and 122 where tokens are read twice, sixteen
-// 76 where they are read once.
+// Tiles are listed token block by token block, or (strips) in strips of QC_STRIP feature tiles, a strip's token blocks one after the
+// other: the workgroups at work at one time then write neighbouring lines of a few rows of XT instead of lines of all rows, a row
+// pitch apart, and read 512 bytes of a token instead of all of it.  Where that pays: see cols_in_strips() in gg_fp8.hip.
 constexpr int QC_FEATS = 64, QC_STRIP = 4;
 constexpr int QC_LDS_BYTES = 128 * 128 + 7 * 32;
 
@@ -261,7 +259,7 @@ template <bool SNT>
 __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint16_t* __restrict__ X,
                                                                      const int32_t* __restrict__ row_src,
                                                                      uint8_t* __restrict__ XT, float* __restrict__ SX,
-                                                                     int64_t T, int M_total, int K, int MB) {
+                                                                     int64_t T, int M_total, int K, int MB, int strips) {
   __shared__ __attribute__((aligned(16))) uint8_t tile[QC_LDS_BYTES];
   const int t = threadIdx.x;
   const int kt = K / QC_FEATS;
@@ -270,11 +268,16 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
   // piece t + 256 i of a tile: token (t + 256 i) / 8 of the block, features 8 (t % 8) .. + 7
   q_v4i raw[4];
   auto place = [&](int64_t id, int& j, int& k0) __attribute__((always_inline)) {      // token block and first feature of a tile
+    if (!strips) {
+      j = (int)(id / kt);
+      k0 = (int)(id - (int64_t)j * kt) * QC_FEATS;
+      return;
+    }
     const int strip = (int)(id / ((int64_t)QC_STRIP * MB));
-    const int64_t in = id - (int64_t)strip * QC_STRIP * MB;
-    const int left = kt - strip * QC_STRIP, width = left < QC_STRIP ? left : QC_STRIP;
-    j = (int)((unsigned)in / (unsigned)width);
-    k0 = (strip * QC_STRIP + (int)((unsigned)in - (unsigned)j * (unsigned)width)) * QC_FEATS;
+    const unsigned in = (unsigned)(id - (int64_t)strip * QC_STRIP * MB);
+    const unsigned width = (unsigned)(kt - strip * QC_STRIP < QC_STRIP ? kt - strip * QC_STRIP : QC_STRIP);
+    j = (int)(in / width);
+    k0 = (strip * QC_STRIP + (int)(in - (unsigned)j * width)) * QC_FEATS;
   };
   auto load_tile = [&](int64_t id) __attribute__((always_inline)) {
     int j, k0;

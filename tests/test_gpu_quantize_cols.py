@@ -132,9 +132,20 @@ def test_streamed_bytes_equal_the_others():
     assert torch.equal(got, want) and torch.equal(s_got.view(torch.int32), s_want.view(torch.int32))
 
 
-@pytest.mark.parametrize("tiles", [1, 3, 4, 5, 8, 11])
-@pytest.mark.parametrize("tokens", [16, 128, 400, 2064])
-def test_strips_of_feature_tiles(tiles, tokens):
-    """The tile list runs in strips of four feature tiles: fewer, whole strips, a narrower last one; one token block to seventeen."""
-    rng = np.random.default_rng(100 * tiles + tokens)
-    check(bf16_bits(rng.normal(0, 1, (tokens, 64 * tiles)).astype(np.float32)))
+@pytest.mark.parametrize("M,K", [(196608, 256), (180224, 320), (65536, 832)])
+def test_strips_of_feature_tiles(M, K):
+    """Large outputs of a repeated gather: the tile list runs in strips of four feature tiles, here one whole strip, one and a narrow
+    one, three and a narrow one.  Sampled token blocks against the oracle, and all of it against the row quantiser."""
+    assert M * K >= 48 << 20
+    rng = np.random.default_rng(K)
+    T = 4096
+    xb = bf16_bits(rng.normal(0, 1, (T, K)).astype(np.float32))
+    X = torch.from_numpy(xb.view(np.int16)).view(torch.bfloat16).to(DEV)
+    src = rng.integers(0, T, M).astype(np.int32)
+    XT, SX = gg.quantize_cols(X, torch.from_numpy(src).to(DEV))
+    for j in (0, 1, M // 256, M // 128 - 1):
+        want, s_want = orc.quantize_cols(xb, src[128 * j:128 * j + 128])
+        assert np.array_equal(XT[:, 128 * j:128 * j + 128].cpu().numpy(), want) and np.array_equal(SX[j:j + 1].cpu().numpy(), s_want)
+    G = X[torch.from_numpy(src).long().to(DEV)].t().contiguous()            # [K, M]: its row blocks are the columns' blocks
+    A, SA = gg.quantize_rows(G)
+    assert torch.equal(A, XT) and torch.equal(SA.t().contiguous(), SX)
