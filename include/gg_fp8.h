@@ -192,6 +192,16 @@ int gg_fp8_grouped_gemm_wgrad_ex(const void* XT, const float* SX, const void* DY
                                  const int32_t* group_offsets, void* dW, int G, int64_t M_total, int N, int K, void* stream,
                                  unsigned flags);
 
+/* How gg_fp8_grouped_gemm_wgrad_ex runs for these arguments on the current device: a sum of GG_WGRAD_ bits, 0 for tiles of
+ * 256 features x 128 rows of dY^T one after the other; or a negated GG_ERR_ for what that call refuses.  Of SX and SDY only
+ * the alignment counts.  The bits of dW are the same either way. */
+enum {
+  GG_WGRAD_SQUARE = 1,        /* tiles of 256 x 256 */
+  GG_WGRAD_AHEAD = 2,         /* ... with the operands brought into the last-level cache first */
+  GG_WGRAD_DEALT = 4          /* ... with the tiles dealt to the workgroups by the groups' lengths */
+};
+int gg_fp8_wgrad_route(const float* SX, const float* SDY, int G, int64_t M_total, int N, int K, unsigned flags);
+
 /* The producer of gg_fp8_grouped_gemm_wgrad's operands: the block quantiser of gg_fp8_quantize_rows (the 1x128
  * scaling stated below Table 1 of the paper) applied ALONG THE TOKENS, with the transpose that call wants.  The paper
  * defines neither the operation nor its layouts (Sec. 4 only names the kernels around the grouped GEMM).

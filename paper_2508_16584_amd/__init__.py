@@ -37,5 +37,6 @@ from .binding import (  # noqa: F401
     swiglu_quantize_rows,
     variant_name,
     version,
+    wgrad_route,
     workspace_bytes,
 )

@@ -212,6 +212,8 @@ def load_library() -> ctypes.CDLL:
     lib.gg_fp8_grouped_gemm_wgrad.restype = i32
     lib.gg_fp8_grouped_gemm_wgrad_ex.argtypes = [vp, vp, vp, vp, vp, vp, i32, i64, i32, i32, vp, ctypes.c_uint]
     lib.gg_fp8_grouped_gemm_wgrad_ex.restype = i32
+    lib.gg_fp8_wgrad_route.argtypes = [vp, vp, i32, i64, i32, i32, ctypes.c_uint]
+    lib.gg_fp8_wgrad_route.restype = i32
     lib.gg_fp8_quantize_cols.argtypes = [vp, vp, vp, vp, i64, i64, i32, vp]
     lib.gg_fp8_quantize_cols.restype = i32
     lib.gg_fp8_pad_ex.argtypes = [vp, vp, vp, vp, vp, vp, i32, i64, i64, i32, vp, ctypes.c_uint]
@@ -275,7 +277,7 @@ EXPORTED_SYMBOLS = [
     "gg_fp8_grouped_gemm_variant", "gg_fp8_grouped_gemm_f16", "gg_fp8_grouped_gemm_ex", "gg_fp8_num_variants", "gg_fp8_variant_name", "gg_fp8_auto_variant", "gg_fp8_auto_variant_padded", "gg_fp8_padded_rows_cap",
     "gg_fp8_pad", "gg_fp8_grouped_gemm_padded", "gg_fp8_unpad", "gg_fp8_quantize_rows", "gg_fp8_swiglu_quantize_rows", "gg_fp8_check_offsets",
     "gg_fp8_grouped_gemm_splitk_noalloc", "gg_fp8_noalloc_max_elements", "gg_fp8_pad_ex", "gg_fp8_quantize_rows_ex", "gg_fp8_swiglu_quantize_rows_ex", "gg_fp8_grouped_gemm_swiglu",
-    "gg_fp8_grouped_gemm_wgrad", "gg_fp8_grouped_gemm_wgrad_ex", "gg_fp8_quantize_cols",
+    "gg_fp8_grouped_gemm_wgrad", "gg_fp8_grouped_gemm_wgrad_ex", "gg_fp8_wgrad_route", "gg_fp8_quantize_cols",
 ]
 
 
@@ -392,6 +394,17 @@ def auto_variant(G: int, M_total: int, N: int, K: int) -> int:
     if v < 0:
         raise ValueError(f"gg_fp8_auto_variant: {status_str(-v)}")
     return v
+
+
+def wgrad_route(G: int, M_total: int, N: int, K: int, out_bf16: bool = False, SX=None, SDY=None):
+    """How grouped_gemm_wgrad runs for these sizes (gg_fp8_wgrad_route), as a set: "square" (tiles of 256 x 256), with it "ahead"
+    (the operands are brought into the last-level cache first) and "dealt" (the tiles are dealt out by the groups' lengths); empty for
+    the narrow tiles.  SX, SDY: the scales, where their alignment is in question."""
+    r = load_library().gg_fp8_wgrad_route(None if SX is None else SX.data_ptr(), None if SDY is None else SDY.data_ptr(), G, M_total, N, K,
+                                          GG_OUT_BF16 if out_bf16 else 0)
+    if r < 0:
+        raise ValueError(f"gg_fp8_wgrad_route: {status_str(-r)}")
+    return {name for bit, name in ((1, "square"), (2, "ahead"), (4, "dealt")) if r & bit}
 
 
 def variant_name(v: int):

@@ -65,3 +65,24 @@ def test_large_operands(M, N, K, G):
     X, DY = (XT != 0).float(), (DYT != 0).float() * 2          # products of small integers: exact in float32
     for g in range(G):
         assert torch.equal(got[g], DY[:, off[g]:off[g + 1]] @ X[:, off[g]:off[g + 1]].t().contiguous()), g
+
+
+def test_scales_that_start_between_two_16_byte_pieces():
+    """They stay with the narrow tiles, which fetch four bytes per lane; the result is the same."""
+    G, M, N, K = 8, 8192, 8192, 7936
+    gen = torch.Generator(device=DEV).manual_seed(1)
+    XT = torch.randint(0, 120, (K, M), generator=gen, device=DEV, dtype=torch.uint8)
+    DYT = torch.randint(0, 120, (N, M), generator=gen, device=DEV, dtype=torch.uint8)
+    off = torch.tensor([0, 1000, 1000, 3000, 4003, 5500, 5501, 7900, M], dtype=torch.int32, device=DEV)
+
+    def scales(rows, first):
+        s = torch.rand((M // 128, rows), generator=torch.Generator(device=DEV).manual_seed(2), device=DEV)
+        flat = torch.empty(s.numel() + first, device=DEV)
+        flat[first:] = s.view(-1)
+        return flat[first:].view(M // 128, rows)
+
+    assert "square" in gg.wgrad_route(G, M, N, K, True, scales(K, 0), scales(N, 0))
+    want = gg.grouped_gemm_wgrad(XT, scales(K, 0), DYT, scales(N, 0), off, out_bf16=True)
+    for a, b in ((1, 0), (0, 3)):
+        assert not gg.wgrad_route(G, M, N, K, True, scales(K, a), scales(N, b))
+        assert torch.equal(gg.grouped_gemm_wgrad(XT, scales(K, a), DYT, scales(N, b), off, out_bf16=True).view(torch.int16), want.view(torch.int16))
