@@ -230,8 +230,13 @@ __global__ void __launch_bounds__(WgradSqCfg::NT) gg_wgrad_sq_kernel(const Wgrad
   // The waits for fetches.  In front of row 3 of block b: half 1 of its dY^T, whose fetches were the last two of block b - 2; in
   // front of row 7: what block b - 1 fetched but for its last two.  Newer are 2 + 2 + 7 fetches either way, and the stores
   // issued since (a wave's loads and stores complete in the order they were issued, see wait_vmcnt; where there are more than
-  // are counted here, the wait is longer than it must be).  At most 62 operations are ever outstanding.
-  constexpr int kNewer = 2 + Cfg::ND1 + Cfg::ND2;
+  // are counted here, the wait is longer than it must be).
+  // The counter holds 63.  Most is outstanding where a tile of one block follows another tile: what that one leaves, pieces of the
+  // operands, the fetches of row 0 and the stores of rows 1 and 2 of the last block.  A tile of blocks leaves kNewer + 24 of the wait
+  // in front of its row 7 and its last 8 stores; a tile without blocks kEmptyWait and its 32.
+  constexpr int kNewer = 2 + Cfg::ND1 + Cfg::ND2, kEmptyWait = 12;
+  static_assert(kNewer + 24 + 8 + OperandTouch::TILE + Cfg::ND1 + 8 <= 63 && kEmptyWait + 32 + OperandTouch::TILE + Cfg::ND1 + 8 <= 63,
+                "more operations in flight than vmcnt counts");
   auto wait_fetched = [&](int stores) __attribute__((always_inline)) {
     if (__builtin_expect(stores < 8, 1)) wait_vmcnt<kNewer>();
     else if (stores < 16) wait_vmcnt<kNewer + 8>();
@@ -404,7 +409,7 @@ __global__ void __launch_bounds__(WgradSqCfg::NT) gg_wgrad_sq_kernel(const Wgrad
       static_for<28, 32>(store);
       st_cur = 8;
     } else {
-      wait_vmcnt<20>();
+      wait_vmcnt<kEmptyWait>();
       static_for<0, 32>(store);
       st_cur = 32;
     }

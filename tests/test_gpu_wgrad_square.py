@@ -14,21 +14,13 @@ DEV = "cuda:0"
 LENGTHS = [1, 0, 16, 15, 127, 128, 129, 400, 512, 513, 0, 900, 3]
 
 
-# runs of tiles dealt by cost: whole ones, a partial one per group; listed in order: more than 64 groups, few token blocks per group
-@pytest.mark.parametrize("N,K,G", [(5120, 4096, 8), (4608, 4352, 9), (1280, 2304, 70), (2048, 2048, 41)])
-@pytest.mark.parametrize("out_bf16", [False, True])
-def test_exact_over_lengths(N, K, G, out_bf16):
-    gen = torch.Generator().manual_seed(N + G)
-    sizes = [LENGTHS[i] for i in torch.randint(0, len(LENGTHS), (G,), generator=gen).tolist()]
-    nan, i = G // 2, 0
-    sizes[nan] = 35
-    while sum(sizes) < 220 * G:                  # groups of many blocks, until the launch is one for these tiles
-        sizes[i] = 2100 - i
-        i += 1
+def check_exact(sizes, nan, N, K, out_bf16, seed):
+    """Groups of these sizes, those of group `nan` NaN; returns how the call ran."""
+    G = len(sizes)
     off = torch.tensor([0] + sizes).cumsum(0) + 5
     M = -(-int(off[-1]) // 16) * 16
     MB = -(-M // 128)
-    gen = torch.Generator(device=DEV).manual_seed(G)
+    gen = torch.Generator(device=DEV).manual_seed(seed)
 
     def operand(rows):
         v = torch.randint(-4, 5, (rows, M), generator=gen, device=DEV).float()
@@ -48,6 +40,31 @@ def test_exact_over_lengths(N, K, G, out_bf16):
             continue
         want = (DY[:, off[g]:off[g + 1]].double() @ X[:, off[g]:off[g + 1]].double().t().contiguous()).float()
         assert torch.equal(got[g], want.bfloat16() if out_bf16 else want), (g, sizes[g])
+    return gg.wgrad_route(G, M, N, K, out_bf16, SX, SDY)
+
+
+# runs of tiles dealt by cost: whole ones, a partial one per group; listed in order: more than 64 groups, few token blocks per group
+@pytest.mark.parametrize("N,K,G", [(5120, 4096, 8), (4608, 4352, 9), (1280, 2304, 70), (2048, 2048, 41)])
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_exact_over_lengths(N, K, G, out_bf16):
+    gen = torch.Generator().manual_seed(N + G)
+    sizes = [LENGTHS[i] for i in torch.randint(0, len(LENGTHS), (G,), generator=gen).tolist()]
+    nan, i = G // 2, 0
+    sizes[nan] = 35
+    while sum(sizes) < 220 * G:                  # groups of many blocks, until the launch is one for these tiles
+        sizes[i] = 2100 - i
+        i += 1
+    check_exact(sizes, nan, N, K, out_bf16, seed=G)
+
+
+# The operands brought in ahead beside tiles of no and of one token block: their fetches are counted with the stores.  Dealt out,
+# and (more than 64 groups) in order.
+@pytest.mark.parametrize("G,long,way", [(24, 2400, {"square", "ahead", "dealt"}), (72, 900, {"square", "ahead"})])
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_operands_ahead_of_short_tiles(G, long, way, out_bf16):
+    sizes = [(0, 0, long, 1, 128, 0, long - 77, 0, 16, 35)[g % 10] for g in range(G)]
+    sizes[0] += 1500
+    assert check_exact(sizes, 19, 3840, 4096, out_bf16, seed=G) == way
 
 
 # Operands of 80 MB and more are brought into the last-level cache first: token counts that are and are not whole pieces of
