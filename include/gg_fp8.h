@@ -216,6 +216,14 @@ int gg_fp8_wgrad_route(const float* SX, const float* SDY, int G, int64_t M_total
 int gg_fp8_quantize_cols(const void* X, const int32_t* row_src, void* XT, float* SX, int64_t T, int64_t M_total, int K,
                          void* stream);
 
+/* How gg_fp8_quantize_cols runs for these arguments: a sum of GG_COLS_ bits, or a negated GG_ERR_ for what that call refuses.  Of
+ * XT only the alignment counts.  Bytes and scales are the same either way. */
+enum {
+  GG_COLS_STREAM = 1,         /* the bytes are written past the caches */
+  GG_COLS_STRIPS = 2          /* tiles in strips of features instead of token block by token block */
+};
+int gg_fp8_quantize_cols_route(const void* XT, int64_t T, int64_t M_total, int K);
+
 /* ---- the pad-then-GEMM comparison path (the baseline of Sec. 3) ------------
  * Every group is copied to an offset that is a multiple of 128 rows, pad rows
  * are zero, the same GEMM kernels run on the aligned problem, and the valid

@@ -16,6 +16,7 @@ from .binding import (  # noqa: F401
     grouped_gemm_swiglu,
     grouped_gemm_wgrad,
     quantize_cols,
+    quantize_cols_route,
     library_path,
     load_library,
     load_probe_library,

@@ -216,6 +216,8 @@ def load_library() -> ctypes.CDLL:
     lib.gg_fp8_wgrad_route.restype = i32
     lib.gg_fp8_quantize_cols.argtypes = [vp, vp, vp, vp, i64, i64, i32, vp]
     lib.gg_fp8_quantize_cols.restype = i32
+    lib.gg_fp8_quantize_cols_route.argtypes = [vp, i64, i64, i32]
+    lib.gg_fp8_quantize_cols_route.restype = i32
     lib.gg_fp8_pad_ex.argtypes = [vp, vp, vp, vp, vp, vp, i32, i64, i64, i32, vp, ctypes.c_uint]
     lib.gg_fp8_pad_ex.restype = i32
     lib.gg_fp8_quantize_rows_ex.argtypes = [vp, vp, vp, vp, i64, i64, i32, vp, ctypes.c_uint]
@@ -277,7 +279,7 @@ EXPORTED_SYMBOLS = [
     "gg_fp8_grouped_gemm_variant", "gg_fp8_grouped_gemm_f16", "gg_fp8_grouped_gemm_ex", "gg_fp8_num_variants", "gg_fp8_variant_name", "gg_fp8_auto_variant", "gg_fp8_auto_variant_padded", "gg_fp8_padded_rows_cap",
     "gg_fp8_pad", "gg_fp8_grouped_gemm_padded", "gg_fp8_unpad", "gg_fp8_quantize_rows", "gg_fp8_swiglu_quantize_rows", "gg_fp8_check_offsets",
     "gg_fp8_grouped_gemm_splitk_noalloc", "gg_fp8_noalloc_max_elements", "gg_fp8_pad_ex", "gg_fp8_quantize_rows_ex", "gg_fp8_swiglu_quantize_rows_ex", "gg_fp8_grouped_gemm_swiglu",
-    "gg_fp8_grouped_gemm_wgrad", "gg_fp8_grouped_gemm_wgrad_ex", "gg_fp8_wgrad_route", "gg_fp8_quantize_cols",
+    "gg_fp8_grouped_gemm_wgrad", "gg_fp8_grouped_gemm_wgrad_ex", "gg_fp8_wgrad_route", "gg_fp8_quantize_cols", "gg_fp8_quantize_cols_route",
 ]
 
 
@@ -405,6 +407,15 @@ def wgrad_route(G: int, M_total: int, N: int, K: int, out_bf16: bool = False, SX
     if r < 0:
         raise ValueError(f"gg_fp8_wgrad_route: {status_str(-r)}")
     return {name for bit, name in ((1, "square"), (2, "ahead"), (4, "dealt")) if r & bit}
+
+
+def quantize_cols_route(T: int, M_total: int, K: int, XT=None):
+    """How quantize_cols runs for these sizes (gg_fp8_quantize_cols_route), as a set of "stream" (the bytes are written past the
+    caches) and "strips" (tiles in strips of features).  XT: the output, where its alignment is in question."""
+    r = load_library().gg_fp8_quantize_cols_route(None if XT is None else XT.data_ptr(), T, M_total, K)
+    if r < 0:
+        raise ValueError(f"gg_fp8_quantize_cols_route: {status_str(-r)}")
+    return {name for bit, name in ((1, "stream"), (2, "strips")) if r & bit}
 
 
 def variant_name(v: int):
