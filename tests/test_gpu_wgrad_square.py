@@ -44,17 +44,19 @@ def check_exact(sizes, nan, N, K, out_bf16, seed):
 
 
 # runs of tiles dealt by cost: whole ones, a partial one per group; listed in order: more than 64 groups, few token blocks per group
-@pytest.mark.parametrize("N,K,G", [(5120, 4096, 8), (4608, 4352, 9), (1280, 2304, 70), (2048, 2048, 41)])
+@pytest.mark.parametrize("N,K,G,mean,way", [(5120, 4096, 8, 1100, {"square", "dealt"}), (4608, 4352, 9, 900, {"square", "dealt"}),
+                                            (2560, 2304, 70, 270, {"square"}), (3840, 3072, 41, 200, {"square"})])
 @pytest.mark.parametrize("out_bf16", [False, True])
-def test_exact_over_lengths(N, K, G, out_bf16):
+def test_exact_over_lengths(N, K, G, mean, way, out_bf16):
     gen = torch.Generator().manual_seed(N + G)
     sizes = [LENGTHS[i] for i in torch.randint(0, len(LENGTHS), (G,), generator=gen).tolist()]
     nan, i = G // 2, 0
     sizes[nan] = 35
-    while sum(sizes) < 220 * G:                  # groups of many blocks, until the launch is one for these tiles
-        sizes[i] = 2100 - i
+    while sum(sizes) < mean * G:                 # groups of many blocks, until the launch is one for these tiles
+        if i != nan:
+            sizes[i] = 2100 - i
         i += 1
-    check_exact(sizes, nan, N, K, out_bf16, seed=G)
+    assert way <= check_exact(sizes, nan, N, K, out_bf16, seed=G)
 
 
 # The operands brought in ahead beside tiles of no and of one token block: their fetches are counted with the stores.  Dealt out,
@@ -69,9 +71,9 @@ def test_operands_ahead_of_short_tiles(G, long, way, out_bf16):
 
 # Operands of 80 MB and more are brought into the last-level cache first: token counts that are and are not whole pieces of
 # 1024, rows that do and do not divide over the waves
-@pytest.mark.parametrize("M,N,K,G", [(8192, 4096, 7168, 8), (9008, 6144, 3328, 10), (15376, 1280, 5120, 28)])
+@pytest.mark.parametrize("M,N,K,G", [(8192, 4096, 7168, 8), (9008, 6144, 3328, 10), (15376, 2560, 5120, 28)])
 def test_large_operands(M, N, K, G):
-    assert (N + K) * M >= 80 << 20
+    assert gg.wgrad_route(G, M, N, K) == {"square", "ahead", "dealt"}
     gen = torch.Generator(device=DEV).manual_seed(M)
     XT = torch.randint(0, 2, (K, M), generator=gen, device=DEV, dtype=torch.uint8) * 0x38          # 0 and 1
     DYT = torch.randint(0, 2, (N, M), generator=gen, device=DEV, dtype=torch.uint8) * 0x40         # 0 and 2

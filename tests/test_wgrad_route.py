@@ -17,6 +17,20 @@ def test_scales_between_two_16_byte_pieces_stay_with_the_narrow_tiles(out_bf16):
         assert not gg.wgrad_route(G, M, N, K, out_bf16, flat, flat[first:])
 
 
+# Random problems with the measured times (us) of the narrow and the square tiles: skewed groups in few rounds over the workgroups, or
+# groups so short that the stores bound them; then even or long ones.
+@pytest.mark.parametrize("G,M,N,K,out_bf16,narrow,square", [
+    (214, 28208, 768, 1280, True, 165.1, 213.6), (23, 7552, 4608, 1792, True, 136.5, 169.5), (101, 24000, 2304, 768, True, 165.6, 205.3),
+    (182, 27072, 2048, 512, True, 149.4, 175.9), (125, 28112, 1792, 768, False, 174.1, 204.1), (4, 960, 8192, 8192, False, 211.9, 246.9),
+    (8, 1680, 8192, 8192, False, 427.9, 498.5), (43, 12976, 2560, 1792, True, 170.5, 198.2), (127, 32688, 1280, 1280, False, 225.6, 260.1),
+    (45, 12992, 768, 5120, True, 145.0, 166.0), (26, 11408, 4864, 1536, False, 225.6, 241.9),
+    (99, 20992, 1024, 4864, False, 592.0, 411.3), (55, 31168, 3328, 2048, False, 645.5, 500.4), (17, 28432, 2816, 3584, True, 479.4, 406.7),
+    (17, 12048, 1792, 7424, False, 424.4, 331.9), (4, 6768, 8192, 6144, True, 535.3, 437.8), (202, 28432, 1280, 4608, True, 913.3, 767.5),
+    (13, 13744, 3328, 6400, False, 647.1, 538.2), (37, 19312, 4096, 4096, False, 963.0, 812.7)])
+def test_tiles_where_measured_times_say_which(G, M, N, K, out_bf16, narrow, square):
+    assert ("square" in gg.wgrad_route(G, M, N, K, out_bf16)) == (square < narrow)
+
+
 def test_what_the_call_refuses_has_no_route():
     for G, M, N, K in [(-1, 16, 256, 256), (4, 17, 256, 256), (4, 16, 200, 256), (4, 16, 256, 128), (4, 1 << 24, 256, 256), (4, 16, 256, 1 << 21)]:
         with pytest.raises(ValueError):
