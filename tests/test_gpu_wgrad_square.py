@@ -71,7 +71,8 @@ def test_operands_ahead_of_short_tiles(G, long, way, out_bf16):
 
 # Operands of 80 MB and more are brought into the last-level cache first: token counts that are and are not whole pieces of
 # 1024, rows that do and do not divide over the waves
-@pytest.mark.parametrize("M,N,K,G", [(8192, 4096, 7168, 8), (9008, 6144, 3328, 10), (15376, 2560, 5120, 28)])
+@pytest.mark.parametrize("M,N,K,G", [(8192, 4096, 7168, 8), (9008, 6144, 3328, 10), (15376, 2560, 5120, 28),
+                                     (16384, 7168, 2048, 32)])
 def test_large_operands(M, N, K, G):
     assert gg.wgrad_route(G, M, N, K) == {"square", "ahead", "dealt"}
     gen = torch.Generator(device=DEV).manual_seed(M)

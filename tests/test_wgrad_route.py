@@ -31,6 +31,18 @@ def test_tiles_where_measured_times_say_which(G, M, N, K, out_bf16, narrow, squa
     assert ("square" in gg.wgrad_route(G, M, N, K, out_bf16)) == (square < narrow)
 
 
+# Operands of 140 to 192 MB with the measured times (us) of the square tiles without and with the operands brought in ahead
+@pytest.mark.parametrize("G,M,N,K,out_bf16,plain,ahead", [
+    (17, 28432, 2816, 3584, True, 393.2, 406.7), (10, 16000, 2304, 7424, True, 431.2, 449.4), (9, 21744, 2560, 6656, False, 548.6, 577.8),
+    (18, 22544, 1536, 5632, True, 312.3, 334.5), (19, 24112, 6400, 1536, False, 412.8, 423.4), (26, 18016, 1280, 7680, False, 396.5, 408.1),
+    (23, 26240, 2816, 2816, False, 336.5, 348.7), (19, 23040, 1792, 5632, False, 365.3, 378.7),
+    (110, 30480, 4096, 1024, False, 675.1, 596.0), (191, 29968, 768, 4608, False, 683.1, 610.5), (109, 23312, 5888, 2048, True, 1096.5, 983.9),
+    (93, 29680, 1280, 5376, False, 786.1, 720.9), (76, 27104, 5888, 1280, False, 714.0, 658.8)])
+def test_operands_ahead_where_measured_times_say_so(G, M, N, K, out_bf16, plain, ahead):
+    way = gg.wgrad_route(G, M, N, K, out_bf16)
+    assert "square" in way and ("ahead" in way) == (ahead < plain)
+
+
 def test_what_the_call_refuses_has_no_route():
     for G, M, N, K in [(-1, 16, 256, 256), (4, 17, 256, 256), (4, 16, 200, 256), (4, 16, 256, 128), (4, 1 << 24, 256, 256), (4, 16, 256, 1 << 21)]:
         with pytest.raises(ValueError):
