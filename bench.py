@@ -220,6 +220,12 @@ def bench_quantize_rows(args, cfg, dev):
     print(json.dumps(out))
 
 
+def wgrad_kernel(G, M, N, K, bf16, SX=None, SDY=None):
+    """Name of the kernel that the weight-gradient call launches for these arguments."""
+    import paper_2508_16584_amd as gg
+    return "gg_wgrad_sq_kernel" if "square" in gg.wgrad_route(G, M, N, K, bf16, SX, SDY) else "gg_wgrad_kernel"
+
+
 def bench_wgrad(args, cfg, dev):
     """wgrad: the variable-K grouped GEMM of training on the workload's layer (gg_fp8_grouped_gemm_wgrad):
     XT [K, M_total], DYT [N, M_total] e4m3 with one scale per row and block of 128 tokens -> dW [G, N, K] fp32, the
@@ -267,7 +273,8 @@ def bench_wgrad(args, cfg, dev):
     ms_per_step, kern_avg_ms = timed_region(step, args.steps)
     kern_ms = per_launch_ms(step, args.steps)
     achieved = alg_bytes / (kern_avg_ms * 1e-3) / 1e9
-    wg_traffic = profiled_traffic("wgrad", args.workload, args.wgrad_out, "gg_wgrad_kernel")
+    kernel = wgrad_kernel(G, M, N, K, bf16, SX, SDY)
+    wg_traffic = profiled_traffic("wgrad", args.workload, args.wgrad_out, kernel)
     out = {
         "metric": "FP8 TFLOP/s on the tokens of the groups, variable-K grouped GEMM dW^g = dY^g^T X^g (e4m3 operands scaled per "
                   "128 tokens, fp32 accumulate, " + ("bf16" if bf16 else "fp32") + " out)",
@@ -279,7 +286,7 @@ def bench_wgrad(args, cfg, dev):
                    "clock_warmup_launches": n_ramp},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": wg_traffic,
-                     "traffic_source": TRAFFIC_SOURCE if wg_traffic is not None else None, "kernel": "gg_wgrad_kernel",
+                     "traffic_source": TRAFFIC_SOURCE if wg_traffic is not None else None, "kernel": kernel,
                      "kernel_avg_ms": round(kern_avg_ms, 4), "kernel_median_ms": round(float(np.median(kern_ms)), 4),
                      "kernel_min_ms": round(float(kern_ms.min()), 4), "algorithmic_bytes": int(alg_bytes),
                      "mfma_frac_of_fp8_peak": round(flops / (kern_avg_ms * 1e-3) / 1e12 / FP8_MFMA_PEAK_TFLOPS, 4)},
@@ -465,12 +472,12 @@ def bench_kstep_parts():
 
 
 def bench_wgrad_parts():
-    """The weight-gradient kernel with parts of a token block's work left out (gg_probe_wgrad_parts), on gate_up's
-    layer with 8 equal groups of 1000 tokens (8 blocks each, the first and the last of them cut by a group boundary)
+    """The narrow weight-gradient kernel (tiles of 256 x 128) with parts of a token block's work left out (gg_probe_wgrad_parts), on
+    gate_up's layer, which itself takes the square tiles, with 8 equal groups of 1000 tokens (8 blocks each, the first and the last of them cut by a group boundary)
     and on a store-bound layer (32 groups of 48 tokens, same N and K).  One JSON line; microseconds per launch; the
     ideal is the matrix pipe's time for the same blocks at the nominal clock."""
     import paper_2508_16584_amd as gg
-    parts = [(0, "nothing left out (the kernel as launched)"), (2, "no stores"), (1, "no fetches"),
+    parts = [(0, "nothing left out"), (2, "no stores"), (1, "no fetches"),
              (3, "neither (arithmetic, LDS reads, barrier, masks)"), (7, "the same without the barrier"),
              (11, "neither fetches nor stores, no byte masks"), (19, "neither fetches nor stores, no LDS reads"),
              (31, "matrix instructions and FMAs alone")]

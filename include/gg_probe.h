@@ -86,7 +86,7 @@ int gg_probe_lds_fetch(int pattern, int depth, int reps, double* gbytes_per_s_ou
  * higher clock): for cycles run the same call under `rocprofv3 --pmc GRBM_GUI_ACTIVE`. */
 int gg_probe_gemm_kstep(int tile_rows, int left_out, int groups, int rows_per_group, int n, int k, int reps, double* us_out);
 
-/* The weight-gradient kernel of libgg_fp8 (gg_fp8_grouped_gemm_wgrad: the variable-K grouped GEMM of training, which
+/* The narrow weight-gradient kernel of libgg_fp8 (tiles of 256 x 128; gg_fp8_grouped_gemm_wgrad: the variable-K grouped GEMM of training, which
  * the paper's title names and its text does not define) in measurement builds that LEAVE OUT parts of a token block's
  * work, on a problem this call makes itself: `groups` equal groups of `tokens_per_group` tokens (any count: a group
  * whose ends fall inside a 128-token block has masked first and last blocks), dW [groups, n, k] fp32 (n % 128 == 0,
@@ -94,7 +94,7 @@ int gg_probe_gemm_kstep(int tile_rows, int left_out, int groups, int rows_per_gr
  * scales.
  *   left_out:  sum of 1 the fetches of the token blocks, 2 the stores of dW, 4 the barrier of a block, 8 the byte
  *              masks of a group's first and last block, 16 the LDS reads that refill the operand registers.
- *              Built: 0 (the kernel as the library launches it), 1, 2, 3, 7, 11, 19, 31 (matrix instructions and
+ *              Built: 0 (the kernel of the library's calls that gg_fp8_wgrad_route gives 0 for), 1, 2, 3, 7, 11, 19, 31 (matrix instructions and
  *              FMAs only).  Anything else: hipErrorInvalidValue.  Only accesses, waits and masks are removed, so every
  *              remaining access stays in bounds; the OUTPUT IS MEANINGLESS for every value but 0.
  *   reps:      timed launches (launches of the same build for about 150 ms precede them: the sustained clock)

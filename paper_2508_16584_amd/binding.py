@@ -169,7 +169,7 @@ def probe_gemm_kstep(tile_rows: int, left_out: int, groups: int = 8, rows_per_gr
 
 def probe_wgrad_parts(left_out: int, groups: int = 8, tokens_per_group: int = 1000, n: int = 4096, k: int = 7168,
                       reps: int = 20) -> float:
-    """Microseconds per launch of the weight-gradient kernel with parts of a block's work left out (gg_probe_wgrad_parts)."""
+    """Microseconds per launch of the narrow weight-gradient kernel with parts of a block's work left out (gg_probe_wgrad_parts)."""
     return _probe_call(load_probe_library().gg_probe_wgrad_parts, left_out, groups, tokens_per_group, n, k, reps)
 
 

@@ -1,8 +1,11 @@
 """How the weight-gradient call runs (gg_fp8_wgrad_route), as far as it must not depend on sizes that were measured."""
+import numpy as np
 import pytest
 import torch
 
+import bench
 import paper_2508_16584_amd as gg
+from workloads import CONFIGS, group_sizes
 
 
 @pytest.mark.parametrize("out_bf16", [False, True])
@@ -41,6 +44,13 @@ def test_tiles_where_measured_times_say_which(G, M, N, K, out_bf16, narrow, squa
 def test_operands_ahead_where_measured_times_say_so(G, M, N, K, out_bf16, plain, ahead):
     way = gg.wgrad_route(G, M, N, K, out_bf16)
     assert "square" in way and ("ahead" in way) == (ahead < plain)
+
+
+@pytest.mark.parametrize("workload,kernel", [("gate_up", "gg_wgrad_sq_kernel"), ("down", "gg_wgrad_sq_kernel"), ("decode", "gg_wgrad_kernel")])
+@pytest.mark.parametrize("out_bf16", [False, True])
+def test_the_benchmark_names_the_kernel_that_runs(workload, kernel, out_bf16):
+    c = CONFIGS[workload]
+    assert bench.wgrad_kernel(c.G, int(np.sum(group_sizes(c, c.seed))), c.N, c.K, out_bf16) == kernel
 
 
 def test_what_the_call_refuses_has_no_route():
