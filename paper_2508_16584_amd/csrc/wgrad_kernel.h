@@ -40,7 +40,7 @@ struct WgradArgs {
   const int32_t* off;   // [G + 1]
   float* dW;            // [G, N, K] fp32, or bfloat16 in the OUT16 instantiation
   int G, M_total, N, K, MB;
-  int n_tiles, k_tiles;   // N / 128, K / 256
+  int n_tiles, k_tiles;   // N / 128 (256 x 256 tiles: N / 256), K / 256
   int tiles;              // G * n_tiles * k_tiles
   int slots;              // workgroups per XCD when the grid is a multiple of 8, else 0 (plain round-robin)
   int touch;              // 256 x 256 tiles: the operands are brought into the last-level cache first

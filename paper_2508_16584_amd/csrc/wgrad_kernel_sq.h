@@ -19,9 +19,10 @@
 // stores per wave wait for the block's end (8 groups of 1000 tokens, 4096 x 7168, fp32: 348 -> 340 us).
 //
 // What bounds it: 8 vector instructions per matrix instruction (45 cycles for 32 of the matrix pipe, in a register-only loop: 175 us
-// on those 8 groups; with LDS reads and barriers 225), stores (70) and fetches (55) that hide only in part.
-// Against the 256 x 128 tiles, inputs rotated through 276 MB: 8 groups, 8192 tokens, 4096 x 7168, fp32 451 -> 404 us, bfloat16
-// 374 -> 337; one group of 8192, 8192 x 8192 618 -> 586.
+// on those 8 groups; with LDS reads and barriers 225), stores (70) and fetches (55) that hide only in part (development builds
+// with parts left out, which are not kept).  237 vector registers; 37 scalar ones are spilled into lanes of vector registers.
+// Against the 256 x 128 tiles, inputs rotated through 276 MB: 8 groups, 8192 tokens, 4096 x 7168, fp32 451 -> 404 us, 389 with the
+// operands brought in ahead, bfloat16 374 -> 337; one group of 8192, 8192 x 8192 618 -> 586.
 #pragma once
 #include "wgrad_kernel.h"
 

@@ -87,6 +87,26 @@ def test_large_operands(M, N, K, G):
         assert torch.equal(got[g], DY[:, off[g]:off[g + 1]] @ X[:, off[g]:off[g + 1]].t().contiguous()), g
 
 
+# Offsets past the ends and out of order, as the header promises: clamped, a group that ends before it starts has no tokens
+@pytest.mark.parametrize("N,K,way", [(5120, 4096, {"square", "dealt"}), (8192, 2048, {"square"})])
+def test_bad_offsets_are_clamped(N, K, way):
+    bad = [-50, 1000, 900, 3000, 3001, 20000, 5000, 8000, 8990, 30000, 12000]
+    M, G = 12000, len(bad) - 1
+    if "dealt" not in way:
+        bad, G = bad + [M] * 20, G + 20                # whole rounds per group: nothing to deal
+    assert way <= gg.wgrad_route(G, M, N, K)
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    XT = torch.randint(0, 2, (K, M), generator=gen, device=DEV, dtype=torch.uint8) * 0x38          # 0 and 1
+    DYT = torch.randint(0, 2, (N, M), generator=gen, device=DEV, dtype=torch.uint8) * 0x40         # 0 and 2
+    one = lambda rows: torch.ones((-(-M // 128), rows), device=DEV)
+    got = gg.grouped_gemm_wgrad(XT, one(K), DYT, one(N), torch.tensor(bad, dtype=torch.int32, device=DEV))
+    X, DY = (XT != 0).float(), (DYT != 0).float() * 2
+    for g in range(G):
+        lo = min(max(bad[g], 0), M)
+        hi = min(max(bad[g + 1], lo), M)
+        assert torch.equal(got[g], DY[:, lo:hi] @ X[:, lo:hi].t().contiguous()), g
+
+
 def test_scales_that_start_between_two_16_byte_pieces():
     """They stay with the narrow tiles, which fetch four bytes per lane; the result is the same."""
     G, M, N, K = 8, 8192, 8192, 7936
