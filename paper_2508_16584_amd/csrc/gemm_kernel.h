@@ -248,23 +248,31 @@ __device__ __forceinline__ int swz_key_b(int row) {   // rows read: base + 8*(r/
 struct GroupIndex {
   static constexpr int NONE = 0x7FFFFFFF;      // a work unit that does not exist
   unsigned pre[4];
+  int row0[4], n[4];    // first row and rows of the groups
   int g, base;          // the walk behind the first 256 groups: groups before g hold `base` tiles
   int full, rem_run;    // full rounds over the workgroups; tiles per XCD of the last one
 
   __device__ __forceinline__ static unsigned add_sat(unsigned x, unsigned y) { return __builtin_elementwise_add_sat(x, y); }
 
-  // rows of group group0 + l
-  __device__ __forceinline__ static int rows64(const GemmArgs& a, int group0, int l) {
+  // rows of group group0 + l, and the first of them
+  __device__ __forceinline__ static int rows64(const GemmArgs& a, int group0, int l, int& row0) {
     const int g0 = group0 + l < a.G ? group0 + l : a.G, g1 = g0 + 1 < a.G ? g0 + 1 : a.G;
-    const int row0 = clampi(a.off[g0], 0, a.M_total);
+    row0 = clampi(a.off[g0], 0, a.M_total);
     return clampi(a.off[g1], row0, a.M_total) - row0;
+  }
+  __device__ __forceinline__ static int rows64(const GemmArgs& a, int group0, int l) {
+    int row0;
+    return rows64(a, group0, l, row0);
   }
   // ... of the first 256 groups, for a kernel that looks at them before it knows its tile height
   struct Rows {
-    int r[4];
+    int r[4], row0[4];
     __device__ __forceinline__ void load(const GemmArgs& a, int l) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) r[c] = 64 * c < a.G ? rows64(a, 64 * c, l) : 0;
+      for (int c = 0; c < 4; ++c) {
+        r[c] = row0[c] = 0;
+        if (64 * c < a.G) r[c] = rows64(a, 64 * c, l, row0[c]);
+      }
     }
   };
 
@@ -290,6 +298,8 @@ struct GroupIndex {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       pre[c] = before;
+      row0[c] = rows.row0[c];
+      n[c] = rows.r[c];
       if (64 * c < a.G) {
         pre[c] = add_sat(scan64(a, BM, rows.r[c]), before);
         before = (unsigned)__builtin_amdgcn_readlane((int)pre[c], 63);
@@ -312,17 +322,24 @@ struct GroupIndex {
     return it == full && i < rem_run ? full * (int)gridDim.x + xcd * rem_run + i : NONE;
   }
 
-  // The group of tile T and the tiles before that group, false when there is no such tile.  T never decreases.
+  // The group of tile T, its rows and the tiles before it, false when there is no such tile.  T never decreases.
+  // The rows come out of the registers too: fetched again from the offsets, they are one more memory latency in front of a
+  // workgroup's first fetch and behind every tile.
   // (readfirstlane states the uniformity for the compiler, which otherwise loops over descriptors at every fetch.)
-  __device__ __forceinline__ bool find(const GemmArgs& a, int BM, int T, int& group, int& tiles_before) {
-    int gr = -1, tb = 0;
-    locate(a, BM, T, gr, tb);
-    group = __builtin_amdgcn_readfirstlane(gr);
-    tiles_before = __builtin_amdgcn_readfirstlane(tb);
-    return group >= 0;
+  struct Group {
+    int g, tiles_before, row0, rows;
+  };
+  __device__ __forceinline__ bool find(const GemmArgs& a, int BM, int T, Group& out) {
+    Group f = {-1, 0, 0, 0};
+    locate(a, BM, T, f);
+    out.g = __builtin_amdgcn_readfirstlane(f.g);
+    out.tiles_before = __builtin_amdgcn_readfirstlane(f.tiles_before);
+    out.row0 = __builtin_amdgcn_readfirstlane(f.row0);
+    out.rows = __builtin_amdgcn_readfirstlane(f.rows);
+    return out.g >= 0;
   }
 
-  __device__ __forceinline__ void locate(const GemmArgs& a, int BM, int T, int& group, int& tiles_before) {
+  __device__ __forceinline__ void locate(const GemmArgs& a, int BM, int T, Group& f) {
     int before = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -330,19 +347,22 @@ struct GroupIndex {
       const uint64_t past = __builtin_amdgcn_ballot_w64(pre[c] > (unsigned)T);
       if (past) {
         const int lane = __builtin_ctzll(past);
-        group = 64 * c + lane;
-        tiles_before = lane ? __builtin_amdgcn_readlane((int)pre[c], lane - 1) : before;
+        f.g = 64 * c + lane;
+        f.tiles_before = lane ? __builtin_amdgcn_readlane((int)pre[c], lane - 1) : before;
+        f.row0 = __builtin_amdgcn_readlane(row0[c], lane);
+        f.rows = __builtin_amdgcn_readlane(n[c], lane);
         return;
       }
       before = __builtin_amdgcn_readlane((int)pre[c], 63);
     }
     const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
     for (; g < a.G; ++g) {
-      const int row0 = clampi(offc[g], 0, a.M_total);
-      const int cnt = row_tiles(clampi(offc[g + 1], row0, a.M_total) - row0, BM) * a.n_tiles;
+      f.row0 = clampi(offc[g], 0, a.M_total);
+      f.rows = clampi(offc[g + 1], f.row0, a.M_total) - f.row0;
+      const int cnt = row_tiles(f.rows, BM) * a.n_tiles;
       if (T < base + cnt) {
-        group = g;
-        tiles_before = base;
+        f.g = g;
+        f.tiles_before = base;
         return;
       }
       base += cnt;
@@ -473,10 +493,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
       T >>= 1;
     }
 
-    int g = 0, base = 0;
-    if (!groups.find(a, BM, T, g, base)) return t;
-    const int row0 = clampi(offc[g], 0, a.M_total);
-    const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
+    GroupIndex::Group grp;
+    if (!groups.find(a, BM, T, grp)) return t;
+    const int g = grp.g, base = grp.tiles_before, row0 = clampi(offc[g], 0, a.M_total), Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
     const int mtiles = row_tiles(Mg, BM);
     // order inside a group: chunks of n_chunk n-tiles; inside a chunk m-tile major, n-tile minor
     const int local = T - base;

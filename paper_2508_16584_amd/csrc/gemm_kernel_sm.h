@@ -87,15 +87,13 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::WG_PER_CU) gg_gemm_sm_kernel(con
   };
   GroupIndex groups;
   groups.init(a, BM, l, true);
-  const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
   auto tile_at = [&](int it, GroupIndex& walk) __attribute__((always_inline)) -> Tile {
     Tile t = {false, 0, 0, 0, 0};
     const int T = walk.unit(a, it);
     if (T == GroupIndex::NONE) return t;
-    int g = 0, base = 0;
-    if (!walk.find(a, BM, T, g, base)) return t;
-    const int row0 = clampi(offc[g], 0, a.M_total);
-    const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
+    GroupIndex::Group grp;
+    if (!walk.find(a, BM, T, grp)) return t;
+    const int g = grp.g, base = grp.tiles_before, row0 = grp.row0, Mg = grp.rows;
     const int mtiles = row_tiles(Mg, BM);
     const int local = T - base;
     const int per_chunk = mtiles * a.n_chunk;
