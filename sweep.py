@@ -31,12 +31,13 @@ import numpy as np
 # ---- the automatic choice between the kernels: random problems, every kernel's time, the estimates' constants ----------------
 # What the choice is made between: the second and the fourth kernel with the height they choose themselves (numbers that only the
 # library built by --build-fit takes), 128 x 128, the small tiles.  Beside them, the heights that those two choose between.
-RB, PC = 26, 27
-CHOICES = {RB: "second kernel", PC: "fourth kernel", 2: "128x128", 23: "32x64", 24: "32x128", 25: "64x128"}
-HEIGHTS = {RB: {12: 256, 15: 224, 14: 192, 16: 128}, PC: {28: 32, 29: 64, 30: 96, 31: 128, 32: 160}}
-# rows and columns of a tile, KB of weights that a workgroup has on their way, workgroups per compute unit, as in csrc/gg_fp8.hip
-SMALL_TILES = {23: (32, 64, 24, 4), 24: (32, 128, 32, 3), 25: (64, 128, 32, 2)}
-FUSED_TILES = {14: (192, 256, 72, 1), 15: (224, 256, 72, 1), 12: (256, 256, 72, 1), 24: (32, 256, 96, 1), 25: (64, 256, 64, 1)}
+RB, PC = 29, 30
+CHOICES = {RB: "second kernel", PC: "fourth kernel", 2: "128x128", 23: "32x64", 24: "32x128", 25: "64x128", 26: "16x16/8k", 27: "16x32/4k", 28: "16x32/4ko"}
+HEIGHTS = {RB: {12: 256, 15: 224, 14: 192, 16: 128}, PC: {31: 32, 32: 64, 33: 96, 34: 128, 35: 160}}
+# rows and columns of a tile, KB of weights that a workgroup has on their way, workgroups per compute unit, waves that the K blocks
+# are dealt to, as in csrc/gg_fp8.hip
+SMALL_TILES = {23: (32, 64, 24, 4, 1), 24: (32, 128, 32, 3, 1), 25: (64, 128, 32, 2, 1), 26: (16, 16, 32, 1, 8), 27: (16, 32, 32, 2, 4), 28: (16, 32, 32, 3, 4)}
+FUSED_TILES = {14: (192, 256, 72, 1, 1), 15: (224, 256, 72, 1, 1), 12: (256, 256, 72, 1, 1), 24: (32, 256, 96, 1, 1), 25: (64, 256, 64, 1, 1)}
 
 
 def fit_library():
@@ -251,7 +252,7 @@ def fit_tiles(paths):
     choice_summary(paths)
     if not fused:
         fit_large(rows)
-    for v, (BM, BN, kb_in_flight, per_cu) in (FUSED_TILES if fused else SMALL_TILES).items():
+    for v, (BM, BN, kb_in_flight, per_cu, waves) in (FUSED_TILES if fused else SMALL_TILES).items():
         f, t = [], []
         for r in rows:
             if v not in r["us"]:
@@ -261,7 +262,7 @@ def fit_tiles(paths):
             tiles = max(groups, M / BM + 0.5 * groups) * -(-N // BN)
             weights = groups * N * K
             d = weights / (min(tiles, 256 * per_cu) * kb_in_flight * 1024) * (1.6 if weights > 64e6 else 0.7)
-            f.append((tiles, -(-K // 128), (weights + M * (K + (0.5 if fused else 2) * N)) / 6.8e6, d))
+            f.append((tiles, -(-K // (128 * waves)), (weights + M * (K + (0.5 if fused else 2) * N)) / 6.8e6, d))
             t.append(r["us"][v])
         tiles, kb, c, d = np.array(f).T
         t = np.array(t)

@@ -40,3 +40,9 @@ def test_ragged_n_that_a_256_wide_tile_would_mostly_waste(G, M, N, K, small, nar
 def test_padded_problems_go_by_the_rows_that_their_groups_are_expected_to_hold(G, M, N, K):
     cap = gg.padded_rows_cap(G, M)
     assert gg.auto_variant_padded(G, cap, N, K) == gg.auto_variant(G, cap - 64 * G, N, K)
+
+
+@pytest.mark.parametrize("G,M,N,K,third,fifth", [(1, 16, 5888, 4224, 22.0, 8.5), (4, 65, 640, 5120, 14.5, 6.5), (37, 1, 1280, 7808, 19.1, 7.3), (13, 2, 768, 2176, 8.6, 4.3)])
+def test_chains_of_k_blocks_on_few_tiles(G, M, N, K, third, fifth):
+    """... and here those of the third and the fifth kernel."""
+    assert fifth < 0.7 * third and gg.variant_name(gg.auto_variant(G, M, N, K)) in ("16x16/8x1w/3s", "16x32/4x1w/3s", "16x32/4x1w/2s")

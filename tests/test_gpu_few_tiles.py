@@ -1,0 +1,78 @@
+"""The fifth kernel (K blocks dealt to the waves of a workgroup) where it can go wrong: numbers of K blocks around what a round of
+its waves, one slot and both slots take, rows around its tiles, ragged N and K (which only the automatic choice runs on it), a
+K loop that does not start at block 0, both orders of the scales, both outputs, more groups than one lookup holds."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2508_16584_amd as gg
+from gg_testlib import assert_parity, bits_of
+from oracle import gg_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TILES = ("16x16/8x1w/3s", "16x32/4x1w/3s", "16x32/4x1w/2s")
+FIRST = 2                                  # 128 x 128 tile of the first kernel: any shape
+
+
+def problem(sizes, N, K, seed):
+    rng = np.random.default_rng(seed)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    M, G, KB, NB = int(off[-1]), len(sizes), -(-K // 128), -(-N // 128)
+    A = rng.integers(0, 0x70, (M, K), dtype=np.uint8) | (rng.integers(0, 2, (M, K), dtype=np.uint8) << 7)
+    B = rng.integers(0, 0x48, (G, N, K), dtype=np.uint8) | (rng.integers(0, 2, (G, N, K), dtype=np.uint8) << 7)
+    SA = rng.uniform(0.5, 2.0, (M, KB)).astype(np.float32)
+    SB = rng.uniform(0.5, 2.0, (G, NB, KB)).astype(np.float32)
+    return A, SA, B, SB, off
+
+
+def check(sizes, N, K, seed, tiles=TILES):
+    host = problem(sizes, N, K, seed)
+    dA, dSA, dB, dSB, doff = (torch.from_numpy(x).to(DEV) for x in host)
+    want = gg.grouped_gemm(dA, dSA, dB, dSB, doff, variant=FIRST)
+    assert_parity(bits_of(want), orc.grouped_gemm(*host, with_abs_sum=True), empirical=False, what=f"{sizes} N={N} K={K}")
+    SAk = dSA.t().contiguous()
+    for v in [-1] + [u for u in range(gg.num_variants()) if gg.variant_name(u) in tiles]:
+        for scales, km in ((dSA, False), (SAk, True)):
+            C = torch.full((want.shape[0] + 2, N), 0x7FC1, dtype=torch.int16, device=DEV).view(torch.bfloat16)
+            gg.grouped_gemm(dA, scales, dB, dSB, doff, C=C[:-2], variant=v, sa_kmajor=km)
+            assert torch.equal(C[:-2].view(torch.int16), want.view(torch.int16)), (v, km)
+            assert (C[-2:].view(torch.int16) == 0x7FC1).all(), "wrote past the last row"
+    h = gg.grouped_gemm(dA, dSA, dB, dSB, doff, out_dtype=torch.float16)
+    assert torch.equal(h.view(torch.int16), gg.grouped_gemm(dA, dSA, dB, dSB, doff, variant=FIRST, out_dtype=torch.float16).view(torch.int16))
+
+
+@pytest.mark.parametrize("blocks", [1, 3, 4, 5, 7, 8, 9, 12, 13, 16, 17, 24, 25, 33])
+def test_k_blocks_around_rounds_and_slots(blocks):
+    assert gg.variant_name(gg.auto_variant(5, 36, 256, 128 * blocks)) in TILES
+    check([1, 15, 0, 3, 17], 256, 128 * blocks, blocks)
+
+
+@pytest.mark.parametrize("sizes", [[1], [16], [17], [33, 1], [0, 15, 0, 16, 1]])
+def test_rows_around_tiles(sizes):
+    check(sizes, 384, 640, sum(sizes))
+
+
+@pytest.mark.parametrize("N,K", [(8, 512), (264, 512), (280, 1040), (256, 16), (136, 2000), (504, 400)])
+def test_ragged_shapes_of_the_automatic_choice(N, K):
+    check([5, 0, 20, 2], N, K, N + K, tiles=())
+
+
+def test_rotated_k_loop():
+    check([3, 18], 768, 4096, 1)
+
+
+def test_more_groups_than_one_lookup_holds():
+    sizes = [0] * 300
+    for g in (0, 63, 64, 200, 255, 256, 270, 299):
+        sizes[g] = 1 + g % 3
+    check(sizes, 256, 384, 2)
+
+
+def test_ragged_shapes_are_refused_by_name():
+    dev = tuple(torch.from_numpy(x).to(DEV) for x in problem([4, 2], 264, 400, 3))
+    for v in [u for u in range(gg.num_variants()) if gg.variant_name(u) in TILES]:
+        with pytest.raises(gg.GGError) as e:
+            gg.grouped_gemm(*dev, variant=v)
+        assert e.value.status == 3
+    assert gg.variant_name(gg.auto_variant(2, 6, 264, 400)) not in TILES        # ... and not named by the choice
