@@ -160,6 +160,10 @@ size_t gg_fp8_noalloc_max_elements(void);
 int gg_fp8_grouped_gemm_swiglu(const void* A, const float* SA, const void* B, const float* SB,
                                const int32_t* group_offsets, void* A2, float* SA2, void* act_out,
                                int G, int64_t M_total, int I, int K, void* stream, int variant, unsigned flags);
+/* How a program that can hold the bf16 intermediate [M_total, 2 I] gets the same bytes, scales and activations fastest: 0 with
+ * gg_fp8_grouped_gemm_swiglu (automatic choice), 1 with gg_fp8_grouped_gemm_ex into the intermediate and
+ * gg_fp8_swiglu_quantize_rows_ex behind it.  A negative status for sizes that the fused call refuses. */
+int gg_fp8_swiglu_route(int G, int64_t M_total, int I, int K, unsigned flags);
 
 /* The variable-K grouped GEMM of training: the weight gradient dW^g = dY^g^T X^g of the expert layer whose forward
  * pass gg_fp8_grouped_gemm computes, the contraction running over the tokens of each group, with no group padded

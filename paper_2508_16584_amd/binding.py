@@ -207,6 +207,8 @@ def load_library() -> ctypes.CDLL:
     lib.gg_fp8_noalloc_max_elements.argtypes = []
     lib.gg_fp8_noalloc_max_elements.restype = sz
     lib.gg_fp8_grouped_gemm_swiglu.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i32, i64, i32, i32, vp, i32, ctypes.c_uint]
+    lib.gg_fp8_swiglu_route.restype = i32
+    lib.gg_fp8_swiglu_route.argtypes = [i32, i64, i32, i32, ctypes.c_uint]
     lib.gg_fp8_grouped_gemm_swiglu.restype = i32
     lib.gg_fp8_grouped_gemm_wgrad.argtypes = [vp, vp, vp, vp, vp, vp, i32, i64, i32, i32, vp]
     lib.gg_fp8_grouped_gemm_wgrad.restype = i32
@@ -267,7 +269,7 @@ def _load_calls(lib) -> None:
         loader.exec_module(calls)
         calls.bind(*(ctypes.cast(fn, ctypes.c_void_p).value for fn in (
             lib.gg_fp8_grouped_gemm_ex, lib.gg_fp8_grouped_gemm_swiglu, lib.gg_fp8_grouped_gemm_wgrad_ex,
-            lib.gg_fp8_quantize_rows_ex, lib.gg_fp8_quantize_cols, lib.gg_fp8_swiglu_quantize_rows_ex)), _check)
+            lib.gg_fp8_quantize_rows_ex, lib.gg_fp8_quantize_cols, lib.gg_fp8_swiglu_quantize_rows_ex, lib.gg_fp8_swiglu_route)), _check)
     except (ImportError, AttributeError, TypeError) as e:         # built for another torch of this version, or from another source
         warnings.warn(f"the binding's native calls are not used: {e}")
         return
@@ -278,7 +280,7 @@ EXPORTED_SYMBOLS = [
     "gg_fp8_version", "gg_fp8_status_str", "gg_fp8_workspace_bytes", "gg_fp8_workspace_bytes_variant", "gg_fp8_grouped_gemm",
     "gg_fp8_grouped_gemm_variant", "gg_fp8_grouped_gemm_f16", "gg_fp8_grouped_gemm_ex", "gg_fp8_num_variants", "gg_fp8_variant_name", "gg_fp8_auto_variant", "gg_fp8_auto_variant_padded", "gg_fp8_padded_rows_cap",
     "gg_fp8_pad", "gg_fp8_grouped_gemm_padded", "gg_fp8_unpad", "gg_fp8_quantize_rows", "gg_fp8_swiglu_quantize_rows", "gg_fp8_check_offsets",
-    "gg_fp8_grouped_gemm_splitk_noalloc", "gg_fp8_noalloc_max_elements", "gg_fp8_pad_ex", "gg_fp8_quantize_rows_ex", "gg_fp8_swiglu_quantize_rows_ex", "gg_fp8_grouped_gemm_swiglu",
+    "gg_fp8_grouped_gemm_splitk_noalloc", "gg_fp8_noalloc_max_elements", "gg_fp8_pad_ex", "gg_fp8_quantize_rows_ex", "gg_fp8_swiglu_quantize_rows_ex", "gg_fp8_grouped_gemm_swiglu", "gg_fp8_swiglu_route",
     "gg_fp8_grouped_gemm_wgrad", "gg_fp8_grouped_gemm_wgrad_ex", "gg_fp8_wgrad_route", "gg_fp8_quantize_cols", "gg_fp8_quantize_cols_route",
 ]
 
@@ -509,7 +511,8 @@ def noalloc_max_elements() -> int:
 def grouped_gemm_swiglu(A, SA, B, SB, group_offsets, A2=None, SA2=None, act_out=None, want_act=False, variant: int = -1,
                         stream=None, sa_kmajor=False):
     """gg_fp8_grouped_gemm_swiglu: the grouped GEMM with B [G, 2I, K] (gate rows, then up rows), silu(gate) * up and
-    the 1x128 quantiser in one kernel: returns (A2 uint8 [M_total, I], SA2 float32 [M_total, I/128] or
+    the 1x128 quantiser in one kernel (with fresh outputs in two, where gg_fp8_swiglu_route says that this is faster: the same
+    bytes, through an intermediate of at most 64 MB): returns (A2 uint8 [M_total, I], SA2 float32 [M_total, I/128] or
     [I/128, M_total] with sa_kmajor, act bf16 [M_total, I] or None)."""
     if _calls is not None and A2 is None and SA2 is None and act_out is None and variant == -1 and stream is None:
         out = _calls.grouped_gemm_swiglu(A, SA, B, SB, group_offsets, want_act, sa_kmajor)
@@ -520,6 +523,9 @@ def grouped_gemm_swiglu(A, SA, B, SB, group_offsets, A2=None, SA2=None, act_out=
     if N % 2:
         raise ValueError("B must hold an even number of rows per group (gate | up)")
     inter = N // 2
+    if variant == -1 and stream is None and A2 is None and SA2 is None and act_out is None and \
+            lib.gg_fp8_swiglu_route(G, M_total, inter, K, GG_SA_KMAJOR if sa_kmajor else 0) == 1:
+        return swiglu_quantize_rows(grouped_gemm(A, SA, B, SB, group_offsets, sa_kmajor=sa_kmajor), want_act=want_act, sa_kmajor=sa_kmajor)
     a_shape, sa_shape = (M_total, inter), (inter // 128, M_total) if sa_kmajor else (M_total, inter // 128)
     A2 = _output(A2, "A2", torch.uint8, a_shape, A)
     SA2 = _output(SA2, "SA2", torch.float32, sa_shape, A)

@@ -29,6 +29,7 @@ struct Library {
   decltype(&gg_fp8_quantize_rows_ex) quantize_rows;
   decltype(&gg_fp8_quantize_cols) quantize_cols;
   decltype(&gg_fp8_swiglu_quantize_rows_ex) swiglu_quantize_rows;
+  decltype(&gg_fp8_swiglu_route) swiglu_route;      // null: always the fused call
 } lib;
 PyObject* check;      // the binding's function that raises the exception of a status
 
@@ -165,8 +166,19 @@ PyObject* grouped_gemm_swiglu(PyObject*, PyObject* const* args, Py_ssize_t n) {
     at::Tensor A2 = fresh({g.M, inter}, at::kByte, g.A), act;
     at::Tensor SA2 = km ? fresh({inter / 128, g.M}, at::kFloat, g.A) : fresh({g.M, inter / 128}, at::kFloat, g.A);
     if (want_act) act = fresh({g.M, inter}, at::kBFloat16, g.A);
+    const unsigned order = km ? GG_SA_KMAJOR : 0;
+    if (lib.swiglu_route && lib.swiglu_route((int)g.G, g.M, (int)inter, (int)g.K, order) == 1) {
+      // two launches, one after the other on the current stream, which is the intermediate's own
+      at::Tensor H = fresh({g.M, g.N}, at::kBFloat16, g.A);
+      if (!call(lib.gemm, g.A->data_ptr(), data<float>(g.SA), g.B->data_ptr(), data<float>(g.SB), data<int32_t>(g.off), H.data_ptr(), (int)g.G, g.M, (int)g.N,
+                (int)g.K, nullptr, 0, current_stream(), -1, order) ||
+          !call(lib.swiglu_quantize_rows, H.data_ptr(), A2.data_ptr(), data<float>(SA2), want_act ? act.data_ptr() : nullptr, g.M, (int)inter,
+                current_stream(), order))
+        return nullptr;
+      return pair(A2, SA2, want_act ? &act : nullptr, true);
+    }
     if (!call(lib.gemm_swiglu, g.A->data_ptr(), data<float>(g.SA), g.B->data_ptr(), data<float>(g.SB), data<int32_t>(g.off), A2.data_ptr(), data<float>(SA2),
-                        want_act ? act.data_ptr() : nullptr, (int)g.G, g.M, (int)inter, (int)g.K, current_stream(), -1, km ? GG_SA_KMAJOR : 0))
+                        want_act ? act.data_ptr() : nullptr, (int)g.G, g.M, (int)inter, (int)g.K, current_stream(), -1, order))
       return nullptr;
     return pair(A2, SA2, want_act ? &act : nullptr, true);
   });
@@ -253,28 +265,29 @@ PyObject* swiglu_quantize_rows(PyObject*, PyObject* const* args, Py_ssize_t n) {
   });
 }
 
-// (addresses of the six functions, in the order of Library; the function for `check`)
+// (addresses of the functions, in the order of Library, the last one may be missing; the function for `check`)
 PyObject* bind(PyObject*, PyObject* const* args, Py_ssize_t n) {
-  void* p[6];
-  if (n != 7 || !PyCallable_Check(args[6])) {
-    PyErr_SetString(PyExc_TypeError, "six addresses and a function");
+  void* p[7] = {};
+  if (n < 7 || n > 8 || !PyCallable_Check(args[n - 1])) {
+    PyErr_SetString(PyExc_TypeError, "six or seven addresses and a function");
     return nullptr;
   }
-  for (int i = 0; i < 6; ++i) {
+  for (int i = 0; i < n - 1; ++i) {
     p[i] = PyLong_AsVoidPtr(args[i]);
     if (PyErr_Occurred()) return nullptr;
   }
   // A forked child may not use the GPU that its parent has used: torch says so, in the binding's own code.
   static const int forked = pthread_atfork(nullptr, nullptr, [] { lib = {}; });
   if (forked) Py_RETURN_NONE;
-  Py_INCREF(args[6]);
-  Py_XSETREF(check, args[6]);
+  Py_INCREF(args[n - 1]);
+  Py_XSETREF(check, args[n - 1]);
   lib.gemm = reinterpret_cast<decltype(lib.gemm)>(p[0]);
   lib.gemm_swiglu = reinterpret_cast<decltype(lib.gemm_swiglu)>(p[1]);
   lib.wgrad = reinterpret_cast<decltype(lib.wgrad)>(p[2]);
   lib.quantize_rows = reinterpret_cast<decltype(lib.quantize_rows)>(p[3]);
   lib.quantize_cols = reinterpret_cast<decltype(lib.quantize_cols)>(p[4]);
   lib.swiglu_quantize_rows = reinterpret_cast<decltype(lib.swiglu_quantize_rows)>(p[5]);
+  lib.swiglu_route = reinterpret_cast<decltype(lib.swiglu_route)>(p[6]);
   Py_RETURN_NONE;
 }
 

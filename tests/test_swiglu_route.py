@@ -1,0 +1,70 @@
+"""gg_fp8_swiglu_route: which fused calls run as two launches, and that the two give the bytes of the one."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2508_16584_amd as gg
+from paper_2508_16584_amd import binding
+
+DEV = "cuda:0"
+
+
+def route(G, M, I, K, flags=0):
+    return gg.load_library().gg_fp8_swiglu_route(G, M, I, K, flags)
+
+
+def test_sizes():
+    assert route(37, 1, 640, 7808) == 1 and route(8, 64, 512, 2048) == 1            # few tiles of 256 weight rows
+    assert route(8, 8192, 2048, 7168) == 0                                         # 64 MB of intermediate, and as fast in one
+    assert route(1, 1 << 20, 2048, 7168) == 0                                      # 8 GB
+    assert route(4, 3, 256, 4096) == 0 and route(4, 3, 256, 4096 + 8192) == 0      # K loops that begin elsewhere in the plain GEMM
+    assert route(0, 0, 256, 512) == 0 and route(3, 0, 256, 512) == 0
+    lib = gg.load_library()                                                        # what the fused call refuses
+    for G, M, I, K, flags in [(4, 8, 64, 512, 0), (4, 8, 256, 256, 0), (4, 8, 256, 400, 0), (4, 8, 256, 512, 1), (-1, 8, 256, 512, 0), (4, 8, 1 << 20, 1 << 20, 0)]:
+        null = ctypes.c_void_p()
+        assert route(G, M, I, K, flags) == -lib.gg_fp8_grouped_gemm_swiglu(*[null] * 8, G, M, I, K, null, -1, flags) < 0
+
+
+def problem(sizes, I, K, seed):
+    rng = np.random.default_rng(seed)
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    M, G = int(off[-1]), len(sizes)
+    A = rng.integers(0, 0x50, (M, K), dtype=np.uint8) | (rng.integers(0, 2, (M, K), dtype=np.uint8) << 7)
+    B = rng.integers(0, 0x30, (G, 2 * I, K), dtype=np.uint8) | (rng.integers(0, 2, (G, 2 * I, K), dtype=np.uint8) << 7)
+    SA = rng.uniform(0.5, 2.0, (M, K // 128)).astype(np.float32)
+    SB = rng.uniform(0.5, 2.0, (G, 2 * I // 128, K // 128)).astype(np.float32)
+    return [torch.from_numpy(x).to(DEV) for x in (A, SA, B, SB, off)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("sizes,I,K", [([1], 128, 384), ([0, 3, 17, 1], 640, 1152), ([5, 40], 256, 2176), ([30] * 8, 384, 512)])
+@pytest.mark.parametrize("km", [False, True])
+@pytest.mark.parametrize("native", [True, False])
+def test_two_launches_give_the_bytes_of_the_fused_kernel(sizes, I, K, km, native, monkeypatch):
+    dev = problem(sizes, I, K, K)
+    if km:
+        dev[1] = dev[1].t().contiguous()
+    one = next(v for v in range(gg.num_variants()) if gg.variant_name(v) == "32x128/1x4w/3s")
+    want = gg.grouped_gemm_swiglu(*dev, want_act=True, sa_kmajor=km, variant=one)
+    if not native:
+        monkeypatch.setattr(binding, "_calls", None)
+    assert route(len(sizes), sum(sizes), I, K, 2 if km else 0) == 1
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        runs = [gg.grouped_gemm_swiglu(*dev, want_act=True, sa_kmajor=km) for _ in range(4)]
+        runs.append((*gg.grouped_gemm_swiglu(*dev, sa_kmajor=km)[:2], want[2]))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = gg.grouped_gemm_swiglu(*dev, want_act=True, sa_kmajor=km)
+    for _ in range(3):
+        for t in captured:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        runs.append(tuple(t.clone() for t in captured))
+    for A2, SA2, act in runs:
+        assert torch.equal(A2, want[0]) and torch.equal(SA2, want[1]) and torch.equal(act.view(torch.int16), want[2].view(torch.int16))
