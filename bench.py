@@ -223,7 +223,8 @@ def bench_quantize_rows(args, cfg, dev):
 def wgrad_kernel(G, M, N, K, bf16, SX=None, SDY=None):
     """Name of the kernel that the weight-gradient call launches for these arguments."""
     import paper_2508_16584_amd as gg
-    return "gg_wgrad_sq_kernel" if "square" in gg.wgrad_route(G, M, N, K, bf16, SX, SDY) else "gg_wgrad_kernel"
+    way = gg.wgrad_route(G, M, N, K, bf16, SX, SDY)
+    return "gg_wgrad_sq_kernel" if "square" in way else "gg_wgrad_kp_kernel" if "chain" in way else "gg_wgrad_kernel"
 
 
 def bench_wgrad(args, cfg, dev):

@@ -46,6 +46,15 @@ def test_operands_ahead_where_measured_times_say_so(G, M, N, K, out_bf16, plain,
     assert "square" in way and ("ahead" in way) == (ahead < plain)
 
 
+# Few outputs that meet many tokens, and others: measured times (us) of the narrow tiles and of those with the blocks dealt to the waves
+@pytest.mark.parametrize("G,M,N,K,out_bf16,narrow,chain", [
+    (2, 11472, 256, 768, False, 96.2, 25.9), (1, 944, 1280, 512, False, 24.1, 6.9), (5, 272, 768, 256, False, 11.7, 4.1), (1, 5520, 896, 1024, True, 90.8, 25.5),
+    (2, 2288, 896, 3584, True, 28.8, 42.5), (20, 2288, 640, 512, True, 13.7, 20.2), (220, 64, 384, 512, False, 36.5, 55.2), (7, 112, 256, 2048, True, 6.6, 10.1),
+    (5, 1264, 768, 1280, False, 14.7, 17.8)])
+def test_blocks_dealt_to_waves_where_measured_times_say_so(G, M, N, K, out_bf16, narrow, chain):
+    assert ("chain" in gg.wgrad_route(G, M, N, K, out_bf16)) == (chain < narrow)
+
+
 @pytest.mark.parametrize("workload,kernel", [("gate_up", "gg_wgrad_sq_kernel"), ("down", "gg_wgrad_sq_kernel"), ("decode", "gg_wgrad_kernel")])
 @pytest.mark.parametrize("out_bf16", [False, True])
 def test_the_benchmark_names_the_kernel_that_runs(workload, kernel, out_bf16):
