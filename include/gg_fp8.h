@@ -203,7 +203,8 @@ enum {
   GG_WGRAD_SQUARE = 1,        /* tiles of 256 x 256 */
   GG_WGRAD_AHEAD = 2,         /* ... with the operands brought into the last-level cache first */
   GG_WGRAD_DEALT = 4,         /* ... with the tiles dealt to the workgroups by the groups' lengths */
-  GG_WGRAD_CHAIN = 8          /* tiles of 64 x 64, the token blocks dealt to the waves of a workgroup */
+  GG_WGRAD_CHAIN = 8,         /* tiles of 64 x 64, the token blocks dealt to the waves of a workgroup */
+  GG_WGRAD_HALF = 16          /* tiles of 128 x 128, two workgroups per compute unit */
 };
 int gg_fp8_wgrad_route(const float* SX, const float* SDY, int G, int64_t M_total, int N, int K, unsigned flags);
 

@@ -403,12 +403,13 @@ def auto_variant(G: int, M_total: int, N: int, K: int) -> int:
 def wgrad_route(G: int, M_total: int, N: int, K: int, out_bf16: bool = False, SX=None, SDY=None):
     """How grouped_gemm_wgrad runs for these sizes (gg_fp8_wgrad_route), as a set: "square" (tiles of 256 x 256), with it "ahead"
     (the operands are brought into the last-level cache first) and "dealt" (the tiles are dealt out by the groups' lengths); "chain" (tiles
-    of 64 x 64, the token blocks dealt to the waves of a workgroup); empty for the narrow tiles.  SX, SDY: the scales, where their alignment is in question."""
+    of 64 x 64, the token blocks dealt to the waves of a workgroup); "half" (tiles of 128 x 128, two workgroups per compute unit); empty for the narrow tiles.
+    SX, SDY: the scales, where their alignment is in question."""
     r = load_library().gg_fp8_wgrad_route(None if SX is None else SX.data_ptr(), None if SDY is None else SDY.data_ptr(), G, M_total, N, K,
                                           GG_OUT_BF16 if out_bf16 else 0)
     if r < 0:
         raise ValueError(f"gg_fp8_wgrad_route: {status_str(-r)}")
-    return {name for bit, name in ((1, "square"), (2, "ahead"), (4, "dealt"), (8, "chain")) if r & bit}
+    return {name for bit, name in ((1, "square"), (2, "ahead"), (4, "dealt"), (8, "chain"), (16, "half")) if r & bit}
 
 
 def quantize_cols_route(T: int, M_total: int, K: int, XT=None):

@@ -17,7 +17,7 @@
 // like every other block) and the bytes of tokens outside the group are cleared in registers, in BOTH operands, so
 // that a neighbouring group's bytes (NaN codes included) never reach a product.  A group without tokens gives zeros.
 //
-// Structure: persistent workgroups (8 waves, 4 along k x 2 along n) walk the output tiles of 256 features x 128
+// Structure (with the whole tile; the halved one: WgradHalfCfg): persistent workgroups (8 waves, 4 along k x 2 along n) walk the output tiles of 256 features x 128
 // rows of dY^T; per token block the two operand tiles and their scales go global -> LDS by DMA into a ring of 3
 // buffers, swizzled like the forward kernels' tiles, and the fetch stream runs three blocks ahead of the arithmetic
 // across tile boundaries (a group of 1000 tokens is 8 blocks: without that, every tile would start with an empty
@@ -40,7 +40,7 @@ struct WgradArgs {
   const int32_t* off;   // [G + 1]
   float* dW;            // [G, N, K] fp32, or bfloat16 in the OUT16 instantiation
   int G, M_total, N, K, MB;
-  int n_tiles, k_tiles;   // N / 128 (256 x 256 tiles: N / 256), K / 256
+  int n_tiles, k_tiles;   // N and K in the form's tiles
   int tiles;              // G * n_tiles * k_tiles
   int slots;              // workgroups per XCD when the grid is a multiple of 8, else 0 (plain round-robin)
   int touch;              // 256 x 256 tiles: the operands are brought into the last-level cache first
@@ -51,15 +51,26 @@ struct WgradArgs {
 // cache policy bits of a buffer store: sc0 | nt | sc1
 constexpr int kStoreStreaming = 1 | 2 | 16;
 
-struct WgradCfg {
-  static constexpr int TK = 256, TN = 128, NW = 8, NT = 512, S = 3;
+template <int TK_, int S_>
+struct WgradTile {
+  static constexpr int TK = TK_, TN = 128, NW = TK / 32, NT = 64 * NW, S = S_;
   static constexpr int X_BYTES = TK * 128, Y_BYTES = TN * 128, SX_BYTES = TK * 4, SY_BYTES = TN * 4, DUMP_BYTES = 256;
   static constexpr int STAGE_BYTES = X_BYTES + Y_BYTES + SX_BYTES + SY_BYTES + DUMP_BYTES;
   static constexpr int LDS_BYTES = S * STAGE_BYTES;
   static constexpr int X_ITERS = TK / 8 / NW, Y_ITERS = TN / 8 / NW;   // 8-row slabs per wave
   static constexpr int NDMA = X_ITERS + Y_ITERS + 1;                   // per wave and token block, scale fetch included
-  static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
+  static constexpr int WG_PER_CU = 8 / NW;
+  static __host__ __device__ constexpr int x_step(int i) { return NW == 8 ? 64 * i : 64 * (i >> 1) + 2 * (i & 1); }      // features from a slot to the one 8 NW i on
+  static_assert((NW == 8 || NW == 4) && (S == 3 || S == 2) && NDMA <= 9, "waves of 64 x 64; a fetch in every second slot of a block");
+  static_assert(WG_PER_CU * LDS_BYTES <= 160 * 1024, "LDS budget");
 };
+using WgradCfg = WgradTile<256, 3>;
+// Half a tile in a workgroup of four waves, two of them per compute unit, each with a ring of two buffers (two rings of three are
+// 200 KB): what one has stopped for (stores, fetches, the barrier) the other works through, and few outputs are twice as many tiles.
+// Measured, us, whole and halved: 5 groups, 1264 tokens, 768 x 1280 (150 whole tiles) 14.6, 11.6; one of 336, 512 x 4864 14.0, 7.1;
+// two of 4272, 1792 x 768 73.4, 43.1.  Where the chip is full they ask for 1.33 times the operand bytes: two groups, 5184 tokens,
+// 5888 x 4864 (seven rounds) 203.9, 232.2.
+using WgradHalfCfg = WgradTile<128, 2>;
 
 // The 32 operand bytes of a lane are bytes [32 q, 32 q + 32) of a 128-token block; dword d of the fragment holds
 // tokens 32 q + 4 d .. + 3.  x4 = 4 * (bound - first token of the dword): the number of the dword's bytes below the
@@ -86,9 +97,9 @@ enum : int { kWgNoFetch = 1, kWgNoStore = 2, kWgNoBarrier = 4, kWgNoMask = 8, kW
 constexpr int kWgEarlySteps = 4;
 
 // OUT16: dW is bfloat16 (round to nearest even), half the output bytes.
-template <int TIMING, bool OUT16 = false>
-__global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs a) {
-  using Cfg = WgradCfg;
+template <int TIMING, bool OUT16 = false, class Cfg = WgradCfg>
+__global__ void __launch_bounds__(Cfg::NT, 2) gg_wgrad_kernel(const WgradArgs a) {
+  constexpr int NW = Cfg::NW, S = Cfg::S;
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -145,19 +156,20 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   const __amdgpu_buffer_rsrc_t dSX = __builtin_amdgcn_make_buffer_rsrc((void*)a.SX, 0, a.K * a.MB * 4, GG_RSRC_FLAGS);
   const __amdgpu_buffer_rsrc_t dSY = __builtin_amdgcn_make_buffer_rsrc((void*)a.SDY, 0, a.N * a.MB * 4, GG_RSRC_FLAGS);
   const int lrow = l >> 3, pch = l & 7;
-  const int slab_row = w * 8 + lrow;                               // + 64 i
-  const int vRow = slab_row * M + ((pch ^ swz_key_a(slab_row)) << 4);   // key(row + 64 i) == key(row)
+  const int slab_row = w * 8 + lrow;                               // + 8 NW i
+  const int vRow = slab_row * M + ((pch ^ swz_key_a(slab_row)) << 4);   // key(row + 8 NW i) == key(row)
   // Features change places on the way into LDS: slot 16 f + r of a wave's 64 features (fragment f, row r) holds
   // feature 4 r + f, so that the lane of row r has four neighbouring features in the accumulators of the four
   // fragments and the 16 lanes of an output row write its 64 features with one store of 16 (bfloat16: 8) bytes each.
   auto feature_of_slot = [](int s) { return 64 * (s >> 6) + 4 * (s & 15) + ((s >> 4) & 3); };
   const int vRowX = feature_of_slot(slab_row) * M + ((pch ^ swz_key_a(slab_row)) << 4);
-  // scale fetch, one per wave: waves 0..3 the scales of 64 features each, waves 4, 5 those of 64 dY^T rows each,
-  // waves 6, 7 an out-of-range offset into a dump area (every wave issues the same number of fetches)
-  const bool sx_wave = w < 4, sy_wave = w == 4 || w == 5;
-  const int vS = sx_wave ? (w * 64 + feature_of_slot(l)) * 4 : sy_wave ? ((w - 4) * 64 + l) * 4 : GG_OOB_OFFSET;
+  // scale fetch, one per wave: waves 0 .. SXW - 1 the scales of 64 features each, the two after them those of 64 dY^T rows each,
+  // any others an out-of-range offset into a dump area (every wave issues the same number of fetches)
+  constexpr int SXW = Cfg::TK / 64;
+  const bool sx_wave = w < SXW, sy_wave = w == SXW || w == SXW + 1;
+  const int vS = sx_wave ? (w * 64 + feature_of_slot(l)) * 4 : sy_wave ? ((w - SXW) * 64 + l) * 4 : GG_OOB_OFFSET;
   const int s_pitch = sx_wave ? a.K * 4 : a.N * 4;                 // bytes from one token block's scales to the next
-  const int ldsS = Cfg::X_BYTES + Cfg::Y_BYTES + (sx_wave ? w * 256 : sy_wave ? Cfg::SX_BYTES + (w - 4) * 256 : Cfg::SX_BYTES + Cfg::SY_BYTES);
+  const int ldsS = Cfg::X_BYTES + Cfg::Y_BYTES + (sx_wave ? w * 256 : sy_wave ? Cfg::SX_BYTES + (w - SXW) * 256 : Cfg::SX_BYTES + Cfg::SY_BYTES);
 
   // The fetch stream runs three token blocks ahead of the arithmetic and on from tile to tile: F is the tile whose
   // block sF comes next (tiles without tokens have nothing to fetch and are passed over), so the first blocks of a
@@ -191,11 +203,11 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
     if constexpr (I == 0) {
       __builtin_amdgcn_raw_ptr_buffer_load_lds(sx_wave ? dSX : dSY, GG_LDS_PTR(st + ldsS), 4, vSsel, f_s_off, 0, 0);
     } else if constexpr (I <= Cfg::X_ITERS) {
-      constexpr int i = I - 1;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(dX, GG_LDS_PTR(st + (w + i * 8) * 1024), 16, vXsel, f_x_off + i * 64 * M, 0, 0);
+      constexpr int i = I - 1, ahead = Cfg::x_step(i);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(dX, GG_LDS_PTR(st + (w + i * NW) * 1024), 16, vXsel, f_x_off + ahead * M, 0, 0);
     } else {
       constexpr int i = I - 1 - Cfg::X_ITERS;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(dY, GG_LDS_PTR(st + Cfg::X_BYTES + (w + i * 8) * 1024), 16, vYsel, f_y_off + i * 64 * M, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(dY, GG_LDS_PTR(st + Cfg::X_BYTES + (w + i * NW) * 1024), 16, vYsel, f_y_off + i * 8 * NW * M, 0, 0);
     }
   };
   auto fetch_next = [&](int stage) __attribute__((always_inline)) {     // all of a block at once (the prologue)
@@ -305,8 +317,8 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   // landed and is being read into them, blocks b + 2 and b + 3 are in flight (b + 3 into the buffer block b came from)
   fetch_next(0);
   fetch_next(1);
-  fetch_next(2);
-  wait_vmcnt<2 * Cfg::NDMA>();
+  if constexpr (S == 3) fetch_next(2);
+  wait_vmcnt<(S - 1) * Cfg::NDMA>();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
@@ -326,16 +338,18 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
   // behind it the awaited fetch cannot be among them).
   auto top = [&]() __attribute__((always_inline)) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    const int newer = st_prev + st_late2;     // stores behind the awaited fetches
-    if (newer < 8) wait_vmcnt<Cfg::NDMA>();
-    else if (newer < 16) wait_vmcnt<Cfg::NDMA + 8>();
-    else if (newer < 32) wait_vmcnt<Cfg::NDMA + 16>();
-    else wait_vmcnt<Cfg::NDMA + 32>();
+    // (ring of two buffers: those fetches were issued in the last step, and only stores behind that step's are newer)
+    constexpr int kNewer = (S - 2) * Cfg::NDMA;
+    const int newer = S == 3 ? st_prev + st_late2 : st_late;     // stores behind the awaited fetches
+    if (newer < 8) wait_vmcnt<kNewer>();
+    else if (newer < 16) wait_vmcnt<kNewer + 8>();
+    else if (newer < 32) wait_vmcnt<kNewer + 16>();
+    else wait_vmcnt<kNewer + 32>();
     st_late2 = st_late;
     st_prev = st_late = 0;
     if constexpr (!(TIMING & kWgNoBarrier)) __builtin_amdgcn_s_barrier();       // ... and everybody's; nobody reads the buffer of the coming block any more
     asm volatile("" ::: "memory");
-    if constexpr (!(TIMING & kWgNoFetch)) fetch_prepare();                    // three steps ahead, into that buffer
+    if constexpr (!(TIMING & kWgNoFetch)) fetch_prepare();                    // S steps ahead, into that buffer
   };
   for (int it = 0;; ++it) {
     const Tile cur = tile_at(it);
@@ -368,7 +382,7 @@ __global__ void __launch_bounds__(WgradCfg::NT) gg_wgrad_kernel(const WgradArgs 
     };
     auto step = [&](auto lastc, int s) __attribute__((always_inline)) {
       top();
-      const int next_stage = stage == 2 ? 0 : stage + 1;
+      const int next_stage = stage == S - 1 ? 0 : stage + 1;
       block(lastc, (cur.j0 + s) * 128, cur.lo, cur.hi, lds + next_stage * Cfg::STAGE_BYTES, lds + stage * Cfg::STAGE_BYTES, acc, store);
       stage = next_stage;
     };

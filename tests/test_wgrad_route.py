@@ -55,6 +55,15 @@ def test_blocks_dealt_to_waves_where_measured_times_say_so(G, M, N, K, out_bf16,
     assert ("chain" in gg.wgrad_route(G, M, N, K, out_bf16)) == (chain < narrow)
 
 
+# Narrow tiles, whole and halved: measured times (us)
+@pytest.mark.parametrize("G,M,N,K,out_bf16,whole,half", [
+    (19, 400, 256, 512, True, 7.6, 5.8), (7, 160, 256, 2048, False, 8.3, 6.4), (2, 5120, 640, 2304, True, 47.5, 42.3), (24, 384, 768, 256, True, 7.6, 6.7),
+    (2, 992, 1280, 2816, False, 20.4, 16.1), (7, 272, 640, 3840, True, 15.9, 13.7), (2, 6880, 8064, 1024, True, 78.3, 91.1),
+    (2, 5184, 5888, 4864, True, 203.9, 232.2), (14, 2128, 256, 3584, True, 20.6, 22.1), (96, 64, 384, 3328, True, 48.7, 53.3)])
+def test_halved_tiles_where_measured_times_say_so(G, M, N, K, out_bf16, whole, half):
+    assert ("half" in gg.wgrad_route(G, M, N, K, out_bf16)) == (half < whole)
+
+
 @pytest.mark.parametrize("workload,kernel", [("gate_up", "gg_wgrad_sq_kernel"), ("down", "gg_wgrad_sq_kernel"), ("decode", "gg_wgrad_kernel")])
 @pytest.mark.parametrize("out_bf16", [False, True])
 def test_the_benchmark_names_the_kernel_that_runs(workload, kernel, out_bf16):
