@@ -244,29 +244,32 @@ __device__ __forceinline__ q_v4i swiglu8(const q_v4i g_raw, const q_v4i u_raw) {
 // output token r is input row row_src[r]; feature k's block j holds tokens [128 j, 128 j + 128) of the output order,
 // the last block those that exist.  (The paper defines neither this operation nor its layouts.)
 // A workgroup takes tiles of one token block x 64 features: 128 rows of 128 bytes go through LDS (every group of 16
-// rows shifted by 32 bytes, so that the eight lanes of a feature pair read from different banks); lane 8 f + p then
+// rows shifted by 32 bytes (sixteen lanes: of 8 by 16), so that the eight lanes of a feature pair read from different banks); lane 8 f + p then
 // owns tokens 16 p .. 16 p + 15 of features 2 f and 2 f + 1 (one 4-byte LDS read per token): amax over its 16 values
 // per feature and over the eight lanes, 16 bytes out per feature - the eight lanes of a feature write one 128-byte
-// line of XT.
+// line of XT.  Few tiles are a chain of latencies (token index, row, LDS, reduction, divisions, store): there sixteen lanes own a
+// feature pair, 8 tokens each, and a workgroup has twice the threads (few_tiles in gg_fp8.hip; 1264 x 1280 out of 640 rows
+// 4.6 us, 3.9).
 // Tiles are listed token block by token block, or (strips) in strips of QC_STRIP feature tiles, a strip's token blocks one after the
 // other: the workgroups at work at one time then write neighbouring lines of a few rows of XT instead of lines of all rows, a row
 // pitch apart, and read 512 bytes of a token instead of all of it.  Where that pays: see cols_in_strips() in gg_fp8.hip.
 constexpr int QC_FEATS = 64, QC_STRIP = 4;
-constexpr int QC_LDS_BYTES = 128 * 128 + 7 * 32;
+constexpr int QC_LDS_BYTES = 128 * 128 + 15 * 16;
 
 // SNT: the bytes are written with the streaming policy (see cols_bytes_stream() in gg_fp8.hip).
-template <bool SNT>
-__global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint16_t* __restrict__ X,
+template <bool SNT, int LANES = 8>
+__global__ void __launch_bounds__(32 * LANES) gg_quantize_cols_kernel(const uint16_t* __restrict__ X,
                                                                      const int32_t* __restrict__ row_src,
                                                                      uint8_t* __restrict__ XT, float* __restrict__ SX,
                                                                      int64_t T, int M_total, int K, int MB, int strips) {
+  constexpr int NT = 32 * LANES, TOKS = 128 / LANES, LOADS = 1024 / NT;      // threads, tokens of a lane, 16-byte pieces it brings in
   __shared__ __attribute__((aligned(16))) uint8_t tile[QC_LDS_BYTES];
   const int t = threadIdx.x;
   const int kt = K / QC_FEATS;
   const int64_t tiles = (int64_t)MB * kt;
-  const int fp = t >> 3, part = t & 7;
-  // piece t + 256 i of a tile: token (t + 256 i) / 8 of the block, features 8 (t % 8) .. + 7
-  q_v4i raw[4];
+  const int fp = t / LANES, part = t % LANES;
+  // piece t + NT i of a tile: token (t + NT i) / 8 of the block, features 8 (t % 8) .. + 7
+  q_v4i raw[LOADS];
   auto place = [&](int64_t id, int& j, int& k0) __attribute__((always_inline)) {      // token block and first feature of a tile
     if (!strips) {
       j = (int)(id / kt);
@@ -283,8 +286,8 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
     int j, k0;
     place(id, j, k0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int r = 128 * j + ((t + 256 * i) >> 3);
+    for (int i = 0; i < LOADS; ++i) {
+      const int r = 128 * j + ((t + NT * i) >> 3);
       raw[i] = (q_v4i){0, 0, 0, 0};                        // a token past the end or a source outside [0, T): zeros
       if (r < M_total) {
         const int64_t src = row_src ? (int64_t)row_src[r] : (int64_t)r;
@@ -297,17 +300,17 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
     int j, k0;
     place(id, j, k0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int tok = (t + 256 * i) >> 3;
-      *(q_v4i*)(tile + tok * 128 + (tok >> 4) * 32 + 16 * (t & 7)) = raw[i];
+    for (int i = 0; i < LOADS; ++i) {
+      const int tok = (t + NT * i) >> 3;
+      *(q_v4i*)(tile + tok * 128 + tok / TOKS * (2 * TOKS) + 16 * (t & 7)) = raw[i];
     }
     __syncthreads();
     if (id + gridDim.x < tiles) load_tile(id + gridDim.x);      // the next tile's rows are on their way during this one's arithmetic
-    float v[2][16];
+    float v[2][TOKS];
     unsigned top[2] = {0, 0};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const unsigned two = *(const unsigned*)(tile + (16 * part + i) * 128 + part * 32 + 4 * fp);
+    for (int i = 0; i < TOKS; ++i) {
+      const unsigned two = *(const unsigned*)(tile + (TOKS * part + i) * 128 + part * (2 * TOKS) + 4 * fp);
       v[0][i] = __builtin_bit_cast(float, two << 16);
       v[1][i] = __builtin_bit_cast(float, two & 0xFFFF0000u);
       const unsigned a0 = two & 0x7FFFu, a1 = (two >> 16) & 0x7FFFu;      // |x| of non-NaN values orders like its bit pattern
@@ -316,7 +319,7 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
     }
     // NaNs and infinities are rare: one wave-uniform branch keeps their handling out of the common path
     const bool special = __builtin_amdgcn_ballot_w64((top[0] > top[1] ? top[0] : top[1]) >= 0x7F80u) != 0;
-    q_v4i out[2];
+    int out[2][TOKS / 4];
     float scale[2];
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
@@ -324,29 +327,36 @@ __global__ void __launch_bounds__(Q_THREADS) gg_quantize_cols_kernel(const uint1
       if (special) {
         m = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < TOKS; ++i) {
           const unsigned a = amax_bits_of(v[f][i]) >> 16;               // a NaN counts as zero
           m = m > a ? m : a;
         }
       }
-      const float amax = block_amax(max8(m) << 16);
+      m = max8(m);
+      if constexpr (LANES == 16) {
+        const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, (int)m, 0x128, 0xF, 0xF, false);      // row_ror 8: the other eight
+        m = m > o ? m : o;
+      }
+      const float amax = block_amax(m << 16);
       scale[f] = amax / 448.0f;
       const float inv = 448.0f / amax;
 #pragma unroll
-      for (int d = 0; d < 4; ++d) {
+      for (int d = 0; d < TOKS / 4; ++d) {
         out[f][d] = special ? e4m3x4_of(v[f] + 4 * d, inv) : e4m3x4_of<false>(v[f] + 4 * d, inv);
       }
     }
-    // M_total is a multiple of 16: a 16-byte piece of a row of XT exists whole or not at all
-    const int tok0 = 128 * j + 16 * part;
+    // M_total is a multiple of 16: a lane's piece of a row of XT exists whole or not at all
+    const int tok0 = 128 * j + TOKS * part;
     if (tok0 < M_total) {
       uint8_t* dst = XT + (int64_t)(k0 + 2 * fp) * M_total + tok0;
-      if constexpr (SNT) {
-        __builtin_nontemporal_store(out[0], (q_v4i*)dst);
-        __builtin_nontemporal_store(out[1], (q_v4i*)(dst + M_total));
-      } else {
-        *(q_v4i*)dst = out[0];
-        *(q_v4i*)(dst + M_total) = out[1];
+#pragma unroll
+      for (int f = 0; f < 2; ++f) {
+        typedef int piece __attribute__((ext_vector_type(TOKS / 4)));
+        piece o;
+#pragma unroll
+        for (int d = 0; d < TOKS / 4; ++d) o[d] = out[f][d];
+        if constexpr (SNT) __builtin_nontemporal_store(o, (piece*)(dst + f * (int64_t)M_total));
+        else *(piece*)(dst + f * (int64_t)M_total) = o;
       }
     }
     if (part == 0) *(q_v2i*)(SX + (int64_t)j * K + k0 + 2 * fp) = (q_v2i){__builtin_bit_cast(int, scale[0]), __builtin_bit_cast(int, scale[1])};
