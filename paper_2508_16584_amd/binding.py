@@ -526,7 +526,13 @@ def grouped_gemm_swiglu(A, SA, B, SB, group_offsets, A2=None, SA2=None, act_out=
     inter = N // 2
     if variant == -1 and stream is None and A2 is None and SA2 is None and act_out is None and \
             lib.gg_fp8_swiglu_route(G, M_total, inter, K, GG_SA_KMAJOR if sa_kmajor else 0) == 1:
-        return swiglu_quantize_rows(grouped_gemm(A, SA, B, SB, group_offsets, sa_kmajor=sa_kmajor), want_act=want_act, sa_kmajor=sa_kmajor)
+        try:
+            H = torch.empty((M_total, N), dtype=torch.bfloat16, device=A.device)
+        except torch.OutOfMemoryError:                      # one launch, which needs no intermediate
+            H = None
+        if H is not None:
+            grouped_gemm(A, SA, B, SB, group_offsets, C=H, sa_kmajor=sa_kmajor)
+            return swiglu_quantize_rows(H, want_act=want_act, sa_kmajor=sa_kmajor)
     a_shape, sa_shape = (M_total, inter), (inter // 128, M_total) if sa_kmajor else (M_total, inter // 128)
     A2 = _output(A2, "A2", torch.uint8, a_shape, A)
     SA2 = _output(SA2, "SA2", torch.float32, sa_shape, A)

@@ -168,14 +168,20 @@ PyObject* grouped_gemm_swiglu(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (want_act) act = fresh({g.M, inter}, at::kBFloat16, g.A);
     const unsigned order = km ? GG_SA_KMAJOR : 0;
     if (lib.swiglu_route && lib.swiglu_route((int)g.G, g.M, (int)inter, (int)g.K, order) == 1) {
-      // two launches, one after the other on the current stream, which is the intermediate's own
-      at::Tensor H = fresh({g.M, g.N}, at::kBFloat16, g.A);
-      if (!call(lib.gemm, g.A->data_ptr(), data<float>(g.SA), g.B->data_ptr(), data<float>(g.SB), data<int32_t>(g.off), H.data_ptr(), (int)g.G, g.M, (int)g.N,
-                (int)g.K, nullptr, 0, current_stream(), -1, order) ||
-          !call(lib.swiglu_quantize_rows, H.data_ptr(), A2.data_ptr(), data<float>(SA2), want_act ? act.data_ptr() : nullptr, g.M, (int)inter,
-                current_stream(), order))
-        return nullptr;
-      return pair(A2, SA2, want_act ? &act : nullptr, true);
+      // two launches, one after the other on the current stream, which is the intermediate's own; where memory has no room for it, one
+      at::Tensor H;
+      try {
+        H = fresh({g.M, g.N}, at::kBFloat16, g.A);
+      } catch (const c10::OutOfMemoryError&) {
+      }
+      if (H.defined()) {
+        if (!call(lib.gemm, g.A->data_ptr(), data<float>(g.SA), g.B->data_ptr(), data<float>(g.SB), data<int32_t>(g.off), H.data_ptr(), (int)g.G, g.M, (int)g.N,
+                  (int)g.K, nullptr, 0, current_stream(), -1, order) ||
+            !call(lib.swiglu_quantize_rows, H.data_ptr(), A2.data_ptr(), data<float>(SA2), want_act ? act.data_ptr() : nullptr, g.M, (int)inter,
+                  current_stream(), order))
+          return nullptr;
+        return pair(A2, SA2, want_act ? &act : nullptr, true);
+      }
     }
     if (!call(lib.gemm_swiglu, g.A->data_ptr(), data<float>(g.SA), g.B->data_ptr(), data<float>(g.SB), data<int32_t>(g.off), A2.data_ptr(), data<float>(SA2),
                         want_act ? act.data_ptr() : nullptr, (int)g.G, g.M, (int)inter, (int)g.K, current_stream(), -1, order))

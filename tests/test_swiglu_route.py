@@ -68,3 +68,24 @@ def test_two_launches_give_the_bytes_of_the_fused_kernel(sizes, I, K, km, native
         runs.append(tuple(t.clone() for t in captured))
     for A2, SA2, act in runs:
         assert torch.equal(A2, want[0]) and torch.equal(SA2, want[1]) and torch.equal(act.view(torch.int16), want[2].view(torch.int16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_no_room_for_the_intermediate(native, monkeypatch):
+    dev = problem([32] * 256, 1024, 512, 3)
+    assert route(256, 8192, 1024, 512) == 1                # 32 MB of intermediate, 8 MB of bytes
+    if not native:
+        monkeypatch.setattr(binding, "_calls", None)
+    want = gg.grouped_gemm_swiglu(*dev)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    room = torch.cuda.memory_reserved() + (24 << 20)       # the allocator takes 20 MB at a time for the bytes
+    torch.cuda.set_per_process_memory_fraction(room / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            torch.empty(32 << 20, dtype=torch.uint8, device=DEV)
+        got = gg.grouped_gemm_swiglu(*dev)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
