@@ -248,31 +248,23 @@ __device__ __forceinline__ int swz_key_b(int row) {   // rows read: base + 8*(r/
 struct GroupIndex {
   static constexpr int NONE = 0x7FFFFFFF;      // a work unit that does not exist
   unsigned pre[4];
-  int row0[4], n[4];    // first row and rows of the groups
   int g, base;          // the walk behind the first 256 groups: groups before g hold `base` tiles
   int full, rem_run;    // full rounds over the workgroups; tiles per XCD of the last one
 
   __device__ __forceinline__ static unsigned add_sat(unsigned x, unsigned y) { return __builtin_elementwise_add_sat(x, y); }
 
-  // rows of group group0 + l, and the first of them
-  __device__ __forceinline__ static int rows64(const GemmArgs& a, int group0, int l, int& row0) {
-    const int g0 = group0 + l < a.G ? group0 + l : a.G, g1 = g0 + 1 < a.G ? g0 + 1 : a.G;
-    row0 = clampi(a.off[g0], 0, a.M_total);
-    return clampi(a.off[g1], row0, a.M_total) - row0;
-  }
+  // rows of group group0 + l
   __device__ __forceinline__ static int rows64(const GemmArgs& a, int group0, int l) {
-    int row0;
-    return rows64(a, group0, l, row0);
+    const int g0 = group0 + l < a.G ? group0 + l : a.G, g1 = g0 + 1 < a.G ? g0 + 1 : a.G;
+    const int row0 = clampi(a.off[g0], 0, a.M_total);
+    return clampi(a.off[g1], row0, a.M_total) - row0;
   }
   // ... of the first 256 groups, for a kernel that looks at them before it knows its tile height
   struct Rows {
-    int r[4], row0[4];
+    int r[4];
     __device__ __forceinline__ void load(const GemmArgs& a, int l) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        r[c] = row0[c] = 0;
-        if (64 * c < a.G) r[c] = rows64(a, 64 * c, l, row0[c]);
-      }
+      for (int c = 0; c < 4; ++c) r[c] = 64 * c < a.G ? rows64(a, 64 * c, l) : 0;
     }
   };
 
@@ -298,8 +290,6 @@ struct GroupIndex {
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       pre[c] = before;
-      row0[c] = rows.row0[c];
-      n[c] = rows.r[c];
       if (64 * c < a.G) {
         pre[c] = add_sat(scan64(a, BM, rows.r[c]), before);
         before = (unsigned)__builtin_amdgcn_readlane((int)pre[c], 63);
@@ -322,10 +312,66 @@ struct GroupIndex {
     return it == full && i < rem_run ? full * (int)gridDim.x + xcd * rem_run + i : NONE;
   }
 
-  // The group of tile T, its rows and the tiles before it, false when there is no such tile.  T never decreases.
-  // The rows come out of the registers too: fetched again from the offsets, they are one more memory latency in front of a
-  // workgroup's first fetch and behind every tile.
+  // The group of tile T and the tiles before that group, false when there is no such tile.  T never decreases.
   // (readfirstlane states the uniformity for the compiler, which otherwise loops over descriptors at every fetch.)
+  __device__ __forceinline__ bool find(const GemmArgs& a, int BM, int T, int& group, int& tiles_before) {
+    int gr = -1, tb = 0;
+    locate(a, BM, T, gr, tb);
+    group = __builtin_amdgcn_readfirstlane(gr);
+    tiles_before = __builtin_amdgcn_readfirstlane(tb);
+    return group >= 0;
+  }
+
+  __device__ __forceinline__ void locate(const GemmArgs& a, int BM, int T, int& group, int& tiles_before) {
+    int before = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (64 * c >= a.G) return;
+      const uint64_t past = __builtin_amdgcn_ballot_w64(pre[c] > (unsigned)T);
+      if (past) {
+        const int lane = __builtin_ctzll(past);
+        group = 64 * c + lane;
+        tiles_before = lane ? __builtin_amdgcn_readlane((int)pre[c], lane - 1) : before;
+        return;
+      }
+      before = __builtin_amdgcn_readlane((int)pre[c], 63);
+    }
+    const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
+    for (; g < a.G; ++g) {
+      const int row0 = clampi(offc[g], 0, a.M_total);
+      const int cnt = row_tiles(clampi(offc[g + 1], row0, a.M_total) - row0, BM) * a.n_tiles;
+      if (T < base + cnt) {
+        group = g;
+        tiles_before = base;
+        return;
+      }
+      base += cnt;
+    }
+  }
+};
+
+// The same for the kernels of small tiles, with the rows of the groups: fetched again from the offsets, they are one more memory
+// latency in front of a workgroup's first fetch and behind every tile (a small layer's seven launches 48.4 -> 48.0 us).  The larger tiles
+// gain nothing by it (3 groups, 5616 rows, 768 x 5888 in the fourth kernel: 49.0 us, 50.5 with it).
+struct GroupRows : GroupIndex {
+  int row0[4], n[4];    // first row and rows of the first 256 groups, as pre[]
+
+  __device__ __forceinline__ static int rows64(const GemmArgs& a, int group0, int l, int& row0) {
+    const int g0 = group0 + l < a.G ? group0 + l : a.G, g1 = g0 + 1 < a.G ? g0 + 1 : a.G;
+    row0 = clampi(a.off[g0], 0, a.M_total);
+    return clampi(a.off[g1], row0, a.M_total) - row0;
+  }
+  __device__ __forceinline__ void init(const GemmArgs& a, int BM, int l, bool split) {
+    Rows rows;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      n[c] = row0[c] = 0;
+      if (64 * c < a.G) n[c] = rows64(a, 64 * c, l, row0[c]);
+      rows.r[c] = n[c];
+    }
+    GroupIndex::init(a, rows, BM, l, split);
+  }
+
   struct Group {
     int g, tiles_before, row0, rows;
   };
@@ -493,9 +539,10 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kernel(const GemmArgs a) {
       T >>= 1;
     }
 
-    GroupIndex::Group grp;
-    if (!groups.find(a, BM, T, grp)) return t;
-    const int g = grp.g, base = grp.tiles_before, row0 = clampi(offc[g], 0, a.M_total), Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
+    int g = 0, base = 0;
+    if (!groups.find(a, BM, T, g, base)) return t;
+    const int row0 = clampi(offc[g], 0, a.M_total);
+    const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
     const int mtiles = row_tiles(Mg, BM);
     // order inside a group: chunks of n_chunk n-tiles; inside a chunk m-tile major, n-tile minor
     const int local = T - base;

@@ -53,9 +53,9 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kp_kernel(const GemmArgs a) {
   // Workgroup b runs on XCD b % 8: of every 64 tiles an XCD takes 8 neighbours, and neighbours are row tiles of one column tile,
   // which share its weights.
   const int b = (int)blockIdx.x, T = (b & ~63) | (b & 7) << 3 | (b >> 3 & 7);
-  GroupIndex groups;
+  GroupRows groups;
   groups.init(a, BM, l, false);
-  GroupIndex::Group grp;
+  GroupRows::Group grp;
   if (!groups.find(a, BM, T, grp)) return;
   const int mtiles = row_tiles(grp.rows, BM), local = T - grp.tiles_before;
   const int ntile = local / mtiles, mtile = local - ntile * mtiles;

@@ -91,9 +91,10 @@ __global__ void __launch_bounds__(PcCfg::NT) gg_gemm_pc_kernel(const GemmArgs a)
       Tile t = {0, 0, 0, 0, false};
       const int T = groups.unit(a, it);
       if (T == GroupIndex::NONE) return t;
-      GroupIndex::Group grp;
-      if (!groups.find(a, bm, T, grp)) return t;
-      const int g = grp.g, base = grp.tiles_before, row0 = clampi(offc[g], 0, a.M_total), Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
+      int g = 0, base = 0;
+      if (!groups.find(a, bm, T, g, base)) return t;
+      const int row0 = clampi(offc[g], 0, a.M_total);
+      const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
       const int mtiles = row_tiles(Mg, bm);
       const int local = T - base;
       const int per_chunk = mtiles * a.n_chunk;

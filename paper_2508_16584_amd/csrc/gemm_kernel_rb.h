@@ -224,9 +224,10 @@ __device__ __forceinline__ void rb_run(const GemmArgs& a, const GroupIndex::Rows
     Tile t = {false, 0, 0, 0, 0};
     const int T = groups.unit(a, it);
     if (T == GroupIndex::NONE) return t;
-    GroupIndex::Group grp;
-    if (!groups.find(a, BM, T, grp)) return t;
-    const int g = grp.g, base = grp.tiles_before, row0 = clampi(offc[g], 0, a.M_total), Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
+    int g = 0, base = 0;
+    if (!groups.find(a, BM, T, g, base)) return t;
+    const int row0 = clampi(offc[g], 0, a.M_total);
+    const int Mg = clampi(offc[g + 1], row0, a.M_total) - row0;
     const int mtiles = row_tiles(Mg, BM);
     const int local = T - base;
     const int per_chunk = mtiles * a.n_chunk;

@@ -85,13 +85,13 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::WG_PER_CU) gg_gemm_sm_kernel(con
     int g, n0, rows_valid;
     int64_t grow;
   };
-  GroupIndex groups;
+  GroupRows groups;
   groups.init(a, BM, l, true);
-  auto tile_at = [&](int it, GroupIndex& walk) __attribute__((always_inline)) -> Tile {
+  auto tile_at = [&](int it, GroupRows& walk) __attribute__((always_inline)) -> Tile {
     Tile t = {false, 0, 0, 0, 0};
     const int T = walk.unit(a, it);
     if (T == GroupIndex::NONE) return t;
-    GroupIndex::Group grp;
+    GroupRows::Group grp;
     if (!walk.find(a, BM, T, grp)) return t;
     const int g = grp.g, base = grp.tiles_before, row0 = grp.row0, Mg = grp.rows;
     const int mtiles = row_tiles(Mg, BM);
@@ -111,7 +111,7 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::WG_PER_CU) gg_gemm_sm_kernel(con
   };
   // ---- the fetch stream
   const int nb_all = (N + 127) >> 7;
-  GroupIndex groupsF = groups;   // (the registers are shared: only the walk past 256 groups is a cursor's own)
+  GroupRows groupsF = groups;   // (the registers are shared: only the walk past 256 groups is a cursor's own)
   int itF = 0;
   Tile F = tile_at(0, groupsF);
   if (!F.valid) return;
