@@ -98,7 +98,8 @@ const char* gg_fp8_variant_name(int variant);
  * the sizes are not supported.  The host looks at sizes only and chooses a kernel; the kernels of variants 0 and 3
  * and of 12, 14, 15 and 16 ("-rb"), where they are not asked for by name, then take the tile height that suits the
  * groups, whose sizes they find in group_offsets.  The index passed as `variant` therefore launches the same kernel at
- * the named height: the same results, not always the same time. */
+ * the named height: the same results, not always the same time.  Where the fifth kernel runs on sizes that its tiles do not take
+ * by name (N or K not whole tiles), the best of the others is named. */
 int gg_fp8_auto_variant(int G, int64_t M_total, int N, int K);
 /* The same for gg_fp8_grouped_gemm_padded (and for the _ex call with GG_PADDED_GROUPS), on a capacity of rows (the padded
  * problem of Sec. 3). */
