@@ -80,11 +80,15 @@ def test_no_room_for_the_intermediate(native, monkeypatch):
     want = gg.grouped_gemm_swiglu(*dev)
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
-    room = torch.cuda.memory_reserved() + (24 << 20)       # the allocator takes 20 MB at a time for the bytes
-    torch.cuda.set_per_process_memory_fraction(room / torch.cuda.get_device_properties(0).total_memory)
+    room = torch.empty(8 << 20, dtype=torch.uint8, device=DEV)      # for the bytes, 20 MB as the allocator takes them
+    limit = torch.cuda.memory_reserved() + (4 << 20)
+    torch.cuda.set_per_process_memory_fraction(limit / torch.cuda.get_device_properties(0).total_memory)
+    held = []
     try:
-        with pytest.raises(torch.OutOfMemoryError):
-            torch.empty(32 << 20, dtype=torch.uint8, device=DEV)
+        with pytest.raises(torch.OutOfMemoryError):        # what earlier tests left free in pieces of 32 MB
+            while len(held) < 1000:
+                held.append(torch.empty(32 << 20, dtype=torch.uint8, device=DEV))
+        del room
         got = gg.grouped_gemm_swiglu(*dev)
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
