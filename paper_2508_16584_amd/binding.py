@@ -524,20 +524,20 @@ def grouped_gemm_swiglu(A, SA, B, SB, group_offsets, A2=None, SA2=None, act_out=
     if N % 2:
         raise ValueError("B must hold an even number of rows per group (gate | up)")
     inter = N // 2
-    if variant == -1 and stream is None and A2 is None and SA2 is None and act_out is None and \
-            lib.gg_fp8_swiglu_route(G, M_total, inter, K, GG_SA_KMAJOR if sa_kmajor else 0) == 1:
-        try:
-            H = torch.empty((M_total, N), dtype=torch.bfloat16, device=A.device)
-        except torch.OutOfMemoryError:                      # one launch, which needs no intermediate
-            H = None
-        if H is not None:
-            grouped_gemm(A, SA, B, SB, group_offsets, C=H, sa_kmajor=sa_kmajor)
-            return swiglu_quantize_rows(H, want_act=want_act, sa_kmajor=sa_kmajor)
+    fresh = variant == -1 and stream is None and A2 is None and SA2 is None and act_out is None
     a_shape, sa_shape = (M_total, inter), (inter // 128, M_total) if sa_kmajor else (M_total, inter // 128)
     A2 = _output(A2, "A2", torch.uint8, a_shape, A)
     SA2 = _output(SA2, "SA2", torch.float32, sa_shape, A)
     if act_out is not None or want_act:
         act_out = _output(act_out, "act_out", torch.bfloat16, a_shape, A)
+    if fresh and lib.gg_fp8_swiglu_route(G, M_total, inter, K, GG_SA_KMAJOR if sa_kmajor else 0) == 1:
+        try:                                                # behind the outputs, which every way needs
+            H = torch.empty((M_total, N), dtype=torch.bfloat16, device=A.device)
+        except torch.OutOfMemoryError:                      # one launch, which needs no intermediate
+            H = None
+        if H is not None:
+            grouped_gemm(A, SA, B, SB, group_offsets, C=H, sa_kmajor=sa_kmajor)
+            return swiglu_quantize_rows(H, A2, SA2, act_out, sa_kmajor=sa_kmajor)
     _check(lib.gg_fp8_grouped_gemm_swiglu(_ptr(A), _ptr(SA), _ptr(B), _ptr(SB), _ptr(group_offsets), _ptr(A2), _ptr(SA2),
                                           _ptr(act_out), G, M_total, inter, K, _stream(stream), int(variant),
                                           GG_SA_KMAJOR if sa_kmajor else 0))

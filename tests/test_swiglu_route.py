@@ -27,6 +27,44 @@ def test_sizes():
         assert route(G, M, I, K, flags) == -lib.gg_fp8_grouped_gemm_swiglu(*[null] * 8, G, M, I, K, null, -1, flags) < 0
 
 
+@pytest.mark.parametrize("km", [False, True])
+@pytest.mark.parametrize("want_act", [False, True])
+@pytest.mark.parametrize("room,launches", [("outputs", 1), ("outputs and most of the intermediate", 1), ("outputs and intermediate", 2)])
+def test_outputs_are_allocated_before_the_intermediate(room, launches, want_act, km, monkeypatch):
+    """The binding's Python form on CPU tensors, with an allocator of limited room and a library that launches nothing."""
+    G, M, I, K = 4, 64, 256, 512
+    assert route(G, M, I, K, 2 if km else 0) == 1
+    made = []
+
+    class Library:
+        gg_fp8_swiglu_route = gg.load_library().gg_fp8_swiglu_route
+
+        def __getattr__(self, name):
+            return (lambda *args: 0) if name.startswith("gg_fp8_workspace") else lambda *args: made.append(name) or 0
+
+    cpu = [torch.zeros(M, K, dtype=torch.uint8), torch.zeros((K // 128, M) if km else (M, K // 128)), torch.zeros(G, 2 * I, K, dtype=torch.uint8),
+           torch.zeros(G, 2 * I // 128, K // 128), torch.zeros(G + 1, dtype=torch.int32)]
+    outputs, H = M * I + 4 * M * I // 128 + (2 * M * I if want_act else 0), 4 * M * I
+    left = [{"outputs": outputs, "outputs and most of the intermediate": outputs + H - 1, "outputs and intermediate": outputs + H}[room]]
+    empty = torch.empty
+
+    def limited(*args, **kw):
+        t = empty(*args, **kw)
+        if t.nbytes > left[0]:
+            raise torch.OutOfMemoryError("no room")
+        left[0] -= t.nbytes
+        return t
+
+    monkeypatch.setattr(binding, "_calls", None)
+    monkeypatch.setattr(binding, "_want", lambda *args: None)
+    monkeypatch.setattr(binding, "_stream", lambda stream: None)
+    monkeypatch.setattr(binding, "load_library", Library)
+    monkeypatch.setattr(torch, "empty", limited)
+    A2, SA2, act = gg.grouped_gemm_swiglu(*cpu, want_act=want_act, sa_kmajor=km)
+    assert A2.shape == (M, I) and SA2.shape == ((I // 128, M) if km else (M, I // 128)) and (act is not None) == want_act
+    assert len(made) == launches and ("swiglu" in made[0]) == (launches == 1)
+
+
 def problem(sizes, I, K, seed):
     rng = np.random.default_rng(seed)
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
