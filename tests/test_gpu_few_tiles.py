@@ -69,6 +69,43 @@ def test_more_groups_than_one_lookup_holds():
     check(sizes, 256, 384, 2)
 
 
+def test_groups_past_the_first_256_are_found_64_at_a_time():
+    sizes = [0] * 700
+    for g in (3, 255, 256, 257, 300, 319, 320, 383, 384, 447, 513, 640, 698, 699):
+        sizes[g] = 1 + g % 18
+    assert gg.variant_name(gg.auto_variant(700, sum(sizes), 128, 256)) in TILES
+    check(sizes, 128, 256, 4)
+    check(sizes[:513] + [0] * 187, 128, 256, 5)         # the last rows before the last groups
+
+
+def test_a_lookup_costs_little_however_many_groups_there_are():
+    """Few rows: 5 us with 256 groups, 13 with 2048 (191 where every workgroup walks the groups one by one)."""
+    def us(G, N=256, K=512, M=8, launches=20):
+        A, SA = torch.zeros(M, K, dtype=torch.uint8, device=DEV), torch.ones(M, K // 128, device=DEV)
+        B, SB = torch.zeros(G, N, K, dtype=torch.uint8, device=DEV), torch.ones(G, N // 128, K // 128, device=DEV)
+        off = torch.zeros(G + 1, dtype=torch.int32)
+        off[G - M + 1:] = torch.arange(1, M + 1)        # a row for each of the last groups
+        off, C = off.to(DEV), torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
+        assert gg.variant_name(gg.auto_variant(G, M, N, K)) in TILES
+        gg.grouped_gemm(A, SA, B, SB, off, C=C)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(launches):
+                gg.grouped_gemm(A, SA, B, SB, off, C=C)
+        begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        times = []
+        for _ in range(6):
+            begin.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end) / launches * 1e3)
+        return sorted(times)[2]
+    few, many = us(256), us(2048)
+    assert many < 6 * few, (few, many)
+
+
 def test_ragged_shapes_are_refused_by_name():
     dev = tuple(torch.from_numpy(x).to(DEV) for x in problem([4, 2], 264, 400, 3))
     for v in [u for u in range(gg.num_variants()) if gg.variant_name(u) in TILES]:
