@@ -375,13 +375,9 @@ struct GroupRows : GroupIndex {
   struct Group {
     int g, tiles_before, row0, rows;
   };
-  // ONCE: a workgroup that looks up one tile.  Past the first 256 groups it sums up 64 of them at a time: 0.3 us each, where the walk of a
-  // workgroup that goes on from tile to tile costs 7, once (1024 groups, one row, 512 x 2048 in the fifth kernel 82 -> 7.2 us, a walk
-  // per tile and per workgroup without one; 2048 groups, 64 rows 234 -> 27; up to 256 groups the same).
-  template <bool ONCE = false>
-  __device__ __forceinline__ bool find(const GemmArgs& a, int BM, int l, int T, Group& out) {
+  __device__ __forceinline__ bool find(const GemmArgs& a, int BM, int T, Group& out) {
     Group f = {-1, 0, 0, 0};
-    locate<ONCE>(a, BM, l, T, f);
+    locate(a, BM, T, f);
     out.g = __builtin_amdgcn_readfirstlane(f.g);
     out.tiles_before = __builtin_amdgcn_readfirstlane(f.tiles_before);
     out.row0 = __builtin_amdgcn_readfirstlane(f.row0);
@@ -389,8 +385,31 @@ struct GroupRows : GroupIndex {
     return out.g >= 0;
   }
 
-  template <bool ONCE>
-  __device__ __forceinline__ void locate(const GemmArgs& a, int BM, int l, int T, Group& f) {
+  // The same for a workgroup that looks up one tile.  Past the first 256 groups it sums up 64 of them at a time, 0.3 us each; the walk
+  // below takes 7 for as many, which a workgroup that goes on from tile to tile does once (fifth kernel, by walking and this way: 1024
+  // groups, one row, 512 x 2048 82 and 7.2 us; 2048 groups, 64 rows 234 and 27).
+  __device__ __forceinline__ bool find_once(const GemmArgs& a, int BM, int l, int T, Group& out) {
+    unsigned before = (unsigned)__builtin_amdgcn_readlane((int)pre[3], 63);      // tiles of the first 256 groups
+    if (a.G <= 256 || (unsigned)T < before) return find(a, BM, T, out);
+    for (int c = 256; c < a.G; c += 64) {
+      int first;
+      const int rows = rows64(a, c, l, first);
+      const unsigned upto = add_sat(scan64(a, BM, rows), before);
+      const uint64_t past = __builtin_amdgcn_ballot_w64(upto > (unsigned)T);
+      if (past) {
+        const int lane = __builtin_ctzll(past);
+        out.g = c + lane;
+        out.tiles_before = lane ? __builtin_amdgcn_readlane((int)upto, lane - 1) : (int)before;
+        out.row0 = __builtin_amdgcn_readlane(first, lane);
+        out.rows = __builtin_amdgcn_readlane(rows, lane);
+        return true;
+      }
+      before = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
+    }
+    return false;
+  }
+
+  __device__ __forceinline__ void locate(const GemmArgs& a, int BM, int T, Group& f) {
     int before = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -405,24 +424,6 @@ struct GroupRows : GroupIndex {
         return;
       }
       before = __builtin_amdgcn_readlane((int)pre[c], 63);
-    }
-    if constexpr (ONCE) {
-      for (int c = 256; c < a.G; c += 64) {
-        int first;
-        const int rows = rows64(a, c, l, first);
-        const unsigned upto = add_sat(scan64(a, BM, rows), (unsigned)before);
-        const uint64_t past = __builtin_amdgcn_ballot_w64(upto > (unsigned)T);
-        if (past) {
-          const int lane = __builtin_ctzll(past);
-          f.g = c + lane;
-          f.tiles_before = lane ? __builtin_amdgcn_readlane((int)upto, lane - 1) : before;
-          f.row0 = __builtin_amdgcn_readlane(first, lane);
-          f.rows = __builtin_amdgcn_readlane(rows, lane);
-          return;
-        }
-        before = __builtin_amdgcn_readlane((int)upto, 63);
-      }
-      return;
     }
     const GG_CONST_I32* offc = (const GG_CONST_I32*)a.off;
     for (; g < a.G; ++g) {

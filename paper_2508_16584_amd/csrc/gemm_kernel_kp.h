@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(Cfg::NT) gg_gemm_kp_kernel(const GemmArgs a) {
   GroupRows groups;
   groups.init(a, BM, l, false);
   GroupRows::Group grp;
-  if (!groups.find<true>(a, BM, l, T, grp)) return;
+  if (!groups.find_once(a, BM, l, T, grp)) return;
   const int mtiles = row_tiles(grp.rows, BM), local = T - grp.tiles_before;
   const int ntile = local / mtiles, mtile = local - ntile * mtiles;
   const int n0 = ntile * BN, n_rem = N - n0;

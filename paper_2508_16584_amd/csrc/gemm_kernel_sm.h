@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(Cfg::NT, Cfg::WG_PER_CU) gg_gemm_sm_kernel(con
     const int T = walk.unit(a, it);
     if (T == GroupIndex::NONE) return t;
     GroupRows::Group grp;
-    if (!walk.find(a, BM, l, T, grp)) return t;
+    if (!walk.find(a, BM, T, grp)) return t;
     const int g = grp.g, base = grp.tiles_before, row0 = grp.row0, Mg = grp.rows;
     const int mtiles = row_tiles(Mg, BM);
     const int local = T - base;
