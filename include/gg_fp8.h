@@ -75,7 +75,7 @@ size_t gg_fp8_workspace_bytes(int G, int64_t M_total, int N, int K);
 size_t gg_fp8_workspace_bytes_variant(int G, int64_t M_total, int N, int K, int variant);
 
 /* The padding-free grouped GEMM defined at the top of this file (Sec. 2.1 and
- * 2.2).  One persistent kernel walks the (group, m-tile, n-tile) list derived
+ * 2.2).  One kernel takes the tiles of the (group, m-tile, n-tile) list derived
  * from group_offsets on the device; rows past the end of a group are neither
  * loaded (they read as zero) nor stored; the 16-row activation blocks of a tile that
  * lie past a group's end are not computed either (taller tile variants). */
@@ -104,6 +104,9 @@ int gg_fp8_auto_variant(int G, int64_t M_total, int N, int K);
 /* The same for gg_fp8_grouped_gemm_padded (and for the _ex call with GG_PADDED_GROUPS), on a capacity of rows (the padded
  * problem of Sec. 3). */
 int gg_fp8_auto_variant_padded(int G, int64_t M_pad_cap, int N, int K);
+/* The variant that the automatic choice runs on these sizes, the fifth kernel's also where its tiles are not taken by name; a
+ * negated GG_ERR_ for sizes that gg_fp8_grouped_gemm_ex refuses with variant -1.  flags as there. */
+int gg_fp8_gemm_route(int G, int64_t M_total, int N, int K, unsigned flags);
 
 /* gg_fp8_grouped_gemm_variant with C [M_total, N] written as IEEE binary16 instead of bfloat16: the paper says
  * "half-precision" and App. A only fixes 2 bytes per element, so both 2-byte formats are offered.  Same sum, same

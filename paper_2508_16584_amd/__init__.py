@@ -38,6 +38,7 @@ from .binding import (  # noqa: F401
     swiglu_quantize_rows,
     variant_name,
     version,
+    gemm_route,
     wgrad_route,
     workspace_bytes,
 )

@@ -214,6 +214,8 @@ def load_library() -> ctypes.CDLL:
     lib.gg_fp8_grouped_gemm_wgrad.restype = i32
     lib.gg_fp8_grouped_gemm_wgrad_ex.argtypes = [vp, vp, vp, vp, vp, vp, i32, i64, i32, i32, vp, ctypes.c_uint]
     lib.gg_fp8_grouped_gemm_wgrad_ex.restype = i32
+    lib.gg_fp8_gemm_route.argtypes = [i32, i64, i32, i32, ctypes.c_uint]
+    lib.gg_fp8_gemm_route.restype = i32
     lib.gg_fp8_wgrad_route.argtypes = [vp, vp, i32, i64, i32, i32, ctypes.c_uint]
     lib.gg_fp8_wgrad_route.restype = i32
     lib.gg_fp8_quantize_cols.argtypes = [vp, vp, vp, vp, i64, i64, i32, vp]
@@ -278,7 +280,7 @@ def _load_calls(lib) -> None:
 
 EXPORTED_SYMBOLS = [
     "gg_fp8_version", "gg_fp8_status_str", "gg_fp8_workspace_bytes", "gg_fp8_workspace_bytes_variant", "gg_fp8_grouped_gemm",
-    "gg_fp8_grouped_gemm_variant", "gg_fp8_grouped_gemm_f16", "gg_fp8_grouped_gemm_ex", "gg_fp8_num_variants", "gg_fp8_variant_name", "gg_fp8_auto_variant", "gg_fp8_auto_variant_padded", "gg_fp8_padded_rows_cap",
+    "gg_fp8_grouped_gemm_variant", "gg_fp8_grouped_gemm_f16", "gg_fp8_grouped_gemm_ex", "gg_fp8_num_variants", "gg_fp8_variant_name", "gg_fp8_auto_variant", "gg_fp8_auto_variant_padded", "gg_fp8_gemm_route", "gg_fp8_padded_rows_cap",
     "gg_fp8_pad", "gg_fp8_grouped_gemm_padded", "gg_fp8_unpad", "gg_fp8_quantize_rows", "gg_fp8_swiglu_quantize_rows", "gg_fp8_check_offsets",
     "gg_fp8_grouped_gemm_splitk_noalloc", "gg_fp8_noalloc_max_elements", "gg_fp8_pad_ex", "gg_fp8_quantize_rows_ex", "gg_fp8_swiglu_quantize_rows_ex", "gg_fp8_grouped_gemm_swiglu", "gg_fp8_swiglu_route",
     "gg_fp8_grouped_gemm_wgrad", "gg_fp8_grouped_gemm_wgrad_ex", "gg_fp8_wgrad_route", "gg_fp8_quantize_cols", "gg_fp8_quantize_cols_route",
@@ -397,6 +399,15 @@ def auto_variant(G: int, M_total: int, N: int, K: int) -> int:
     v = load_library().gg_fp8_auto_variant(G, M_total, N, K)
     if v < 0:
         raise ValueError(f"gg_fp8_auto_variant: {status_str(-v)}")
+    return v
+
+
+def gemm_route(G: int, M_total: int, N: int, K: int, padded: bool = False, sa_kmajor: bool = False) -> int:
+    """Index of the variant that grouped_gemm(variant=-1) runs for these sizes (gg_fp8_gemm_route): like auto_variant, but named also
+    where it takes them by the automatic choice only.  padded: the padded GEMM's choice, M_total a capacity."""
+    v = load_library().gg_fp8_gemm_route(G, M_total, N, K, (GG_PADDED_GROUPS if padded else 0) | (GG_SA_KMAJOR if sa_kmajor else 0))
+    if v < 0:
+        raise ValueError(f"gg_fp8_gemm_route: {status_str(-v)}")
     return v
 
 

@@ -3,6 +3,7 @@
 import pytest
 
 import paper_2508_16584_amd as gg
+from paper_2508_16584_amd.binding import load_library
 
 FOURTH = ("160x256/2x4w/3s", "128x256/2x4w/3s")
 
@@ -46,3 +47,27 @@ def test_padded_problems_go_by_the_rows_that_their_groups_are_expected_to_hold(G
 def test_chains_of_k_blocks_on_few_tiles(G, M, N, K, third, fifth):
     """... and here those of the third and the fifth kernel."""
     assert fifth < 0.7 * third and gg.variant_name(gg.auto_variant(G, M, N, K)) in ("16x16/8x1w/3s", "16x32/4x1w/3s", "16x32/4x1w/2s")
+
+
+@pytest.mark.parametrize("G,M,N,K", [(16034763, 2, 4288, 128), (1 << 24, 3, 4096, 256), (1 << 30, 1, 520, 400)])
+def test_groups_without_rows_are_no_tiles_of_the_fifth_kernel(G, M, N, K):
+    """It has a workgroup for every tile there may be, and no more groups hold rows than there are rows."""
+    assert gg.variant_name(gg.gemm_route(G, M, N, K)) in ("16x16/8x1w/3s", "16x32/4x1w/3s", "16x32/4x1w/2s")
+
+
+def test_the_route_is_the_named_choice_where_there_is_one():
+    for G, M, N, K in [(4, 300, 640, 640), (37, 1, 1280, 7808), (8, 8192, 4096, 7168), (64, 2048, 4096, 7168), (256, 128, 2048, 2048), (3, 5, 512, 512)]:
+        assert gg.gemm_route(G, M, N, K) == gg.gemm_route(G, M, N, K, sa_kmajor=True) == gg.auto_variant(G, M, N, K)
+        cap = gg.padded_rows_cap(G, M)
+        assert gg.gemm_route(G, cap, N, K, padded=True) == gg.auto_variant_padded(G, cap, N, K)
+    for G, M, N, K in [(4, 8, 12, 512), (4, 8, 256, 24), (-1, 8, 256, 512), (4, 8, (1 << 21) + 8, 512)]:
+        with pytest.raises(ValueError):
+            gg.gemm_route(G, M, N, K)
+    with pytest.raises(ValueError):
+        gg.gemm_route(4, 1 << 24, 256, 1 << 20, sa_kmajor=True)
+    assert load_library().gg_fp8_gemm_route(4, 8, 256, 512, 8) == -3
+
+
+@pytest.mark.parametrize("G,M,N,K", [(5, 20, 264, 400), (3, 7, 8, 512), (4, 30, 136, 2000)])
+def test_the_route_names_the_fifth_kernel_on_ragged_sizes_too(G, M, N, K):
+    assert gg.gemm_route(G, M, N, K) >= 26 > gg.auto_variant(G, M, N, K)
