@@ -58,6 +58,19 @@ def test_ragged_shapes_of_the_automatic_choice(N, K):
     check([5, 0, 20, 2], N, K, N + K, tiles=())
 
 
+@pytest.mark.parametrize("tile,sizes,N,K", [
+    # N no multiple of the tile's columns, of 16 and of 32; short last K blocks in the first round and after one, two and more refills
+    (0, [14], 8, 560), (0, [0, 29, 1, 15], 24, 1136), (0, [3, 17], 40, 2080), (0, [2, 0, 31], 264, 3152), (0, [5, 12], 136, 4368), (0, [20], 40, 3840),
+    (1, [114], 520, 592), (1, [60, 0, 41, 5], 472, 1120), (1, [99], 712, 1920), (1, [17, 33, 1, 48], 664, 1712), (1, [107], 688, 3344), (1, [111], 552, 640),
+    (2, [11], 24, 32), (2, [40, 0, 70, 8], 1192, 544), (2, [5, 33, 64, 16], 1240, 1136), (2, [17, 0, 33, 16, 1, 49, 1], 1192, 1696),
+    (2, [3, 30, 0, 16, 17, 1, 33, 10, 7], 1192, 2064), (2, [17, 0, 33, 17, 1, 49, 1], 1224, 1920)])
+def test_ragged_shapes_on_every_tile(tile, sizes, N, K):
+    """Only the automatic choice runs these sizes on the fifth kernel: on the tile that the route names."""
+    G, M = len(sizes), sum(sizes)
+    assert gg.variant_name(gg.gemm_route(G, M, N, K)) == gg.variant_name(gg.gemm_route(G, M, N, K, sa_kmajor=True)) == TILES[tile]
+    check(sizes, N, K, N + K, tiles=())
+
+
 def test_rotated_k_loop():
     check([3, 18], 768, 4096, 1)
 
