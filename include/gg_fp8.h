@@ -166,7 +166,9 @@ int gg_fp8_grouped_gemm_swiglu(const void* A, const float* SA, const void* B, co
                                int G, int64_t M_total, int I, int K, void* stream, int variant, unsigned flags);
 /* How a program that can hold the bf16 intermediate [M_total, 2 I] gets the same bytes, scales and activations fastest: 0 with
  * gg_fp8_grouped_gemm_swiglu (automatic choice), 1 with gg_fp8_grouped_gemm_ex into the intermediate and
- * gg_fp8_swiglu_quantize_rows_ex behind it.  A negative status for sizes that the fused call refuses. */
+ * gg_fp8_swiglu_quantize_rows_ex behind it.  The same bytes in the rows of the groups: a row of no group (offsets that do not cover
+ * M_total) the fused call leaves as it is, while the activation kernel, which knows no offsets, writes what it makes of the intermediate's
+ * unwritten row there.  A negative status for sizes that the fused call refuses. */
 int gg_fp8_swiglu_route(int G, int64_t M_total, int I, int K, unsigned flags);
 
 /* The variable-K grouped GEMM of training: the weight gradient dW^g = dY^g^T X^g of the expert layer whose forward

@@ -524,7 +524,8 @@ def grouped_gemm_swiglu(A, SA, B, SB, group_offsets, A2=None, SA2=None, act_out=
                         stream=None, sa_kmajor=False):
     """gg_fp8_grouped_gemm_swiglu: the grouped GEMM with B [G, 2I, K] (gate rows, then up rows), silu(gate) * up and
     the 1x128 quantiser in one kernel (with fresh outputs in two, where gg_fp8_swiglu_route says that this is faster: the same
-    bytes, through an intermediate of at most 64 MB): returns (A2 uint8 [M_total, I], SA2 float32 [M_total, I/128] or
+    bytes, through an intermediate of at most 64 MB; a caller's own outputs get the one kernel, which leaves their rows of no group as
+    they are, where the two write something; in fresh outputs those rows hold anything): returns (A2 uint8 [M_total, I], SA2 float32 [M_total, I/128] or
     [I/128, M_total] with sa_kmajor, act bf16 [M_total, I] or None)."""
     if _calls is not None and A2 is None and SA2 is None and act_out is None and variant == -1 and stream is None:
         out = _calls.grouped_gemm_swiglu(A, SA, B, SB, group_offsets, want_act, sa_kmajor)

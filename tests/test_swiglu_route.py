@@ -109,6 +109,33 @@ def test_two_launches_give_the_bytes_of_the_fused_kernel(sizes, I, K, km, native
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("km", [False, True])
+@pytest.mark.parametrize("native", [True, False])
+def test_rows_of_no_group(km, native, monkeypatch):
+    """Offsets that leave rows out in front and behind: with fresh outputs (two launches) the groups' rows are those of the one launch, in a
+    caller's own outputs (one launch) the other rows stay as they were."""
+    sizes, I, K = [0, 3, 17, 1], 640, 1152
+    dev = problem([4] + sizes + [9], I, K, 5)              # rows, weights
+    dev[2], dev[3] = dev[2][1:5], dev[3][1:5]
+    dev[4] = dev[4][1:6].contiguous()                      # [4, 4, 7, 24, 25] of 34 rows
+    if km:
+        dev[1] = dev[1].t().contiguous()
+    if not native:
+        monkeypatch.setattr(binding, "_calls", None)
+    assert route(4, 34, I, K, 2 if km else 0) == 1
+    A2 = torch.full((34, I), 0xAB, dtype=torch.uint8, device=DEV)
+    SA2 = torch.full((I // 128, 34) if km else (34, I // 128), -7.0, device=DEV)
+    act = torch.full((34, I), 3.0, dtype=torch.bfloat16, device=DEV)
+    gg.grouped_gemm_swiglu(*dev, A2=A2, SA2=SA2, act_out=act, sa_kmajor=km)
+    fresh = gg.grouped_gemm_swiglu(*dev, want_act=True, sa_kmajor=km)
+    rows = lambda t: t.t() if km and t.dtype == torch.float32 else t
+    for own, other, mark in zip((A2, SA2, act), fresh, (0xAB, -7.0, 3.0)):
+        bits = {1: torch.uint8, 2: torch.int16, 4: torch.int32}[own.element_size()]
+        assert torch.equal(rows(own)[4:25].contiguous().view(bits), rows(other)[4:25].contiguous().view(bits))
+        assert (rows(own)[:4] == mark).all() and (rows(own)[25:] == mark).all()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("native", [True, False])
 def test_no_room_for_the_intermediate(native, monkeypatch):
     dev = problem([32] * 256, 1024, 512, 3)
