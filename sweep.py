@@ -244,39 +244,50 @@ def fit_large(rows):
           f"mean error {np.mean(np.abs(np.log(narrow(x) / T[2])[other])):.3f}")
 
 
-def fit_tiles(paths):
-    """latency, work and extra K steps of the small tiles and of the tiles of the fused kernel (kTileTimes, kFusedTimes)."""
+def fit_tile(rows, v, tile, fused):
+    """Constants of one small tile or tile of the fused kernel: latency, work, extra K steps, and the start-up time of the fifth kernel's.
+    Returns them, their mean error and on how many problems that is (the fifth kernel's: on the half that was not fitted)."""
     from scipy.optimize import minimize
+    BM, BN, kb_in_flight, per_cu, waves = tile
+    f, t = [], []
+    for r in rows:
+        if v not in r["us"]:
+            continue
+        G, M, N, K = r["G"], r["M"], r["N"], r["K"]
+        groups = G * (1 - math.exp(-M / G))
+        tiles = max(groups, M / BM + 0.5 * groups) * -(-N // BN)
+        weights = groups * N * K
+        d = weights / (min(tiles, 256 * per_cu) * kb_in_flight * 1024) * (1.6 if weights > 64e6 else 0.7)
+        f.append((tiles, -(-K // (128 * waves)), (weights + M * (K + (0.5 if fused else 2) * N)) / 6.8e6, d))
+        t.append(r["us"][v])
+    tiles, kb, c, d = np.array(f).T
+    t, chain = np.array(t), waves > 1                 # the fifth kernel has no term for the weights in flight
+
+    def estimate(p):
+        latency, work, extra, start = [*np.exp(p), 4.2][:4]
+        a, b = np.maximum(tiles / (256 * per_cu), 1) * (kb + extra) * latency, tiles * (kb + extra) * work / 256
+        return start + (a ** 4 + b ** 4 + c ** 4 + (0 if chain else d ** 4)) ** 0.25
+
+    def off(p, some):
+        return np.abs(np.log(estimate(p) / t))[some]
+    fitted, other = (slice(0, None, 2), slice(1, None, 2)) if chain else (slice(None), slice(None))
+    fits = [minimize(lambda p: np.mean(off(p, fitted) ** 1.5), np.log([s, s] + ([1, 3] if chain else [4])), method="Nelder-Mead",
+                     options=dict(maxiter=6000, maxfev=6000)) for s in (0.3, 1.2)]
+    best = min(fits, key=lambda x: x.fun).x
+    return np.exp(best), np.mean(off(best, other)), len(t[other])
+
+
+def fit_tiles(paths):
+    """The constants of the choice (kTileTimes, kChainTimes and what fit_large fits; kFusedTimes)."""
     rows = read_tiles(paths)
     fused = rows[0]["fused"]
     choice_summary(paths)
     if not fused:
         fit_large(rows)
-    for v, (BM, BN, kb_in_flight, per_cu, waves) in (FUSED_TILES if fused else SMALL_TILES).items():
-        f, t = [], []
-        for r in rows:
-            if v not in r["us"]:
-                continue
-            G, M, N, K = r["G"], r["M"], r["N"], r["K"]
-            groups = G * (1 - math.exp(-M / G))
-            tiles = max(groups, M / BM + 0.5 * groups) * -(-N // BN)
-            weights = groups * N * K
-            d = weights / (min(tiles, 256 * per_cu) * kb_in_flight * 1024) * (1.6 if weights > 64e6 else 0.7)
-            f.append((tiles, -(-K // (128 * waves)), (weights + M * (K + (0.5 if fused else 2) * N)) / 6.8e6, d))
-            t.append(r["us"][v])
-        tiles, kb, c, d = np.array(f).T
-        t = np.array(t)
-
-        def estimate(p):
-            latency, work, extra = np.exp(p)
-            a, b = np.maximum(tiles / (256 * per_cu), 1) * (kb + extra) * latency, tiles * (kb + extra) * work / 256
-            return 4.2 + (a ** 4 + b ** 4 + c ** 4 + d ** 4) ** 0.25
-
-        fits = [minimize(lambda p: np.mean(np.abs(np.log(estimate(p) / t)) ** 1.5), np.log([s, s, 4]), method="Nelder-Mead",
-                         options=dict(maxiter=6000, maxfev=6000)) for s in (0.3, 1.2)]
-        best = min(fits, key=lambda x: x.fun).x
-        print(f"{v:3d} {BM}x{BN}{' fused' if fused else ''} latency {math.exp(best[0]):.3f} work {math.exp(best[1]):.3f} extra {math.exp(best[2]):.2f}  "
-              f"mean error {np.mean(np.abs(np.log(estimate(best) / t))):.3f} on {len(t)} problems")
+    for v, tile in (FUSED_TILES if fused else SMALL_TILES).items():
+        best, error, problems = fit_tile(rows, v, tile, fused)
+        print(f"{v:3d} {tile[0]}x{tile[1]}{' fused' if fused else ''} latency {best[0]:.3f} work {best[1]:.3f} extra {best[2]:.2f}  "
+              + (f"start {best[3]:.2f}  " if len(best) > 3 else "") + f"mean error {error:.3f} on {problems} problems")
 
 
 def main():
