@@ -386,27 +386,41 @@ struct GroupRows : GroupIndex {
   }
 
   // The same for a workgroup that looks up one tile.  Past the first 256 groups it sums up 64 of them at a time, 0.3 us each; the walk
-  // below takes 7 for as many, which a workgroup that goes on from tile to tile does once (fifth kernel, by walking and this way: 1024
-  // groups, one row, 512 x 2048 82 and 7.2 us; 2048 groups, 64 rows 234 and 27).
+  // below takes 7 for as many, which a workgroup that goes on from tile to tile does once (fifth kernel, 40 random problems of 257 to
+  // 2048 groups: 0.20 of the time with the walk; 1024 groups, one row, 512 x 2048 82 and 7.2 us; 2048 groups, 64 rows 234 and 27).  Up to
+  // 256 groups 0.997 on 180 (1.009 where the walk's code was kept beside it: the smallest launches wait for their instructions too).
   __device__ __forceinline__ bool find_once(const GemmArgs& a, int BM, int l, int T, Group& out) {
-    unsigned before = (unsigned)__builtin_amdgcn_readlane((int)pre[3], 63);      // tiles of the first 256 groups
-    if (a.G <= 256 || (unsigned)T < before) return find(a, BM, T, out);
+    int before = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (64 * c >= a.G) return false;
+      const uint64_t past = __builtin_amdgcn_ballot_w64(pre[c] > (unsigned)T);
+      if (past) {
+        hit(c * 64, past, pre[c], before, row0[c], n[c], out);
+        return true;
+      }
+      before = __builtin_amdgcn_readlane((int)pre[c], 63);
+    }
     for (int c = 256; c < a.G; c += 64) {
       int first;
       const int rows = rows64(a, c, l, first);
-      const unsigned upto = add_sat(scan64(a, BM, rows), before);
+      const unsigned upto = add_sat(scan64(a, BM, rows), (unsigned)before);
       const uint64_t past = __builtin_amdgcn_ballot_w64(upto > (unsigned)T);
       if (past) {
-        const int lane = __builtin_ctzll(past);
-        out.g = c + lane;
-        out.tiles_before = lane ? __builtin_amdgcn_readlane((int)upto, lane - 1) : (int)before;
-        out.row0 = __builtin_amdgcn_readlane(first, lane);
-        out.rows = __builtin_amdgcn_readlane(rows, lane);
+        hit(c, past, upto, before, first, rows, out);
         return true;
       }
-      before = (unsigned)__builtin_amdgcn_readlane((int)upto, 63);
+      before = __builtin_amdgcn_readlane((int)upto, 63);
     }
     return false;
+  }
+  // the group of the first lane past the tile, of the 64 from c on
+  __device__ __forceinline__ static void hit(int c, uint64_t past, unsigned upto, int before, int first, int rows, Group& out) {
+    const int lane = __builtin_ctzll(past);
+    out.g = c + lane;
+    out.tiles_before = lane ? __builtin_amdgcn_readlane((int)upto, lane - 1) : before;
+    out.row0 = __builtin_amdgcn_readlane(first, lane);
+    out.rows = __builtin_amdgcn_readlane(rows, lane);
   }
 
   __device__ __forceinline__ void locate(const GemmArgs& a, int BM, int T, Group& f) {
