@@ -7,7 +7,7 @@
 // only the last step, acc = fma(p, s, acc) with the product p of a K block and its factor s.  So here the K blocks are dealt to
 // the waves of a workgroup: wave w takes blocks w, w + NW, ..., each through LDS slots of its own without any barrier, and puts
 // its products and factors into LDS; after one barrier per NW blocks the waves that own a fragment of the tile add them up in
-// order.  A workgroup has NW x U K blocks on their way at once.
+// order.  A workgroup starts with NW x U K blocks on their way (two slots per wave); how far ahead it stays: see OVERLAY.
 //
 // A workgroup computes one tile and ends: the launch has as many as there may be tiles, the hardware deals them out, and nothing
 // stands between the launch and the first fetch but the lookup of the group.  (With persistent workgroups whose fetches run on
@@ -15,12 +15,14 @@
 // and more gain.)
 //
 // OVERLAY: the products go where their operands were, which leaves room for more workgroups per compute unit; a slot is then
-// free only when they have been added up, a barrier later.  Better for short K loops and many tiles; the long chains are better
-// off with an area for the products and a slot that is refilled at once (one row, N = 1280, K = 7808: 10.3 -> 7.3 us).
+// free only when they have been added up: it is fetched again behind the barrier of the next round and awaited in the round after, so
+// from the third round on a wave has at most one block on its way, hidden behind the sums and the other workgroups of the compute unit
+// alone.  Better for short K loops and many tiles; the long chains are better off with an area for the products and a slot that is
+// refilled as soon as it has been read, two rounds ahead of its use (one row, N = 1280, K = 7808: 10.3 -> 7.3 us).
 //
 // Measured, us per launch in a graph (third kernel -> this one, bytes at 6.8 TB/s): 1 group of 16 rows, 5888 x 4224 22.0 -> 8.2
 // (3.7); 4 groups, 65 rows, 640 x 5120 14.5 -> 6.5 (2.0); 4 groups, 600 rows, 256 x 256 4.6 -> 3.3; 54 groups, 193 rows,
-// 1152 x 4608 39.3 -> 36.4 (30.7).
+// 1152 x 4608 39.3 -> 36.4 (30.7), which is too little for the choice to take it (kChainTimes in gg_fp8.hip).
 #pragma once
 #include "gemm_kernel.h"
 

@@ -18,8 +18,8 @@
 // that a neighbouring group's bytes (NaN codes included) never reach a product.  A group without tokens gives zeros.
 //
 // Structure (with the whole tile; the halved one: WgradHalfCfg): persistent workgroups (8 waves, 4 along k x 2 along n) walk the output tiles of 256 features x 128
-// rows of dY^T; per token block the two operand tiles and their scales go global -> LDS by DMA into a ring of 3
-// buffers, swizzled like the forward kernels' tiles, and the fetch stream runs three blocks ahead of the arithmetic
+// rows of dY^T; per token block the two operand tiles and their scales go global -> LDS by DMA into a ring of 3 (halved: 2)
+// buffers, swizzled like the forward kernels' tiles, and the fetch stream runs as many blocks ahead of the arithmetic
 // across tile boundaries (a group of 1000 tokens is 8 blocks: without that, every tile would start with an empty
 // pipeline and end with an idle one).  A wave holds the 4 + 4 operand fragments and the scales of the block it
 // multiplies in registers and refills them from the next block's buffer while it multiplies, and 64 x 64 fp32
@@ -171,13 +171,13 @@ __global__ void __launch_bounds__(Cfg::NT, 2) gg_wgrad_kernel(const WgradArgs a)
   const int s_pitch = sx_wave ? a.K * 4 : a.N * 4;                 // bytes from one token block's scales to the next
   const int ldsS = Cfg::X_BYTES + Cfg::Y_BYTES + (sx_wave ? w * 256 : sy_wave ? Cfg::SX_BYTES + (w - SXW) * 256 : Cfg::SX_BYTES + Cfg::SY_BYTES);
 
-  // The fetch stream runs three token blocks ahead of the arithmetic and on from tile to tile: F is the tile whose
+  // The fetch stream runs S token blocks ahead of the arithmetic and on from tile to tile: F is the tile whose
   // block sF comes next (tiles without tokens have nothing to fetch and are passed over), so the first blocks of a
   // workgroup's next tile are in flight while the current one is finished and stored.
   Tile F = tile_at(0);
   int itF = 0, sF = 0;
   // A block's fetches are prepared at the top of a step (the cursor moves on, the scalar offsets are formed) and
-  // issued one at a time between the matrix instructions of the step: issued together, the eight waves' 56 fetches
+  // issued one at a time between the matrix instructions of the step: issued together, the waves' fetches (56 of eight waves)
   // wait for the address unit one behind the other, and a wave that waits there issues no matrix instruction.
   int f_x_off = 0, f_y_off = 0, f_s_off = 0;     // scalar offsets of the prepared block: XT, DYT, scales
   int vXsel = GG_OOB_OFFSET, vYsel = GG_OOB_OFFSET, vSsel = GG_OOB_OFFSET;   // lane offsets, out of range when no tile is left
@@ -313,8 +313,8 @@ __global__ void __launch_bounds__(Cfg::NT, 2) gg_wgrad_kernel(const WgradArgs a)
       for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(acc[nf][i]));
   };
 
-  // ---- ring of 3 LDS buffers + the registers: while block b is multiplied out of the registers, block b + 1 has
-  // landed and is being read into them, blocks b + 2 and b + 3 are in flight (b + 3 into the buffer block b came from)
+  // ---- ring of S LDS buffers + the registers: while block b is multiplied out of the registers, block b + 1 has
+  // landed and is being read into them, the blocks from b + 2 to b + S are in flight (b + S into the buffer block b came from)
   fetch_next(0);
   fetch_next(1);
   if constexpr (S == 3) fetch_next(2);
@@ -331,7 +331,7 @@ __global__ void __launch_bounds__(Cfg::NT, 2) gg_wgrad_kernel(const WgradArgs a)
   int stage = 0;            // the buffer the block in the registers came from
   int st_prev = 0, st_late = 0, st_late2 = 0;   // stores issued since the last top of a step; those of them behind the step's fetches; the same between the two before
   // The top of a step.  This wave has read all of the block it multiplies next, and its part of the following block
-  // has landed: those fetches were issued two steps ago; newer are the fetches of the last step and the stores of
+  // has landed: with three buffers those fetches were issued two steps ago; newer are the fetches of the last step and the stores of
   // the tiles finished since, which may all stay in flight (a wave's loads and stores complete in the order they were
   // issued, see wait_vmcnt; the counter holds 63 and never gets there: a batch of stores behind a block begins with no more
   // than 31 outstanding, a block with stores inside with no more than the 39 of the waits here, and adds 23; and with three batches

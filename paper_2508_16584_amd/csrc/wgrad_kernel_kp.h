@@ -9,8 +9,10 @@
 // rows of dY^T fragment w, in order.  A workgroup computes one tile and ends; the hardware deals them out.
 // Measured, us per launch (narrow tiles -> these): those 2 groups 96.2 -> 25.9; 1 group of 944 tokens, 1280 x 512, 24.1 -> 6.9; 5 groups,
 // 4000 tokens, 256 x 512, 24.5 -> 9.0; 3 groups, 448 tokens, 640 x 768, 11.2 -> 6.5 (fp32 all).
-// What bounds it with many tiles: LDS (operands in and out, products in and out: 64 KB per block) and a quarter of the operand reuse of a 256 x 256
-// tile, hence only where few outputs meet many tokens (see wgrad_chain in gg_fp8.hip).
+// What bounds it: in long chains the latency of the fetches.  A slot is free when its products have been added up, is fetched again behind
+// the barrier of the next round and awaited in the round after: from the third round on a wave has at most one block on its way, behind the sums
+// alone (those 12 rounds: 2 us each).  With many tiles LDS (operands in and out, products in and out: 64 KB per block) and a quarter of the
+// operand reuse of a 256 x 256 tile, hence only where few outputs meet many tokens (see wgrad_chain in gg_fp8.hip).
 #pragma once
 #include "wgrad_kernel.h"
 
