@@ -49,6 +49,13 @@ def test_chains_of_k_blocks_on_few_tiles(G, M, N, K, third, fifth):
     assert fifth < 0.7 * third and gg.variant_name(gg.auto_variant(G, M, N, K)) in ("16x16/8x1w/3s", "16x32/4x1w/3s", "16x32/4x1w/2s")
 
 
+@pytest.mark.parametrize("G,M,N,K,other,fifth", [(49, 4, 7168, 3328, 18.4, 22.8), (221, 13, 2304, 3072, 18.3, 22.5), (13, 6, 5376, 2560, 16.1, 18.5),
+                                                 (4, 43, 6376, 3968, 22.8, 25.9), (8, 27, 3480, 4912, 25.7, 27.7), (9, 151, 1920, 512, 7.0, 7.4)])
+def test_a_little_more_than_one_round_of_chains(G, M, N, K, other, fifth):
+    """The last tiles take as long as all others: the 16 x 32 tiles are taken up to one round (here: with the best other kernel's time)."""
+    assert other < fifth and gg.variant_name(gg.gemm_route(G, M, N, K)) not in ("16x32/4x1w/3s", "16x32/4x1w/2s")
+
+
 @pytest.mark.parametrize("G,M,N,K", [(16034763, 2, 4288, 128), (1 << 24, 3, 4096, 256), (1 << 30, 1, 520, 400)])
 def test_groups_without_rows_are_no_tiles_of_the_fifth_kernel(G, M, N, K):
     """It has a workgroup for every tile there may be, and no more groups hold rows than there are rows."""
