@@ -64,6 +64,15 @@ def test_halved_tiles_where_measured_times_say_so(G, M, N, K, out_bf16, whole, h
     assert ("half" in gg.wgrad_route(G, M, N, K, out_bf16)) == (half < whole)
 
 
+# The same where K is a multiple of 2048 and the halves are more than a round
+@pytest.mark.parametrize("G,M,N,K,out_bf16,whole,half", [
+    (13, 608, 1024, 2048, False, 24.4, 32.6), (8, 848, 1024, 2048, False, 19.1, 22.1), (8, 272, 1024, 4096, False, 29.2, 32.4), (4, 320, 896, 4096, True, 13.6, 14.9),
+    (6, 704, 1280, 4096, True, 24.0, 25.6), (59, 7472, 256, 2048, False, 32.6, 34.6)])
+def test_rows_of_whole_4_kb_are_not_halved(G, M, N, K, out_bf16, whole, half):
+    assert whole < half and "half" not in gg.wgrad_route(G, M, N, K, out_bf16)
+    assert "half" in gg.wgrad_route(G, M, N, K - 256, out_bf16) and "half" in gg.wgrad_route(1, 128, 768, K, out_bf16)
+
+
 @pytest.mark.parametrize("workload,kernel", [("gate_up", "gg_wgrad_sq_kernel"), ("down", "gg_wgrad_sq_kernel"), ("decode", "gg_wgrad_kernel")])
 @pytest.mark.parametrize("out_bf16", [False, True])
 def test_the_benchmark_names_the_kernel_that_runs(workload, kernel, out_bf16):
